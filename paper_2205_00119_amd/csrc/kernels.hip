@@ -15,7 +15,7 @@
 // speed of 16-byte aligned ones; 2-byte aligned ones lose about 20 %.  So the element-wise
 // kernels use 128-bit accesses on under-aligned vector types everywhere, a lane that would
 // cross the end of a buffer works element by element inside the same kernel (no tail
-// launches), and only the bf16/fp16 gradient pointers are rounded down to 4 bytes first.
+// launches), and only the gradient pointers are rounded down first (align_gradient_pointers).
 //
 // Arithmetic rules (they make the results reproducible bit for bit):
 //   - no fused multiply-add (-ffp-contract=off and the pragma below),
@@ -67,7 +67,7 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #define MICS_RSA_BLOCK 64
 #endif
 #ifndef MICS_RSA_UNALIGNED_BLOCK
-#define MICS_RSA_UNALIGNED_BLOCK 512     // accumulator or gradients off 16 bytes: 6070 against 5740 with 64
+#define MICS_RSA_UNALIGNED_BLOCK 512     // gradients off 16 bytes: 6070 against 5740 with 64
 #endif
 #ifndef MICS_RSA_WAVES
 #define MICS_RSA_WAVES 10
@@ -485,13 +485,13 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
 // without bf16), 2 = binary32 (plain float32 training).  Widening to binary32 is exact.
 //
 // One kernel for every alignment.  The kernel works in a "virtual" element index space in
-// which element e of every (rounded-down) gradient pointer sits at a 4-byte aligned address
-// whenever e is a multiple of the lane's element count; the call's elements are the virtual
-// range [lead, lead + count), lead = 0 or 1 (1 when the bf16/fp16 pointers had to be rounded
-// down by one element).  A lane owns the virtual elements [EPL*i, EPL*i + EPL): one load per
+// which element 0 of every (rounded-down) gradient pointer sits at a 16-byte aligned address (at
+// least a 4-byte aligned one, where the pointers differ); the call's elements are the virtual
+// range [lead, lead + count), lead = the elements that the pointers were rounded down by.
+// A lane owns the virtual elements [EPL*i, EPL*i + EPL): one load per
 // rank buffer, one load and one store of the accumulator (which is then 4-byte aligned at
 // worst).  A lane whose elements are not all inside the range -- at most the first and the
-// last one -- adds its elements one by one.
+// last one -- leaves them to rsa_edges.
 //
 // VEC = dwords per load: 4 for bandwidth (8 bf16/fp16 or 4 fp32 elements per lane); 1 for
 // small messages on large groups, where the time is the launch plus the serial chain of
@@ -793,8 +793,8 @@ __global__ __launch_bounds__(128) void rsa_split_kernel(
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
 // tile x - tile_begin[t] of segment t.  Every segment has its own virtual index space as in
-// rsa_kernel: src0 = position of its virtual element 0 in the rank buffers (for 2-byte
-// gradients a multiple of 2 elements from the 4-byte aligned base), [lead, end) = its elements,
+// rsa_kernel: src0 = position of its virtual element 0 in the rounded-down rank buffers, a
+// multiple of a 16-byte line (4-byte unit) of them, [lead, end) = its elements,
 // dst = accumulator index of virtual element `lead`.
 struct ReduceSeg {
     unsigned long long end, src0, dst;
@@ -1214,6 +1214,28 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
 
 namespace {
 
+// Rounds gradient pointers down to 16 bytes when all of them sit at the same position inside
+// their 16-byte line (rank g's slices of separately allocated buffers do: they all start g*S
+// elements in); returns how many elements they moved back (the kernels' `lead`, 0 .. 7).  The p
+// gradient loads of a lane are then aligned and only its accumulator access is not, 8 of 2p+8
+// bytes.  A 1 KiB load of a wavefront that is off its 128-byte lines touches nine of them instead
+// of eight, and with non-temporal loads the shared ones are fetched twice.  With pointers rounded
+// down to 4 bytes / to 16 bytes, all 2 or 10 bytes off: p = 32, 9.8 M elements 124 / 117 us;
+// p = 16, 50 M elements 343 / 322 us.
+// With mixed positions 2-byte elements are still brought to 4 bytes if their parity agrees; else
+// the pointers stay and the odd ones are read with 2-byte aligned 128-bit loads.
+// *line = the alignment they have afterwards: 16, 4 or 1 bytes (1: that of their elements).
+unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* line_out)
+{
+    uintptr_t differ = 0;                                  // address bits in which the pointers differ
+    for (int q = 1; q < p; ++q) differ |= (uintptr_t)g.ptr[q] ^ (uintptr_t)g.ptr[0];
+    const uintptr_t line = (differ & 15) == 0 ? 16 : (differ & 3) == 0 ? 4 : 1;
+    const uintptr_t back = (uintptr_t)g.ptr[0] & (line - 1);
+    *line_out = (unsigned)line;
+    for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] - back;
+    return (unsigned)(back / (uintptr_t)elem_bytes);
+}
+
 template <int KIND, int VEC, int P, bool ACCUM, bool SA>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
                const Shape& sh, hipStream_t st)
@@ -1229,9 +1251,10 @@ int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count
 }
 
 template <int KIND>
-int rsa_launch_kind(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, bool accumulate,
-                    hipStream_t st)
+int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate, hipStream_t st)
 {
+    unsigned line = 0;
+    const unsigned lead = align_gradient_pointers(g, p, GradFormat<KIND>::kElemBytes, &line);
     constexpr size_t PD = GradFormat<KIND>::kPerDword;
     unsigned blocks = 0;
     // small message on a group of more than 64: one dword per lane and buffer, the buffers split
@@ -1255,18 +1278,16 @@ int rsa_launch_kind(float* acc, const PtrTable& g, int p, unsigned lead, size_t 
     const bool streamed = stream_acc(count, p);
     const size_t traffic = count * ((size_t)GradFormat<KIND>::kElemBytes * (size_t)p + 8);
     Shape sh = shape_of(kFamReduce, streamed, traffic, p + 2, 18);
-    // Single-wavefront workgroups are the fastest when every access is 16-byte aligned; with the
-    // accumulator or the gradients off that alignment full-size workgroups are (6070 against
-    // 5740 GB/s at 50 M elements).  A call too small to give every compute unit half a
+    // Single-wavefront workgroups are the fastest when every gradient load is 16-byte aligned, with
+    // those off that alignment full-size workgroups are (6070 against 5740 GB/s at 50 M elements).
+    // A call too small to give every compute unit half a
     // full-size workgroup runs in single wavefronts in any case, uncapped (a unit moves about
     // 100 GB/s on its own: 0.5 M elements at p = 16 take 5.3 us instead of 6.2).
     int cus = 0;
     if (int e = compute_units(&cus)) return e;
-    bool aligned16 = lead == 0 && ((uintptr_t)acc & 15) == 0;
-    for (int q = 0; q < p && aligned16; ++q) aligned16 = ((uintptr_t)g.ptr[q] & 15) == 0;
     if (g_lanes[kFamReduce].load() == 0) {
         if (nlanes * 2 <= (size_t)kMaxBlock * (size_t)cus) sh = Shape{64, 0};
-        else if (!aligned16) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
+        else if (line != 16) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
     }
     // binary16 gradients cost a conversion per element: the arithmetic then needs every wavefront
     // that fits (p = 16, 50 M elements: 6430 GB/s uncapped, 4450 with 10 wavefronts per unit)
@@ -1287,36 +1308,16 @@ int rsa_launch_kind(float* acc, const PtrTable& g, int p, unsigned lead, size_t 
     });
 }
 
-// Rounds 2-byte element pointers down to 4 bytes when all of them sit at the same position
-// inside their dword (rank g's slices of separately allocated buffers do: they all start g*S
-// elements in); returns how many elements they moved back (the kernels' `lead`, 0 or 1).  With
-// mixed positions the pointers stay and the odd ones are read with 2-byte aligned 128-bit loads
-// (about 20 % slower).  Rounding further down, to 16 bytes, was measured too: no gain at
-// p = 16 and a 5 % loss at p = 32, the accumulator then being addressed further off its own
-// alignment.
-unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes)
-{
-    if (elem_bytes != 2) return 0;
-    const uintptr_t odd = (uintptr_t)g.ptr[0] & 2;
-    for (int q = 1; q < p; ++q)
-        if (((uintptr_t)g.ptr[q] & 2) != odd) return 0;
-    if (!odd) return 0;
-    for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] - 2;
-    return 1;
-}
-
 }  // namespace
 
 int launch_reduce_scatter_accum(float* acc, const PtrTable& grads, size_t count, int p, bool accumulate,
                                 int kind, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    PtrTable g = grads;
-    const unsigned lead = align_gradient_pointers(g, p, kind == 2 ? 4 : 2);
     switch (kind) {
-        case 0: return rsa_launch_kind<0>(acc, g, p, lead, count, accumulate, st);
-        case 1: return rsa_launch_kind<1>(acc, g, p, lead, count, accumulate, st);
-        default: return rsa_launch_kind<2>(acc, g, p, lead, count, accumulate, st);
+        case 0: return rsa_launch_kind<0>(acc, grads, p, count, accumulate, st);
+        case 1: return rsa_launch_kind<1>(acc, grads, p, count, accumulate, st);
+        default: return rsa_launch_kind<2>(acc, grads, p, count, accumulate, st);
     }
 }
 
@@ -1448,30 +1449,28 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
                           hipStream_t st)
 {
     constexpr size_t GB = GradFormat<KIND>::kElemBytes, EPL = 4 * GradFormat<KIND>::kPerDword;
-    const size_t base_lead = align_gradient_pointers(g, p, (int)GB);
+    unsigned line = 0;
+    const size_t base_lead = align_gradient_pointers(g, p, (int)GB, &line);
+    const size_t unit = line == 16 ? EPL : 4 / GB;             // elements that a segment's lead is counted in
     for (int first = 0; first < n; first += kMaxSeg) {
         ReduceSegTable tab;
         tab.n = n - first < kMaxSeg ? n - first : kMaxSeg;
         size_t elements = 0;
         for (int t = 0; t < tab.n; ++t) elements += segs[first + t].numel;
         const bool streamed = stream_acc(elements, p);
-        // as in rsa_launch_kind: single-wavefront workgroups if every access is 16-byte aligned
+        // as in rsa_launch_kind: single-wavefront workgroups if every gradient load is 16-byte aligned
         // (h = 8192 layer: 6460 against 6220 GB/s), full-size ones otherwise; binary16 uncapped
         Shape sh = shape_of(kFamReduce, streamed, elements * (GB * (size_t)p + 8), p + 2, 18);
-        bool aligned16 = base_lead == 0 && ((uintptr_t)acc & 15) == 0;
-        for (int q = 0; q < p && aligned16; ++q) aligned16 = ((uintptr_t)g.ptr[q] & 15) == 0;
-        for (int t = 0; t < tab.n && aligned16; ++t)
-            aligned16 = segs[first + t].src_offset % (16 / GB) == 0 && segs[first + t].dst_offset % 4 == 0;
-        if (!aligned16 && g_lanes[kFamReduce].load() == 0) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
+        if (line != 16 && g_lanes[kFamReduce].load() == 0) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
         if (KIND == 1 && g_waves[kFamReduce].load() == 0) sh.waves_per_cu = 0;
         const size_t tile_elems = (size_t)sh.lanes * EPL;
         size_t tiles = 0;
         for (int t = 0; t < tab.n; ++t) {
             const Segment& sg = segs[first + t];
-            // position of the segment's first element in the (for 2-byte gradients rounded-down)
-            // buffers; its virtual element 0 is the 4-byte aligned position at or below it
+            // position of the segment's first element in the rounded-down buffers; its virtual
+            // element 0 is the 16-byte (4-byte: see align_gradient_pointers) aligned one at or below it
             const size_t src = sg.src_offset + base_lead;
-            const unsigned lead = GB == 2 ? (unsigned)(src & 1) : 0u;
+            const unsigned lead = (unsigned)(src % unit);
             tab.tile_begin[t] = (unsigned)tiles;
             tab.seg[t].lead = lead;
             tab.seg[t].pad = 0;

@@ -1,0 +1,65 @@
+"""Edges of the kernels' tiles, lines and dispatch rules, against the oracle (bit for bit: the
+contract fixes the order and the rounding of every operation)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+mics = pytest.importorskip("paper_2205_00119_amd")
+from gpu_util import Guarded  # noqa: E402
+
+FORMATS = {"bf16": (0, np.uint16), "f16": (1, np.uint16), "f32": (2, np.float32)}
+
+
+def grad_table(gen, name):
+    if name == "bf16":
+        return gen.normal_table(1e-3, "bf16")
+    if name == "f16":
+        return gen.normal_table(1e-2, "f32").astype(np.float16).view(np.uint16)
+    return gen.normal_table(1e-3, "f32")
+
+
+def rank_buffers(gen, name, p, n, skews, seed=4100):
+    tab = grad_table(gen, name)
+    host = [gen.fill_host(gen.stream_key(seed, gen.ROLE_GRAD, 0, 0, q), 0, n, tab) for q in range(p)]
+    dev = [Guarded(n, FORMATS[name][1], skew=skews[q % len(skews)], fill=h) for q, h in enumerate(host)]
+    return host, dev
+
+
+def start_acc(gen, n, skew=0):
+    ref = gen.fill_host(gen.stream_key(4101, gen.ROLE_ACC), 0, n, gen.normal_table(1e-2, "f32"))
+    return ref, Guarded(n, np.float32, skew=skew, fill=ref)
+
+
+def same_bits(dev, ref):
+    return np.array_equal(dev.numpy().view(np.uint32), ref.view(np.uint32)) and dev.guards_intact()
+
+
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [3, 16, 48, 72])
+def test_reduce_at_every_position_inside_a_line(orc, gen, name, p):
+    """Gradient pointers are rounded down to 16 bytes: every position inside the line, at counts
+    around a lane's, a wavefront's and a workgroup's elements, flat and as segments of one call."""
+    code = FORMATS[name][0]
+    for phase in range(8 if name != "f32" else 4):
+        for count in (1, 6, 8, 9, 511, 513, 4099):
+            host, dev = rank_buffers(gen, name, p, phase + count + 3, [0])
+            for accumulate in (False, True):
+                ref, acc = start_acc(gen, count, skew=phase % 3)
+                mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], phase, count, accumulate, code)
+                orc.reduce_scatter_accum_typed(ref, host, phase, accumulate, code)
+                torch.cuda.synchronize()
+                assert same_bits(acc, ref), (phase, count, accumulate)
+    numels, src, dst, segs = (1, 8, 515, 7, 1030), 0, 0, []
+    for i, n in enumerate(numels):
+        src += i                                            # segments start at changing positions
+        segs.append((n, 0, src, dst))
+        src, dst = src + n, dst + n
+    for skew in (0, 1, 5):
+        host, dev = rank_buffers(gen, name, p, src + 2, [skew])
+        ref, acc = start_acc(gen, dst, skew=1)
+        mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, True, code)
+        orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, True, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), skew
