@@ -63,21 +63,6 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #ifndef MICS_REORDER_NTS
 #define MICS_REORDER_NTS 1
 #endif
-#ifndef MICS_RSA_BLOCK
-#define MICS_RSA_BLOCK 64
-#endif
-#ifndef MICS_RSA_UNALIGNED_BLOCK
-#define MICS_RSA_UNALIGNED_BLOCK 512     // gradients off 16 bytes: 6070 against 5740 with 64
-#endif
-#ifndef MICS_RSA_WAVES
-#define MICS_RSA_WAVES 10
-#endif
-#ifndef MICS_RSA_WAVES_STREAMED
-#define MICS_RSA_WAVES_STREAMED 4
-#endif
-#ifndef MICS_RSA_STREAM_FROM_P
-#define MICS_RSA_STREAM_FROM_P 32
-#endif
 #ifndef MICS_RSA_BPC
 #define MICS_RSA_BPC 4096
 #endif
@@ -209,6 +194,29 @@ __device__ __forceinline__ void st_f32(float* p, const float (&a)[N])
             MICS_ST(NT, (f32x4_a4*)p + h, t);
         }
     }
+}
+
+// Cache policy bits of a gfx950 buffer store: sc0 + sc1 = system scope, the store is written through
+// the L2 at once instead of being left there for a later write-back.
+constexpr int kWriteThrough = 17, kNonTemporal = 2;
+
+// How a reduction writes its accumulator (accum_policy): non-temporal stores, write-through stores
+// from the wavefronts that write whole 128-byte lines, or write-through stores everywhere.
+enum { kThroughNever = 0, kThroughLines = 1, kThroughAlways = 2 };
+
+// A buffer descriptor over `bytes` bytes from a wavefront-uniform address.  Stores outside are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(void* base, int bytes)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)base);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)base >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((uintptr_t)hi << 32 | lo), 0, bytes, 0x00027000);
+}
+
+// `through` is wavefront-uniform.
+__device__ __forceinline__ void store_out(__amdgpu_buffer_rsrc_t to, unsigned byte, f32x4 v, bool through)
+{
+    if (through) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to, (int)byte, 0, kWriteThrough);
+    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to, (int)byte, 0, kNonTemporal);
 }
 
 // fp32 -> bf16, round to nearest even, two at a time (gfx950 converts a pair
@@ -579,6 +587,11 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             #pragma unroll
             for (int b = 0; b < BATCH; ++b)
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
+            // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
+            // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
+            // loads it keeps about 10 in flight by itself, and more cost occupancy (p = 16, 7.5 M: 52.4
+            // against 50.7 us).
+            if constexpr (P <= 8) __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 if (q0 + b < P) {
@@ -606,19 +619,14 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
 }
 
 // a[0 .. EPL) = (ACCUM ? acc_e[0 .. EPL) : +0) + partial sum at virtual element `elem`.
-// SA ("stream the accumulator"): non-temporal accumulator loads and stores.  An accumulator
-// that fits the 256 MB Infinity Cache is best left cacheable -- its stores are absorbed there
-// and the next micro-step finds it again (plain/plain 6.3 TB/s, NT/NT 6.1 at S = 50 M) -- while
-// a larger one is best streamed past the caches (NT/NT 5.8 TB/s, plain/plain 5.4, and the
-// mixed NT-load/plain-store 5.1 at S = 200 M); the launcher picks by size.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool SA, typename Tab>
+template <int KIND, int VEC, int P, int BATCH, bool ACCUM, typename Tab>
 __device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const float* acc_e,
                                         const Tab& g, int p, size_t elem)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
-    if (ACCUM) ld_f32<EPL, SA>(a, acc_e);          // issued before the gradient loads are consumed
+    if (ACCUM) ld_f32<EPL, VEC == 4>(a, acc_e);     // issued before the gradient loads are consumed
     float s[EPL];
     rsa_partial<KIND, VEC, P, BATCH>(s, g, p, elem);
     #pragma unroll
@@ -651,41 +659,49 @@ __device__ __forceinline__ void rsa_element(float* acc_e, const Tab& g, int p, s
 // find nothing to do).  A lane whose elements are not all inside the range does nothing:
 // those elements -- fewer than EPL at either end -- are rsa_edges' work.
 //
-// Streamed accumulators of 8-element lanes are stored through LDS: a lane's two 128-bit
-// stores are 32 bytes apart, so each store instruction of the wavefront would fill every
-// other 16 bytes of its cache lines, and with non-temporal stores about one line in ten left
-// the L2 between the two halves (WRITE_SIZE 1.10 x the accumulator's bytes at 800 M elements).
-// Passing the results through 2 KiB of LDS per wavefront lets every store instruction cover
-// one contiguous KiB.  Only wavefronts whose 64 lanes all hold full vectors take this path.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool SA, typename Tab>
+// Accumulators of 8-element lanes are stored through LDS: a lane's two 128-bit stores are 32
+// bytes apart, so each store instruction of the wavefront would fill every other 16 bytes of its
+// cache lines, which leave the L2 between the two halves.  Passing the results through 2 KiB of LDS
+// per wavefront lets every store instruction cover one contiguous KiB.  Vector j of the wavefront's
+// 128 holds half of the elements of lane j / 2.
+template <int KIND, int VEC, int P, int BATCH, bool ACCUM, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
-                                         size_t lead, size_t end)
+                                         size_t lead, size_t end, int through)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const bool full = v0 >= lead && v0 + EPL <= end;
-    if constexpr (SA && EPL == 8) {
-        if (__builtin_amdgcn_ballot_w64(full) == ~0ull) {       // wavefront-uniform
+    float a[EPL];
+    if constexpr (VEC == 4) {
+        const unsigned lane = threadIdx.x & 63u;
+        const size_t wave_v0 = v0 - EPL * lane;
+        float* const wave_acc = acc + (wave_v0 - lead);
+        const __amdgpu_buffer_rsrc_t out = wave_buffer(wave_acc, 64 * EPL * 4);
+        const bool wt = through == kThroughAlways ||
+                        (through == kThroughLines && (__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)wave_acc) & 127) == 0);
+        if constexpr (EPL == 4) {
+            if (full) {
+                rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
+                store_out(out, 16 * lane, f32x4{a[0], a[1], a[2], a[3]}, wt);
+            }
+        } else {
             extern __shared__ f32x4 stage[];                     // blockDim.x * 2 vectors (launcher)
-            const unsigned lane = threadIdx.x & 63u;
             f32x4* mine = stage + (threadIdx.x - lane) * 2;      // this wavefront's 128 vectors
-            float* acc_e = acc + (v0 - lead);
-            float a[EPL];
-            rsa_sum<KIND, VEC, P, BATCH, ACCUM, SA>(a, acc_e, g, p, src0 + v0);
-            mine[2 * lane] = f32x4{a[0], a[1], a[2], a[3]};
-            mine[2 * lane + 1] = f32x4{a[4], a[5], a[6], a[7]};
+            if (full) {
+                rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
+                mine[2 * lane] = f32x4{a[0], a[1], a[2], a[3]};
+                mine[2 * lane + 1] = f32x4{a[4], a[5], a[6], a[7]};
+            }
             // LDS operations of one wavefront complete in order: no barrier between these
-            const f32x4 r0 = mine[lane], r1 = mine[64 + lane];
-            f32x4_a4* wave_base = (f32x4_a4*)(acc_e - 8 * lane);
-            MICS_ST(true, wave_base + lane, r0);
-            MICS_ST(true, wave_base + 64 + lane, r1);
-            return;
+            __builtin_amdgcn_wave_barrier();
+            #pragma unroll
+            for (unsigned h = 0; h < 2; ++h) {
+                const size_t owner = wave_v0 + 256 * h + 8 * (lane / 2);
+                if (owner >= lead && owner + 8 <= end) store_out(out, 1024 * h + 16 * lane, mine[64 * h + lane], wt);
+            }
         }
-    }
-    if (full) {
-        float* acc_e = acc + (v0 - lead);
-        float a[EPL];
-        rsa_sum<KIND, VEC, P, BATCH, ACCUM, SA>(a, acc_e, g, p, src0 + v0);
-        st_f32<EPL, SA>(acc_e, a);
+    } else if (full) {
+        rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
+        st_f32<EPL, false>(acc + (v0 - lead), a);
     }
 }
 
@@ -708,9 +724,9 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
-template <int KIND, int VEC, int P, bool ACCUM, bool SA, typename Tab>
+template <int KIND, int VEC, int P, bool ACCUM, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
-    float* __restrict__ acc, Tab g, int p, unsigned lead, size_t count)
+    float* __restrict__ acc, Tab g, int p, unsigned lead, size_t count, int through)
 {
     constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : MICS_NARROW_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
@@ -724,7 +740,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM, SA>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end);
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, through);
 }
 
 // Small messages on groups of more than 64: the one-dword-per-lane form with the buffers split
@@ -806,9 +822,9 @@ struct ReduceSegTable {
     ReduceSeg seg[kMaxSeg];
 };
 
-template <int KIND, int P, bool ACCUM, bool SA, typename Tab>
+template <int KIND, int P, bool ACCUM, typename Tab>
 __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
-    float* __restrict__ acc, Tab g, int p, ReduceSegTable tab)
+    float* __restrict__ acc, Tab g, int p, ReduceSegTable tab, int through)
 {
     constexpr int EPL = 4 * GradFormat<KIND>::kPerDword;
     const unsigned x = blockIdx.x;
@@ -816,7 +832,8 @@ __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
     const size_t end = tab.seg[t].end, lead = tab.seg[t].lead;
     const size_t v0 = ((size_t)(x - tab.tile_begin[t]) * blockDim.x + threadIdx.x) * EPL;
     if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
-    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM, SA>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end);
+    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end,
+                                                through);
 }
 
 // ---------------------------------------------------------------------------
@@ -1018,22 +1035,38 @@ __global__ __launch_bounds__(kMaxBlock) void avg_adam_kernel(
 // ---------------------------------------------------------------------------
 
 std::atomic<int> g_blocks_per_cu{0};
-// Built-in policy: accumulators (reduce) and outputs (replica average) of up to 224 MiB -- what
-// the 256 MB Infinity Cache absorbs -- are left cacheable, larger ones are streamed (see
-// rsa_sum); the accumulator of a reduction over 32 or more buffers is always streamed.  There
-// it is at most 8 of 72 bytes per element, so a cache hit saves little, while the orderly write
-// path of the streaming kernels is worth more (p = 32, 9.8 M elements, the same accumulator on
-// consecutive calls: 5.76 TB/s cacheable, 6.02 streamed; fp32 gradients 6.18 / 6.51; p = 16,
-// 12.6 M elements: 6.38 / 6.12).  An explicit threshold (0 = none) replaces the policy.
+// Built-in policy for outputs (replica average) and the launch shapes of the update: up to 224 MiB
+// -- what the 256 MB Infinity Cache absorbs -- they are left cacheable, larger ones are streamed.
+// An explicit threshold (0 = none) replaces the policy.
 constexpr size_t kDefaultStreamBytes = 224u << 20;
-constexpr int kStreamFromGroup = MICS_RSA_STREAM_FROM_P;
 std::atomic<size_t> g_stream_bytes{0};
 
-inline bool stream_acc(size_t elements, int p = 0)
+inline bool stream_acc(size_t elements)
 {
     const size_t t = g_stream_bytes.load();
-    if (t) return elements * 4 > t;
-    return elements * 4 > kDefaultStreamBytes || p >= kStreamFromGroup;
+    return elements * 4 > (t ? t : kDefaultStreamBytes);
+}
+
+// The accumulator is read with non-temporal loads and written through the L2 (sc0 sc1): the next
+// micro-step finds it in the Infinity Cache if nothing has displaced it, and if something has, the
+// writes have reached memory in the order of the stream.  us per call, accumulator resident on
+// consecutive calls / not:
+//                                 plain          NT loads,       NT loads, write-
+//                                                NT stores       through stores
+//   p = 16, 50 M elements (201 MB)  304 / 335    311 / 311       291 / 315
+//   p = 8,  25 M (101 MB)           89  / 103    97  / 97        88  / 96
+//   p = 8,  9.8 M (39 MB)           40.2 / 40.0  40.0 / 38.9     36.5 / 37.0
+// Non-temporal stores win where the accumulator is beyond the 224 MiB that the cache absorbs (p = 8,
+// 101 M elements: 364 against 375), for 32 and more buffers beyond 64 MiB (p = 32, 25 M: 289, 302),
+// and where the lines at the two ends of a wavefront's piece are not whole (accumulator off 128
+// bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read and
+// the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).
+int accum_policy(size_t count, int p)
+{
+    constexpr size_t kSmall = 64u << 20;
+    if (stream_acc(count)) return kThroughNever;
+    if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kThroughNever;
+    return p < 16 && count * 4 <= kSmall ? kThroughAlways : kThroughLines;
 }
 
 int compute_units(int* out)
@@ -1102,7 +1135,7 @@ struct Shape {
 };
 constexpr Shape kDefaultShape[kFamilies][2] = {
     /* reorder */ {{MICS_REORDER_BLOCK, 0}, {MICS_REORDER_BLOCK, 0}},
-    /* reduce  */ {{MICS_RSA_BLOCK, MICS_RSA_WAVES}, {MICS_RSA_BLOCK, MICS_RSA_WAVES_STREAMED}},
+    /* reduce  */ {{64, 0}, {64, 0}},                         // see reduce_shape
     /* average */ {{MICS_AVG_BLOCK, MICS_AVG_WAVES}, {MICS_AVG_BLOCK, MICS_AVG_WAVES_STREAMED}},
     /* Adam    */ {{MICS_ADAM_BLOCK, MICS_ADAM_WAVES}, {MICS_ADAM_BLOCK, MICS_ADAM_WAVES_STREAMED}},
     /* fused   */ {{MICS_FUSED_BLOCK, MICS_FUSED_WAVES}, {MICS_FUSED_BLOCK, MICS_FUSED_WAVES_STREAMED}},
@@ -1150,12 +1183,11 @@ size_t lds_for(const Shape& sh, size_t needed = 0)
     return bytes > needed ? bytes : needed;
 }
 
-// Calls f(std::bool_constant<a>, std::bool_constant<b>) for two runtime flags.
+// Calls f(std::bool_constant<a>) for a runtime flag.
 template <typename F>
-int dispatch2(bool a, bool b, F&& f)
+int dispatch_bool(bool a, F&& f)
 {
-    if (a) return b ? f(std::true_type{}, std::true_type{}) : f(std::true_type{}, std::false_type{});
-    return b ? f(std::false_type{}, std::true_type{}) : f(std::false_type{}, std::false_type{});
+    return a ? f(std::true_type{}) : f(std::false_type{});
 }
 
 template <int N>
@@ -1236,18 +1268,66 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
     return (unsigned)(back / (uintptr_t)elem_bytes);
 }
 
-template <int KIND, int VEC, int P, bool ACCUM, bool SA>
+// Launch shape of a reduction over p buffers with `nlanes` lanes of work.  Measured per call on
+// buffers that rotate through 1 GB, p = 1 .. 128, 16 MB .. 1.6 GB of traffic, three formats; the lines
+// below lie where the best shape changes, and the shapes next to the chosen one lose 1 to 3 %.
+//   - From some 0.8 M lanes on, single-wavefront workgroups with a cap on the wavefronts of a compute
+//     unit that falls with the buffers a lane reads: what counts is the number of request streams
+//     (p = 8, 33 M elements: 64 x 10 121 us, 512 x 32 129; p = 32, 11 M: 64 x 6 132, 64 x 16 143,
+//     512 x 32 149).  The line moves down for 32 and more buffers (0.6 M; p = 32, 5.6 M elements: 64 x 6
+//     71, 512 x 32 74), up for 12 to 24 buffers of 2-byte elements (1.2 M; p = 12, 7.8 M elements:
+//     64 x 10 44.5, 512 x 32 42.9), and up again where the accumulator is off 16 bytes in the lanes'
+//     grid, because the partial lines between two wavefronts then meet in one workgroup (2 M for p < 16;
+//     p = 8, 9.8 M: 64 x 10 40.7, 512 x 32 39.2; 30 M: 114, 119).  Gradients off 16 bytes: 512 x 16
+//     (p = 16, 50 M: 344, 64 x 8 350).
+//   - Below, where a compute unit gets fewer than four full-size workgroups, all run at once and the
+//     slowest unit decides: the largest workgroups whose rounded-up number per unit wastes at most
+//     12 % (p = 64, 1.1 M elements, 269 workgroups of 512 lanes on 256 units: 34.6 us, of 64 lanes
+//     27.6; p = 16, 2.5 M: 512 lanes 19.7, 256 lanes 18.8; p = 8, 4.2 M, where 512 fits: 17.2, 64
+//     lanes 18.4).
+//   - A call that gives a compute unit less than half a full-size workgroup runs in single wavefronts:
+//     a unit moves about 100 GB/s on its own (0.5 M elements at p = 16: 5.3 us instead of 6.2).
+int reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, Shape* out)
+{
+    int cus = 0;
+    if (int e = compute_units(&cus)) return e;
+    const size_t units = (size_t)cus;
+    const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
+    Shape sh = {64, 0};
+    if (nlanes >= units * many) {
+        if (grads16) sh.waves_per_cu = p < 4 ? 0 : p < 6 ? (nlanes < units * 12000 ? 0 : 16) : p < 8 ? 14 : p < 16 ? 10 : p < 32 ? 8 : 6;
+        else sh = Shape{kMaxBlock, 16};
+    } else if (nlanes >= units * (4 * kMaxBlock)) {
+        sh.lanes = kMaxBlock;
+    } else if (nlanes * 2 > (size_t)kMaxBlock * units) {
+        // lanes that the fullest compute unit is given, against an even share
+        auto waste = [&](size_t lanes) {
+            const size_t wgs = (nlanes + lanes - 1) / lanes;
+            return (double)((wgs + units - 1) / units * units * lanes) / (double)nlanes;
+        };
+        if (waste(512) <= 1.12) sh.lanes = 512;
+        else if (waste(256) <= 1.12) sh.lanes = 256;
+        else if (p >= 6) sh.waves_per_cu = 16;
+    }
+    if (const int l = g_lanes[kFamReduce].load()) sh.lanes = l;
+    if (const int w = g_waves[kFamReduce].load()) sh.waves_per_cu = w;
+    if (sh.waves_per_cu >= 32) sh.waves_per_cu = 0;
+    *out = sh;
+    return 0;
+}
+
+template <int KIND, int VEC, int P, bool ACCUM>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
                const Shape& sh, hipStream_t st)
 {
-    // the streamed-accumulator kernels pass their results through 32 bytes of LDS per lane
-    const size_t lds = lds_for(sh, SA && VEC == 4 && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
+    // lanes of 8 elements pass their results through 32 bytes of LDS
+    const size_t lds = lds_for(sh, VEC == 4 && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
     if constexpr (P > 0)
-        return launch(rsa_kernel<KIND, VEC, P, ACCUM, SA, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
-                      acc, small<P>(g), p, lead, count);
+        return launch(rsa_kernel<KIND, VEC, P, ACCUM, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
+                      acc, small<P>(g), p, lead, count, accum_policy(count, p));
     else
-        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, SA, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, acc,
-                      g, p, lead, count);
+        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, acc,
+                      g, p, lead, count, accum_policy(count, p));
 }
 
 template <int KIND>
@@ -1271,40 +1351,18 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
         const Shape narrow = {kNarrowBlock, 0};
         const size_t nlanes = (lead + count + PD - 1) / PD;
         if (int e = grid_for(nlanes, kNarrowBlock, MICS_RSA_BPC, &blocks)) return e;
-        return accumulate ? rsa_launch<KIND, 1, 0, true, false>(acc, g, p, lead, count, blocks, narrow, st)
-                          : rsa_launch<KIND, 1, 0, false, false>(acc, g, p, lead, count, blocks, narrow, st);
+        return accumulate ? rsa_launch<KIND, 1, 0, true>(acc, g, p, lead, count, blocks, narrow, st)
+                          : rsa_launch<KIND, 1, 0, false>(acc, g, p, lead, count, blocks, narrow, st);
     }
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
-    const bool streamed = stream_acc(count, p);
-    const size_t traffic = count * ((size_t)GradFormat<KIND>::kElemBytes * (size_t)p + 8);
-    Shape sh = shape_of(kFamReduce, streamed, traffic, p + 2, 18);
-    // Single-wavefront workgroups are the fastest when every gradient load is 16-byte aligned, with
-    // those off that alignment full-size workgroups are (6070 against 5740 GB/s at 50 M elements).
-    // A call too small to give every compute unit half a
-    // full-size workgroup runs in single wavefronts in any case, uncapped (a unit moves about
-    // 100 GB/s on its own: 0.5 M elements at p = 16 take 5.3 us instead of 6.2).
-    int cus = 0;
-    if (int e = compute_units(&cus)) return e;
-    if (g_lanes[kFamReduce].load() == 0) {
-        if (nlanes * 2 <= (size_t)kMaxBlock * (size_t)cus) sh = Shape{64, 0};
-        else if (line != 16) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
-    }
-    // binary16 gradients cost a conversion per element: the arithmetic then needs every wavefront
-    // that fits (p = 16, 50 M elements: 6430 GB/s uncapped, 4450 with 10 wavefronts per unit)
-    if (KIND == 1 && g_waves[kFamReduce].load() == 0) sh.waves_per_cu = 0;
+    Shape sh;
+    const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
+    if (int e = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line == 16, acc16, &sh)) return e;
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
-    return dispatch2(accumulate, streamed, [&](auto A, auto SA) {
-        if constexpr (KIND == 0) {
-            return dispatch_group(p, [&](auto P) {
-                return rsa_launch<KIND, 4, P.value, A.value, SA.value>(acc, g, p, lead, count, blocks, sh, st);
-            });
-        } else {
-            switch (p) {
-                case 8: return rsa_launch<KIND, 4, 8, A.value, SA.value>(acc, g, p, lead, count, blocks, sh, st);
-                case 16: return rsa_launch<KIND, 4, 16, A.value, SA.value>(acc, g, p, lead, count, blocks, sh, st);
-                default: return rsa_launch<KIND, 4, 0, A.value, SA.value>(acc, g, p, lead, count, blocks, sh, st);
-            }
-        }
+    return dispatch_bool(accumulate, [&](auto A) {
+        return dispatch_group(p, [&](auto P) {
+            return rsa_launch<KIND, 4, P.value, A.value>(acc, g, p, lead, count, blocks, sh, st);
+        });
     });
 }
 
@@ -1330,7 +1388,7 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_AVG_BPC, &blocks)) return e;
     const dim3 gr(blocks), bl(sh.lanes);
-    return dispatch2(streamed, false, [&](auto SO, auto) {
+    return dispatch_bool(streamed, [&](auto SO) {
         switch (r) {
             case 1: return launch(avg_kernel<1, SO.value, SmallTable<1>>, gr, bl, lds, st, out, small<1>(a), r, scale, count);
             case 2: return launch(avg_kernel<2, SO.value, SmallTable<2>>, gr, bl, lds, st, out, small<2>(a), r, scale, count);
@@ -1457,12 +1515,13 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         tab.n = n - first < kMaxSeg ? n - first : kMaxSeg;
         size_t elements = 0;
         for (int t = 0; t < tab.n; ++t) elements += segs[first + t].numel;
-        const bool streamed = stream_acc(elements, p);
-        // as in rsa_launch_kind: single-wavefront workgroups if every gradient load is 16-byte aligned
-        // (h = 8192 layer: 6460 against 6220 GB/s), full-size ones otherwise; binary16 uncapped
-        Shape sh = shape_of(kFamReduce, streamed, elements * (GB * (size_t)p + 8), p + 2, 18);
-        if (line != 16 && g_lanes[kFamReduce].load() == 0) sh = Shape{MICS_RSA_UNALIGNED_BLOCK, 0};
-        if (KIND == 1 && g_waves[kFamReduce].load() == 0) sh.waves_per_cu = 0;
+        Shape sh;
+        bool acc16 = true;
+        for (int t = 0; t < tab.n; ++t) {
+            const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
+            acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
+        }
+        if (int e = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line == 16, acc16, &sh)) return e;
         const size_t tile_elems = (size_t)sh.lanes * EPL;
         size_t tiles = 0;
         for (int t = 0; t < tab.n; ++t) {
@@ -1483,26 +1542,19 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         }
         for (int t = tab.n; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
         if (tiles == 0) continue;
-        const int err = dispatch2(accumulate, streamed, [&](auto A, auto SA) {
-            // the streamed-accumulator kernels pass their results through 32 bytes of LDS per lane
-            const size_t lds = lds_for(sh, SA.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
+        const int through = accum_policy(elements, p);
+        const int err = dispatch_bool(accumulate, [&](auto A) {
+            // lanes of 8 elements pass their results through 32 bytes of LDS
+            const size_t lds = lds_for(sh, EPL == 8 ? (size_t)sh.lanes * 32 : 0);
             const dim3 gr((unsigned)tiles), bl(sh.lanes);
-            if constexpr (KIND == 0) {
-                return dispatch_group(p, [&](auto P) {
-                    if constexpr (P.value > 0)
-                        return launch(rsa_seg_kernel<KIND, P.value, A.value, SA.value, SmallTable<P.value>>, gr, bl,
-                                      lds, st, acc, small<P.value>(g), p, tab);
-                    else
-                        return launch(rsa_seg_kernel<KIND, 0, A.value, SA.value, PtrTable>, gr, bl, lds, st, acc, g,
-                                      p, tab);
-                });
-            } else {
-                switch (p) {
-                    case 8: return launch(rsa_seg_kernel<KIND, 8, A.value, SA.value, SmallTable<8>>, gr, bl, lds, st, acc, small<8>(g), p, tab);
-                    case 16: return launch(rsa_seg_kernel<KIND, 16, A.value, SA.value, SmallTable<16>>, gr, bl, lds, st, acc, small<16>(g), p, tab);
-                    default: return launch(rsa_seg_kernel<KIND, 0, A.value, SA.value, PtrTable>, gr, bl, lds, st, acc, g, p, tab);
-                }
-            }
+            return dispatch_group(p, [&](auto P) {
+                if constexpr (P.value > 0)
+                    return launch(rsa_seg_kernel<KIND, P.value, A.value, SmallTable<P.value>>, gr, bl, lds, st, acc,
+                                  small<P.value>(g), p, tab, through);
+                else
+                    return launch(rsa_seg_kernel<KIND, 0, A.value, PtrTable>, gr, bl, lds, st, acc, g, p, tab,
+                                  through);
+            });
         });
         if (err) return err;
     }

@@ -63,3 +63,21 @@ def test_reduce_at_every_position_inside_a_line(orc, gen, name, p):
         orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, True, code)
         torch.cuda.synchronize()
         assert same_bits(acc, ref), skew
+
+
+@pytest.mark.parametrize("p,count", [(6, 530001), (6, 1250003), (6, 2500000), (6, 4194311), (6, 6600001), (16, 1250001)])
+@pytest.mark.parametrize("threshold", [0, 1, 1 << 40])
+def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, threshold):
+    """Sizes on both sides of the launch rule's lines (64, 256 and 512 lanes, capped and not), with the
+    accumulator on and off the 128-byte lines that decide how it is stored."""
+    host, dev = rank_buffers(gen, "bf16", p, count + 9, [0])
+    try:
+        mics.mics_set_stream_threshold_bytes(threshold)
+        for offset, skew in ((0, 0), (3, 0), (0, 5)):
+            ref, acc = start_acc(gen, count, skew=skew)
+            mics.mics_reduce_scatter_accum(acc.t, [d.t for d in dev], offset, count, True)
+            orc.reduce_scatter_accum(ref, host, offset, True)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), (offset, skew)
+    finally:
+        mics.mics_set_stream_threshold_bytes(0)
