@@ -72,53 +72,17 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #ifndef MICS_RSA_BATCH
 #define MICS_RSA_BATCH 16
 #endif
-#ifndef MICS_AVG_BLOCK
-#define MICS_AVG_BLOCK 64
-#endif
-#ifndef MICS_AVG_WAVES
-#define MICS_AVG_WAVES 12
-#endif
-#ifndef MICS_AVG_WAVES_STREAMED
-#define MICS_AVG_WAVES_STREAMED 10
-#endif
 #ifndef MICS_AVG_BPC
 #define MICS_AVG_BPC 4096
 #endif
 #ifndef MICS_AVG_NTL
 #define MICS_AVG_NTL 1
 #endif
-#ifndef MICS_ADAM_BLOCK
-#define MICS_ADAM_BLOCK 64
-#endif
-#ifndef MICS_ADAM_WAVES
-#define MICS_ADAM_WAVES 12
-#endif
-#ifndef MICS_ADAM_WAVES_STREAMED
-#define MICS_ADAM_WAVES_STREAMED 9
-#endif
-#ifndef MICS_FUSED_BLOCK
-#define MICS_FUSED_BLOCK 64
-#endif
-#ifndef MICS_FUSED_WAVES
-#define MICS_FUSED_WAVES 6
-#endif
-#ifndef MICS_FUSED_WAVES_STREAMED
-#define MICS_FUSED_WAVES_STREAMED 5
-#endif
-#ifndef MICS_FUSED_COPIES_FIRST
-#define MICS_FUSED_COPIES_FIRST 1
-#endif
-#ifndef MICS_FUSED_NTL_COPIES
-#define MICS_FUSED_NTL_COPIES MICS_ADAM_NTL
-#endif
 #ifndef MICS_ADAM_BPC
 #define MICS_ADAM_BPC 4096
 #endif
 #ifndef MICS_ADAM_NTL
 #define MICS_ADAM_NTL 1
-#endif
-#ifndef MICS_ADAM_NTS
-#define MICS_ADAM_NTS 1
 #endif
 // Small messages on large groups (see rsa_kernel): workgroup size of the one-dword-per-lane
 // variant, the loads it keeps in flight, and the largest call (p * count buffer elements)
@@ -144,7 +108,7 @@ constexpr int kNarrowBlock = MICS_NARROW_BLOCK;
 constexpr bool kReorderNtl = MICS_REORDER_NTL, kReorderNts = MICS_REORDER_NTS;
 constexpr bool kRsaNtl = MICS_RSA_NTL;   // gradient loads; the accumulator's hint is chosen per launch
 constexpr bool kAvgNtl = MICS_AVG_NTL;   // input loads; the output's hint is chosen per launch
-constexpr bool kAdamNtl = MICS_ADAM_NTL, kAdamNts = MICS_ADAM_NTS;
+constexpr bool kAdamNtl = MICS_ADAM_NTL;
 
 // Compile-time sized pointer table for the unrolled kernels (keeps the
 // kernel-argument segment small); the launcher copies out of PtrTable.
@@ -212,11 +176,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(void* base, int by
     return __builtin_amdgcn_make_buffer_rsrc((void*)((uintptr_t)hi << 32 | lo), 0, bytes, 0x00027000);
 }
 
-// `through` is wavefront-uniform.
-__device__ __forceinline__ void store_out(__amdgpu_buffer_rsrc_t to, unsigned byte, f32x4 v, bool through)
+template <int POLICY>
+__device__ __forceinline__ void store_vec(__amdgpu_buffer_rsrc_t to, unsigned byte, f32x4 v)
 {
-    if (through) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to, (int)byte, 0, kWriteThrough);
-    else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to, (int)byte, 0, kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), to, (int)byte, 0, POLICY);
 }
 
 // fp32 -> bf16, round to nearest even, two at a time (gfx950 converts a pair
@@ -681,7 +644,8 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
         if constexpr (EPL == 4) {
             if (full) {
                 rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
-                store_out(out, 16 * lane, f32x4{a[0], a[1], a[2], a[3]}, wt);
+                if (wt) store_vec<kWriteThrough>(out, 16 * lane, f32x4{a[0], a[1], a[2], a[3]});
+                else st_f32<EPL, true>(acc + (v0 - lead), a);
             }
         } else {
             extern __shared__ f32x4 stage[];                     // blockDim.x * 2 vectors (launcher)
@@ -696,7 +660,11 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             #pragma unroll
             for (unsigned h = 0; h < 2; ++h) {
                 const size_t owner = wave_v0 + 256 * h + 8 * (lane / 2);
-                if (owner >= lead && owner + 8 <= end) store_out(out, 1024 * h + 16 * lane, mine[64 * h + lane], wt);
+                if (owner >= lead && owner + 8 <= end) {
+                    const f32x4 v = mine[64 * h + lane];
+                    if (wt) store_vec<kWriteThrough>(out, 1024 * h + 16 * lane, v);
+                    else MICS_ST(true, (f32x4_a4*)(wave_acc + 256 * h) + lane, v);
+                }
             }
         }
     } else if (full) {
@@ -902,7 +870,9 @@ __global__ __launch_bounds__(kMaxBlock) void avg_kernel(
         const size_t x = 4 * i;
         if (x + 4 <= count) {
             const f32x4 sum = avg_sum4<R, kAvgNtl>(a, r, x);
-            MICS_ST(SO, (f32x4_a4*)(out + x), sum * scale);
+            const unsigned lane = threadIdx.x & 63u;
+            if constexpr (SO) MICS_ST(true, (f32x4_a4*)(out + x), sum * scale);
+            else store_vec<kWriteThrough>(wave_buffer(out + (x - 4 * lane), 1024), 16 * lane, sum * scale);
         }
     }
     // the last count mod 4 elements: one per lane
@@ -942,7 +912,7 @@ __device__ __forceinline__ void adam_element(float& w, float& m, float& v, float
 template <int OUT>
 __device__ __forceinline__ void adam_update4(float* master, float* exp_avg, float* exp_avg_sq,
                                              uint16_t* param_bf16, size_t x, f32x4 g, f32x4 w, f32x4 m,
-                                             f32x4 v, const AdamScalars& hp)
+                                             f32x4 v, const AdamScalars& hp, bool through)
 {
     #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -950,12 +920,20 @@ __device__ __forceinline__ void adam_update4(float* master, float* exp_avg, floa
         adam_element(we, me, ve, g[e], hp);
         w[e] = we; m[e] = me; v[e] = ve;
     }
-    MICS_ST(kAdamNts, (f32x4_a4*)(master + x), w);
-    MICS_ST(kAdamNts, (f32x4_a4*)(exp_avg + x), m);
-    MICS_ST(kAdamNts, (f32x4_a4*)(exp_avg_sq + x), v);
+    if (through) {                                             // wavefront-uniform
+        const unsigned lane = threadIdx.x & 63u;
+        const size_t x0 = x - 4 * lane;
+        store_vec<kWriteThrough | kNonTemporal>(wave_buffer(master + x0, 1024), 16 * lane, w);
+        store_vec<kWriteThrough | kNonTemporal>(wave_buffer(exp_avg + x0, 1024), 16 * lane, m);
+        store_vec<kWriteThrough | kNonTemporal>(wave_buffer(exp_avg_sq + x0, 1024), 16 * lane, v);
+    } else {
+        MICS_ST(true, (f32x4_a4*)(master + x), w);
+        MICS_ST(true, (f32x4_a4*)(exp_avg + x), m);
+        MICS_ST(true, (f32x4_a4*)(exp_avg_sq + x), v);
+    }
     if constexpr (OUT != kParamNone) {
         u32x2 b = {param_pack<OUT>(w.x, w.y), param_pack<OUT>(w.z, w.w)};
-        MICS_ST(kAdamNts, (u32x2_a2*)(param_bf16 + x), b);
+        MICS_ST(true, (u32x2_a2*)(param_bf16 + x), b);
     }
 }
 
@@ -978,7 +956,7 @@ __device__ __forceinline__ void adam_update1(float* master, float* exp_avg, floa
 template <int OUT>
 __global__ __launch_bounds__(kMaxBlock) void adam_kernel(
     float* __restrict__ master, float* __restrict__ exp_avg, float* __restrict__ exp_avg_sq,
-    uint16_t* __restrict__ param_bf16, const float* __restrict__ grad, size_t count, AdamScalars hp)
+    uint16_t* __restrict__ param_bf16, const float* __restrict__ grad, size_t count, AdamScalars hp, bool through)
 {
     const size_t nlanes = (count + 3) / 4;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -989,7 +967,7 @@ __global__ __launch_bounds__(kMaxBlock) void adam_kernel(
             const f32x4 w = MICS_LD(kAdamNtl, (const f32x4_a4*)(master + x));
             const f32x4 m = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg + x));
             const f32x4 v = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg_sq + x));
-            adam_update4<OUT>(master, exp_avg, exp_avg_sq, param_bf16, x, g, w, m, v, hp);
+            adam_update4<OUT>(master, exp_avg, exp_avg_sq, param_bf16, x, g, w, m, v, hp, through);
         } else {
             for (size_t e = x; e < count; ++e)
                 adam_update1<OUT>(master, exp_avg, exp_avg_sq, param_bf16, e, grad[e], hp);
@@ -1005,23 +983,35 @@ __global__ __launch_bounds__(kMaxBlock) void adam_kernel(
 template <int R, int OUT, typename Tab>
 __global__ __launch_bounds__(kMaxBlock) void avg_adam_kernel(
     float* __restrict__ master, float* __restrict__ exp_avg, float* __restrict__ exp_avg_sq,
-    uint16_t* __restrict__ param_bf16, Tab a, int r, float scale, size_t count, AdamScalars hp)
+    uint16_t* __restrict__ param_bf16, Tab a, int r, float scale, size_t count, AdamScalars hp, bool through)
 {
     const size_t nlanes = (count + 3) / 4;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nlanes; i += stride) {
         const size_t x = 4 * i;
         if (x + 4 <= count) {
-#if MICS_FUSED_COPIES_FIRST
-            const f32x4 sum = avg_sum4<R, MICS_FUSED_NTL_COPIES>(a, r, x);
-#endif
-            const f32x4 w = MICS_LD(kAdamNtl, (const f32x4_a4*)(master + x));
-            const f32x4 m = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg + x));
-            const f32x4 v = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg_sq + x));
-#if !MICS_FUSED_COPIES_FIRST
-            const f32x4 sum = avg_sum4<R, MICS_FUSED_NTL_COPIES>(a, r, x);
-#endif
-            adam_update4<OUT>(master, exp_avg, exp_avg_sq, param_bf16, x, sum * scale, w, m, v, hp);
+            f32x4 sum, w, m, v;
+            auto states = [&] {
+                w = MICS_LD(kAdamNtl, (const f32x4_a4*)(master + x));
+                m = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg + x));
+                v = MICS_LD(kAdamNtl, (const f32x4_a4*)(exp_avg_sq + x));
+            };
+            if constexpr (R > 0) {
+                // every load in flight before the first use: left to itself the compiler may trade the
+                // loads for registers (r = 8, 50 M elements: 514 against 440 us)
+                f32x4 c[R];
+                #pragma unroll
+                for (int i = 0; i < R; ++i) c[i] = MICS_LD(kAdamNtl, (const f32x4_a4*)((const float*)a.ptr[i] + x));
+                states();
+                __builtin_amdgcn_sched_barrier(0);
+                sum = c[0];
+                #pragma unroll
+                for (int i = 1; i < R; ++i) sum = sum + c[i];
+            } else {
+                sum = avg_sum4<0, kAdamNtl>(a, r, x);
+                states();
+            }
+            adam_update4<OUT>(master, exp_avg, exp_avg_sq, param_bf16, x, sum * scale, w, m, v, hp, through);
         }
     }
     // the last count mod 4 elements: one per lane
@@ -1046,6 +1036,11 @@ inline bool stream_acc(size_t elements)
     const size_t t = g_stream_bytes.load();
     return elements * 4 > (t ? t : kDefaultStreamBytes);
 }
+
+// The optimizer states are written non-temporally, and through the L2 as well (nt sc0 sc1) in calls
+// that no cache could hold: Adam, 50 M elements 227.4 -> 226.3 us, 101 M 456 -> 453; average + Adam,
+// 50 M, r = 2 257.3 -> 253.4, r = 4 322 -> 317, r = 8 442 -> 433.  A call at 150 to 250 MB loses 2 to 3 %.
+inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 
 // The accumulator is read with non-temporal loads and written through the L2 (sc0 sc1): the next
 // micro-step finds it in the Infinity Cache if nothing has displaced it, and if something has, the
@@ -1085,6 +1080,14 @@ int compute_units(int* out)
     return 0;
 }
 
+int compute_units(size_t* out)
+{
+    int n = 0;
+    const int e = compute_units(&n);
+    *out = (size_t)n;
+    return e;
+}
+
 // Workgroups of `block` lanes for `items` lane-sized work items: enough to cover them, at
 // most `bpc` per compute unit (the kernels stride over the rest).
 int grid_for(size_t items, int block, int bpc, unsigned* blocks)
@@ -1114,58 +1117,85 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStrea
     return (int)hipLaunchKernel((const void*)kernel, grid, block, ptrs, lds, st);
 }
 
-// Launch shape of a kernel family: lanes per workgroup and the most wavefronts a compute unit
-// may hold at a time (0 = whatever fits).
+// Launch shape: lanes per workgroup and the most wavefronts a compute unit may hold at a time (0 =
+// whatever fits).
 //
-// Measured on MI355X (same buffers, one process; GB/s of algorithmic bytes): these streaming
-// kernels run fastest in single-wavefront workgroups -- a finished wavefront's slot is refilled
-// at once instead of when the last of a workgroup's 8 wavefronts has finished -- and with fewer
-// wavefronts per compute unit than fit, i.e. with fewer but longer request streams at the memory
-// controllers.  lanes x wavefronts per compute unit (32 = no cap), at 50 M elements (outputs
-// fit the Infinity Cache) / 200 M elements (they do not):
-//   reorder (3.2 GB)  256x32 6335         64x32 6580          64x16 5990           64x8 3860
-//   reduce p = 16     512x32 6190 / 5790  64x32 6295 / 6050   64x10 6365 / 5985    64x4 6150 / 6150
-//   average r = 8     512x32 5935 / 5570  64x32 6325 / 6185   64x12 6370 / 6365    64x8 6140 / 6170
-//   Adam              128x32 6040 / 5715  64x32 5965 / 5830   64x12 6530 / 6305    64x10 6385 / 6510
-//   average + Adam    128x32 5845 / 5560  64x32 5910 / 5865   64x8  6235 / 6155    64x6 6395 / 6370
+// These streaming kernels run fastest in single-wavefront workgroups -- a finished wavefront's slot
+// is refilled at once instead of when the last of a workgroup's 8 wavefronts has finished -- and,
+// the reorder aside, with fewer wavefronts per compute unit than fit, i.e. with fewer but longer
+// request streams at the memory controllers.  Measured on MI355X (GB/s of algorithmic bytes; lanes
+// x wavefronts per compute unit, 32 = no cap; 50 M elements):
+//   reorder (3.2 GB)  256x32 6335  64x32 6580  64x16 5990  64x8  3860
+//   average r = 2                  64x32 6540  64x16 6470  64x12 6200
+//   average r = 8     512x32 5935  64x32 6325  64x10 6580  64x8  6650
+//   Adam              128x32 6040  64x32 5965  64x12 6670  64x10 6630
+//   average + Adam, r = 8          64x12 6290  64x8  6530  64x6  6740
 // The cap is enforced with otherwise unused dynamic LDS: a workgroup that asks for 1/n of a
 // compute unit's LDS shares the unit with at most n - 1 others.
 struct Shape {
     int lanes, waves_per_cu;
 };
-constexpr Shape kDefaultShape[kFamilies][2] = {
-    /* reorder */ {{MICS_REORDER_BLOCK, 0}, {MICS_REORDER_BLOCK, 0}},
-    /* reduce  */ {{64, 0}, {64, 0}},                         // see reduce_shape
-    /* average */ {{MICS_AVG_BLOCK, MICS_AVG_WAVES}, {MICS_AVG_BLOCK, MICS_AVG_WAVES_STREAMED}},
-    /* Adam    */ {{MICS_ADAM_BLOCK, MICS_ADAM_WAVES}, {MICS_ADAM_BLOCK, MICS_ADAM_WAVES_STREAMED}},
-    /* fused   */ {{MICS_FUSED_BLOCK, MICS_FUSED_WAVES}, {MICS_FUSED_BLOCK, MICS_FUSED_WAVES_STREAMED}},
-};
 std::atomic<int> g_lanes[kFamilies], g_waves[kFamilies];       // 0 = built-in choice
 
-// The tuned shapes pay from a certain amount of traffic per call on; below it a call is over
-// before the capped pipeline has filled, and full-size uncapped workgroups are faster (measured
-// per launch, buffers rotated so that nothing is cache-resident: reduce p = 16 at 320 MB 57 us
-// against 61 us, at 640 MB 108 against 103; average r = 8 at 72 MB 14.3 against 15.9, at 576 MB
-// 100 against 94; fused at 116 MB 22.4 against 24.8, at 464 MB 89 against 75; reorder at 32 MB
-// 7.7 against 8.7, at 64 MB 13.1 against 12.0; Adam: no difference below 100 MB).
-constexpr size_t kTunedFromBytes[kFamilies] = {48u << 20, 448u << 20, 256u << 20, 0, 200u << 20};
-constexpr Shape kSmallCallShape = {512, 0};
-
-// `traffic` = algorithmic bytes of the call; `streams` = buffers a lane reads in this call,
-// `tuned_streams` = the number the built-in cap was measured with: a lane with fewer loads in
-// flight needs proportionally more wavefronts beside it (a lane with more keeps the cap).
-Shape shape_of(int family, bool streamed, size_t traffic, int streams = 1, int tuned_streams = 1,
-               int default_lanes = 0)
+Shape with_knobs(int family, Shape sh)
 {
-    Shape sh = kDefaultShape[family][streamed ? 1 : 0];
-    if (default_lanes) sh.lanes = default_lanes;
-    if (sh.waves_per_cu > 0 && streams < tuned_streams)
-        sh.waves_per_cu = (sh.waves_per_cu * tuned_streams + streams - 1) / streams;
-    if (traffic < kTunedFromBytes[family]) sh = kSmallCallShape;
     if (const int l = g_lanes[family].load()) sh.lanes = l;
     if (const int w = g_waves[family].load()) sh.waves_per_cu = w;
     if (sh.waves_per_cu >= 32) sh.waves_per_cu = 0;
     return sh;
+}
+
+// A call that is over before a capped pipeline has filled: uncapped, in full-size workgroups.  Where a
+// compute unit gets fewer than four of them, all run at once and the slowest unit decides: the
+// largest workgroups whose rounded-up number per unit wastes at most 12 % (reduce, p = 64, 1.1 M
+// elements, 269 workgroups of 512 lanes on 256 units: 34.6 us, of 64 lanes 27.6; p = 16, 2.5 M: 512
+// lanes 19.7, 256 lanes 18.8; p = 8, 4.2 M, where 512 fits: 17.2, 64 lanes 18.4; average + Adam,
+// r = 2, 0.74 M: 512 lanes 9.9, 64 lanes 8.7).  A call that gives a unit less than half a
+// full-size workgroup runs in single wavefronts: a unit moves about 100 GB/s on its own (reduce,
+// 0.5 M elements at p = 16: 5.3 us instead of 6.2).
+Shape small_call(size_t nlanes, size_t units)
+{
+    auto waste = [&](size_t lanes) {                           // of the fullest unit against an even share
+        const size_t wgs = (nlanes + lanes - 1) / lanes;
+        return (double)((wgs + units - 1) / units * units * lanes) / (double)nlanes;
+    };
+    if (nlanes >= units * (4 * kMaxBlock)) return Shape{kMaxBlock, 0};
+    if (nlanes * 2 <= (size_t)kMaxBlock * units) return Shape{64, 0};
+    return Shape{waste(512) <= 1.12 ? 512 : waste(256) <= 1.12 ? 256 : 64, 0};
+}
+
+// Where a single buffer spans gigabytes (all the shards of a group in one call), still fewer request
+// streams are better, us with the caps above / with those for huge calls: reduce p = 16, 805 M elements
+// 5436 / 5278, p = 8, 201 M 742 / 730; Adam, 402 M 1940 / 1900, 805 M 3980 / 3830; average + Adam, r = 4,
+// 402 M 2660 / 2590; average r = 2, 402 M 749 / 735.
+constexpr size_t kHugeElements = 192u << 20;
+
+// The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
+// 64x16 14.9, r = 8 at 151 MB 27.3, 64x10 26.1; average + Adam at 143 MB 25.5, 64x10 26.1, at 334 MB
+// 55.8, 52.9, r = 8 already at 100 MB 20.0, 64x10 19.1; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
+Shape average_shape(int r, size_t count, bool streamed, size_t units)
+{
+    const size_t traffic = count * (4 * (size_t)r + 4);
+    // few copies, few loads in flight per lane: every wavefront that fits
+    if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
+    if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call((count + 3) / 4, units));
+    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 10 : traffic < (600u << 20) || (r < 5 && streamed) ? 16 : 12});
+}
+
+Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 12}); }
+
+Shape fused_shape(int r, size_t count, size_t units)
+{
+    const size_t traffic = count * (4 * (size_t)r + 26);
+    if (r >= 6 && traffic >= (80u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
+    if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
+    if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 7 : 5});
+    return with_knobs(kFamFused, Shape{64, r < 2 ? 12 : r < 3 ? 10 : r < 8 ? (68 + r) / (r + 3) : 6});
+}
+
+Shape reorder_shape(size_t traffic, int lanes)
+{
+    return with_knobs(kFamReorder, traffic < (48u << 20) ? Shape{kMaxBlock, 0} : Shape{lanes, 0});
 }
 
 // Dynamic LDS that keeps the wavefronts of `sh` on a compute unit at or below its cap, at least
@@ -1234,7 +1264,7 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
     if (vec16) {
         // spread the block budget over the p chunks
         unsigned total = 0;
-        const Shape sh = shape_of(kFamReorder, true, 2 * n_valid_bytes);
+        const Shape sh = reorder_shape(2 * n_valid_bytes, MICS_REORDER_BLOCK);
         if (int e = grid_for(shard_bytes / 16 * (size_t)p, sh.lanes, MICS_REORDER_BPC, &total)) return e;
         unsigned bx = (total + (unsigned)p - 1) / (unsigned)p;
         return launch(reorder_vec_kernel, dim3(bx, (unsigned)p), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
@@ -1280,40 +1310,23 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
 //     grid, because the partial lines between two wavefronts then meet in one workgroup (2 M for p < 16;
 //     p = 8, 9.8 M: 64 x 10 40.7, 512 x 32 39.2; 30 M: 114, 119).  Gradients off 16 bytes: 512 x 16
 //     (p = 16, 50 M: 344, 64 x 8 350).
-//   - Below, where a compute unit gets fewer than four full-size workgroups, all run at once and the
-//     slowest unit decides: the largest workgroups whose rounded-up number per unit wastes at most
-//     12 % (p = 64, 1.1 M elements, 269 workgroups of 512 lanes on 256 units: 34.6 us, of 64 lanes
-//     27.6; p = 16, 2.5 M: 512 lanes 19.7, 256 lanes 18.8; p = 8, 4.2 M, where 512 fits: 17.2, 64
-//     lanes 18.4).
-//   - A call that gives a compute unit less than half a full-size workgroup runs in single wavefronts:
-//     a unit moves about 100 GB/s on its own (0.5 M elements at p = 16: 5.3 us instead of 6.2).
-int reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, Shape* out)
+//   - Below, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
+//     uncapped 28.7).
+Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, size_t units)
 {
-    int cus = 0;
-    if (int e = compute_units(&cus)) return e;
-    const size_t units = (size_t)cus;
     const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
-    Shape sh = {64, 0};
-    if (nlanes >= units * many) {
-        if (grads16) sh.waves_per_cu = p < 4 ? 0 : p < 6 ? (nlanes < units * 12000 ? 0 : 16) : p < 8 ? 14 : p < 16 ? 10 : p < 32 ? 8 : 6;
-        else sh = Shape{kMaxBlock, 16};
-    } else if (nlanes >= units * (4 * kMaxBlock)) {
-        sh.lanes = kMaxBlock;
-    } else if (nlanes * 2 > (size_t)kMaxBlock * units) {
-        // lanes that the fullest compute unit is given, against an even share
-        auto waste = [&](size_t lanes) {
-            const size_t wgs = (nlanes + lanes - 1) / lanes;
-            return (double)((wgs + units - 1) / units * units * lanes) / (double)nlanes;
-        };
-        if (waste(512) <= 1.12) sh.lanes = 512;
-        else if (waste(256) <= 1.12) sh.lanes = 256;
-        else if (p >= 6) sh.waves_per_cu = 16;
+    Shape sh;
+    if (nlanes < units * many) {
+        sh = small_call(nlanes, units);
+        if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
+    } else if (grads16) {
+        const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
+        sh = Shape{64, p < 4 ? 0 : p < 6 ? (nlanes < units * 12000 ? 0 : huge ? 12 : 16) : p < 8 ? 14 :
+                       p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
+    } else {
+        sh = Shape{kMaxBlock, 16};
     }
-    if (const int l = g_lanes[kFamReduce].load()) sh.lanes = l;
-    if (const int w = g_waves[kFamReduce].load()) sh.waves_per_cu = w;
-    if (sh.waves_per_cu >= 32) sh.waves_per_cu = 0;
-    *out = sh;
-    return 0;
+    return with_knobs(kFamReduce, sh);
 }
 
 template <int KIND, int VEC, int P, bool ACCUM>
@@ -1354,10 +1367,11 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
         return accumulate ? rsa_launch<KIND, 1, 0, true>(acc, g, p, lead, count, blocks, narrow, st)
                           : rsa_launch<KIND, 1, 0, false>(acc, g, p, lead, count, blocks, narrow, st);
     }
+    size_t units = 0;
+    if (int e = compute_units(&units)) return e;
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
-    Shape sh;
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
-    if (int e = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line == 16, acc16, &sh)) return e;
+    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line == 16, acc16, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         return dispatch_group(p, [&](auto P) {
@@ -1384,7 +1398,9 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
     hipStream_t st = (hipStream_t)stream;
     unsigned blocks = 0;
     const bool streamed = stream_acc(count);
-    const Shape sh = shape_of(kFamAverage, streamed, count * (4 * (size_t)r + 4), r + 1, 9);
+    size_t units = 0;
+    if (int e = compute_units(&units)) return e;
+    const Shape sh = average_shape(r, count, streamed, units);
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_AVG_BPC, &blocks)) return e;
     const dim3 gr(blocks), bl(sh.lanes);
@@ -1415,11 +1431,11 @@ int launch_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* para
 {
     hipStream_t st = (hipStream_t)stream;
     unsigned blocks = 0;
-    const Shape sh = shape_of(kFamAdam, stream_acc(count), count * 30);
+    const Shape sh = adam_shape(count);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto OUT) {
         return launch(adam_kernel<OUT.value>, dim3(blocks), dim3(sh.lanes), lds_for(sh), st, master, exp_avg,
-                      exp_avg_sq, param_bf16, grad, count, hp);
+                      exp_avg_sq, param_bf16, grad, count, hp, states_through(count * 30));
     });
 }
 
@@ -1434,7 +1450,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
         if (vec16) {
             size_t moved = 0;
             for (int t = 0; t < nt; ++t) moved += 2 * segs[first + t].numel * eb;
-            const Shape sh = shape_of(kFamReorder, true, moved, 1, 1, kSegLanes);
+            const Shape sh = reorder_shape(moved, kSegLanes);
             const size_t tile_vecs = (size_t)sh.lanes * MICS_SEG_U;
             ReorderSegTable tab;
             tab.n = nt;
@@ -1456,7 +1472,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
         } else {
             size_t moved = 0;
             for (int t = 0; t < nt; ++t) moved += 2 * segs[first + t].numel * eb;
-            const Shape sh = shape_of(kFamReorder, true, moved, 1, 1, MICS_SHIFT_BLOCK);
+            const Shape sh = reorder_shape(moved, MICS_SHIFT_BLOCK);
             const size_t tile_bytes = (size_t)sh.lanes * MICS_SHIFT_U * 16;
             // tiles of full destination vectors; at least one per tensor, for the chunk ends
             auto tiles_of = [&](const ByteSeg& sg) {
@@ -1509,19 +1525,20 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     constexpr size_t GB = GradFormat<KIND>::kElemBytes, EPL = 4 * GradFormat<KIND>::kPerDword;
     unsigned line = 0;
     const size_t base_lead = align_gradient_pointers(g, p, (int)GB, &line);
+    size_t units = 0;
+    if (int e = compute_units(&units)) return e;
     const size_t unit = line == 16 ? EPL : 4 / GB;             // elements that a segment's lead is counted in
     for (int first = 0; first < n; first += kMaxSeg) {
         ReduceSegTable tab;
         tab.n = n - first < kMaxSeg ? n - first : kMaxSeg;
         size_t elements = 0;
         for (int t = 0; t < tab.n; ++t) elements += segs[first + t].numel;
-        Shape sh;
         bool acc16 = true;
         for (int t = 0; t < tab.n; ++t) {
             const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
             acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
         }
-        if (int e = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line == 16, acc16, &sh)) return e;
+        const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line == 16, acc16, units);
         const size_t tile_elems = (size_t)sh.lanes * EPL;
         size_t tiles = 0;
         for (int t = 0; t < tab.n; ++t) {
@@ -1580,17 +1597,20 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
 {
     hipStream_t st = (hipStream_t)stream;
     unsigned blocks = 0;
-    const Shape sh = shape_of(kFamFused, stream_acc(count), count * (4 * (size_t)r + 26), r + 3, 11);
+    size_t units = 0;
+    if (int e = compute_units(&units)) return e;
+    const Shape sh = fused_shape(r, count, units);
+    const bool through = states_through(count * (4 * (size_t)r + 26));
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto BF) {
         const dim3 gr(blocks), bl(sh.lanes);
         switch (r) {
-            case 1: return launch(avg_adam_kernel<1, BF.value, SmallTable<1>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<1>(copies), r, scale, count, hp);
-            case 2: return launch(avg_adam_kernel<2, BF.value, SmallTable<2>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<2>(copies), r, scale, count, hp);
-            case 4: return launch(avg_adam_kernel<4, BF.value, SmallTable<4>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<4>(copies), r, scale, count, hp);
-            case 8: return launch(avg_adam_kernel<8, BF.value, SmallTable<8>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<8>(copies), r, scale, count, hp);
-            default: return launch(avg_adam_kernel<0, BF.value, PtrTable>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, copies, r, scale, count, hp);
+            case 1: return launch(avg_adam_kernel<1, BF.value, SmallTable<1>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<1>(copies), r, scale, count, hp, through);
+            case 2: return launch(avg_adam_kernel<2, BF.value, SmallTable<2>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<2>(copies), r, scale, count, hp, through);
+            case 4: return launch(avg_adam_kernel<4, BF.value, SmallTable<4>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<4>(copies), r, scale, count, hp, through);
+            case 8: return launch(avg_adam_kernel<8, BF.value, SmallTable<8>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<8>(copies), r, scale, count, hp, through);
+            default: return launch(avg_adam_kernel<0, BF.value, PtrTable>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, copies, r, scale, count, hp, through);
         }
     });
 }

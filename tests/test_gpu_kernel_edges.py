@@ -81,3 +81,36 @@ def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, thresho
             assert same_bits(acc, ref), (offset, skew)
     finally:
         mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("r,count,skew", [(2, 300001, 0), (2, 2100003, 1), (3, 9000001, 0), (1, 11000003, 0),
+                                          (5, 6000002, 3), (8, 2600001, 0), (8, 6000003, 0), (11, 300007, 1)])
+def test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew):
+    """Sizes on both sides of the lines of the average's and the update's launch rules and of the
+    kinds of store, with a ragged end."""
+    hp = dict(lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01)
+    scale = float(np.float32(1.0 / (r * 16)))
+    tab = gen.normal_table(1e-2, "f32")
+    copies_h = [gen.fill_host(gen.stream_key(4200, gen.ROLE_ACC, c), 0, count, tab) for c in range(r)]
+    copies = [Guarded(count, np.float32, skew=skew, fill=h) for h in copies_h]
+    grad = orc.replica_average(copies_h, scale)
+    avg = Guarded(count, np.float32, skew=skew)
+    mics.mics_replica_average(avg.t, [c.t for c in copies], count, scale)
+    torch.cuda.synchronize()
+    assert same_bits(avg, grad)
+    start = [gen.fill_host(gen.stream_key(4201, gen.ROLE_MASTER), 0, count, gen.normal_table(0.02, "f32")),
+             gen.fill_host(gen.stream_key(4202, gen.ROLE_MASTER), 0, count, gen.normal_table(1e-3, "f32")),
+             np.abs(gen.fill_host(gen.stream_key(4203, gen.ROLE_MASTER), 0, count, gen.normal_table(1e-5, "f32")))]
+    ref = [s.copy() for s in start]
+    param_ref = orc.adam_shard(*ref, grad, step=3, f32=True, **hp)
+    for fused in (False, True):
+        dev = [Guarded(count, np.float32, skew=skew, fill=s) for s in start]
+        param = Guarded(count, np.uint16, skew=skew)
+        state = [d.t for d in dev] + [param.t]
+        if fused:
+            mics.mics_replica_average_adam_shard(*state, [c.t for c in copies], count, scale, step=3, **hp)
+        else:
+            mics.mics_adam_shard(*state, avg.t, count, step=3, **hp)
+        torch.cuda.synchronize()
+        assert all(same_bits(d, x) for d, x in zip(dev, ref)), fused
+        assert np.array_equal(param.numpy(), param_ref) and param.guards_intact(), fused
