@@ -84,27 +84,8 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #ifndef MICS_ADAM_NTL
 #define MICS_ADAM_NTL 1
 #endif
-// Small messages on large groups (see rsa_kernel): workgroup size of the one-dword-per-lane
-// variant, the loads it keeps in flight, and the largest call (p * count buffer elements)
-// and smallest group it is used for.  Measured per launch, 1 MB .. 256 MB of gradient per rank:
-// for p = 64 / 128 the variant wins up to 64 MB (1 MB: 7.0 / 11.9 us against 9.5 / 17.6 us for
-// the 128-bit kernel in single-wavefront workgroups, 12.5 / 20.6 us before either existed) and
-// loses from 128 MB on; for p <= 32 the 128-bit kernel is as fast or faster at every size.
-#ifndef MICS_NARROW_BLOCK
-#define MICS_NARROW_BLOCK 64
-#endif
-#ifndef MICS_NARROW_BATCH
-#define MICS_NARROW_BATCH 64
-#endif
-#ifndef MICS_NARROW_MAX_ELEMS
-#define MICS_NARROW_MAX_ELEMS (34u << 20)
-#endif
-#ifndef MICS_NARROW_MIN_P
-#define MICS_NARROW_MIN_P 40
-#endif
-
 constexpr int kMaxBlock = 512;           // most lanes per workgroup of the element-wise kernels
-constexpr int kNarrowBlock = MICS_NARROW_BLOCK;
+constexpr int kNarrowBlock = 64;         // ... of the one-dword-per-lane reduction
 constexpr bool kReorderNtl = MICS_REORDER_NTL, kReorderNts = MICS_REORDER_NTS;
 constexpr bool kRsaNtl = MICS_RSA_NTL;   // gradient loads; the accumulator's hint is chosen per launch
 constexpr bool kAvgNtl = MICS_AVG_NTL;   // input loads; the output's hint is chosen per launch
@@ -116,6 +97,23 @@ template <int N>
 struct SmallTable {
     const void* ptr[N];
 };
+
+// What a kernel indexes: a SmallTable itself (constant indices), or a table through the
+// kernel-argument segment, so that run-time indices stay scalar loads, of several pointers at once
+// where they are consecutive.  (Indexing the by-value parameter at run time made one dependent
+// 8-byte load of every pointer, 64 of them 5 us.)  The kernels have their table as the first
+// parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer repeat it
+// (pad_table).
+struct KernargTable {
+    const void* const __attribute__((address_space(4)))* ptr;
+};
+template <int N>
+__device__ __forceinline__ const SmallTable<N>& table_view(const SmallTable<N>& t) { return t; }
+__device__ __forceinline__ KernargTable kernarg_table()
+{
+    return {(const void* const __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr()};
+}
+__device__ __forceinline__ KernargTable table_view(const PtrTable&) { return kernarg_table(); }
 
 // Load / store through a pointer whose pointee type carries the alignment (macros, not function
 // templates: a template parameter would drop the typedef's alignment and promise 16 bytes).
@@ -164,9 +162,11 @@ __device__ __forceinline__ void st_f32(float* p, const float (&a)[N])
 // the L2 at once instead of being left there for a later write-back.
 constexpr int kWriteThrough = 17, kNonTemporal = 2;
 
-// How a reduction writes its accumulator (accum_policy): non-temporal stores, write-through stores
-// from the wavefronts that write whole 128-byte lines, or write-through stores everywhere.
-enum { kThroughNever = 0, kThroughLines = 1, kThroughAlways = 2 };
+// How a reduction passes its accumulator through the caches (accum_policy): plain loads and stores;
+// otherwise non-temporal loads and write-through stores from the wavefronts whose lines are whole, with
+// plain loads and either of non-temporal and write-through stores from the others; non-temporal stores
+// from all.
+enum { kAccCached = 0, kAccThroughLines = 1, kAccThrough = 2, kAccStreamed = 3 };
 
 // A buffer descriptor over `bytes` bytes from a wavefront-uniform address.  Stores outside are dropped.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(void* base, int bytes)
@@ -174,6 +174,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wave_buffer(void* base, int by
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)base);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)base >> 32));
     return __builtin_amdgcn_make_buffer_rsrc((void*)((uintptr_t)hi << 32 | lo), 0, bytes, 0x00027000);
+}
+
+template <int POLICY>
+__device__ __forceinline__ f32x4 load_vec(__amdgpu_buffer_rsrc_t from, unsigned byte)
+{
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(from, (int)byte, 0, POLICY));
 }
 
 template <int POLICY>
@@ -468,7 +474,9 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
 // small messages on large groups, where the time is the launch plus the serial chain of
 // load round trips of one lane: one dword per buffer and lane spreads a 1 MB message over
 // 32 compute units instead of 1 and lets a lane keep 64 loads in flight, so p = 128 needs
-// two round trips.
+// two round trips.  (Splitting the buffers of p > 64 over two wavefronts, one round trip, takes
+// longer than the second one since the pointers arrive in wide loads: 5.3 against 4.5 us for 33 k
+// elements at p = 128; 7.9 while each pointer was a load of its own.)
 // ---------------------------------------------------------------------------
 
 template <int KIND> struct GradFormat {
@@ -536,10 +544,38 @@ __device__ __forceinline__ void rsa_add(float* s, const GradVec<KIND, VEC>& v)
     }
 }
 
+// s = (((s + g_q0) + g_{q0+1}) + ...) + g_{q0+n-1} for the lane's elements starting at virtual
+// element `elem`, at most N buffers: N loads in flight, unconditional.  n > N - PAD; what is loaded
+// beyond n is the last buffer again (see KernargTable) and not added.
+template <int KIND, int VEC, int N, int PAD, typename Tab>
+__device__ __forceinline__ void rsa_batch(float* s, const Tab& g, int q0, int n, size_t elem)
+{
+    GradVec<KIND, VEC> v[N];
+    #pragma unroll
+    for (int b = 0; b < N; ++b) v[b].load(g.ptr[q0 + b], elem);
+    // as in rsa_partial; the 64 single dwords of a full batch are better left to the compiler (p = 64,
+    // 74 k elements: 4.0 against 4.6 us)
+    if constexpr (N < 64) __builtin_amdgcn_sched_barrier(0);
+    #pragma unroll
+    for (int b = 0; b < N; ++b)
+        if (b <= N - PAD || b < n) rsa_add<KIND, VEC, false>(s, v[b]);
+}
+
+// The last `n` < N buffers: the smallest batch of a multiple of PAD loads that holds them.
+template <int KIND, int VEC, int N, int PAD, typename Tab>
+__device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, size_t elem)
+{
+    if constexpr (N > PAD) {
+        if (n > N - 2 * PAD) rsa_batch<KIND, VEC, N - PAD, PAD>(s, g, q0, n, elem);
+        else rsa_rest<KIND, VEC, N - PAD, PAD>(s, g, q0, n, elem);
+    }
+}
+
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
-// batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).
+// batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
+// binary32 addition (-0 + x is x, also for x = -0 and x = +0).
 template <int KIND, int VEC, int P, int BATCH, typename Tab>
 __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem)
 {
@@ -564,53 +600,56 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             }
         }
     } else {
-        {
-            GradVec<KIND, VEC> first;
-            first.load(g.ptr[0], elem);
-            rsa_add<KIND, VEC, true>(s, first);
-        }
-        for (int q0 = 1; q0 < p; q0 += BATCH) {
-            GradVec<KIND, VEC> v[BATCH];
-            #pragma unroll
-            for (int b = 0; b < BATCH; ++b)
-                if (q0 + b < p) v[b].load(g.ptr[q0 + b], elem);
-            #pragma unroll
-            for (int b = 0; b < BATCH; ++b)
-                if (q0 + b < p) rsa_add<KIND, VEC, false>(s, v[b]);
-        }
+        // 128-bit loads: exactly the buffers that are left; single dwords, whose time is latency: whole
+        // groups of 8
+        constexpr int PAD = VEC == 1 ? 8 : 1;
+        #pragma unroll
+        for (int e = 0; e < VEC * GradFormat<KIND>::kPerDword; ++e) s[e] = -0.0f;
+        int q0 = 0;
+        for (; q0 + BATCH <= p; q0 += BATCH) rsa_batch<KIND, VEC, BATCH, 1>(s, g, q0, BATCH, elem);
+        if (q0 < p) rsa_rest<KIND, VEC, BATCH + (PAD > 1 ? PAD : 0), PAD>(s, g, q0, p - q0, elem);
     }
 }
 
-// a[0 .. EPL) = (ACCUM ? acc_e[0 .. EPL) : +0) + partial sum at virtual element `elem`.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, typename Tab>
-__device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const float* acc_e,
-                                        const Tab& g, int p, size_t elem)
+// a[0 .. EPL) = a[0 .. EPL) + partial sum at virtual element `elem`.
+template <int KIND, int VEC, int P, int BATCH, typename Tab>
+__device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const Tab& g, int p, size_t elem)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
-    #pragma unroll
-    for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
-    if (ACCUM) ld_f32<EPL, VEC == 4>(a, acc_e);     // issued before the gradient loads are consumed
     float s[EPL];
     rsa_partial<KIND, VEC, P, BATCH>(s, g, p, elem);
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = a[e] + s[e];
 }
 
-// One element, the p loads in flight 16 at a time (a lane that waited for each of 128 loads in
-// turn would hold up a small call for tens of microseconds).
-template <int KIND, bool ACCUM, typename Tab>
+// One element, the loads in flight 16 at a time (a lane that waited for each of 128 loads in
+// turn would hold up a small call for tens of microseconds); any p: the last ones in a whole group
+// of 8 (see KernargTable).
+template <int KIND, int N, typename Tab>
+__device__ __forceinline__ void rsa_element_batch(float& s, const Tab& g, int q0, int n, size_t elem)
+{
+    float w[N];
+    #pragma unroll
+    for (int b = 0; b < N; ++b) w[b] = widen_one<KIND>(g.ptr[q0 + b], elem);
+    #pragma unroll
+    for (int b = 0; b < N; ++b)
+        if (b < n) s = s + w[b];
+}
+template <int KIND, int P, bool ACCUM, typename Tab>
 __device__ __forceinline__ void rsa_element(float* acc_e, const Tab& g, int p, size_t elem)
 {
-    constexpr int B = 16;
-    float partial = widen_one<KIND>(g.ptr[0], elem);
-    for (int q0 = 1; q0 < p; q0 += B) {
-        float w[B];
-        #pragma unroll
-        for (int b = 0; b < B; ++b)
-            if (q0 + b < p) w[b] = widen_one<KIND>(g.ptr[q0 + b], elem);
-        #pragma unroll
-        for (int b = 0; b < B; ++b)
-            if (q0 + b < p) partial = partial + w[b];
+    float partial = -0.0f;                          // the identity, see rsa_partial
+    if constexpr (P > 0 && P <= 16) {
+        rsa_element_batch<KIND, P>(partial, g, 0, P, elem);
+    } else {
+        int q0 = 0;
+        // not unrolled: the 64 scalar registers of 32 pointers leave none to spare
+        #pragma unroll 1
+        for (; q0 + 16 <= p; q0 += 16) rsa_element_batch<KIND, 16>(partial, g, q0, 16, elem);
+        if constexpr (P == 0) {
+            if (p - q0 > 8) rsa_element_batch<KIND, 16>(partial, g, q0, p - q0, elem);
+            else if (p > q0) rsa_element_batch<KIND, 8>(partial, g, q0, p - q0, elem);
+        }
     }
     *acc_e = (ACCUM ? *acc_e : 0.0f) + partial;
 }
@@ -629,29 +668,48 @@ __device__ __forceinline__ void rsa_element(float* acc_e, const Tab& g, int p, s
 // 128 holds half of the elements of lane j / 2.
 template <int KIND, int VEC, int P, int BATCH, bool ACCUM, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
-                                         size_t lead, size_t end, int through)
+                                         size_t lead, size_t end, int how)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const bool full = v0 >= lead && v0 + EPL <= end;
     float a[EPL];
+    #pragma unroll
+    for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
     if constexpr (VEC == 4) {
         const unsigned lane = threadIdx.x & 63u;
         const size_t wave_v0 = v0 - EPL * lane;
         float* const wave_acc = acc + (wave_v0 - lead);
         const __amdgpu_buffer_rsrc_t out = wave_buffer(wave_acc, 64 * EPL * 4);
-        const bool wt = through == kThroughAlways ||
-                        (through == kThroughLines && (__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)wave_acc) & 127) == 0);
-        if constexpr (EPL == 4) {
-            if (full) {
-                rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
-                if (wt) store_vec<kWriteThrough>(out, 16 * lane, f32x4{a[0], a[1], a[2], a[3]});
-                else st_f32<EPL, true>(acc + (v0 - lead), a);
+        const bool whole = (__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)wave_acc) & 127) == 0;
+        const bool ntl = whole && how != kAccCached;
+        const bool wt = how == kAccThrough || (whole && how == kAccThroughLines);
+        auto store = [&](unsigned i, f32x4 v) {
+            if (wt) store_vec<kWriteThrough>(out, 16 * i, v);
+            else if (how == kAccCached) store_vec<0>(out, 16 * i, v);
+            else MICS_ST(true, (f32x4_a4*)wave_acc + i, v);
+        };
+        if (full) {
+            // issued before the gradient loads are consumed; with more than 8 buffers the choice between
+            // two kinds of loads costs more registers than it gives (p = 32: 158 instead of 99)
+            if constexpr (ACCUM && P > 0 && P <= 8) {
+                f32x4 t[EPL / 4];
+                #pragma unroll
+                for (int h = 0; h < EPL / 4; ++h)
+                    if (ntl) t[h] = load_vec<kNonTemporal>(out, 4 * EPL * lane + 16 * h);
+                    else t[h] = load_vec<0>(out, 4 * EPL * lane + 16 * h);
+                #pragma unroll
+                for (int e = 0; e < EPL; ++e) a[e] = t[e / 4][e % 4];
+            } else if constexpr (ACCUM) {
+                ld_f32<EPL, true>(a, acc + (v0 - lead));
             }
+            rsa_sum<KIND, VEC, P, BATCH>(a, g, p, src0 + v0);
+        }
+        if constexpr (EPL == 4) {
+            if (full) store(lane, f32x4{a[0], a[1], a[2], a[3]});
         } else {
             extern __shared__ f32x4 stage[];                     // blockDim.x * 2 vectors (launcher)
             f32x4* mine = stage + (threadIdx.x - lane) * 2;      // this wavefront's 128 vectors
             if (full) {
-                rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
                 mine[2 * lane] = f32x4{a[0], a[1], a[2], a[3]};
                 mine[2 * lane + 1] = f32x4{a[4], a[5], a[6], a[7]};
             }
@@ -660,15 +718,12 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             #pragma unroll
             for (unsigned h = 0; h < 2; ++h) {
                 const size_t owner = wave_v0 + 256 * h + 8 * (lane / 2);
-                if (owner >= lead && owner + 8 <= end) {
-                    const f32x4 v = mine[64 * h + lane];
-                    if (wt) store_vec<kWriteThrough>(out, 1024 * h + 16 * lane, v);
-                    else MICS_ST(true, (f32x4_a4*)(wave_acc + 256 * h) + lane, v);
-                }
+                if (owner >= lead && owner + 8 <= end) store(64 * h + lane, mine[64 * h + lane]);
             }
         }
     } else if (full) {
-        rsa_sum<KIND, VEC, P, BATCH, ACCUM>(a, acc + (v0 - lead), g, p, src0 + v0);
+        if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
+        rsa_sum<KIND, VEC, P, BATCH>(a, g, p, src0 + v0);
         st_f32<EPL, false>(acc + (v0 - lead), a);
     }
 }
@@ -676,7 +731,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
 // The elements that no lane holds as a full vector: virtual [lead, head) with head = lead
 // rounded up to EPL (or `end`), and [tail, end) with tail = `end` rounded down to EPL (or
 // head).  One element per lane, lanes 0 .. 2*EPL-1 of the calling workgroup.
-template <int KIND, int EPL, bool ACCUM, typename Tab>
+template <int KIND, int EPL, int P, bool ACCUM, typename Tab>
 __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_t src0, size_t lead, size_t end)
 {
     if (threadIdx.x >= 2 * EPL) return;
@@ -686,7 +741,9 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
     if (tail < head) tail = head;
     const size_t e = threadIdx.x < EPL ? lead + threadIdx.x : tail + (threadIdx.x - EPL);
     const size_t stop = threadIdx.x < EPL ? head : end;
-    if (e < stop) rsa_element<KIND, ACCUM>(acc + (e - lead), g, p, src0 + e);
+    if (e >= stop) return;
+    if constexpr (P <= 16) rsa_element<KIND, P, ACCUM>(acc + (e - lead), g, p, src0 + e);
+    else rsa_element<KIND, P, ACCUM>(acc + (e - lead), kernarg_table(), P, src0 + e);
 }
 
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
@@ -694,85 +751,22 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
 // for the edge elements, so that their load chains run beside the vector work.
 template <int KIND, int VEC, int P, bool ACCUM, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
-    float* __restrict__ acc, Tab g, int p, unsigned lead, size_t count, int through)
+    Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
-    constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : MICS_NARROW_BATCH;
+    const auto& g = table_view(tab);
+    constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const size_t end = (size_t)lead + count;
     const size_t nlanes = (end + EPL - 1) / EPL;
     const size_t block = blockDim.x;
     // the last workgroup of the grid does nothing but the edge elements
     if (blockIdx.x == gridDim.x - 1) {
-        rsa_edges<KIND, EPL, ACCUM>(acc, g, p, 0, lead, end);
+        rsa_edges<KIND, EPL, P, ACCUM>(acc, g, p, 0, lead, end);
         return;
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, through);
-}
-
-// Small messages on groups of more than 64: the one-dword-per-lane form with the buffers split
-// over the two wavefronts of a workgroup, so that all p <= 128 loads of an element pair are in
-// flight at once (a wavefront can wait for 64 loads at most).  Wavefront 1 passes its dwords
-// through LDS; wavefront 0 adds everything in rank order.  One round trip to memory instead
-// of two: a 1 MB message at p = 128 takes 7.7 us instead of 12.2, 32 MB 9.1 instead of 12.8;
-// at 64 MB (33 M buffer elements per call) the two forms are even.
-#ifndef MICS_SPLIT_MIN_P
-#define MICS_SPLIT_MIN_P 65
-#endif
-#ifndef MICS_SPLIT_MAX_ELEMS
-#define MICS_SPLIT_MAX_ELEMS (20u << 20)     // buffer elements per call (p * count) up to which it wins
-#endif
-template <int KIND, bool ACCUM>
-__global__ __launch_bounds__(128) void rsa_split_kernel(
-    float* __restrict__ acc, PtrTable g, int p, unsigned lead, size_t count)
-{
-    constexpr int PD = GradFormat<KIND>::kPerDword;
-    __shared__ uint32_t passed[64 * 64];                       // [buffer - 64][lane]
-    const size_t end = (size_t)lead + count;
-    if (blockIdx.x == gridDim.x - 1) {                         // the edge elements, as in rsa_kernel
-        rsa_edges<KIND, PD, ACCUM>(acc, g, p, 0, lead, end);
-        return;
-    }
-    const unsigned lane = threadIdx.x & 63u;
-    const int half = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const size_t v0 = ((size_t)blockIdx.x * 64 + lane) * PD;
-    const bool full = v0 >= lead && v0 + PD <= end;
-    const int q_lo = half * 64, q_n = (p - q_lo < 64 ? p - q_lo : 64);      // this wavefront's buffers
-    GradVec<KIND, 1> v[64];
-    if (full) {
-        #pragma unroll
-        for (int b = 0; b < 64; ++b)
-            if (b < q_n) v[b].load(g.ptr[q_lo + b], v0);
-    }
-    float s[PD];
-    if (half == 1) {
-        if (full) {
-            #pragma unroll
-            for (int b = 0; b < 64; ++b)
-                if (b < q_n) passed[b * 64 + lane] = v[b].dword(0);
-        }
-    } else if (full) {
-        rsa_add<KIND, 1, true>(s, v[0]);
-        #pragma unroll
-        for (int b = 1; b < 64; ++b) rsa_add<KIND, 1, false>(s, v[b]);       // p > 64: all 64 are there
-    }
-    __syncthreads();
-    if (half == 0 && full) {
-        float a[PD];
-        float* acc_e = acc + (v0 - lead);
-        #pragma unroll
-        for (int e = 0; e < PD; ++e) a[e] = 0.0f;
-        if (ACCUM) ld_f32<PD, false>(a, acc_e);
-        for (int q = 64; q < p; ++q) {
-            GradVec<KIND, 1> w;
-            w.v = passed[(q - 64) * 64 + lane];
-            rsa_add<KIND, 1, false>(s, w);
-        }
-        #pragma unroll
-        for (int e = 0; e < PD; ++e) a[e] = a[e] + s[e];
-        st_f32<PD, false>(acc_e, a);
-    }
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -792,16 +786,17 @@ struct ReduceSegTable {
 
 template <int KIND, int P, bool ACCUM, typename Tab>
 __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
-    float* __restrict__ acc, Tab g, int p, ReduceSegTable tab, int through)
+    Tab gtab, float* __restrict__ acc, int p, ReduceSegTable tab, int how)
 {
+    const auto& g = table_view(gtab);
     constexpr int EPL = 4 * GradFormat<KIND>::kPerDword;
     const unsigned x = blockIdx.x;
     const int t = segment_of(tab.tile_begin, x);
     const size_t end = tab.seg[t].end, lead = tab.seg[t].lead;
     const size_t v0 = ((size_t)(x - tab.tile_begin[t]) * blockDim.x + threadIdx.x) * EPL;
-    if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
+    if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, P, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
     rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end,
-                                                through);
+                                                how);
 }
 
 // ---------------------------------------------------------------------------
@@ -1055,13 +1050,18 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // 101 M elements: 364 against 375), for 32 and more buffers beyond 64 MiB (p = 32, 25 M: 289, 302),
 // and where the lines at the two ends of a wavefront's piece are not whole (accumulator off 128
 // bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read and
-// the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).
+// the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it plainly where few
+// buffers are read, so that the second one to need a line finds it in the L2 (all with non-temporal
+// loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134; bf16, p = 4, 1.6 M 6.3 / 6.0).  An accumulator that the
+// L2 of 8 x 4 MB holds is left there if few buffers are read (p = 2, bf16, 1.2 M 4.4 / 4.05 us; p = 1, 6.4 M, 26
+// MB, would lose: 12.8 / 14.0).
 int accum_policy(size_t count, int p)
 {
-    constexpr size_t kSmall = 64u << 20;
-    if (stream_acc(count)) return kThroughNever;
-    if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kThroughNever;
-    return p < 16 && count * 4 <= kSmall ? kThroughAlways : kThroughLines;
+    constexpr size_t kSmall = 64u << 20, kTiny = 12u << 20;
+    if (stream_acc(count)) return kAccStreamed;
+    if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
+    if (p < 12 && count * 4 <= kTiny) return kAccCached;
+    return p < 16 && count * 4 <= kSmall ? kAccThrough : kAccThroughLines;
 }
 
 int compute_units(int* out)
@@ -1150,9 +1150,10 @@ Shape with_knobs(int family, Shape sh)
 // largest workgroups whose rounded-up number per unit wastes at most 12 % (reduce, p = 64, 1.1 M
 // elements, 269 workgroups of 512 lanes on 256 units: 34.6 us, of 64 lanes 27.6; p = 16, 2.5 M: 512
 // lanes 19.7, 256 lanes 18.8; p = 8, 4.2 M, where 512 fits: 17.2, 64 lanes 18.4; average + Adam,
-// r = 2, 0.74 M: 512 lanes 9.9, 64 lanes 8.7).  A call that gives a unit less than half a
-// full-size workgroup runs in single wavefronts: a unit moves about 100 GB/s on its own (reduce,
-// 0.5 M elements at p = 16: 5.3 us instead of 6.2).
+// r = 2, 0.74 M: 512 lanes 9.9, 64 lanes 8.7).  Up to one full-size workgroup per unit the launch of many
+// small ones takes longer than idle units cost (reduce, p = 8, 0.88 M: 5.0 us, 64 lanes 5.6), but a call
+// that gives a unit less than half of one runs in single wavefronts: a unit moves about 100 GB/s on
+// its own (reduce, 0.5 M elements at p = 16: 5.3 us instead of 6.2).
 Shape small_call(size_t nlanes, size_t units)
 {
     auto waste = [&](size_t lanes) {                           // of the fullest unit against an even share
@@ -1161,6 +1162,7 @@ Shape small_call(size_t nlanes, size_t units)
     };
     if (nlanes >= units * (4 * kMaxBlock)) return Shape{kMaxBlock, 0};
     if (nlanes * 2 <= (size_t)kMaxBlock * units) return Shape{64, 0};
+    if (nlanes <= (size_t)kMaxBlock * units) return Shape{kMaxBlock, 0};
     return Shape{waste(512) <= 1.12 ? 512 : waste(256) <= 1.12 ? 256 : 64, 0};
 }
 
@@ -1172,7 +1174,7 @@ constexpr size_t kHugeElements = 192u << 20;
 
 // The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
 // 64x16 14.9, r = 8 at 151 MB 27.3, 64x10 26.1; average + Adam at 143 MB 25.5, 64x10 26.1, at 334 MB
-// 55.8, 52.9, r = 8 already at 100 MB 20.0, 64x10 19.1; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
+// 55.8, 52.9, r = 8 at 122 MB 22.3, 64x10 22.9, at 243 MB 48.3, 45.3; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
 Shape average_shape(int r, size_t count, bool streamed, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 4);
@@ -1187,7 +1189,7 @@ Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= 
 Shape fused_shape(int r, size_t count, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 26);
-    if (r >= 6 && traffic >= (80u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
+    if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
     if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 7 : 5});
     return with_knobs(kFamFused, Shape{64, r < 2 ? 12 : r < 3 ? 10 : r < 8 ? (68 + r) / (r + 3) : 6});
@@ -1276,6 +1278,12 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
 
 namespace {
 
+// Repeats the last of n pointers up to a multiple of 8: kernels may load through those entries.
+void pad_table(PtrTable& t, int n)
+{
+    for (int i = n; i < (n + 7) / 8 * 8; ++i) t.ptr[i] = t.ptr[n - 1];
+}
+
 // Rounds gradient pointers down to 16 bytes when all of them sit at the same position inside
 // their 16-byte line (rank g's slices of separately allocated buffers do: they all start g*S
 // elements in); returns how many elements they moved back (the kernels' `lead`, 0 .. 7).  The p
@@ -1295,6 +1303,7 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
     const uintptr_t back = (uintptr_t)g.ptr[0] & (line - 1);
     *line_out = (unsigned)line;
     for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] - back;
+    pad_table(g, p);
     return (unsigned)(back / (uintptr_t)elem_bytes);
 }
 
@@ -1329,6 +1338,17 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
     return with_knobs(kFamReduce, sh);
 }
 
+// Small messages on large groups take the one-dword-per-lane kernel (VEC = 1).  us per call, one dword /
+// 128 bits per lane: p = 64, 66 k elements 3.8 / 6.8, 262 k 7.6 / 8.8, 524 k 13.8 / 13.4; p = 128, 33 k 4.5 /
+// 11.0, 262 k 13.0 / 15.4; p = 48, 262 k 6.1 / 7.2, 1 M 20.1 / 18.7; smaller groups of 2-byte elements
+// only while the call is all latency: p = 32, 131 k 3.8 / 4.6, 524 k 8.1 / 8.1; p = 24, 350 k 5.3 / 6.4;
+// p = 16, 262 k 4.0 / 3.9.
+inline bool narrow_call(int p, size_t elem_bytes, size_t count)
+{
+    const size_t bytes = count * (size_t)p * elem_bytes;
+    return p >= 40 ? bytes <= (68u << 20) : p >= 20 && elem_bytes == 2 && bytes <= (24u << 20);
+}
+
 template <int KIND, int VEC, int P, bool ACCUM>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
                const Shape& sh, hipStream_t st)
@@ -1337,10 +1357,10 @@ int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count
     const size_t lds = lds_for(sh, VEC == 4 && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
     if constexpr (P > 0)
         return launch(rsa_kernel<KIND, VEC, P, ACCUM, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
-                      acc, small<P>(g), p, lead, count, accum_policy(count, p));
+                      small<P>(g), acc, p, lead, count, accum_policy(count, p));
     else
-        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, acc,
-                      g, p, lead, count, accum_policy(count, p));
+        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
+                      acc, p, lead, count, accum_policy(count, p));
 }
 
 template <int KIND>
@@ -1350,17 +1370,9 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const unsigned lead = align_gradient_pointers(g, p, GradFormat<KIND>::kElemBytes, &line);
     constexpr size_t PD = GradFormat<KIND>::kPerDword;
     unsigned blocks = 0;
-    // small message on a group of more than 64: one dword per lane and buffer, the buffers split
-    // over two wavefronts
-    if (p >= MICS_SPLIT_MIN_P && count <= (size_t)MICS_SPLIT_MAX_ELEMS / (size_t)p) {
-        const size_t nlanes = (lead + count + PD - 1) / PD;
-        if (int e = grid_for(nlanes, 64, MICS_RSA_BPC, &blocks)) return e;
-        if (blocks == (nlanes + 63) / 64)                      // one pass per lane (the kernel has no stride loop)
-            return accumulate ? launch(rsa_split_kernel<KIND, true>, dim3(blocks + 1), dim3(128), 0, st, acc, g, p, lead, count)
-                              : launch(rsa_split_kernel<KIND, false>, dim3(blocks + 1), dim3(128), 0, st, acc, g, p, lead, count);
-    }
     // small message on a large group: one dword per lane and buffer
-    if (p >= MICS_NARROW_MIN_P && count <= (size_t)MICS_NARROW_MAX_ELEMS / (size_t)p) {
+    constexpr size_t GB = GradFormat<KIND>::kElemBytes;
+    if (narrow_call(p, GB, count)) {
         const Shape narrow = {kNarrowBlock, 0};
         const size_t nlanes = (lead + count + PD - 1) / PD;
         if (int e = grid_for(nlanes, kNarrowBlock, MICS_RSA_BPC, &blocks)) return e;
@@ -1559,18 +1571,18 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         }
         for (int t = tab.n; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
         if (tiles == 0) continue;
-        const int through = accum_policy(elements, p);
+        const int how = accum_policy(elements, p);
         const int err = dispatch_bool(accumulate, [&](auto A) {
             // lanes of 8 elements pass their results through 32 bytes of LDS
             const size_t lds = lds_for(sh, EPL == 8 ? (size_t)sh.lanes * 32 : 0);
             const dim3 gr((unsigned)tiles), bl(sh.lanes);
             return dispatch_group(p, [&](auto P) {
                 if constexpr (P.value > 0)
-                    return launch(rsa_seg_kernel<KIND, P.value, A.value, SmallTable<P.value>>, gr, bl, lds, st, acc,
-                                  small<P.value>(g), p, tab, through);
+                    return launch(rsa_seg_kernel<KIND, P.value, A.value, SmallTable<P.value>>, gr, bl, lds, st,
+                                  small<P.value>(g), acc, p, tab, how);
                 else
-                    return launch(rsa_seg_kernel<KIND, 0, A.value, PtrTable>, gr, bl, lds, st, acc, g, p, tab,
-                                  through);
+                    return launch(rsa_seg_kernel<KIND, 0, A.value, PtrTable>, gr, bl, lds, st, g, acc, p, tab,
+                                  how);
             });
         });
         if (err) return err;

@@ -65,7 +65,43 @@ def test_reduce_at_every_position_inside_a_line(orc, gen, name, p):
         assert same_bits(acc, ref), skew
 
 
-@pytest.mark.parametrize("p,count", [(6, 530001), (6, 1250003), (6, 2500000), (6, 4194311), (6, 6600001), (16, 1250001)])
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [1, 3, 5, 9, 15, 17, 20, 24, 31, 32, 33, 39, 40, 47, 63, 65, 71, 72, 100, 127, 128])
+def test_reduce_with_every_remainder_of_the_load_batches(orc, gen, name, p):
+    """Loads go out in batches; what is left of a group takes a batch of its own, padded with repeats of
+    the last buffer in the one-dword kernel and in the edge elements.  Flat and as segments, whose
+    kernels have 128-bit lanes at every size."""
+    code = FORMATS[name][0]
+    count = 1027
+    host, dev = rank_buffers(gen, name, p, count + 2, [0])
+    for accumulate in (False, True):
+        ref, acc = start_acc(gen, count)
+        mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], 1, count, accumulate, code)
+        orc.reduce_scatter_accum_typed(ref, host, 1, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
+        segs = [(515, 0, 0, 0), (512, 0, 517, 515)]
+        ref, acc = start_acc(gen, count)
+        mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+        orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
+
+
+@pytest.mark.parametrize("elem_bytes,p", [(2, 20), (2, 40), (4, 40)])
+def test_reduce_on_both_sides_of_the_one_dword_rule(orc, gen, elem_bytes, p):
+    limit = (24 if p < 40 else 68) << 20
+    for count in (limit // (p * elem_bytes), limit // (p * elem_bytes) + 1):
+        name = "bf16" if elem_bytes == 2 else "f32"
+        host, dev = rank_buffers(gen, name, p, count, [0])
+        ref, acc = start_acc(gen, count)
+        mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], 0, count, True, FORMATS[name][0])
+        orc.reduce_scatter_accum_typed(ref, host, 0, True, FORMATS[name][0])
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), count
+
+
+@pytest.mark.parametrize("p,count", [(2, 530001), (2, 3200001), (8, 4000001), (6, 530001), (6, 1250003), (6, 2500000), (6, 4194311), (6, 6600001), (16, 1250001)])
 @pytest.mark.parametrize("threshold", [0, 1, 1 << 40])
 def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, threshold):
     """Sizes on both sides of the launch rule's lines (64, 256 and 512 lanes, capped and not), with the
@@ -84,7 +120,7 @@ def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, thresho
 
 
 @pytest.mark.parametrize("r,count,skew", [(2, 300001, 0), (2, 2100003, 1), (3, 9000001, 0), (1, 11000003, 0),
-                                          (5, 6000002, 3), (8, 2600001, 0), (8, 6000003, 0), (11, 300007, 1)])
+                                          (5, 6000002, 3), (8, 2600001, 0), (8, 3600001, 1), (8, 6000003, 0), (11, 300007, 1)])
 def test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew):
     """Sizes on both sides of the lines of the average's and the update's launch rules and of the
     kinds of store, with a ragged end."""
