@@ -370,27 +370,39 @@ struct OneTensor {
     }
 };
 
-// Destination vectors are written aligned.  gfx950 executes a 128-bit load at any 4-byte
-// aligned address at full speed, so a chunk whose source is a multiple of 4 bytes off its
-// destination's 16-byte grid is a plain copy with under-aligned loads.  Otherwise (2 bytes off, odd shard sizes of
-// 2-byte elements) a lane loads the 16 bytes from 2 bytes before its source -- 4-byte aligned --
-// and takes the last 2 bytes it needs from the next lane's first dword through a lane shift;
-// only the last lane of a wavefront (or of the chunk) loads those 2 bytes itself.  The phase
-// is the same for every vector of a chunk, so the branches are workgroup-uniform.  Partial
-// vectors at the two ends of a chunk go in 2-byte units on lanes 0 .. 15 of the chunk's first
-// workgroup.  Global memory is touched only inside the chunk.  (An earlier form staged every
-// tile in LDS and rebuilt the vectors from two LDS reads: 5.2 TB/s on the layer with odd shards
-// where this one reaches 5.8, and 4.6 against 5.0 with 16 tensors per launch.)
-#ifndef MICS_SHIFT_U
-#define MICS_SHIFT_U 2
-#endif
-#ifndef MICS_SHIFT_BLOCK
-#define MICS_SHIFT_BLOCK 256     // 64 lanes: 5.40 TB/s, 128 .. 512: 5.76 .. 5.84
-#endif
-#ifndef MICS_SHIFT_NTL
-#define MICS_SHIFT_NTL 1
-#endif
-template <typename Where>
+// The 16 bytes that start 4 * W + sub bytes into `lo`, the rest from the first W + 1 dwords of `next`.
+template <int W>
+__device__ __forceinline__ u32x4 bytes_from(u32x4 lo, u32x4 next, unsigned sub)
+{
+    u32x4 out;
+    #pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t below = W + d < 4 ? lo[(W + d) & 3] : next[(W + d) & 3];
+        const uint32_t above = W + d + 1 < 4 ? lo[(W + d + 1) & 3] : next[(W + d + 1) & 3];
+        out[d] = __builtin_amdgcn_alignbyte(above, below, sub);
+    }
+    return out;
+}
+
+// Lane n's `mine` of lane n + 1; lane 63 gets its own `last`.
+__device__ __forceinline__ uint32_t from_next_lane(uint32_t mine, uint32_t last)
+{
+    constexpr int kWaveShiftLeft1 = 0x130;
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)mine, kWaveShiftLeft1, 0xf, 0xf, false);
+}
+
+// Both sides move whole aligned lines.  A wavefront writes U * 1 KiB of the destination, on 128-byte
+// boundaries, from the aligned 16-byte source vectors that cover them; a vector of the destination
+// is the end of one of those and the beginning of the next, which is the next lane's (lane 63: lane
+// 0's of the next KiB, and behind the last KiB one vector more that it loads itself).  Loads that are
+// off 16 bytes by themselves run at full speed on gfx950, but 1 KiB of them touches nine lines
+// instead of eight, and so does a store off the lines.  The shift is the same for every vector of a
+// chunk.  Partial vectors at the two ends of a chunk go in 2-byte units on lanes 0 .. 15 of the
+// chunk's first workgroup; the first and the last whole vector, whose source lines reach beyond the
+// chunk, are loaded from where they start: memory is touched only inside the chunk.
+// GB/s of a layer with odd shards (2 x 629 MB, p = 32), loads off 16 bytes / so: 5880 / 6300; tensor by
+// tensor with 16 per launch (3.2 GB) 5640 / 6340; 40 MB in one call 3700 / 4200.
+template <typename Where, int U>
 __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
     unsigned char* __restrict__ dst, PtrTable src, Where where, int k)
 {
@@ -417,41 +429,55 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
         const bool on = threadIdx.x < 8 ? b < head_end : (b >= head_end && b < d_hi);
         if (on) *(uint16_t*)b = *(const uint16_t*)(s_chunk + (b - d_lo));
     }
-    const size_t i0 = tile * ((size_t)blockDim.x * MICS_SHIFT_U);
-    if (i0 >= nfull) return;                                                // workgroup-uniform
-    const uintptr_t s_lo = s_chunk + (a_lo - d_lo);                         // source of full vector 0
-    const bool odd = (s_lo & 2) != 0;                                       // chunk-uniform
 
-    #pragma unroll
-    for (int u = 0; u < MICS_SHIFT_U; ++u) {
-        const size_t i = i0 + (size_t)u * blockDim.x + threadIdx.x;
-        const bool has = i < nfull;
-        const uintptr_t s = s_lo + 16 * i;
-        u32x4 out = {0, 0, 0, 0};
-        if (!odd) {
-            if (has) out = MICS_LD(MICS_SHIFT_NTL, (const u32x4_a4*)s);
-        } else {
-            // vector 0 of a chunk whose destination starts on a 16-byte line has nothing in
-            // front of it inside the chunk: that one lane loads from its 2-byte aligned source
-            const bool direct = s - 2 < s_chunk;
-            u32x4 w = {0, 0, 0, 0};
-            if (has) {
-                if (direct) w = MICS_LD(MICS_SHIFT_NTL, (const u32x4_a2*)s);
-                else w = MICS_LD(MICS_SHIFT_NTL, (const u32x4_a4*)(s - 2));
-            }
-            uint32_t next = (uint32_t)__shfl_down((int)w.x, 1);             // every lane takes part
-            if (has && ((threadIdx.x & 63u) == 63u || i + 1 >= nfull)) next = *(const uint16_t*)(s + 14);
-            if (direct) {
-                out = w;
-            } else {
-                out.x = (w.x >> 16) | (w.y << 16);
-                out.y = (w.y >> 16) | (w.z << 16);
-                out.z = (w.z >> 16) | (w.w << 16);
-                out.w = (w.w >> 16) | (next << 16);
-            }
+    // vector i is the destination's at d_line + 16 i; the chunk's are [first, last)
+    const uintptr_t d_line = d_lo & ~(uintptr_t)127;
+    const size_t first = (a_lo - d_line) / 16, last = first + nfull;
+    const unsigned lane = threadIdx.x & 63u;
+    const size_t w0 = (tile * blockDim.x + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u)) * U;   // of the wavefront
+    if (w0 >= last) return;
+    const uintptr_t s_line = s_chunk + (d_line - d_lo);                     // source of vector 0
+    const unsigned phase = (unsigned)(s_line & 15), sub = phase & 3;        // chunk-uniform
+    const uintptr_t s_vec = s_line - phase;                                 // its aligned source line
+
+    auto move = [&](auto ALL) {                    // ALL: every vector, and the one behind, is inside the chunk
+        u32x4 v[U + 1];
+        #pragma unroll
+        for (int u = 0; u <= U; ++u) {
+            const size_t i = w0 + 64 * u + (u < U ? lane : 0);
+            v[u] = u32x4{0, 0, 0, 0};
+            const bool inside = i >= first && i < last && s_vec + 16 * i >= s_chunk;
+            if (u < U ? ALL.value || inside : phase != 0 && lane == 63 && (ALL.value || inside))
+                v[u] = MICS_LD(true, (const u32x4*)(s_vec + 16 * i));
         }
-        if (has) MICS_ST(kReorderNts, (u32x4*)(a_lo + 16 * i), out);
-    }
+        auto put = [&](auto W) {
+            #pragma unroll
+            for (int u = 0; u < U; ++u) {
+                u32x4 out = v[u];
+                if constexpr (W.value >= 0) {
+                    u32x4 next = {0, 0, 0, 0};
+                    #pragma unroll
+                    for (int d = 0; d <= W.value; ++d)
+                        next[d] = from_next_lane(v[u][d], u + 1 < U ? __builtin_amdgcn_readfirstlane(v[u + 1][d]) : v[U][d]);
+                    out = bytes_from<W.value>(v[u], next, sub);
+                }
+                const size_t i = w0 + 64 * u + lane;
+                if constexpr (!ALL.value) {
+                    if (i < first || i >= last) continue;
+                    if (phase != 0 && (s_vec + 16 * i < s_chunk || i + 1 == last))
+                        out = MICS_LD(true, (const u32x4_a2*)(s_line + 16 * i));
+                }
+                MICS_ST(kReorderNts, (u32x4*)(d_line + 16 * i), out);
+            }
+        };
+        if (phase == 0) put(std::integral_constant<int, -1>{});
+        else if (phase < 4) put(std::integral_constant<int, 0>{});
+        else if (phase < 8) put(std::integral_constant<int, 1>{});
+        else if (phase < 12) put(std::integral_constant<int, 2>{});
+        else put(std::integral_constant<int, 3>{});
+    };
+    if (w0 >= first && w0 + 64 * U < last && s_vec + 16 * w0 >= s_chunk) move(std::true_type{});
+    else move(std::false_type{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1484,12 +1510,18 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
         } else {
             size_t moved = 0;
             for (int t = 0; t < nt; ++t) moved += 2 * segs[first + t].numel * eb;
-            const Shape sh = reorder_shape(moved, MICS_SHIFT_BLOCK);
-            const size_t tile_bytes = (size_t)sh.lanes * MICS_SHIFT_U * 16;
-            // tiles of full destination vectors; at least one per tensor, for the chunk ends
+            // Vectors per lane: more of them, fewer wavefronts that share a source line at their ends;
+            // fewer, a call that is spread further.  Speed against loads off 16 bytes, one tensor, 512
+            // lanes x 1 / 64 x 4: 39 MB 1.15 / 1.11, 134 MB 1.11 / 1.12 and (p = 48) 1.08 / 1.05, 268 MB 1.04 / 1.10,
+            // 1.26 GB 1.05 / 1.07; many tensors per launch, whose tile has to be found first, 128 x 2 / 64 x 4 /
+            // 512 x 1: 315 MB 1.12 / 1.08 / 0.83, 3.2 GB 1.13 / 1.07 / 0.81.
+            const bool spread = nt == 1 && moved < (160u << 20);
+            const int u = nt > 1 ? 2 : spread ? 1 : 4;
+            const Shape sh = reorder_shape(moved, nt > 1 ? 128 : spread ? kMaxBlock : 64);
+            const size_t tile_bytes = (size_t)sh.lanes * u * 16;
+            // tiles start on a 128-byte line of the destination; at least one per tensor, for the chunk ends
             auto tiles_of = [&](const ByteSeg& sg) {
-                const size_t t = (sg.shard_bytes + tile_bytes - 1) / tile_bytes;
-                return sg.valid_bytes ? (t ? t : 1) : 0;
+                return sg.valid_bytes ? (sg.shard_bytes + 127 + tile_bytes - 1) / tile_bytes : 0;
             };
             if (nt == 1) {
                 const Segment& sg = segs[first];
@@ -1501,8 +1533,9 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
                 tiles = tiles_of(one.seg);
                 if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
                 if (tiles == 0) continue;
-                if (int e = launch(reorder_shift_kernel<OneTensor>, dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes),
-                                   lds_for(sh), st, (unsigned char*)dst, src, one, k))
+                if (int e = launch(spread ? reorder_shift_kernel<OneTensor, 1> : reorder_shift_kernel<OneTensor, 4>,
+                                   dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes), lds_for(sh), st,
+                                   (unsigned char*)dst, src, one, k))
                     return e;
                 continue;
             }
@@ -1520,7 +1553,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
             }
             for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
             if (tiles == 0) continue;
-            if (int e = launch(reorder_shift_kernel<ByteSegTable>, dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes),
+            if (int e = launch(reorder_shift_kernel<ByteSegTable, 2>, dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes),
                                lds_for(sh), st, (unsigned char*)dst, src, tab, k))
                 return e;
         }

@@ -150,3 +150,48 @@ def test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, co
         torch.cuda.synchronize()
         assert all(same_bits(d, x) for d, x in zip(dev, ref)), fused
         assert np.array_equal(param.numpy(), param_ref) and param.guards_intact(), fused
+
+
+@pytest.mark.parametrize("src_skew", range(8))
+@pytest.mark.parametrize("eb,dst_skew", [(2, 0), (2, 3), (2, 7), (4, 0), (4, 1)])
+def test_gather_at_every_shift_between_source_and_destination(orc, gen, eb, src_skew, dst_skew):
+    """All byte shifts of a chunk, at chunks around a vector's, a 128-byte line's, a wavefront's and a
+    tile's bytes, one tensor and several per launch."""
+    dtype = np.uint16 if eb == 2 else np.uint32
+    tab = gen.normal_table(1.0, "bf16") if eb == 2 else gen.normal_table(1.0, "f32").view(np.uint32)
+    p, k = 4, 2
+    shards_of = (1, 7, 8, 9, 63, 65, 511, 513, 1025, 2049, 4095, 8193, 16391)
+    segs, src, dst_at = [], 0, 0
+    for S in shards_of:
+        segs.append((p * S - S // 3, S, src, dst_at))
+        src, dst_at = src + p // k * S + 1, dst_at + p * S + 2
+    T = [gen.fill_host(gen.stream_key(4300 + l, gen.ROLE_PARAM), 0, src, tab) for l in range(k)]
+    T_dev = [Guarded(src, dtype, skew=(src_skew + l) % 8, fill=t) for l, t in enumerate(T)]
+    dst = Guarded(dst_at, dtype, skew=dst_skew)
+    want = dst.numpy().copy()
+    mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, eb)
+    orc.hier_gather_reorder_coalesced(T, segs, p, want)
+    torch.cuda.synchronize()
+    assert np.array_equal(dst.numpy(), want) and dst.guards_intact()
+    for n, S, at, _ in segs:
+        one = Guarded(p * S, dtype, skew=dst_skew)
+        before = one.numpy().copy()
+        mics.mics_hier_gather_reorder(one.t, [t.t[at:] for t in T_dev], n, S, p, k, eb)
+        torch.cuda.synchronize()
+        got = one.numpy()
+        assert np.array_equal(got[:n], orc.hier_gather_reorder([t[at:at + p // k * S] for t in T], n, S, p)), S
+        assert np.array_equal(got[n:], before[n:]) and one.guards_intact(), S
+
+
+@pytest.mark.parametrize("skews", [(0, 1), (3, 0), (1, 4), (5, 5)])
+def test_gather_of_a_large_unaligned_tensor(gen, skews):
+    """Beyond 160 MB moved a lane holds four vectors."""
+    S = 21_000_003
+    bufs = [Guarded(S, np.uint16, skew=(skews[0] + l) % 8, fill=gen.fill_host(
+        gen.stream_key(4400 + l, gen.ROLE_PARAM), 0, S, gen.normal_table(1.0, "bf16"))) for l in range(2)]
+    dst = Guarded(2 * S, np.uint16, skew=skews[1])
+    before = dst.t[2 * S - 5:].clone()
+    mics.mics_hier_gather_reorder(dst.t, [b.t for b in bufs], 2 * S - 5, S, 2, 2, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(dst.t[:S], bufs[0].t) and torch.equal(dst.t[S:2 * S - 5], bufs[1].t[:S - 5])
+    assert torch.equal(dst.t[2 * S - 5:], before) and dst.guards_intact()
