@@ -229,30 +229,41 @@ __device__ __forceinline__ uint16_t param_single(float a)
 // ---------------------------------------------------------------------------
 // Step 1: chunk rearrangement of the hierarchical all-gather (Section 3.3).
 // Chunk g of the result comes from slot g div k of the stage-1 buffer of local
-// rank g mod k.  blockIdx.y = g, blockIdx.x strides over the chunk.
+// rank g mod k.  blockIdx.y = g mod k, blockIdx.z = g div k (dividing g in
+// every wavefront cost 1 % of a coalesced call), blockIdx.x strides over the chunk.
 // ---------------------------------------------------------------------------
+
+// Vector i of a wavefront's 64 consecutive ones from d: non-temporal, and through the L2 (nt / nt sc0 sc1:
+// p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480).  It needs whole 128-byte lines: with chunks that begin
+// in the middle of one, p = 48, 537 MB takes 91.0 (nt: 89.5), with wavefronts moved to the lines 84.0.
+__device__ __forceinline__ void put_line(u32x4* d, size_t i, u32x4 v)
+{
+    const unsigned lane = threadIdx.x & 63u;
+    store_vec<kNonTemporal | kWriteThrough>(wave_buffer(d + (i - lane), 1024), 16 * lane, __builtin_bit_cast(f32x4, v));
+}
 
 // All addresses and the shard size are multiples of 16 bytes: a remapped copy.
 __global__ __launch_bounds__(kMaxBlock) void reorder_vec_kernel(
     u32x4* __restrict__ dst, PtrTable src, size_t shard_vecs, size_t n_valid_bytes, int k)
 {
-    const size_t g = blockIdx.y;
+    const size_t l = blockIdx.y, j = blockIdx.z, g = j * (size_t)k + l;
     const size_t chunk_begin = g * shard_vecs * 16;
     if (chunk_begin >= n_valid_bytes) return;
     size_t valid = n_valid_bytes - chunk_begin;
     if (valid > shard_vecs * 16) valid = shard_vecs * 16;
     const size_t nfull = valid / 16;
-    const size_t j = g / (size_t)k, l = g % (size_t)k;
     const u32x4* __restrict__ s = (const u32x4*)src.ptr[l] + j * shard_vecs;
-    u32x4* __restrict__ d = dst + g * shard_vecs;
+    u32x4* const d = dst + g * shard_vecs;
+    // wavefronts begin on 128-byte lines of the destination
+    const unsigned lead = (unsigned)((uintptr_t)d / 16 & 7);
 
     // One vector per lane and pass.  Workgroups are dispatched in blockIdx order, so the lanes
     // in flight cover one compact, advancing window of the source and of the destination; a
     // lane that strides far ahead (several loads a grid stride apart) measurably lowers the
     // achieved bandwidth, for loads and even more for stores.
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nfull; i += stride)
-        MICS_ST(kReorderNts, d + i, MICS_LD(kReorderNtl, s + i));
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nfull + lead; i += stride)
+        if (i >= lead) put_line(d - lead, i, MICS_LD(kReorderNtl, s + (i - lead)));
 
     // ragged end of the logical buffer: fewer than 16 valid bytes remain
     const size_t tail_halves = (valid - nfull * 16) / 2;
@@ -264,13 +275,13 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_vec_kernel(
 }
 
 // Coalesced form (many separately sharded tensors in one launch, all 16-byte aligned):
-// blockIdx.y = chunk g, blockIdx.x = tile x - tile_begin[t] of tensor t's chunk.  A tile is
+// blockIdx.y and .z = chunk, blockIdx.x = tile x - tile_begin[t] of tensor t's chunk.  A tile is
 // MICS_SEG_U runs of blockDim.x vectors: the table look-up in every wavefront's prologue has to
 // be paid for by two vectors per lane (one: -15 %), more spreads the window (four: -3 %).
-// Measured on the h = 8192 layer with two vectors per lane (GB/s): 64 lanes 6375, 128: 6340,
-// 256: 6200, 512: 5950.  A small chunk (a bias of h/p elements) costs one workgroup.
+// Measured on the h = 8192 layer with two vectors per lane (GB/s): 64 lanes 6470, 128: 6540,
+// 256: 6180.  A small chunk (a bias of h/p elements) costs one workgroup.
 #ifndef MICS_SEG_BLOCK
-#define MICS_SEG_BLOCK 64
+#define MICS_SEG_BLOCK 128
 #endif
 constexpr int kSegLanes = MICS_SEG_BLOCK;
 #ifndef MICS_SEG_U
@@ -309,31 +320,31 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
     const unsigned x = blockIdx.x;
     const int t = segment_of(tab.tile_begin, x);
     const size_t shard_vecs = tab.seg[t].shard_vecs, valid_bytes = tab.seg[t].valid_bytes;
-    const size_t g = blockIdx.y;
+    const size_t l = blockIdx.y, j = blockIdx.z, g = j * (size_t)k + l;
     const size_t chunk_begin = g * shard_vecs * 16;
     if (chunk_begin >= valid_bytes) return;
     size_t valid = valid_bytes - chunk_begin;
     if (valid > shard_vecs * 16) valid = shard_vecs * 16;
     const size_t nfull = valid / 16;
-    const size_t j = g / (size_t)k, l = g % (size_t)k;
     const u32x4* __restrict__ s = (const u32x4*)src.ptr[l] + tab.seg[t].src_vec + j * shard_vecs;
     u32x4* __restrict__ d = dst + tab.seg[t].dst_vec + g * shard_vecs;
     const size_t tile_vecs = (size_t)blockDim.x * MICS_SEG_U;
     const size_t tile0 = (size_t)(x - tab.tile_begin[t]) * tile_vecs;
+    const unsigned lead = (unsigned)((uintptr_t)d / 16 & 7);          // as in reorder_vec_kernel
     u32x4 v[MICS_SEG_U];
     #pragma unroll
     for (int u = 0; u < MICS_SEG_U; ++u) {
         const size_t i = tile0 + (size_t)u * blockDim.x + threadIdx.x;
-        if (i < nfull) v[u] = MICS_LD(kReorderNtl, s + i);
+        if (i >= lead && i < nfull + lead) v[u] = MICS_LD(kReorderNtl, s + (i - lead));
     }
     #pragma unroll
     for (int u = 0; u < MICS_SEG_U; ++u) {
         const size_t i = tile0 + (size_t)u * blockDim.x + threadIdx.x;
-        if (i < nfull) MICS_ST(kReorderNts, d + i, v[u]);
+        if (i >= lead && i < nfull + lead) put_line(d - lead, i, v[u]);
     }
     // ragged end of the tensor: the tile that holds vector index nfull moves the last bytes
     const size_t tail_halves = (valid - nfull * 16) / 2;
-    if (tail_halves && nfull / tile_vecs == x - tab.tile_begin[t] && threadIdx.x < tail_halves) {
+    if (tail_halves && (nfull + lead) / tile_vecs == x - tab.tile_begin[t] && threadIdx.x < tail_halves) {
         const uint16_t* sh = (const uint16_t*)(s + nfull);
         uint16_t* dh = (uint16_t*)(d + nfull);
         dh[threadIdx.x] = sh[threadIdx.x];
@@ -409,12 +420,11 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
     size_t tile;
     const ByteSeg& sg = where.locate(blockIdx.x, &tile);
     const size_t shard_bytes = sg.shard_bytes, n_valid_bytes = sg.valid_bytes;
-    const size_t g = blockIdx.y;
+    const size_t l = blockIdx.y, j = blockIdx.z, g = j * (size_t)k + l;
     const size_t chunk_begin = g * shard_bytes;
     if (chunk_begin >= n_valid_bytes) return;
     size_t valid = n_valid_bytes - chunk_begin;
     if (valid > shard_bytes) valid = shard_bytes;
-    const size_t j = g / (size_t)k, l = g % (size_t)k;
 
     const uintptr_t d_lo = (uintptr_t)dst + sg.dst_byte + chunk_begin;      // chunk in dst
     const uintptr_t d_hi = d_lo + valid;
@@ -1285,6 +1295,12 @@ void set_launch_shape(int family, int lanes, int waves_per_cu)
 
 const char* hip_error_text(int err) { return hipGetErrorString((hipError_t)err); }
 
+// Most vectors that a chunk's tiles have in front of it, since they begin on 128-byte lines.
+static size_t off_line(const void* dst, size_t dst_byte, size_t shard_bytes)
+{
+    return (((uintptr_t)dst + dst_byte) | shard_bytes) % 128 ? 7 : 0;
+}
+
 int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t shard_bytes, int p,
                    int k, bool vec16, void* stream)
 {
@@ -1293,9 +1309,9 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
         // spread the block budget over the p chunks
         unsigned total = 0;
         const Shape sh = reorder_shape(2 * n_valid_bytes, MICS_REORDER_BLOCK);
-        if (int e = grid_for(shard_bytes / 16 * (size_t)p, sh.lanes, MICS_REORDER_BPC, &total)) return e;
+        if (int e = grid_for((shard_bytes / 16 + off_line(dst, 0, shard_bytes)) * (size_t)p, sh.lanes, MICS_REORDER_BPC, &total)) return e;
         unsigned bx = (total + (unsigned)p - 1) / (unsigned)p;
-        return launch(reorder_vec_kernel, dim3(bx, (unsigned)p), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
+        return launch(reorder_vec_kernel, dim3(bx, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
                       shard_bytes / 16, n_valid_bytes, k);
     }
     const Segment one = {n_valid_bytes, shard_bytes, 0, 0};
@@ -1499,12 +1515,12 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
                 tab.seg[t].valid_bytes = sg.numel * eb;
                 tab.seg[t].src_vec = sg.src_offset * eb / 16;
                 tab.seg[t].dst_vec = sg.dst_offset * eb / 16;
-                tiles += (tab.seg[t].shard_vecs + tile_vecs - 1) / tile_vecs;
+                tiles += sg.shard_elems ? (tab.seg[t].shard_vecs + off_line(dst, sg.dst_offset * eb, sg.shard_elems * eb) + tile_vecs - 1) / tile_vecs : 0;
                 if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
             }
             for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
             if (tiles == 0) continue;
-            if (int e = launch(reorder_seg_kernel, dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes), lds_for(sh), st,
+            if (int e = launch(reorder_seg_kernel, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
                                (u32x4*)dst, src, tab, k))
                 return e;
         } else {
@@ -1534,7 +1550,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
                 if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
                 if (tiles == 0) continue;
                 if (int e = launch(spread ? reorder_shift_kernel<OneTensor, 1> : reorder_shift_kernel<OneTensor, 4>,
-                                   dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes), lds_for(sh), st,
+                                   dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
                                    (unsigned char*)dst, src, one, k))
                     return e;
                 continue;
@@ -1553,7 +1569,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
             }
             for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
             if (tiles == 0) continue;
-            if (int e = launch(reorder_shift_kernel<ByteSegTable, 2>, dim3((unsigned)tiles, (unsigned)p), dim3(sh.lanes),
+            if (int e = launch(reorder_shift_kernel<ByteSegTable, 2>, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes),
                                lds_for(sh), st, (unsigned char*)dst, src, tab, k))
                 return e;
         }

@@ -195,3 +195,34 @@ def test_gather_of_a_large_unaligned_tensor(gen, skews):
     torch.cuda.synchronize()
     assert torch.equal(dst.t[:S], bufs[0].t) and torch.equal(dst.t[S:2 * S - 5], bufs[1].t[:S - 5])
     assert torch.equal(dst.t[2 * S - 5:], before) and dst.guards_intact()
+
+
+@pytest.mark.parametrize("dst_vecs", [0, 1, 5, 7])
+@pytest.mark.parametrize("unit", [8, 24, 64])
+def test_aligned_gather_off_the_128_byte_lines(orc, gen, dst_vecs, unit):
+    """16-byte aligned geometry: wavefronts begin on 128-byte lines of the destination, at every
+    position of a chunk in its line; with ragged ends around a tile's last vector."""
+    p, k = 6, 3
+    skew = 8 * dst_vecs
+    segs, src, dst_at = [], 0, 0
+    for i, vecs in enumerate((1, 2, 31, 64, 127, 128, 129, 255, 256, 257, 1025)):
+        S = vecs * unit
+        n = p * S - (0, 1, 7, 8, S // 2, 8 * 8 + 3, S + 5)[i % 7]
+        segs.append((max(n, 1), S, src, dst_at))
+        src, dst_at = src + p // k * S, dst_at + p * S
+    T = [gen.fill_host(gen.stream_key(4500 + l, gen.ROLE_PARAM), 0, src, gen.normal_table(1.0, "bf16")) for l in range(k)]
+    T_dev = [Guarded(src, np.uint16, skew=8 * l, fill=t) for l, t in enumerate(T)]
+    dst = Guarded(dst_at, np.uint16, skew=skew)
+    want = dst.numpy().copy()
+    mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, 2)
+    orc.hier_gather_reorder_coalesced(T, segs, p, want)
+    torch.cuda.synchronize()
+    assert np.array_equal(dst.numpy(), want) and dst.guards_intact()
+    for n, S, at, _ in segs:
+        one = Guarded(p * S, np.uint16, skew=skew)
+        before = one.numpy().copy()
+        mics.mics_hier_gather_reorder(one.t, [t.t[at:] for t in T_dev], n, S, p, k, 2)
+        torch.cuda.synchronize()
+        got = one.numpy()
+        assert np.array_equal(got[:n], orc.hier_gather_reorder([t[at:at + p // k * S] for t in T], n, S, p)), S
+        assert np.array_equal(got[n:], before[n:]) and one.guards_intact(), S
