@@ -39,15 +39,17 @@ class MicsError(RuntimeError):
         self.code = code
 
 
-if not os.path.exists(LIB_PATH):
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
+if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL_PATH)):
     raise ImportError(
-        f"{LIB_PATH} is not built. Run `python -c 'import __graft_entry__ as g; g.build()'` "
+        f"{LIB_PATH} and {MARSHAL_PATH} are not both built. Run `python -c 'import __graft_entry__ as g; g.build()'` "
         "(or `python paper_2205_00119_amd/build.py`) first; there is no fallback path.")
 
 # PyTorch ships its own HIP runtime (soname libamdhip64.so.7).  It must be in the process before
 # libmics.so is opened, so that the library binds to that one runtime -- the one that owns the
 # device memory and streams the caller passes in -- instead of loading a second copy.
 import torch  # noqa: E402,F401
+from . import _marshal  # noqa: E402
 
 lib = ctypes.CDLL(LIB_PATH)
 
@@ -107,7 +109,9 @@ lib.mics_reduce_scatter_accum_typed.restype = _i
 
 def _segments(segs) -> ctypes.Array:
     """(numel, shard_elems, src_offset, dst_offset) tuples -> C array of mics_segment."""
-    return (mics_segment * len(segs))(*[mics_segment(*map(int, sg)) for sg in segs])
+    arr = (mics_segment * len(segs))()
+    _marshal.segments(arr, segs)
+    return arr
 
 
 def _check(rc: int) -> None:
@@ -115,25 +119,24 @@ def _check(rc: int) -> None:
         raise MicsError(rc, lib.mics_last_error().decode("utf-8", "replace"))
 
 
-def _dev_ptr(x) -> Optional[int]:
-    """Device address of a torch tensor (must be contiguous), or a raw integer address."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return x
-    if not x.is_contiguous():
-        raise ValueError("tensor must be contiguous")
-    return x.data_ptr()
+# Device address of a torch tensor (must be contiguous, else ValueError), or a raw integer address.
+_dev_ptr = _marshal.address
 
 
 def _table(items: Sequence) -> ctypes.Array:
-    return (ctypes.c_void_p * len(items))(*[_dev_ptr(t) for t in items])
+    arr = (ctypes.c_void_p * len(items))()
+    _marshal.addresses(arr, items)
+    return arr
+
+
+# The raw handle of torch's current stream, without the Stream object around it.
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
 
 
 def _stream(stream) -> Optional[int]:
     """hipStream_t handle: explicit integer, a torch stream, or torch's current stream."""
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream or None
+        return _raw_stream(_device()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

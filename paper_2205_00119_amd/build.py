@@ -1,4 +1,4 @@
-"""Compile libmics.so (gfx950) in-tree with hipcc."""
+"""Compile libmics.so (gfx950) in-tree with hipcc, and the Python binding's argument marshalling."""
 from __future__ import annotations
 
 import os
@@ -33,6 +33,29 @@ def build(extra_flags=(), out: str = LIB, verbose: bool = False) -> str:
     return out
 
 
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL = os.path.join(HERE, "_marshal.so")
+
+
+def build_marshal(out: str = MARSHAL) -> str:
+    """The CPython module that turns tensors and segment tuples into the library's tables (host code)."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    tmp = out + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-L" + os.path.join(root, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, out)
+    return out
+
+
 EXAMPLE_SRC = os.path.join(HERE, "examples", "step_from_c.cpp")
 EXAMPLE_BIN = os.path.join(HERE, "examples", "step_from_c")
 
@@ -54,3 +77,5 @@ if __name__ == "__main__":
     # usage: build.py [out.so] [-DNAME=VALUE ...]   (variants for measurements)
     out = next((a for a in sys.argv[1:] if not a.startswith("-")), LIB)
     print(build([a for a in sys.argv[1:] if a.startswith("-")], out=out, verbose=True))
+    if out == LIB:
+        print(build_marshal())
