@@ -48,7 +48,7 @@
  *   - Pointers must be aligned to their element size; that is all the
  *     element-wise calls (reduce, average, Adam) need for full speed, except
  *     that the gradient buffers of one call should all start at the same
- *     position inside a 16-byte line (otherwise up to about 7 % slower).  The reorder
+ *     position inside a 128-byte line (otherwise up to about 12 % slower).  The reorder
  *     runs at copy speed when every buffer and the shard size are multiples
  *     of 16 bytes and through a re-phasing kernel (about 8 % slower) otherwise.
  *   - Buffers of one call must not overlap unless stated.

@@ -808,7 +808,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
 // tile x - tile_begin[t] of segment t.  Every segment has its own virtual index space as in
 // rsa_kernel: src0 = position of its virtual element 0 in the rounded-down rank buffers, a
-// multiple of a 16-byte line (4-byte unit) of them, [lead, end) = its elements,
+// multiple of a line (align_gradient_pointers) of them, [lead, end) = its elements,
 // dst = accumulator index of virtual element `lead`.
 struct ReduceSeg {
     unsigned long long end, src0, dst;
@@ -1326,22 +1326,24 @@ void pad_table(PtrTable& t, int n)
     for (int i = n; i < (n + 7) / 8 * 8; ++i) t.ptr[i] = t.ptr[n - 1];
 }
 
-// Rounds gradient pointers down to 16 bytes when all of them sit at the same position inside
-// their 16-byte line (rank g's slices of separately allocated buffers do: they all start g*S
-// elements in); returns how many elements they moved back (the kernels' `lead`, 0 .. 7).  The p
-// gradient loads of a lane are then aligned and only its accumulator access is not, 8 of 2p+8
-// bytes.  A 1 KiB load of a wavefront that is off its 128-byte lines touches nine of them instead
-// of eight, and with non-temporal loads the shared ones are fetched twice.  With pointers rounded
-// down to 4 bytes / to 16 bytes, all 2 or 10 bytes off: p = 32, 9.8 M elements 124 / 117 us;
-// p = 16, 50 M elements 343 / 322 us.
+// Rounds gradient pointers down to a 128-byte line when all of them sit at the same position inside
+// theirs (rank g's slices of separately allocated buffers do: they all start g*S elements in);
+// returns how many elements they moved back (the kernels' `lead`, 0 .. 63).  The p gradient loads of a
+// wavefront then cover whole lines and only its accumulator accesses do not, 8 of 2p+8 bytes.  A 1 KiB
+// load that is off the lines touches nine of them instead of eight, and with non-temporal loads the
+// shared ones are fetched twice.  us with pointers rounded down to 16 / to 128 bytes, all 64 bytes off:
+// p = 8, 27 M elements 92 / 84; p = 16, 12.5 M 90 / 82; p = 32, 7 M 90 / 81; 1.7 M 23.9 / 21.8; p = 64, 0.2 M
+// 11.0 / 8.8.  Up to 3 buffers the accumulator is most of the traffic: p = 2, 30 MB 6.7 / 6.9, so they go
+// down to 16 bytes only, which keeps its vectors of 16 bytes together (down to 4 / to 16 bytes, all 2 or 10
+// bytes off: p = 32, 9.8 M 124 / 117; p = 16, 50 M 343 / 322).
 // With mixed positions 2-byte elements are still brought to 4 bytes if their parity agrees; else
 // the pointers stay and the odd ones are read with 2-byte aligned 128-bit loads.
-// *line = the alignment they have afterwards: 16, 4 or 1 bytes (1: that of their elements).
+// *line = the alignment they have afterwards: 128, 16, 4 or 1 bytes (1: that of their elements).
 unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* line_out)
 {
     uintptr_t differ = 0;                                  // address bits in which the pointers differ
     for (int q = 1; q < p; ++q) differ |= (uintptr_t)g.ptr[q] ^ (uintptr_t)g.ptr[0];
-    const uintptr_t line = (differ & 15) == 0 ? 16 : (differ & 3) == 0 ? 4 : 1;
+    const uintptr_t line = p >= 4 && (differ & 127) == 0 ? 128 : (differ & 15) == 0 ? 16 : (differ & 3) == 0 ? 4 : 1;
     const uintptr_t back = (uintptr_t)g.ptr[0] & (line - 1);
     *line_out = (unsigned)line;
     for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] - back;
@@ -1425,7 +1427,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     if (int e = compute_units(&units)) return e;
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
-    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line == 16, acc16, units);
+    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         return dispatch_group(p, [&](auto P) {
@@ -1588,7 +1590,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     const size_t base_lead = align_gradient_pointers(g, p, (int)GB, &line);
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
-    const size_t unit = line == 16 ? EPL : 4 / GB;             // elements that a segment's lead is counted in
+    const size_t unit = line >= 16 ? line / GB : 4 / GB;             // elements that a segment's lead is counted in
     for (int first = 0; first < n; first += kMaxSeg) {
         ReduceSegTable tab;
         tab.n = n - first < kMaxSeg ? n - first : kMaxSeg;
@@ -1599,13 +1601,13 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
             const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
             acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
         }
-        const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line == 16, acc16, units);
+        const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, units);
         const size_t tile_elems = (size_t)sh.lanes * EPL;
         size_t tiles = 0;
         for (int t = 0; t < tab.n; ++t) {
             const Segment& sg = segs[first + t];
             // position of the segment's first element in the rounded-down buffers; its virtual
-            // element 0 is the 16-byte (4-byte: see align_gradient_pointers) aligned one at or below it
+            // element 0 is the one on a line (of 128, 16 or 4 bytes: see align_gradient_pointers) at or below it
             const size_t src = sg.src_offset + base_lead;
             const unsigned lead = (unsigned)(src % unit);
             tab.tile_begin[t] = (unsigned)tiles;

@@ -101,6 +101,34 @@ def test_reduce_on_both_sides_of_the_one_dword_rule(orc, gen, elem_bytes, p):
         assert same_bits(acc, ref), count
 
 
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [2, 3, 4, 8, 16, 48])
+def test_reduce_at_positions_inside_a_128_byte_line(orc, gen, name, p):
+    """Groups of 4 and more round their pointers down to the line: calls that end before, at and behind
+    the first whole vector of the first wavefront, flat and as segments."""
+    code, per_line = FORMATS[name][0], 64 if name != "f32" else 32
+    for phase in (4, 8, per_line // 2, per_line - 9, per_line - 1, per_line + 5):
+        for count in (1, 5, 8, 9, 63, 64, 449, 512, 1537):
+            host, dev = rank_buffers(gen, name, p, phase + count + 3, [0])
+            ref, acc = start_acc(gen, count, skew=phase % 5)
+            mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], phase, count, True, code)
+            orc.reduce_scatter_accum_typed(ref, host, phase, True, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), (phase, count)
+    segs, src, dst = [], 3, 0
+    for i, n in enumerate((1, 8, 515, 70, 1030, 64, 129)):
+        src += (8, 24, 1, 32, 57, 0, 13)[i]
+        segs.append((n, 0, src, dst))
+        src, dst = src + n, dst + n
+    for skews in ([0], [8], [40], [0, 32], [16, 48]):       # the last two: 16-byte lines only
+        host, dev = rank_buffers(gen, name, p, src + 2, skews)
+        ref, acc = start_acc(gen, dst, skew=1)
+        mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, False, code)
+        orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, False, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), skews
+
+
 @pytest.mark.parametrize("p,count", [(2, 530001), (2, 3200001), (8, 4000001), (6, 530001), (6, 1250003), (6, 2500000), (6, 4194311), (6, 6600001), (16, 1250001)])
 @pytest.mark.parametrize("threshold", [0, 1, 1 << 40])
 def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, threshold):
