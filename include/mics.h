@@ -50,7 +50,7 @@
  *     that the gradient buffers of one call should all start at the same
  *     position inside a 128-byte line (otherwise up to about 12 % slower).  The reorder
  *     runs at copy speed when every buffer and the shard size are multiples
- *     of 16 bytes and through a re-phasing kernel (about 8 % slower) otherwise.
+ *     of 16 bytes and through a re-phasing kernel (about 5 % slower) otherwise.
  *   - Buffers of one call must not overlap unless stated.
  */
 #ifndef MICS_H

@@ -117,7 +117,7 @@ def main():
            f"# rocprofv3 summary: libmics kernels, workload {cfg.name} (p={cfg.p}, k={cfg.k}, r={cfg.r}, "
            f"s={cfg.s}), {args.view} view ({count} elements per reduce/average/Adam call), one MI355X\n",
            f"Kernel source: `paper_2205_00119_amd/csrc/kernels.hip`, SHA-256 `{sha}`.\n",
-           "Commands (from /tmp on the GPU box, `R` = repository root; each in a run of its own), then "
+           "Commands (from /tmp on the GPU machine, `R` = repository root; each in a run of its own), then "
            f"`python profile_summary.py --dir {args.dir} --config {args.config} --view {args.view} "
            f"--variant {args.variant} --bench-args \"{args.bench_args}\" --out {args.out}`:\n",
            "```"]
