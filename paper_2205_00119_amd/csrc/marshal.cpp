@@ -135,8 +135,12 @@ PyObject* segments(PyObject*, PyObject* const* args, Py_ssize_t nargs)
                 PyErr_SetString(PyExc_RuntimeError, "sequence changed its length");
                 return nullptr;
             }
-            // a tuple of its own: what its numbers' __int__ does cannot change it
-            PyObject* sg = PySequence_Tuple(PySequence_Fast_GET_ITEM(t.seq, i));
+            // a tuple of its own: what its numbers' __int__ does cannot change it.  The item's __iter__ may
+            // drop the list's reference to it.
+            PyObject* item = PySequence_Fast_GET_ITEM(t.seq, i);
+            Py_INCREF(item);
+            PyObject* sg = PySequence_Tuple(item);
+            Py_DECREF(item);
             if (!sg) return nullptr;
             const Py_ssize_t m = PyTuple_GET_SIZE(sg);
             bool ok = m <= kFields;

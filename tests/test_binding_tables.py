@@ -1,5 +1,8 @@
 """The binding's native marshalling against the per-element Python it stands for."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -80,3 +83,45 @@ def test_segment_arrays(segs):
 def test_what_is_no_segment_is_refused(segs, error):
     with pytest.raises(error):
         mics._segments(segs)
+
+
+DROPPED = """
+import ctypes
+import paper_2205_00119_amd as mics
+
+class Item:
+    def __init__(self, outer):
+        self.outer = outer
+        outer.append(self)
+    def __iter__(self):
+        self.outer.clear()
+        return iter((1, 2))
+    def __length_hint__(self):
+        return 2
+
+outer = []
+Item(outer)
+assert bytes(mics._segments(outer)) == bytes((mics.mics_segment * 1)(mics.mics_segment(1, 2)))
+
+class Address:
+    def __init__(self, outer):
+        self.outer = outer
+        outer.append(self)
+    def is_contiguous(self):
+        self.outer.clear()
+        return True
+    def data_ptr(self):
+        return 4096
+
+Address(outer)
+assert bytes(mics._table(outer)) == bytes((ctypes.c_void_p * 1)(4096))
+"""
+
+
+def test_an_item_that_leaves_its_list_while_it_is_read():
+    """The list's reference is the item's last one.  The allocator overwrites freed objects, in a process of
+    its own."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", DROPPED], cwd=root, env=dict(os.environ, PYTHONMALLOC="debug"),
+                         capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
