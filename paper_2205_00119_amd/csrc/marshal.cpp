@@ -3,6 +3,7 @@
 // of 64 gradient buffers) took twice as long as the kernel of an 8 MB reduction.
 //
 // No state.  Everything is called with the GIL held; nothing outlives the call.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
@@ -47,15 +48,17 @@ bool address_of(PyObject* x, uint64_t* out)
     return !(*out == (uint64_t)-1 && PyErr_Occurred());
 }
 
+// C++ exceptions become the Python ones that the tensor's own methods raise (type, and text without
+// the C++ stack).
 template <typename F>
 PyObject* guarded(F&& f)
 {
     try {
         return f();
-    } catch (const std::exception& e) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (const std::exception&) {
+        torch::translate_exception_to_python(std::current_exception());
     } catch (...) {
-        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
+        PyErr_SetString(PyExc_RuntimeError, "unknown C++ exception");
     }
     return nullptr;
 }

@@ -70,6 +70,23 @@ def test_what_is_no_address_is_refused(bad, error):
         mics._table(iter([BASE]))
 
 
+@pytest.mark.parametrize("kind", ["csr", "mkldnn", "vmap"])
+def test_tensors_without_an_address_raise_what_their_methods_raise(kind):
+    def check(x):
+        with pytest.raises(RuntimeError) as want:
+            address(x)
+        for call in (lambda: mics._table([BASE, x]), lambda: mics._dev_ptr(x)):
+            with pytest.raises(RuntimeError) as got:
+                call()
+            assert type(got.value) is type(want.value) and str(got.value) == str(want.value)
+        return BASE[0]
+
+    if kind == "vmap":
+        torch.func.vmap(check)(BASE)
+    else:
+        check(BASE.to_sparse_csr() if kind == "csr" else BASE.to_mkldnn())
+
+
 @pytest.mark.parametrize("segs", [[], [(1, 2, 3, 4)], ((5, 0, 2 ** 40, 7), [8, 9, 10, 11]), [(1, 2)], [()],
                                   [tuple(np.int64(x) for x in (3, 4, 5, 6)), np.arange(4)], [(1.0, 2.9, True, "7")],
                                   [(-1, 2 ** 64 + 5, 0, 0)], np.arange(8).reshape(2, 4)])
