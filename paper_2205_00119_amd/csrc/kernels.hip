@@ -690,6 +690,15 @@ __device__ __forceinline__ void rsa_element(float* acc_e, const Tab& g, int p, s
     *acc_e = (ACCUM ? *acc_e : 0.0f) + partial;
 }
 
+// Orders LDS accesses of one wavefront's lanes before and after it.  They complete in program order, so this
+// is no instruction: it tells the compiler, to whom the lanes' addresses do not alias, to keep that order.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // The lane's virtual elements [v0, v0 + EPL) of a call (or segment) whose elements are the
 // virtual range [lead, end): `acc` is the accumulator address of virtual element `lead`, and
 // virtual element e sits at element src0 + e of every rank buffer.  Consecutive lanes of a
@@ -749,13 +758,13 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
                 mine[2 * lane] = f32x4{a[0], a[1], a[2], a[3]};
                 mine[2 * lane + 1] = f32x4{a[4], a[5], a[6], a[7]};
             }
-            // LDS operations of one wavefront complete in order: no barrier between these
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
             #pragma unroll
             for (unsigned h = 0; h < 2; ++h) {
                 const size_t owner = wave_v0 + 256 * h + 8 * (lane / 2);
                 if (owner >= lead && owner + 8 <= end) store(64 * h + lane, mine[64 * h + lane]);
             }
+            wave_lds_order();                                    // the next pass writes there again
         }
     } else if (full) {
         if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
