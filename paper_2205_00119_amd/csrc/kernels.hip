@@ -162,10 +162,10 @@ __device__ __forceinline__ void st_f32(float* p, const float (&a)[N])
 // the L2 at once instead of being left there for a later write-back.
 constexpr int kWriteThrough = 17, kNonTemporal = 2;
 
-// How a reduction passes its accumulator through the caches (accum_policy): plain loads and stores;
-// otherwise non-temporal loads and write-through stores from the wavefronts whose lines are whole, with
-// plain loads and either of non-temporal and write-through stores from the others; non-temporal stores
-// from all.
+// How a reduction passes its accumulator through the caches (accum_policy): plain loads and stores
+// (kernels of their own); otherwise write-through stores from the wavefronts whose lines are whole and
+// non-temporal or write-through ones from the others; non-temporal stores from all.  Wavefronts whose lines
+// are whole load it non-temporally, the others plainly up to 8 buffers and non-temporally above.
 enum { kAccCached = 0, kAccThroughLines = 1, kAccThrough = 2, kAccStreamed = 3 };
 
 // A buffer descriptor over `bytes` bytes from a wavefront-uniform address.  Stores outside are dropped.
@@ -597,7 +597,8 @@ __device__ __forceinline__ void rsa_batch(float* s, const Tab& g, int q0, int n,
         if (b <= N - PAD || b < n) rsa_add<KIND, VEC, false>(s, v[b]);
 }
 
-// The last `n` < N buffers: the smallest batch of a multiple of PAD loads that holds them.
+// The last `n` < N buffers: the smallest batch of a multiple of PAD loads that holds them.  (Found by halving,
+// f32, p = 3, 50 k elements took 2.9 us instead of 2.6: the jumps cost more than the comparisons.)
 template <int KIND, int VEC, int N, int PAD, typename Tab>
 __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, size_t elem)
 {
@@ -608,12 +609,14 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 }
 
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
+// `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more
+// instructions, and a small call is over in a few times the latency of what stands in front of its loads.
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
 // batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
 // binary32 addition (-0 + x is x, also for x = -0 and x = +0).
-template <int KIND, int VEC, int P, int BATCH, typename Tab>
-__device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem)
+template <int KIND, int VEC, int P, int BATCH, bool HOLD, typename Tab, typename Issue>
+__device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
     if constexpr (P > 0) {
         #pragma unroll
@@ -624,9 +627,11 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
-            // loads it keeps about 10 in flight by itself, and more cost occupancy (p = 16, 7.5 M: 52.4
-            // against 50.7 us).
-            if constexpr (P <= 8) __builtin_amdgcn_sched_barrier(0);
+            // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (p = 16, 7.5 M: 52.4
+            // against 50.7 us), except in the small calls that HOLD stands for, where latency counts (f32, p = 16,
+            // 42 k elements: 2.4 us, not held 4.0; p = 32, 59 k: 3.7, 5.4; bf16, p = 16, 75 k: 2.7, 3.1).
+            if (q0 == 0) accumulator();
+            if constexpr (P <= 8 || HOLD) __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
                 if (q0 + b < P) {
@@ -641,6 +646,7 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         constexpr int PAD = VEC == 1 ? 8 : 1;
         #pragma unroll
         for (int e = 0; e < VEC * GradFormat<KIND>::kPerDword; ++e) s[e] = -0.0f;
+        accumulator();
         int q0 = 0;
         for (; q0 + BATCH <= p; q0 += BATCH) rsa_batch<KIND, VEC, BATCH, 1>(s, g, q0, BATCH, elem);
         if (q0 < p) rsa_rest<KIND, VEC, BATCH + (PAD > 1 ? PAD : 0), PAD>(s, g, q0, p - q0, elem);
@@ -648,12 +654,13 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
 }
 
 // a[0 .. EPL) = a[0 .. EPL) + partial sum at virtual element `elem`.
-template <int KIND, int VEC, int P, int BATCH, typename Tab>
-__device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const Tab& g, int p, size_t elem)
+template <int KIND, int VEC, int P, int BATCH, bool HOLD, typename Tab, typename Issue>
+__device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const Tab& g, int p, size_t elem,
+                                        Issue&& accumulator)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     float s[EPL];
-    rsa_partial<KIND, VEC, P, BATCH>(s, g, p, elem);
+    rsa_partial<KIND, VEC, P, BATCH, HOLD>(s, g, p, elem, accumulator);
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = a[e] + s[e];
 }
@@ -706,12 +713,16 @@ __device__ __forceinline__ void wave_lds_order()
 // find nothing to do).  A lane whose elements are not all inside the range does nothing:
 // those elements -- fewer than EPL at either end -- are rsa_edges' work.
 //
-// Accumulators of 8-element lanes are stored through LDS: a lane's two 128-bit stores are 32
+// CACHED (kAccCached): plain accesses, straight from the lane.  A kernel of its own, because in small calls
+// every instruction in front of the loads and between sum and store counts (bf16, p = 8, 125 k elements: 2.4
+// us; with the choice made at run time, or through LDS, 2.7).
+//
+// Otherwise accumulators of 8-element lanes are stored through LDS: a lane's two 128-bit stores are 32
 // bytes apart, so each store instruction of the wavefront would fill every other 16 bytes of its
 // cache lines, which leave the L2 between the two halves.  Passing the results through 2 KiB of LDS
 // per wavefront lets every store instruction cover one contiguous KiB.  Vector j of the wavefront's
 // 128 holds half of the elements of lane j / 2.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, typename Tab>
+template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
                                          size_t lead, size_t end, int how)
 {
@@ -720,34 +731,40 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
     float a[EPL];
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
-    if constexpr (VEC == 4) {
+    if constexpr (CACHED) {
+        if (full) {
+            rsa_sum<KIND, VEC, P, BATCH, VEC == 4>(a, g, p, src0 + v0, [&] {
+                if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
+            });
+            st_f32<EPL, false>(acc + (v0 - lead), a);
+        }
+    } else {
         const unsigned lane = threadIdx.x & 63u;
         const size_t wave_v0 = v0 - EPL * lane;
         float* const wave_acc = acc + (wave_v0 - lead);
         const __amdgpu_buffer_rsrc_t out = wave_buffer(wave_acc, 64 * EPL * 4);
         const bool whole = (__builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)wave_acc) & 127) == 0;
-        const bool ntl = whole && how != kAccCached;
         const bool wt = how == kAccThrough || (whole && how == kAccThroughLines);
         auto store = [&](unsigned i, f32x4 v) {
             if (wt) store_vec<kWriteThrough>(out, 16 * i, v);
-            else if (how == kAccCached) store_vec<0>(out, 16 * i, v);
             else MICS_ST(true, (f32x4_a4*)wave_acc + i, v);
         };
         if (full) {
-            // issued before the gradient loads are consumed; with more than 8 buffers the choice between
-            // two kinds of loads costs more registers than it gives (p = 32: 158 instead of 99)
-            if constexpr (ACCUM && P > 0 && P <= 8) {
-                f32x4 t[EPL / 4];
-                #pragma unroll
-                for (int h = 0; h < EPL / 4; ++h)
-                    if (ntl) t[h] = load_vec<kNonTemporal>(out, 4 * EPL * lane + 16 * h);
-                    else t[h] = load_vec<0>(out, 4 * EPL * lane + 16 * h);
-                #pragma unroll
-                for (int e = 0; e < EPL; ++e) a[e] = t[e / 4][e % 4];
-            } else if constexpr (ACCUM) {
-                ld_f32<EPL, true>(a, acc + (v0 - lead));
-            }
-            rsa_sum<KIND, VEC, P, BATCH>(a, g, p, src0 + v0);
+            rsa_sum<KIND, VEC, P, BATCH, false>(a, g, p, src0 + v0, [&] {
+                // with more than 8 buffers the choice between two kinds of loads costs more registers than it
+                // gives (p = 32: 158 instead of 99)
+                if constexpr (ACCUM && P > 0 && P <= 8) {
+                    f32x4 t[EPL / 4];
+                    #pragma unroll
+                    for (int h = 0; h < EPL / 4; ++h)
+                        if (whole) t[h] = load_vec<kNonTemporal>(out, 4 * EPL * lane + 16 * h);
+                        else t[h] = load_vec<0>(out, 4 * EPL * lane + 16 * h);
+                    #pragma unroll
+                    for (int e = 0; e < EPL; ++e) a[e] = t[e / 4][e % 4];
+                } else if constexpr (ACCUM) {
+                    ld_f32<EPL, true>(a, acc + (v0 - lead));
+                }
+            });
         }
         if constexpr (EPL == 4) {
             if (full) store(lane, f32x4{a[0], a[1], a[2], a[3]});
@@ -766,10 +783,6 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             }
             wave_lds_order();                                    // the next pass writes there again
         }
-    } else if (full) {
-        if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
-        rsa_sum<KIND, VEC, P, BATCH>(a, g, p, src0 + v0);
-        st_f32<EPL, false>(acc + (v0 - lead), a);
     }
 }
 
@@ -794,7 +807,7 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
-template <int KIND, int VEC, int P, bool ACCUM, typename Tab>
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
     Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
@@ -811,7 +824,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -829,7 +842,7 @@ struct ReduceSegTable {
     ReduceSeg seg[kMaxSeg];
 };
 
-template <int KIND, int P, bool ACCUM, typename Tab>
+template <int KIND, int P, bool ACCUM, bool CACHED, typename Tab>
 __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
     Tab gtab, float* __restrict__ acc, int p, ReduceSegTable tab, int how)
 {
@@ -840,8 +853,8 @@ __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
     const size_t end = tab.seg[t].end, lead = tab.seg[t].lead;
     const size_t v0 = ((size_t)(x - tab.tile_begin[t]) * blockDim.x + threadIdx.x) * EPL;
     if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, P, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
-    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end,
-                                                how);
+    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM, CACHED>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end,
+                                                        how);
 }
 
 // ---------------------------------------------------------------------------
@@ -1082,7 +1095,7 @@ inline bool stream_acc(size_t elements)
 // 50 M, r = 2 257.3 -> 253.4, r = 4 322 -> 317, r = 8 442 -> 433.  A call at 150 to 250 MB loses 2 to 3 %.
 inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 
-// The accumulator is read with non-temporal loads and written through the L2 (sc0 sc1): the next
+// A large accumulator is read with non-temporal loads and written through the L2 (sc0 sc1): the next
 // micro-step finds it in the Infinity Cache if nothing has displaced it, and if something has, the
 // writes have reached memory in the order of the stream.  us per call, accumulator resident on
 // consecutive calls / not:
@@ -1097,15 +1110,21 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read and
 // the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it plainly where few
 // buffers are read, so that the second one to need a line finds it in the L2 (all with non-temporal
-// loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134; bf16, p = 4, 1.6 M 6.3 / 6.0).  An accumulator that the
-// L2 of 8 x 4 MB holds is left there if few buffers are read (p = 2, bf16, 1.2 M 4.4 / 4.05 us; p = 1, 6.4 M, 26
-// MB, would lose: 12.8 / 14.0).
-int accum_policy(size_t count, int p)
+// loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134; bf16, p = 4, 1.6 M 6.3 / 6.0).
+// An accumulator that the L2 of 8 x 4 MB holds is left there (plain, resident / not, against write-through):
+//   p = 4,  3.7 M (15 MB)  10.2 / 11.3, 11.1 / 11.1     p = 8,  1.0 M (4 MB)   4.9 / 5.5,  5.8 / 5.8
+//   p = 6,  6.0 M (24 MB)  17.9 / 19.5, 19.6 / 19.8     p = 8,  5.0 M (20 MB)  18.7 / 19.8, 19.7 / 19.6
+//   p = 16, 0.8 M (3 MB)   6.4 / 7.0,   6.9 / 6.9       f32, p = 2, 5.3 M (21 MB)  11.2 / 13.8, 13.6 / 13.6
+// but not where the gradients are hardly more than it (bf16, p = 2, 5.0 M, 20 MB: 9.8 / 13.1, 10.6 / 11.5), nor
+// where they are so many that it would be gone before its turn (p = 16, 7.5 M, 30 MB: 51.9 / 52.2, 48.6 / 49.3;
+// p = 32, 0.6 M, 2.5 MB: 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
+int accum_policy(size_t count, int p, int elem_bytes)
 {
-    constexpr size_t kSmall = 64u << 20, kTiny = 12u << 20;
+    constexpr size_t kSmall = 64u << 20;
+    const size_t cached = p < 4 && elem_bytes == 2 ? 16u << 20 : p < 12 ? 32u << 20 : p < 32 ? 12u << 20 : 1u << 20;
     if (stream_acc(count)) return kAccStreamed;
+    if (count * 4 <= cached) return kAccCached;
     if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
-    if (p < 12 && count * 4 <= kTiny) return kAccCached;
     return p < 16 && count * 4 <= kSmall ? kAccThrough : kAccThroughLines;
 }
 
@@ -1282,7 +1301,11 @@ int dispatch_group(int p, F&& f)
     switch (p) {
         case 1: return f(std::integral_constant<int, 1>{});
         case 2: return f(std::integral_constant<int, 2>{});
+        case 3: return f(std::integral_constant<int, 3>{});
         case 4: return f(std::integral_constant<int, 4>{});
+        case 5: return f(std::integral_constant<int, 5>{});
+        case 6: return f(std::integral_constant<int, 6>{});
+        case 7: return f(std::integral_constant<int, 7>{});
         case 8: return f(std::integral_constant<int, 8>{});
         case 16: return f(std::integral_constant<int, 16>{});
         case 32: return f(std::integral_constant<int, 32>{});
@@ -1402,18 +1425,18 @@ inline bool narrow_call(int p, size_t elem_bytes, size_t count)
     return p >= 40 ? bytes <= (68u << 20) : p >= 20 && elem_bytes == 2 && bytes <= (24u << 20);
 }
 
-template <int KIND, int VEC, int P, bool ACCUM>
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
-               const Shape& sh, hipStream_t st)
+               const Shape& sh, int how, hipStream_t st)
 {
-    // lanes of 8 elements pass their results through 32 bytes of LDS
-    const size_t lds = lds_for(sh, VEC == 4 && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
+    // lanes of 8 elements pass their results through 32 bytes of LDS (rsa_lane)
+    const size_t lds = lds_for(sh, !CACHED && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
     if constexpr (P > 0)
-        return launch(rsa_kernel<KIND, VEC, P, ACCUM, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
-                      small<P>(g), acc, p, lead, count, accum_policy(count, p));
+        return launch(rsa_kernel<KIND, VEC, P, ACCUM, CACHED, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
+                      small<P>(g), acc, p, lead, count, how);
     else
-        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
-                      acc, p, lead, count, accum_policy(count, p));
+        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, CACHED, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
+                      acc, p, lead, count, how);
 }
 
 template <int KIND>
@@ -1424,13 +1447,13 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     constexpr size_t PD = GradFormat<KIND>::kPerDword;
     unsigned blocks = 0;
     // small message on a large group: one dword per lane and buffer
-    constexpr size_t GB = GradFormat<KIND>::kElemBytes;
+    constexpr int GB = GradFormat<KIND>::kElemBytes;
     if (narrow_call(p, GB, count)) {
         const Shape narrow = {kNarrowBlock, 0};
         const size_t nlanes = (lead + count + PD - 1) / PD;
         if (int e = grid_for(nlanes, kNarrowBlock, MICS_RSA_BPC, &blocks)) return e;
-        return accumulate ? rsa_launch<KIND, 1, 0, true>(acc, g, p, lead, count, blocks, narrow, st)
-                          : rsa_launch<KIND, 1, 0, false>(acc, g, p, lead, count, blocks, narrow, st);
+        return accumulate ? rsa_launch<KIND, 1, 0, true, true>(acc, g, p, lead, count, blocks, narrow, kAccCached, st)
+                          : rsa_launch<KIND, 1, 0, false, true>(acc, g, p, lead, count, blocks, narrow, kAccCached, st);
     }
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
@@ -1438,9 +1461,12 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
+    const int how = accum_policy(count, p, GB);
     return dispatch_bool(accumulate, [&](auto A) {
-        return dispatch_group(p, [&](auto P) {
-            return rsa_launch<KIND, 4, P.value, A.value>(acc, g, p, lead, count, blocks, sh, st);
+        return dispatch_bool(how == kAccCached, [&](auto C) {
+            return dispatch_group(p, [&](auto P) {
+                return rsa_launch<KIND, 4, P.value, A.value, C.value>(acc, g, p, lead, count, blocks, sh, how, st);
+            });
         });
     });
 }
@@ -1631,18 +1657,20 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         }
         for (int t = tab.n; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
         if (tiles == 0) continue;
-        const int how = accum_policy(elements, p);
+        const int how = accum_policy(elements, p, (int)GB);
         const int err = dispatch_bool(accumulate, [&](auto A) {
-            // lanes of 8 elements pass their results through 32 bytes of LDS
-            const size_t lds = lds_for(sh, EPL == 8 ? (size_t)sh.lanes * 32 : 0);
-            const dim3 gr((unsigned)tiles), bl(sh.lanes);
-            return dispatch_group(p, [&](auto P) {
-                if constexpr (P.value > 0)
-                    return launch(rsa_seg_kernel<KIND, P.value, A.value, SmallTable<P.value>>, gr, bl, lds, st,
-                                  small<P.value>(g), acc, p, tab, how);
-                else
-                    return launch(rsa_seg_kernel<KIND, 0, A.value, PtrTable>, gr, bl, lds, st, g, acc, p, tab,
-                                  how);
+            return dispatch_bool(how == kAccCached, [&](auto C) {
+                // lanes of 8 elements pass their results through 32 bytes of LDS
+                const size_t lds = lds_for(sh, !C.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
+                const dim3 gr((unsigned)tiles), bl(sh.lanes);
+                return dispatch_group(p, [&](auto P) {
+                    if constexpr (P.value > 0)
+                        return launch(rsa_seg_kernel<KIND, P.value, A.value, C.value, SmallTable<P.value>>, gr, bl, lds,
+                                      st, small<P.value>(g), acc, p, tab, how);
+                    else
+                        return launch(rsa_seg_kernel<KIND, 0, A.value, C.value, PtrTable>, gr, bl, lds, st, g, acc, p,
+                                      tab, how);
+                });
             });
         });
         if (err) return err;

@@ -147,6 +147,21 @@ def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, thresho
         mics.mics_set_stream_threshold_bytes(0)
 
 
+@pytest.mark.parametrize("name,p,count", [("bf16", 2, 4194307), ("bf16", 7, 8388611), ("f32", 3, 8388617), ("f16", 11, 8388609),
+                                          ("bf16", 16, 3145735), ("f32", 32, 262147), ("bf16", 32, 3300001)])
+def test_reduce_at_the_largest_accumulator_that_stays_in_the_l2(orc, gen, name, p, count):
+    """Accumulators beyond what the caches are left with take the kernels that store whole lines, by groups; at
+    the line and behind it, on and off the 128-byte lines."""
+    code = FORMATS[name][0]
+    host, dev = rank_buffers(gen, name, p, count + 5, [0])
+    for n, offset, skew in ((count - 8, 0, 0), (count, 0, 0), (count, 5, 0), (count, 0, 3)):
+        ref, acc = start_acc(gen, n, skew=skew)
+        mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], offset, n, True, code)
+        orc.reduce_scatter_accum_typed(ref, host, offset, True, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), (n, offset, skew)
+
+
 @pytest.mark.parametrize("r,count,skew", [(2, 300001, 0), (2, 2100003, 1), (3, 9000001, 0), (1, 11000003, 0),
                                           (5, 6000002, 3), (8, 2600001, 0), (8, 3600001, 1), (8, 6000003, 0), (11, 300007, 1)])
 def test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew):
