@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <initializer_list>
 #include <type_traits>
 
 #include "internal.h"
@@ -911,9 +912,10 @@ __device__ __forceinline__ float avg_sum1(const Tab& a, int r, size_t x)
     return sum;
 }
 
-// SO ("stream the output"): non-temporal stores for results too large for the Infinity Cache,
-// as for the accumulator of the reduce kernels.
-template <int R, bool SO, typename Tab>
+// STORE: how the result passes the caches (average_store).
+enum { kOutPlain = 0, kOutThrough = 1, kOutStreamed = 2 };
+
+template <int R, int STORE, typename Tab>
 __global__ __launch_bounds__(kMaxBlock) void avg_kernel(
     float* out, Tab a, int r, float scale, size_t count)
 {
@@ -923,9 +925,11 @@ __global__ __launch_bounds__(kMaxBlock) void avg_kernel(
         const size_t x = 4 * i;
         if (x + 4 <= count) {
             const f32x4 sum = avg_sum4<R, kAvgNtl>(a, r, x);
-            const unsigned lane = threadIdx.x & 63u;
-            if constexpr (SO) MICS_ST(true, (f32x4_a4*)(out + x), sum * scale);
-            else store_vec<kWriteThrough>(wave_buffer(out + (x - 4 * lane), 1024), 16 * lane, sum * scale);
+            [[maybe_unused]] const unsigned lane = threadIdx.x & 63u;
+            if constexpr (STORE == kOutThrough)
+                store_vec<kWriteThrough>(wave_buffer(out + (x - 4 * lane), 1024), 16 * lane, sum * scale);
+            else
+                MICS_ST(STORE == kOutStreamed, (f32x4_a4*)(out + x), sum * scale);
         }
     }
     // the last count mod 4 elements: one per lane
@@ -1230,29 +1234,64 @@ Shape small_call(size_t nlanes, size_t units)
     return Shape{waste(512) <= 1.12 ? 512 : waste(256) <= 1.12 ? 256 : 64, 0};
 }
 
+// True if the buffers begin on 128-byte lines.
+bool on_lines(std::initializer_list<const void*> buffers)
+{
+    uintptr_t bits = 0;
+    for (const void* b : buffers) bits |= (uintptr_t)b;
+    return bits % 128 == 0;
+}
+bool on_lines(const PtrTable& t, int n)
+{
+    uintptr_t bits = 0;
+    for (int i = 0; i < n; ++i) bits |= (uintptr_t)t.ptr[i];
+    return bits % 128 == 0;
+}
+
 // Where a single buffer spans gigabytes (all the shards of a group in one call), still fewer request
 // streams are better, us with the caps above / with those for huge calls: reduce p = 16, 805 M elements
 // 5436 / 5278, p = 8, 201 M 742 / 730; Adam, 402 M 1940 / 1900, 805 M 3980 / 3830; average + Adam, r = 4,
 // 402 M 2660 / 2590; average r = 2, 402 M 749 / 735.
 constexpr size_t kHugeElements = 192u << 20;
 
+// Wavefronts whose copies or states begin off the 128-byte lines share a line at each end with the next one,
+// which finds it in the L2 only if both run at about the same time: full-size workgroups, uncapped.  us, everything 4
+// bytes off, 64 lanes / 512: average + Adam, r = 8, 1.4 M elements 18.0 / 16.5, r = 6, 4 M 41 / 38; average, r = 4, 10 M
+// 34.4 / 32.3.
+Shape off_lines(size_t nlanes, size_t units)
+{
+    return nlanes * 2 <= (size_t)kMaxBlock * units ? Shape{64, 0} : Shape{kMaxBlock, 0};
+}
+
+// The average's result is left in the L2 by small calls and written through it by larger ones, us plain / through:
+// r = 2, 1.2 M elements 3.7 / 4.0, 3.3 M 7.3 / 7.7, 6.7 M 15.0 / 14.5; r = 4, 1 M 4.85 / 5.0, 3 M 11.0 / 10.7, 5.5 M 20.8 / 18.4;
+// r = 16, 0.88 M 10.9 / 11.2, 1.6 M 19.3 / 19.2.  A single copy: 1 M 3.0 / 3.2, 2.5 M 5.0 / 4.75.
+int average_store(int r, size_t count, bool streamed)
+{
+    if (streamed) return kOutStreamed;
+    return count * (4 * (size_t)r + 4) < ((r < 2 ? 18u : 64u) << 20) ? kOutPlain : kOutThrough;
+}
+
 // The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
 // 64x16 14.9, r = 8 at 151 MB 27.3, 64x10 26.1; average + Adam at 143 MB 25.5, 64x10 26.1, at 334 MB
 // 55.8, 52.9, r = 8 at 122 MB 22.3, 64x10 22.9, at 243 MB 48.3, 45.3; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
-Shape average_shape(int r, size_t count, bool streamed, size_t units)
+Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units)
 {
-    const size_t traffic = count * (4 * (size_t)r + 4);
+    const size_t traffic = count * (4 * (size_t)r + 4), nlanes = (count + 3) / 4;
+    // a single copy below 18 MB: 1 M elements 2.94, 64x32 3.02; 1.7 M 3.8, 4.0
+    if (!lines || (r < 2 && traffic < (18u << 20))) return with_knobs(kFamAverage, off_lines(nlanes, units));
     // few copies, few loads in flight per lane: every wavefront that fits
     if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
-    if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call((count + 3) / 4, units));
+    if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call(nlanes, units));
     return with_knobs(kFamAverage, Shape{64, r >= 6 ? 10 : traffic < (600u << 20) || (r < 5 && streamed) ? 16 : 12});
 }
 
 Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 12}); }
 
-Shape fused_shape(int r, size_t count, size_t units)
+Shape fused_shape(int r, size_t count, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 26);
+    if (!lines) return with_knobs(kFamFused, off_lines((count + 3) / 4, units));
     if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
     if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 7 : 5});
@@ -1491,11 +1530,11 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
     const bool streamed = stream_acc(count);
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
-    const Shape sh = average_shape(r, count, streamed, units);
+    const Shape sh = average_shape(r, count, streamed, on_lines(a, r), units);
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_AVG_BPC, &blocks)) return e;
     const dim3 gr(blocks), bl(sh.lanes);
-    return dispatch_bool(streamed, [&](auto SO) {
+    auto run = [&](auto SO) {
         switch (r) {
             case 1: return launch(avg_kernel<1, SO.value, SmallTable<1>>, gr, bl, lds, st, out, small<1>(a), r, scale, count);
             case 2: return launch(avg_kernel<2, SO.value, SmallTable<2>>, gr, bl, lds, st, out, small<2>(a), r, scale, count);
@@ -1503,7 +1542,12 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
             case 8: return launch(avg_kernel<8, SO.value, SmallTable<8>>, gr, bl, lds, st, out, small<8>(a), r, scale, count);
             default: return launch(avg_kernel<0, SO.value, PtrTable>, gr, bl, lds, st, out, a, r, scale, count);
         }
-    });
+    };
+    switch (average_store(r, count, streamed)) {
+        case kOutPlain: return run(std::integral_constant<int, kOutPlain>{});
+        case kOutThrough: return run(std::integral_constant<int, kOutThrough>{});
+        default: return run(std::integral_constant<int, kOutStreamed>{});
+    }
 }
 
 namespace {
@@ -1699,8 +1743,10 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
     unsigned blocks = 0;
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
-    const Shape sh = fused_shape(r, count, units);
-    const bool through = states_through(count * (4 * (size_t)r + 26));
+    const bool lines = on_lines(copies, r) && on_lines({master, exp_avg, exp_avg_sq});
+    const Shape sh = fused_shape(r, count, lines, units);
+    // off the lines: 17.6 M elements, r = 2, 110 us, through the L2 124
+    const bool through = lines && states_through(count * (4 * (size_t)r + 26));
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto BF) {

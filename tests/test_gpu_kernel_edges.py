@@ -163,7 +163,7 @@ def test_reduce_at_the_largest_accumulator_that_stays_in_the_l2(orc, gen, name, 
 
 
 @pytest.mark.parametrize("r,count,skew", [(2, 300001, 0), (2, 2100003, 1), (3, 9000001, 0), (1, 11000003, 0),
-                                          (5, 6000002, 3), (8, 2600001, 0), (8, 3600001, 1), (8, 6000003, 0), (11, 300007, 1)])
+                                          (1, 900001, 0), (1, 2700001, 1), (8, 5600001, 32), (5, 6000002, 3), (8, 2600001, 0), (8, 3600001, 1), (8, 6000003, 0), (11, 300007, 1)])
 def test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew):
     """Sizes on both sides of the lines of the average's and the update's launch rules and of the
     kinds of store, with a ragged end."""
