@@ -1292,7 +1292,10 @@ Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units
     // few copies, few loads in flight per lane: every wavefront that fits
     if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
     if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call(nlanes, units));
-    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 10 : traffic < (600u << 20) || (r < 5 && streamed) ? 16 : 12});
+    // 4 copies, caps of 16 / 12: 450 MB 67 / 68 us, 600 MB 97 / 93, 1.1 GB 176 / 165, streamed 1.5 GB 232 / 254; 5 copies:
+    // 150 MB 24.4 / 25.1, 300 MB 46.8 / 46.0, 1.1 GB 174 / 165, streamed 2.5 GB 389 / 367
+    const bool wide = r < 5 ? traffic < (500u << 20) || streamed : traffic < (250u << 20);
+    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 10 : wide ? 16 : 12});
 }
 
 Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 12}); }
@@ -1304,7 +1307,10 @@ Shape fused_shape(int r, size_t count, bool lines, size_t units)
     if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
     if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 7 : 5});
-    return with_knobs(kFamFused, Shape{64, r < 2 ? 12 : r < 3 ? 10 : r < 8 ? (68 + r) / (r + 3) : 6});
+    // us at 50 M elements with caps of 7 / 8 / 10 / 12: r = 3 386 / 317 / 297 / 284, r = 4 322 / 319 / 324 / 327, r = 5 408 / 349 /
+    // 342 / 358, r = 6 422 / 372 / 379 / 392, r = 7 436 / 406 / 419 / 430; within 1 % of that order from 10 to 100 M
+    constexpr int kCap[8] = {0, 12, 10, 12, 8, 10, 8, 8};
+    return with_knobs(kFamFused, Shape{64, r < 8 ? kCap[r] : 6});
 }
 
 Shape reorder_shape(size_t traffic, int lanes)
@@ -1455,7 +1461,7 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
     } else if (grads16) {
         const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
-        sh = Shape{64, p < 4 ? 0 : p < 6 ? (nlanes < units * 12000 ? 0 : huge ? 12 : 16) : p < 8 ? 14 :
+        sh = Shape{64, p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
                        p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
     } else {
         sh = Shape{kMaxBlock, 16};
