@@ -1469,15 +1469,20 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
     return with_knobs(kFamReduce, sh);
 }
 
-// Small messages on large groups take the one-dword-per-lane kernel (VEC = 1).  us per call, one dword /
-// 128 bits per lane: p = 64, 66 k elements 3.8 / 6.8, 262 k 7.6 / 8.8, 524 k 13.8 / 13.4; p = 128, 33 k 4.5 /
-// 11.0, 262 k 13.0 / 15.4; p = 48, 262 k 6.1 / 7.2, 1 M 20.1 / 18.7; smaller groups of 2-byte elements
-// only while the call is all latency: p = 32, 131 k 3.8 / 4.6, 524 k 8.1 / 8.1; p = 24, 350 k 5.3 / 6.4;
-// p = 16, 262 k 4.0 / 3.9.
-inline bool narrow_call(int p, size_t elem_bytes, size_t count)
+// Small messages on large groups take the one-dword-per-lane kernel (VEC = 1), MB of gradients up to which it
+// wins.  us per call, one dword / 128 bits per lane:
+//   bf16, p = 20 5 MB 3.4 / 3.9, 19 MB 6.0 / 6.0, 32 MB 8.9 / 8.2      p = 32 13 MB 4.3 / 4.7, 24 MB 6.4 / 6.3
+//         p = 48 13 MB 4.5 / 5.8, 49 MB 10.7 / 12.2, 63 MB 13.7 / 12.9  p = 40 49 MB 10.9 / 11.6, 62 MB 13.6 / 12.9
+//         p = 64 1 MB 3.0 / 6.4, 50 MB 10.7 / 11.6, 65 MB 13.5 / 14.6   p = 128 3 MB 4.3 / 11.2, 67 MB 12.7 / 15.9
+//   f32 alike: p = 48 51 MB 10.3 / 11.4, 66 MB 13.1 / 12.7; p = 64 67 MB 12.8 / 14.3; p = 96 79 MB 15.0 / 15.2
+// and about half of that where the buffers sit at different positions inside their lines, which costs every dword
+// load (bf16, p = 24 12 MB 5.4 / 5.5, 23 MB 8.3 / 7.2; p = 48 21 MB 7.1 / 7.1, 35 MB 10.6 / 9.3; p = 64 31 MB 9.2 / 8.9;
+// p = 128 52 MB 14.5 / 15.2, 67 MB 18.4 / 17.7).
+inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line)
 {
-    const size_t bytes = count * (size_t)p * elem_bytes;
-    return p >= 40 ? bytes <= (68u << 20) : p >= 20 && elem_bytes == 2 && bytes <= (24u << 20);
+    const size_t most = p >= 96 ? (same_line ? 72 : 52) : p >= 56 ? (same_line ? 68 : 28) : p >= 40 ? (same_line ? 54 : 22)
+                        : p >= 20 && elem_bytes == 2 ? (same_line ? 24 : 12) : 0;
+    return count <= (most << 20) / ((size_t)p * elem_bytes);
 }
 
 template <int KIND, int VEC, int P, bool ACCUM, bool CACHED>
@@ -1503,7 +1508,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     unsigned blocks = 0;
     // small message on a large group: one dword per lane and buffer
     constexpr int GB = GradFormat<KIND>::kElemBytes;
-    if (narrow_call(p, GB, count)) {
+    if (narrow_call(p, GB, count, line >= 16)) {
         const Shape narrow = {kNarrowBlock, 0};
         const size_t nlanes = (lead + count + PD - 1) / PD;
         if (int e = grid_for(nlanes, kNarrowBlock, MICS_RSA_BPC, &blocks)) return e;

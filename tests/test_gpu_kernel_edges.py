@@ -88,12 +88,14 @@ def test_reduce_with_every_remainder_of_the_load_batches(orc, gen, name, p):
         assert same_bits(acc, ref), accumulate
 
 
-@pytest.mark.parametrize("elem_bytes,p", [(2, 20), (2, 40), (4, 40)])
-def test_reduce_on_both_sides_of_the_one_dword_rule(orc, gen, elem_bytes, p):
-    limit = (24 if p < 40 else 68) << 20
+@pytest.mark.parametrize("elem_bytes,p,limit,skews", [(2, 20, 24, [0]), (2, 40, 54, [0]), (4, 40, 54, [0]), (2, 64, 68, [0]),
+                                                      (4, 96, 72, [0]), (2, 24, 12, [0, 1]), (4, 48, 22, [0, 1]), (2, 64, 28, [0, 3]),
+                                                      (2, 100, 52, [1, 0])])
+def test_reduce_on_both_sides_of_the_one_dword_rule(orc, gen, elem_bytes, p, limit, skews):
+    limit <<= 20
     for count in (limit // (p * elem_bytes), limit // (p * elem_bytes) + 1):
         name = "bf16" if elem_bytes == 2 else "f32"
-        host, dev = rank_buffers(gen, name, p, count, [0])
+        host, dev = rank_buffers(gen, name, p, count, skews)
         ref, acc = start_acc(gen, count)
         mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], 0, count, True, FORMATS[name][0])
         orc.reduce_scatter_accum_typed(ref, host, 0, True, FORMATS[name][0])
