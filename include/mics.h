@@ -45,12 +45,14 @@
  *   - Return value: MICS_OK or a negative MICS_ERR_*; mics_last_error() gives
  *     the text for the calling thread's most recent failure.
  *   - bf16 values travel as uint16_t bit patterns (upper half of a binary32).
- *   - Pointers must be aligned to their element size; that is all the
- *     element-wise calls (reduce, average, Adam) need for full speed, except
- *     that the gradient buffers of one call should all start at the same
- *     position inside a 128-byte line (otherwise up to about 12 % slower).  The reorder
- *     runs at copy speed when every buffer and the shard size are multiples
- *     of 16 bytes and through a re-phasing kernel (about 5 % slower) otherwise.
+ *   - Pointers must be aligned to their element size.  Full speed needs 128-byte
+ *     aligned buffers, as separate allocations are: averages and updates on
+ *     copies or states off that alignment are 15 to 40 % slower, reductions into
+ *     such an accumulator 2 to 10 %.  Gradient buffers may start anywhere as
+ *     long as those of one call all start at the same position inside a
+ *     128-byte line (otherwise 4 to 16 % slower).  The reorder runs at copy
+ *     speed when every buffer and the shard size are multiples of 16 bytes
+ *     and through a re-phasing kernel (about 5 % slower) otherwise.
  *   - Buffers of one call must not overlap unless stated.
  */
 #ifndef MICS_H

@@ -1,7 +1,7 @@
 /*
  * libmics -- measurement and test knobs.  Not part of the method (no citation of the paper
- * applies): neither call changes any result, only how the kernels of later calls are
- * launched.  Both are process-wide and may be called at any time; calls that are already
+ * applies): none of the three calls changes any result, only how the kernels of later calls are
+ * launched.  They are process-wide and may be called at any time; calls that are already
  * enqueued are not affected.  The benchmark, the sweeps and the tests use them; a training
  * loop has no reason to.
  */

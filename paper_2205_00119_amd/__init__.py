@@ -1,7 +1,7 @@
 """MI355X-native per-GPU data path of MiCS partitioned data parallelism.
 
 Thin ctypes binding over ``libmics.so`` (see ``include/mics.h`` for the contract of each
-call, ``include/mics_tuning.h`` for the two measurement knobs).  The functions here only marshal arguments -- device pointers, sizes and the
+call, ``include/mics_tuning.h`` for the three measurement knobs).  The functions here only marshal arguments -- device pointers, sizes and the
 current HIP stream; every step of the path runs in the library's HIP kernels.  There is
 no CPU fallback: if the library is missing, importing this package fails.
 """

@@ -10,12 +10,12 @@
 // MI355X: a lane that owns several vectors a grid stride apart, or a small
 // persistent grid, loses 5-30 % of the bandwidth, stores most of all).
 //
-// Alignment.  gfx950 executes a 128-bit global access at any address.  Measured on MI355X
-// (p = 16 reduce, 50 M and 200 M elements): accesses that are only 4-byte aligned run at the
-// speed of 16-byte aligned ones; 2-byte aligned ones lose about 20 %.  So the element-wise
-// kernels use 128-bit accesses on under-aligned vector types everywhere, a lane that would
-// cross the end of a buffer works element by element inside the same kernel (no tail
-// launches), and only the gradient pointers are rounded down first (align_gradient_pointers).
+// Alignment.  gfx950 executes a 128-bit global access at any address, at full speed from 4 bytes on (2-byte
+// aligned ones lose about 20 % of a p = 16 reduction).  What costs is the 128-byte lines that two wavefronts share:
+// a 1 KiB access off the lines touches nine instead of eight (Adam, everything 4 bytes off, 20 M elements 92 us ->
+// 122).  So the element-wise kernels use 128-bit accesses on under-aligned vector types everywhere, a lane
+// that would cross the end of a buffer works element by element inside the same kernel (no tail launches), and
+// the gradient pointers, most of a reduction's bytes, are rounded down to the lines (align_gradient_pointers).
 //
 // Arithmetic rules (they make the results reproducible bit for bit):
 //   - no fused multiply-add (-ffp-contract=off and the pragma below),
@@ -51,7 +51,7 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 // Launch shape and cache hints per kernel family; the defaults are the measured best on
 // MI355X for the h = 8192, p = 16 shard shapes.  *_BLOCK = workgroup size, *_BPC = cap on
 // workgroups per compute unit (the grid covers the data with one pass per lane unless the
-// cap is reached; lanes stride over the rest), *_NTL / *_NTS = non-temporal loads / stores.
+// cap is reached; lanes stride over the rest), *_NTL = non-temporal loads.
 #ifndef MICS_REORDER_BLOCK
 #define MICS_REORDER_BLOCK 64
 #endif
@@ -60,9 +60,6 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #endif
 #ifndef MICS_REORDER_NTL
 #define MICS_REORDER_NTL 1
-#endif
-#ifndef MICS_REORDER_NTS
-#define MICS_REORDER_NTS 1
 #endif
 #ifndef MICS_RSA_BPC
 #define MICS_RSA_BPC 4096
@@ -87,7 +84,7 @@ typedef f32x2 f32x2_a4 __attribute__((aligned(4)));
 #endif
 constexpr int kMaxBlock = 512;           // most lanes per workgroup of the element-wise kernels
 constexpr int kNarrowBlock = 64;         // ... of the one-dword-per-lane reduction
-constexpr bool kReorderNtl = MICS_REORDER_NTL, kReorderNts = MICS_REORDER_NTS;
+constexpr bool kReorderNtl = MICS_REORDER_NTL;
 constexpr bool kRsaNtl = MICS_RSA_NTL;   // gradient loads; the accumulator's hint is chosen per launch
 constexpr bool kAvgNtl = MICS_AVG_NTL;   // input loads; the output's hint is chosen per launch
 constexpr bool kAdamNtl = MICS_ADAM_NTL;
@@ -99,11 +96,12 @@ struct SmallTable {
     const void* ptr[N];
 };
 
-// What a kernel indexes: a SmallTable itself (constant indices), or a table through the
+// What a reduction indexes: a SmallTable itself (constant indices), or a table through the
 // kernel-argument segment, so that run-time indices stay scalar loads, of several pointers at once
-// where they are consecutive.  (Indexing the by-value parameter at run time made one dependent
-// 8-byte load of every pointer, 64 of them 5 us.)  The kernels have their table as the first
-// parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer repeat it
+// where they are consecutive.  (Indexing the by-value parameter at run time makes one dependent
+// 8-byte load of every pointer, 64 of them 5 us; the averages of 3, 5, 6, 7 and more than 8 copies still do, because
+// large calls measured slower with whole batches: r = 6, 190 -> 197 us.)  Its kernels have their table as the
+// first parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer repeat it
 // (pad_table).
 struct KernargTable {
     const void* const __attribute__((address_space(4)))* ptr;
@@ -487,7 +485,7 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
                     if (phase != 0 && (s_vec + 16 * i < s_chunk || i + 1 == last))
                         out = MICS_LD(true, (const u32x4_a2*)(s_line + 16 * i));
                 }
-                MICS_ST(kReorderNts, (u32x4*)(d_line + 16 * i), out);
+                MICS_ST(true, (u32x4*)(d_line + 16 * i), out);
             }
         };
         if (phase == 0) put(std::integral_constant<int, -1>{});

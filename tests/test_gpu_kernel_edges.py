@@ -39,8 +39,9 @@ def same_bits(dev, ref):
 @pytest.mark.parametrize("name", list(FORMATS))
 @pytest.mark.parametrize("p", [3, 16, 48, 72])
 def test_reduce_at_every_position_inside_a_line(orc, gen, name, p):
-    """Gradient pointers are rounded down to 16 bytes: every position inside the line, at counts
-    around a lane's, a wavefront's and a workgroup's elements, flat and as segments of one call."""
+    """Gradient pointers are rounded down to a line (128 bytes from 4 buffers on, else 16): the first 16 bytes'
+    positions, at counts around a lane's, a wavefront's and a workgroup's elements, flat and as segments of
+    one call."""
     code = FORMATS[name][0]
     for phase in range(8 if name != "f32" else 4):
         for count in (1, 6, 8, 9, 511, 513, 4099):
