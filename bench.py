@@ -182,12 +182,12 @@ class Workload:
             self.T_views = [W[l * nodes * S:(l + 1) * nodes * S] for l in range(k)]
 
             # a2: per micro-step, p gradient buffers covering the elements this call owns.  Each rank
-            # buffer is its own 16-byte aligned allocation in a real run, and the rank reads it from
+            # buffer is its own allocation in a real run (256-byte aligned), and the rank reads it from
             # element offset g*S on: rows are padded so that every view below starts at the same
-            # position inside a 16-byte line as that offset would (0 unless S is odd).
+            # position inside 256 bytes as that offset would.
             n_sets = 1 if group else s
-            lead = offset % 8
-            row = -(-(lead + count) // 8) * 8
+            lead = offset % (256 // self.gb)
+            row = self.allocation_row(lead + count)
             grads = torch.empty((n_sets, p, row), dtype=g_dt, device=dev)
             for t in range(n_sets):
                 for q in range(p):
@@ -219,7 +219,7 @@ class Workload:
             # a2: every rank's full gradient buffer (all tensors, p*S_t each); the rank reads its slices
             # distinct gradient data per micro-step as far as ~120 GB go (every set is far beyond any cache)
             n_sets = max(1, min(s, 4, int(120e9 // (self.gb * p * lay.grad_off[-1]))))
-            grads = torch.empty((n_sets, p, -(-lay.grad_off[-1] // 8) * 8), dtype=g_dt, device=dev)
+            grads = torch.empty((n_sets, p, self.allocation_row(lay.grad_off[-1])), dtype=g_dt, device=dev)
             for t in range(n_sets):
                 for q in range(p):
                     fill(grads[t, q], synth.stream_key(cfg.seed, synth.ROLE_GRAD, 0, t, q), 0, g_tab, self.gb,
@@ -255,6 +255,11 @@ class Workload:
         self.hp = dict(lr=cfg.lr, beta1=cfg.beta1, beta2=cfg.beta2, eps=cfg.eps, weight_decay=cfg.weight_decay)
         torch.cuda.synchronize()
         self.marks = []
+
+    def allocation_row(self, elements):
+        """Elements per row of a gradient tensor whose rows stand for allocations of their own."""
+        unit = 256 // self.gb
+        return -(-elements // unit) * unit
 
     def gather(self):
         a, cfg, m = self.args, self.cfg, self.mics
@@ -435,7 +440,7 @@ class Workload:
             },
             "roofline": {
                 "kernel": (f"rsa_seg_kernel<{p}> (mics_reduce_scatter_accum_coalesced)" if a.coalesced
-                           else f"rsa_kernel<{kind}, 4, {p if p in (1, 2, 4, 8, 16, 32) else 0}> "
+                           else f"rsa_kernel<{kind}, 4, {p if p in (1, 2, 3, 4, 5, 6, 7, 8, 16, 32) else 0}> "
                                 f"({'mics_reduce_scatter_accum' if kind == 0 else 'mics_reduce_scatter_accum_typed'})"),
                 "bound": "hbm",
                 "achieved": round(a2_gbps, 1),
