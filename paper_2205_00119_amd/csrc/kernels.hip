@@ -1119,8 +1119,8 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // Non-temporal stores win where the accumulator is beyond the 224 MiB that the cache absorbs (p = 8,
 // 101 M elements: 364 against 375), for 32 and more buffers beyond 64 MiB (p = 32, 25 M: 289, 302),
 // and where the lines at the two ends of a wavefront's piece are not whole (accumulator off 128
-// bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read and
-// the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it plainly where few
+// bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read (p = 2, 42 M: 85.5, 79.8;
+// f32, p = 3, 40 M: 137, 132) or the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it plainly where few
 // buffers are read, so that the second one to need a line finds it in the L2 (all with non-temporal
 // loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134; bf16, p = 4, 1.6 M 6.3 / 6.0).
 // An accumulator that the L2 of 8 x 4 MB holds is left there (plain, resident / not, against write-through):
@@ -1137,7 +1137,7 @@ int accum_policy(size_t count, int p, int elem_bytes)
     if (stream_acc(count)) return kAccStreamed;
     if (count * 4 <= cached) return kAccCached;
     if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
-    return p < 16 && count * 4 <= kSmall ? kAccThrough : kAccThroughLines;
+    return p < 4 || (p < 16 && count * 4 <= kSmall) ? kAccThrough : kAccThroughLines;
 }
 
 int compute_units(int* out)
@@ -1448,7 +1448,8 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
 //     64 x 10 44.5, 512 x 32 42.9), and up again where the accumulator is off 16 bytes in the lanes'
 //     grid, because the partial lines between two wavefronts then meet in one workgroup (2 M for p < 16;
 //     p = 8, 9.8 M: 64 x 10 40.7, 512 x 32 39.2; 30 M: 114, 119).  Gradients off 16 bytes: 512 x 16
-//     (p = 16, 50 M: 344, 64 x 8 350).
+//     (p = 16, 50 M: 344, 64 x 8 350).  Up to 3 two-byte buffers with either off: 256 lanes, uncapped (p = 2,
+//     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5).
 //   - Below, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
 //     uncapped 28.7).
 Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, size_t units)
@@ -1460,10 +1461,10 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
     } else if (grads16) {
         const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
-        sh = Shape{64, p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
+        sh = Shape{p < 4 && elem_bytes == 2 && !acc16 ? 256 : 64, p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
                        p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
     } else {
-        sh = Shape{kMaxBlock, 16};
+        sh = p < 4 && elem_bytes == 2 ? Shape{256, 0} : Shape{kMaxBlock, 16};
     }
     return with_knobs(kFamReduce, sh);
 }
