@@ -634,12 +634,12 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             #pragma unroll
             for (int b = 0; b < BATCH; ++b)
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
+            if (q0 == 0) accumulator();
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
             // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (p = 16, 7.5 M: 52.4
             // against 50.7 us), except in the small calls that HOLD stands for, where latency counts (f32, p = 16,
             // 42 k elements: 2.4 us, not held 4.0; p = 32, 59 k: 3.7, 5.4; bf16, p = 16, 75 k: 2.7, 3.1).
-            if (q0 == 0) accumulator();
             if constexpr (P <= 8 || HOLD) __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
@@ -1090,9 +1090,9 @@ __global__ __launch_bounds__(kMaxBlock) void avg_adam_kernel(
 // ---------------------------------------------------------------------------
 
 std::atomic<int> g_blocks_per_cu{0};
-// Built-in policy for outputs (replica average) and the launch shapes of the update: up to 224 MiB
-// -- what the 256 MB Infinity Cache absorbs -- they are left cacheable, larger ones are streamed.
-// An explicit threshold (0 = none) replaces the policy.
+// Accumulators and averages of up to 224 MiB -- what the 256 MB Infinity Cache absorbs -- are written so
+// that the next call can find them there, larger ones are streamed.  An explicit threshold (0 = none)
+// replaces this line.
 constexpr size_t kDefaultStreamBytes = 224u << 20;
 std::atomic<size_t> g_stream_bytes{0};
 
@@ -1120,9 +1120,9 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // 101 M elements: 364 against 375), for 32 and more buffers beyond 64 MiB (p = 32, 25 M: 289, 302),
 // and where the lines at the two ends of a wavefront's piece are not whole (accumulator off 128
 // bytes: p = 16, 50 M: 324, 374; p = 32, 9.8 M: 123, 129) unless few buffers are read (p = 2, 42 M: 85.5, 79.8;
-// f32, p = 3, 40 M: 137, 132) or the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it plainly where few
-// buffers are read, so that the second one to need a line finds it in the L2 (all with non-temporal
-// loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134; bf16, p = 4, 1.6 M 6.3 / 6.0).
+// f32, p = 3, 40 M: 137, 132) or the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it
+// plainly up to 8 buffers, so that the second one to need a line finds it in the L2 (all with non-temporal
+// loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134).
 // An accumulator that the L2 of 8 x 4 MB holds is left there (plain, resident / not, against write-through):
 //   p = 4,  3.7 M (15 MB)  10.2 / 11.3, 11.1 / 11.1     p = 8,  1.0 M (4 MB)   4.9 / 5.5,  5.8 / 5.8
 //   p = 6,  6.0 M (24 MB)  17.9 / 19.5, 19.6 / 19.8     p = 8,  5.0 M (20 MB)  18.7 / 19.8, 19.7 / 19.6
