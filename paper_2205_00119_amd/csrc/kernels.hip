@@ -618,8 +618,9 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 }
 
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
-// `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more
-// instructions, and a small call is over in a few times the latency of what stands in front of its loads.
+// `accumulator` issues the accumulator's loads; where latency counts behind those of the buffers, because it needs
+// more instructions and a small call is over in a few times the latency of what stands in front of its
+// loads, else in front of them (p = 16, 50 M elements: 303.0 us, behind 304.5).
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
 // batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
@@ -628,13 +629,15 @@ template <int KIND, int VEC, int P, int BATCH, bool HOLD, typename Tab, typename
 __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
     if constexpr (P > 0) {
+        constexpr bool kBehind = HOLD || P <= 8;
+        if (!kBehind) accumulator();
         #pragma unroll
         for (int q0 = 0; q0 < P; q0 += BATCH) {
             GradVec<KIND, VEC> v[BATCH];
             #pragma unroll
             for (int b = 0; b < BATCH; ++b)
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
-            if (q0 == 0) accumulator();
+            if (q0 == 0 && kBehind) accumulator();
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
             // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (p = 16, 7.5 M: 52.4
@@ -1127,13 +1130,14 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 //   p = 4,  3.7 M (15 MB)  10.2 / 11.3, 11.1 / 11.1     p = 8,  1.0 M (4 MB)   4.9 / 5.5,  5.8 / 5.8
 //   p = 6,  6.0 M (24 MB)  17.9 / 19.5, 19.6 / 19.8     p = 8,  5.0 M (20 MB)  18.7 / 19.8, 19.7 / 19.6
 //   p = 16, 0.8 M (3 MB)   6.4 / 7.0,   6.9 / 6.9       f32, p = 2, 5.3 M (21 MB)  11.2 / 13.8, 13.6 / 13.6
-// but not where the gradients are hardly more than it (bf16, p = 2, 5.0 M, 20 MB: 9.8 / 13.1, 10.6 / 11.5), nor
-// where they are so many that it would be gone before its turn (p = 16, 7.5 M, 30 MB: 51.9 / 52.2, 48.6 / 49.3;
-// p = 32, 0.6 M, 2.5 MB: 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
+// but not to the last byte (p = 8, 8.4 M, 32 MiB: 37.4 / 37.3, 34.6 / 34.7), nor where the gradients are hardly more than
+// it (bf16, p = 2, 5.0 M, 20 MB: 9.8 / 13.1, 10.6 / 11.5), nor where they are so many that it would be gone before
+// its turn (p = 16, 3 M, 12 MB: 18.9 / 21.2, 19.9 / 20.2; 7.5 M, 30 MB: 51.9 / 52.2, 48.6 / 49.3; p = 32, 0.6 M, 2.5 MB:
+// 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
 int accum_policy(size_t count, int p, int elem_bytes)
 {
     constexpr size_t kSmall = 64u << 20;
-    const size_t cached = p < 4 && elem_bytes == 2 ? 16u << 20 : p < 12 ? 32u << 20 : p < 32 ? 12u << 20 : 1u << 20;
+    const size_t cached = p < 4 && elem_bytes == 2 ? 16u << 20 : p < 12 ? 30u << 20 : p < 32 ? 8u << 20 : 1u << 20;
     if (stream_acc(count)) return kAccStreamed;
     if (count * 4 <= cached) return kAccCached;
     if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
@@ -1474,15 +1478,15 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
 //   bf16, p = 20 5 MB 3.4 / 3.9, 19 MB 6.0 / 6.0, 32 MB 8.9 / 8.2      p = 32 13 MB 4.3 / 4.7, 24 MB 6.4 / 6.3
 //         p = 48 13 MB 4.5 / 5.8, 49 MB 10.7 / 12.2, 63 MB 13.7 / 12.9  p = 40 49 MB 10.9 / 11.6, 62 MB 13.6 / 12.9
 //         p = 64 1 MB 3.0 / 6.4, 50 MB 10.7 / 11.6, 65 MB 13.5 / 14.6   p = 128 3 MB 4.3 / 11.2, 67 MB 12.7 / 15.9
-//   f32 alike: p = 48 51 MB 10.3 / 11.4, 66 MB 13.1 / 12.7; p = 64 67 MB 12.8 / 14.3; p = 96 79 MB 15.0 / 15.2
+//   f32 alike: p = 48 59 MB 11.5 / 12.0, 66 MB 13.1 / 12.7; p = 64 67 MB 12.8 / 14.3; p = 96 79 MB 15.0 / 15.2
 // and about half of that where the buffers sit at different positions inside their lines, which costs every dword
 // load (bf16, p = 24 12 MB 5.4 / 5.5, 23 MB 8.3 / 7.2; p = 48 21 MB 7.1 / 7.1, 35 MB 10.6 / 9.3; p = 64 31 MB 9.2 / 8.9;
-// p = 128 52 MB 14.5 / 15.2, 67 MB 18.4 / 17.7).
+// p = 128 52 MB 14.5 / 15.2, 67 MB 18.4 / 17.7; f16, p = 128 59 MB 15.6 / 16.6).
 inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line)
 {
-    const size_t most = p >= 96 ? (same_line ? 72 : 52) : p >= 56 ? (same_line ? 68 : 28) : p >= 40 ? (same_line ? 54 : 22)
-                        : p >= 20 && elem_bytes == 2 ? (same_line ? 24 : 12) : 0;
-    return count <= (most << 20) / ((size_t)p * elem_bytes);
+    const int most = p >= 56 ? (same_line ? (p >= 96 ? 72 : 68) : p / 2) : p >= 48 ? (same_line ? 60 : 25)
+                     : p >= 40 ? (same_line ? 54 : 22) : p >= 20 && elem_bytes == 2 ? (same_line ? 24 : 12) : 0;
+    return count <= ((size_t)most << 20) / ((size_t)p * elem_bytes);
 }
 
 template <int KIND, int VEC, int P, bool ACCUM, bool CACHED>

@@ -90,8 +90,8 @@ def test_reduce_with_every_remainder_of_the_load_batches(orc, gen, name, p):
 
 
 @pytest.mark.parametrize("elem_bytes,p,limit,skews", [(2, 20, 24, [0]), (2, 40, 54, [0]), (4, 40, 54, [0]), (2, 64, 68, [0]),
-                                                      (4, 96, 72, [0]), (2, 24, 12, [0, 1]), (4, 48, 22, [0, 1]), (2, 64, 28, [0, 3]),
-                                                      (2, 100, 52, [1, 0])])
+                                                      (4, 96, 72, [0]), (2, 24, 12, [0, 1]), (4, 48, 25, [0, 1]), (2, 64, 32, [0, 3]),
+                                                      (2, 100, 50, [1, 0])])
 def test_reduce_on_both_sides_of_the_one_dword_rule(orc, gen, elem_bytes, p, limit, skews):
     limit <<= 20
     for count in (limit // (p * elem_bytes), limit // (p * elem_bytes) + 1):
@@ -150,8 +150,8 @@ def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, thresho
         mics.mics_set_stream_threshold_bytes(0)
 
 
-@pytest.mark.parametrize("name,p,count", [("bf16", 2, 17000003), ("bf16", 2, 4194307), ("bf16", 7, 8388611), ("f32", 3, 8388617), ("f16", 11, 8388609),
-                                          ("bf16", 16, 3145735), ("f32", 32, 262147), ("bf16", 32, 3300001)])
+@pytest.mark.parametrize("name,p,count", [("bf16", 2, 17000003), ("bf16", 2, 4194307), ("bf16", 7, 7864323), ("f32", 3, 7864328), ("f16", 11, 7864321),
+                                          ("bf16", 16, 2097159), ("f32", 32, 262147), ("bf16", 32, 3300001)])
 def test_reduce_at_the_largest_accumulator_that_stays_in_the_l2(orc, gen, name, p, count):
     """Accumulators beyond what the caches are left with take the kernels that store whole lines, by groups; at
     the line and behind it, on and off the 128-byte lines."""
