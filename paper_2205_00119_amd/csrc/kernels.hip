@@ -618,26 +618,26 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 }
 
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
-// `accumulator` issues the accumulator's loads; where latency counts behind those of the buffers, because it needs
-// more instructions and a small call is over in a few times the latency of what stands in front of its
-// loads, else in front of them (p = 16, 50 M elements: 303.0 us, behind 304.5).
+// `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more instructions,
+// and a small call is over in a few times the latency of what stands in front of its loads.  FIRST: in front of them,
+// in the flat kernels of large calls, where the order is worth a little either way (us, first / behind: flat, p = 16,
+// 50 M elements 303.0 / 304.5; 16 tensors, p = 16, 50 M 309 / 303).
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
 // batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
 // binary32 addition (-0 + x is x, also for x = -0 and x = +0).
-template <int KIND, int VEC, int P, int BATCH, bool HOLD, typename Tab, typename Issue>
+template <int KIND, int VEC, int P, int BATCH, bool HOLD, bool FIRST, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
     if constexpr (P > 0) {
-        constexpr bool kBehind = HOLD || P <= 8;
-        if (!kBehind) accumulator();
+        if (FIRST) accumulator();
         #pragma unroll
         for (int q0 = 0; q0 < P; q0 += BATCH) {
             GradVec<KIND, VEC> v[BATCH];
             #pragma unroll
             for (int b = 0; b < BATCH; ++b)
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
-            if (q0 == 0 && kBehind) accumulator();
+            if (q0 == 0 && !FIRST) accumulator();
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
             // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (p = 16, 7.5 M: 52.4
@@ -666,13 +666,13 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
 }
 
 // a[0 .. EPL) = a[0 .. EPL) + partial sum at virtual element `elem`.
-template <int KIND, int VEC, int P, int BATCH, bool HOLD, typename Tab, typename Issue>
+template <int KIND, int VEC, int P, int BATCH, bool HOLD, bool FIRST, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const Tab& g, int p, size_t elem,
                                         Issue&& accumulator)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     float s[EPL];
-    rsa_partial<KIND, VEC, P, BATCH, HOLD>(s, g, p, elem, accumulator);
+    rsa_partial<KIND, VEC, P, BATCH, HOLD, FIRST>(s, g, p, elem, accumulator);
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = a[e] + s[e];
 }
@@ -734,7 +734,7 @@ __device__ __forceinline__ void wave_lds_order()
 // cache lines, which leave the L2 between the two halves.  Passing the results through 2 KiB of LDS
 // per wavefront lets every store instruction cover one contiguous KiB.  Vector j of the wavefront's
 // 128 holds half of the elements of lane j / 2.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, typename Tab>
+template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, bool FIRST, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
                                          size_t lead, size_t end, int how)
 {
@@ -745,7 +745,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
     for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
     if constexpr (CACHED) {
         if (full) {
-            rsa_sum<KIND, VEC, P, BATCH, VEC == 4>(a, g, p, src0 + v0, [&] {
+            rsa_sum<KIND, VEC, P, BATCH, VEC == 4, false>(a, g, p, src0 + v0, [&] {
                 if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
             });
             st_f32<EPL, false>(acc + (v0 - lead), a);
@@ -762,7 +762,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             else MICS_ST(true, (f32x4_a4*)wave_acc + i, v);
         };
         if (full) {
-            rsa_sum<KIND, VEC, P, BATCH, false>(a, g, p, src0 + v0, [&] {
+            rsa_sum<KIND, VEC, P, BATCH, false, FIRST>(a, g, p, src0 + v0, [&] {
                 // with more than 8 buffers the choice between two kinds of loads costs more registers than it
                 // gives (p = 32: 158 instead of 99)
                 if constexpr (ACCUM && P > 0 && P <= 8) {
@@ -836,7 +836,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8)>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -865,8 +865,8 @@ __global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
     const size_t end = tab.seg[t].end, lead = tab.seg[t].lead;
     const size_t v0 = ((size_t)(x - tab.tile_begin[t]) * blockDim.x + threadIdx.x) * EPL;
     if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, P, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
-    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM, CACHED>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead, end,
-                                                        how);
+    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM, CACHED, false>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead,
+                                                               end, how);
 }
 
 // ---------------------------------------------------------------------------
