@@ -1275,13 +1275,17 @@ Shape off_lines(size_t nlanes, size_t units)
     return nlanes * 2 <= (size_t)kMaxBlock * units ? Shape{64, 0} : Shape{kMaxBlock, 0};
 }
 
-// The average's result is left in the L2 by small calls and written through it by larger ones, us plain / through:
-// r = 2, 1.2 M elements 3.7 / 4.0, 3.3 M 7.3 / 7.7, 6.7 M 15.0 / 14.5; r = 4, 1 M 4.85 / 5.0, 3 M 11.0 / 10.7, 5.5 M 20.8 / 18.4;
-// r = 16, 0.88 M 10.9 / 11.2, 1.6 M 19.3 / 19.2.  A single copy: 1 M 3.0 / 3.2, 2.5 M 5.0 / 4.75.
+// The average's result is left in the L2 by calls of a middle size and written through it by larger ones and by
+// the smallest, which end sooner without a write-back behind them, us plain / through: r = 2, 0.12 M elements 1.88 /
+// 1.81, 1.2 M 3.7 / 4.0, 3.3 M 7.3 / 7.7, 6.7 M 15.0 / 14.5; r = 4, 0.15 M 2.6 / 2.25, 1 M 4.85 / 5.0, 3 M 11.0 / 10.7, 5.5 M
+// 20.8 / 18.4; r = 8, 0.11 M 2.7 / 2.4; r = 16, 0.88 M 10.9 / 11.2, 1.6 M 19.3 / 19.2.  A single copy: 0.25 M 2.0 / 1.8, 1 M 3.0 /
+// 3.2, 2.5 M 5.0 / 4.75.
 int average_store(int r, size_t count, bool streamed)
 {
     if (streamed) return kOutStreamed;
-    return count * (4 * (size_t)r + 4) < ((r < 2 ? 18u : 64u) << 20) ? kOutPlain : kOutThrough;
+    const size_t traffic = count * (4 * (size_t)r + 4);
+    const bool middle = traffic >= ((r < 4 ? 3u : 12u) << 20) && traffic < ((r < 2 ? 18u : 64u) << 20);
+    return middle ? kOutPlain : kOutThrough;
 }
 
 // The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
