@@ -233,10 +233,9 @@ __device__ __forceinline__ uint16_t param_single(float a)
 // ---------------------------------------------------------------------------
 
 // Vector i of a wavefront's 64 consecutive ones from d, non-temporal; THROUGH: and through the L2 (nt / nt sc0 sc1:
-// p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480; smaller calls lose: p = 2, 4 MB 2.7 / 2.9, 25 MB 6.1 / 6.35, the
-// 16 tensors of 13 MB 4.8 / 5.1; the smallest end sooner without the write-back behind them: p = 8, 2 MB 2.5 / 2.3).
-// That needs whole 128-byte lines: with chunks that begin in the middle of one, p = 48, 537 MB takes 91.0 (nt:
-// 89.5), with wavefronts moved to the lines 84.0.
+// p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480; small calls lose: p = 2, 4 MB 2.7 / 2.9, 25 MB 6.1 / 6.35, the
+// 16 tensors of 13 MB 4.8 / 5.1).  That needs whole 128-byte lines: with chunks that begin in the middle of one,
+// p = 48, 537 MB takes 91.0 (nt: 89.5), with wavefronts moved to the lines 84.0.
 template <bool THROUGH>
 __device__ __forceinline__ void put_line(u32x4* d, size_t i, u32x4 v)
 {
@@ -247,7 +246,7 @@ __device__ __forceinline__ void put_line(u32x4* d, size_t i, u32x4 v)
         MICS_ST(true, d + i, v);
     }
 }
-inline bool gather_through(size_t traffic) { return traffic < (3u << 20) || traffic >= (30u << 20); }
+constexpr size_t kGatherThroughBytes = 30u << 20;         // read and written
 
 // All addresses and the shard size are multiples of 16 bytes: a remapped copy.
 template <bool THROUGH>
@@ -1404,7 +1403,7 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
         const Shape sh = reorder_shape(2 * n_valid_bytes, MICS_REORDER_BLOCK);
         if (int e = grid_for((shard_bytes / 16 + off_line(dst, 0, shard_bytes)) * (size_t)p, sh.lanes, MICS_REORDER_BPC, &total)) return e;
         unsigned bx = (total + (unsigned)p - 1) / (unsigned)p;
-        const auto kernel = gather_through(2 * n_valid_bytes) ? reorder_vec_kernel<true> : reorder_vec_kernel<false>;
+        const auto kernel = 2 * n_valid_bytes < kGatherThroughBytes ? reorder_vec_kernel<false> : reorder_vec_kernel<true>;
         return launch(kernel, dim3(bx, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
                       shard_bytes / 16, n_valid_bytes, k);
     }
@@ -1630,7 +1629,7 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
             }
             for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
             if (tiles == 0) continue;
-            const auto kernel = gather_through(moved) ? reorder_seg_kernel<true> : reorder_seg_kernel<false>;
+            const auto kernel = moved < kGatherThroughBytes ? reorder_seg_kernel<false> : reorder_seg_kernel<true>;
             if (int e = launch(kernel, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh),
                                st, (u32x4*)dst, src, tab, k))
                 return e;
