@@ -232,24 +232,16 @@ __device__ __forceinline__ uint16_t param_single(float a)
 // every wavefront cost 1 % of a coalesced call), blockIdx.x strides over the chunk.
 // ---------------------------------------------------------------------------
 
-// Vector i of a wavefront's 64 consecutive ones from d, non-temporal; THROUGH: and through the L2 (nt / nt sc0 sc1:
-// p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480; small calls lose: p = 2, 4 MB 2.7 / 2.9, 25 MB 6.1 / 6.35, the
-// 16 tensors of 13 MB 4.8 / 5.1).  That needs whole 128-byte lines: with chunks that begin in the middle of one,
-// p = 48, 537 MB takes 91.0 (nt: 89.5), with wavefronts moved to the lines 84.0.
-template <bool THROUGH>
+// Vector i of a wavefront's 64 consecutive ones from d: non-temporal, and through the L2 (nt / nt sc0 sc1:
+// p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480).  It needs whole 128-byte lines: with chunks that begin
+// in the middle of one, p = 48, 537 MB takes 91.0 (nt: 89.5), with wavefronts moved to the lines 84.0.
 __device__ __forceinline__ void put_line(u32x4* d, size_t i, u32x4 v)
 {
-    if constexpr (THROUGH) {
-        const unsigned lane = threadIdx.x & 63u;
-        store_vec<kNonTemporal | kWriteThrough>(wave_buffer(d + (i - lane), 1024), 16 * lane, __builtin_bit_cast(f32x4, v));
-    } else {
-        MICS_ST(true, d + i, v);
-    }
+    const unsigned lane = threadIdx.x & 63u;
+    store_vec<kNonTemporal | kWriteThrough>(wave_buffer(d + (i - lane), 1024), 16 * lane, __builtin_bit_cast(f32x4, v));
 }
-constexpr size_t kGatherThroughBytes = 30u << 20;         // read and written
 
 // All addresses and the shard size are multiples of 16 bytes: a remapped copy.
-template <bool THROUGH>
 __global__ __launch_bounds__(kMaxBlock) void reorder_vec_kernel(
     u32x4* __restrict__ dst, PtrTable src, size_t shard_vecs, size_t n_valid_bytes, int k)
 {
@@ -270,7 +262,7 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_vec_kernel(
     // achieved bandwidth, for loads and even more for stores.
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nfull + lead; i += stride)
-        if (i >= lead) put_line<THROUGH>(d - lead, i, MICS_LD(kReorderNtl, s + (i - lead)));
+        if (i >= lead) put_line(d - lead, i, MICS_LD(kReorderNtl, s + (i - lead)));
 
     // ragged end of the logical buffer: fewer than 16 valid bytes remain
     const size_t tail_halves = (valid - nfull * 16) / 2;
@@ -321,7 +313,6 @@ struct ReorderSegTable {
     ReorderSeg seg[kMaxSeg];
 };
 
-template <bool THROUGH>
 __global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
     u32x4* __restrict__ dst, PtrTable src, ReorderSegTable tab, int k)
 {
@@ -348,7 +339,7 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
     #pragma unroll
     for (int u = 0; u < MICS_SEG_U; ++u) {
         const size_t i = tile0 + (size_t)u * blockDim.x + threadIdx.x;
-        if (i >= lead && i < nfull + lead) put_line<THROUGH>(d - lead, i, v[u]);
+        if (i >= lead && i < nfull + lead) put_line(d - lead, i, v[u]);
     }
     // ragged end of the tensor: the tile that holds vector index nfull moves the last bytes
     const size_t tail_halves = (valid - nfull * 16) / 2;
@@ -1403,8 +1394,7 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
         const Shape sh = reorder_shape(2 * n_valid_bytes, MICS_REORDER_BLOCK);
         if (int e = grid_for((shard_bytes / 16 + off_line(dst, 0, shard_bytes)) * (size_t)p, sh.lanes, MICS_REORDER_BPC, &total)) return e;
         unsigned bx = (total + (unsigned)p - 1) / (unsigned)p;
-        const auto kernel = 2 * n_valid_bytes < kGatherThroughBytes ? reorder_vec_kernel<false> : reorder_vec_kernel<true>;
-        return launch(kernel, dim3(bx, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
+        return launch(reorder_vec_kernel, dim3(bx, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
                       shard_bytes / 16, n_valid_bytes, k);
     }
     const Segment one = {n_valid_bytes, shard_bytes, 0, 0};
@@ -1629,9 +1619,8 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
             }
             for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
             if (tiles == 0) continue;
-            const auto kernel = moved < kGatherThroughBytes ? reorder_seg_kernel<false> : reorder_seg_kernel<true>;
-            if (int e = launch(kernel, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh),
-                               st, (u32x4*)dst, src, tab, k))
+            if (int e = launch(reorder_seg_kernel, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
+                               (u32x4*)dst, src, tab, k))
                 return e;
         } else {
             size_t moved = 0;

@@ -272,28 +272,3 @@ def test_aligned_gather_off_the_128_byte_lines(orc, gen, dst_vecs, unit):
         got = one.numpy()
         assert np.array_equal(got[:n], orc.hier_gather_reorder([t[at:at + p // k * S] for t in T], n, S, p)), S
         assert np.array_equal(got[n:], before[n:]) and one.guards_intact(), S
-
-
-@pytest.mark.parametrize("dst_vecs", [0, 3])
-@pytest.mark.parametrize("vecs", [(15 << 20) // 2 // 16 // 2 - 8, (15 << 20) // 2 // 16 // 2 + 8, (15 << 20) // 2 // 16 + 5])
-def test_aligned_gather_on_both_sides_of_the_write_through_rule(gen, dst_vecs, vecs):
-    """Two shards in one call and as two tensors, around the 30 MB read and written from which the destination
-    is written through the L2."""
-    S = vecs * 8 * 2
-    bufs = [Guarded(S, np.uint16, skew=8 * l, fill=gen.fill_host(
-        gen.stream_key(4600 + l, gen.ROLE_PARAM), 0, S, gen.normal_table(1.0, "bf16"))) for l in range(2)]
-    n = 2 * S - 3
-    dst = Guarded(2 * S, np.uint16, skew=8 * dst_vecs)
-    before = dst.t[n:].clone()
-    mics.mics_hier_gather_reorder(dst.t, [b.t for b in bufs], n, S, 2, 2, 2)
-    torch.cuda.synchronize()
-    assert torch.equal(dst.t[:S], bufs[0].t) and torch.equal(dst.t[S:n], bufs[1].t[:n - S])
-    assert torch.equal(dst.t[n:], before) and dst.guards_intact()
-    dst.t.zero_()
-    h = S // 2
-    mics.mics_hier_gather_reorder_coalesced(dst.t, [b.t for b in bufs], [(S, h, 0, 0), (S, h, h, S)], 2, 2, 2)
-    torch.cuda.synchronize()
-    for t in range(2):
-        for l in range(2):
-            assert torch.equal(dst.t[t * S + l * h:t * S + (l + 1) * h], bufs[l].t[t * h:(t + 1) * h]), (t, l)
-    assert dst.guards_intact()
