@@ -235,6 +235,8 @@ __device__ __forceinline__ uint16_t param_single(float a)
 // Vector i of a wavefront's 64 consecutive ones from d: non-temporal, and through the L2 (nt / nt sc0 sc1:
 // p = 16, 268 MB 43.0 / 41.2 us, 3.2 GB 481 / 480).  It needs whole 128-byte lines: with chunks that begin
 // in the middle of one, p = 48, 537 MB takes 91.0 (nt: 89.5), with wavefronts moved to the lines 84.0.
+// At every size: from 3 to 30 MB calls whose buffers no cache holds would be 1 to 4 % faster without, those whose
+// buffers are still in one 2 to 8 % slower (p = 8, 7 MB 2.7, nt 3.0).
 __device__ __forceinline__ void put_line(u32x4* d, size_t i, u32x4 v)
 {
     const unsigned lane = threadIdx.x & 63u;
@@ -1116,18 +1118,18 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // f32, p = 3, 40 M: 137, 132) or the accumulator is small (p = 8, 9.8 M: 40.6, 37.9).  Those wavefronts load it
 // plainly up to 8 buffers, so that the second one to need a line finds it in the L2 (all with non-temporal
 // loads / so: f32, p = 1, 16.7 M 38.8 / 33.5, p = 2, 50 M 142 / 134).
-// An accumulator that the L2 of 8 x 4 MB holds is left there (plain, resident / not, against write-through):
-//   p = 4,  3.7 M (15 MB)  10.2 / 11.3, 11.1 / 11.1     p = 8,  1.0 M (4 MB)   4.9 / 5.5,  5.8 / 5.8
-//   p = 6,  6.0 M (24 MB)  17.9 / 19.5, 19.6 / 19.8     p = 8,  5.0 M (20 MB)  18.7 / 19.8, 19.7 / 19.6
-//   p = 16, 0.8 M (3 MB)   6.4 / 7.0,   6.9 / 6.9       f32, p = 2, 5.3 M (21 MB)  11.2 / 13.8, 13.6 / 13.6
-// but not to the last byte (p = 8, 8.4 M, 32 MiB: 37.4 / 37.3, 34.6 / 34.7), nor where the gradients are hardly more than
-// it (bf16, p = 2, 5.0 M, 20 MB: 9.8 / 13.1, 10.6 / 11.5), nor where they are so many that it would be gone before
-// its turn (p = 16, 3 M, 12 MB: 18.9 / 21.2, 19.9 / 20.2; 7.5 M, 30 MB: 51.9 / 52.2, 48.6 / 49.3; p = 32, 0.6 M, 2.5 MB:
-// 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
+// A small accumulator is left in the L2 (8 x 4 MB).  Speed of that against write-through, over resident and not, first
+// micro-step and accumulating, geometric means with buffers rotating through 1 GB / through three sets:
+//   p = 4..11         10 MiB 1.04 / 1.00   12 MiB 1.01 / 0.98   16..20 MiB 0.95..0.99 in both   28 MiB 0.98 / 0.98
+//   f32, p = 1..3     8 MiB  1.06 / 0.98   12 MiB 1.02 / 0.96   20 MiB 0.98 / 0.97              28 MiB 0.96 / 0.96
+//   bf16, p = 1..3    4 MiB  1.03 / 0.95   7 MiB  1.04 / 0.96   8 MiB  0.97 / 0.86              16 MiB 0.95 / 0.84
+// Calls that accumulate in a resident buffer still gain from it beyond the lines (p = 4..11, 16..24 MiB 1.03..1.07;
+// bf16, p = 4, 28 MiB 17.7 / 19.8 us); first micro-steps lose more (16 MiB 0.91..0.93).  With many gradients it would be gone before its turn (p = 16, 3 M, 12 MB 18.9 / 21.2, 19.9 / 20.2; 7.5 M, 30 MB 51.9 / 52.2,
+// 48.6 / 49.3; p = 32, 0.6 M, 2.5 MB 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
 int accum_policy(size_t count, int p, int elem_bytes)
 {
     constexpr size_t kSmall = 64u << 20;
-    const size_t cached = p < 4 && elem_bytes == 2 ? 16u << 20 : p < 12 ? 30u << 20 : p < 32 ? 8u << 20 : 1u << 20;
+    const size_t cached = p < 4 && elem_bytes == 2 ? 7u << 20 : p < 12 ? 12u << 20 : p < 32 ? 8u << 20 : 1u << 20;
     if (stream_acc(count)) return kAccStreamed;
     if (count * 4 <= cached) return kAccCached;
     if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
@@ -1269,12 +1271,13 @@ Shape off_lines(size_t nlanes, size_t units)
 // the smallest, which end sooner without a write-back behind them, us plain / through: r = 2, 0.12 M elements 1.88 /
 // 1.81, 1.2 M 3.7 / 4.0, 3.3 M 7.3 / 7.7, 6.7 M 15.0 / 14.5; r = 4, 0.15 M 2.6 / 2.25, 1 M 4.85 / 5.0, 3 M 11.0 / 10.7, 5.5 M
 // 20.8 / 18.4; r = 8, 0.11 M 2.7 / 2.4; r = 16, 0.88 M 10.9 / 11.2, 1.6 M 19.3 / 19.2.  A single copy: 0.25 M 2.0 / 1.8, 1 M 3.0 /
-// 3.2, 2.5 M 5.0 / 4.75.
+// 3.2, 2.5 M 5.0 / 4.75.  (Copies that no cache holds.  If one still does, writing through wins from about 40 MB on: r = 3,
+// 3.4 M 10.6 / 9.9, r = 6, 2 M 10.5 / 9.9.)
 int average_store(int r, size_t count, bool streamed)
 {
     if (streamed) return kOutStreamed;
     const size_t traffic = count * (4 * (size_t)r + 4);
-    const bool middle = traffic >= ((r < 4 ? 3u : 12u) << 20) && traffic < ((r < 2 ? 18u : 64u) << 20);
+    const bool middle = traffic >= ((r < 4 ? 3u : 12u) << 20) && traffic < ((r < 2 ? 12u : 44u) << 20);
     return middle ? kOutPlain : kOutThrough;
 }
 

@@ -150,7 +150,7 @@ def test_reduce_in_every_launch_shape_and_store_kind(orc, gen, p, count, thresho
         mics.mics_set_stream_threshold_bytes(0)
 
 
-@pytest.mark.parametrize("name,p,count", [("bf16", 2, 17000003), ("bf16", 2, 4194307), ("bf16", 7, 7864323), ("f32", 3, 7864328), ("f16", 11, 7864321),
+@pytest.mark.parametrize("name,p,count", [("bf16", 2, 17000003), ("bf16", 2, 1835011), ("bf16", 7, 3145731), ("f32", 3, 3145736), ("f16", 11, 3145729),
                                           ("bf16", 16, 2097159), ("f32", 32, 262147), ("bf16", 32, 3300001)])
 def test_reduce_at_the_largest_accumulator_that_stays_in_the_l2(orc, gen, name, p, count):
     """Accumulators beyond what the caches are left with take the kernels that store whole lines, by groups; at
