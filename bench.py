@@ -519,7 +519,7 @@ def cpu_baseline(cfg, args):
     m = min(cfg.S, args.cpu_sample)
     offset = args.rank * cfg.S
     host_cores = os.cpu_count() or 1
-    cores = min(16, host_cores)      # a one-GPU machine gives a job 16 of the host's cores
+    cores = min(16, host_cores)      # a one-GPU job's share of the host's cores
     gtab = synth.normal_table(cfg.sigma_grad, "bf16")
     gout = synth.normal_table(cfg.sigma_grad * cfg.outlier_scale, "bf16") if cfg.outlier_frac else None
     ptab = synth.normal_table(cfg.sigma_master, "bf16")

@@ -2,18 +2,18 @@
 """Turns the raw rocprofv3 output of bench.py runs into the short summaries under profiles/.
 
 Three runs of the same bench.py command belong together (each in a run of its own, from /tmp on
-the GPU box, R = repository root):
+the GPU machine, R = repository root):
 
-    rocprofv3 --kernel-trace --stats --output-format csv -d $R/gpurun_out/<tag>/kt -o kt -- \\
+    rocprofv3 --kernel-trace --stats --output-format csv -d $R/prof/<tag>/kt -o kt -- \\
         python3 $R/bench.py <bench args> --no-cpu-baseline --no-group-view
-    rocprofv3 --pmc FETCH_SIZE --output-format csv -d $R/gpurun_out/<tag>/fetch -o fetch -- \\
+    rocprofv3 --pmc FETCH_SIZE --output-format csv -d $R/prof/<tag>/fetch -o fetch -- \\
         python3 $R/bench.py <bench args> --steps 2 --warmup 0 --no-cpu-baseline --no-group-view --calibration-copy
-    rocprofv3 --pmc WRITE_SIZE --output-format csv -d $R/gpurun_out/<tag>/write -o write -- \\
+    rocprofv3 --pmc WRITE_SIZE --output-format csv -d $R/prof/<tag>/write -o write -- \\
         python3 $R/bench.py <bench args> --steps 2 --warmup 0 --no-cpu-baseline --no-group-view --calibration-copy
 
 and then, here:
 
-    python profile_summary.py --dir gpurun_out/<tag> --config h8192 --view rank \\
+    python profile_summary.py --dir prof/<tag> --config h8192 --view rank \\
         --bench-args "<bench args>" --out profiles/<name>.md
 
 The summary holds the kernel trace statistics, the counters scaled by what they read for a plain
@@ -113,21 +113,22 @@ def main():
     count = args.count or (cfg.N_pad if args.view == "group" else cfg.S)
     pb = 2
     sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()[:16]
+    shown = "prof/" + os.path.basename(os.path.normpath(args.dir))
     out = [(f"\n---\n\n## {args.title}\n\n" if args.title else "") +
            f"# rocprofv3 summary: libmics kernels, workload {cfg.name} (p={cfg.p}, k={cfg.k}, r={cfg.r}, "
            f"s={cfg.s}), {args.view} view ({count} elements per reduce/average/Adam call), one MI355X\n",
            f"Kernel source: `paper_2205_00119_amd/csrc/kernels.hip`, SHA-256 `{sha}`.\n",
            "Commands (from /tmp on the GPU machine, `R` = repository root; each in a run of its own), then "
-           f"`python profile_summary.py --dir {args.dir} --config {args.config} --view {args.view} "
+           f"`python profile_summary.py --dir {shown} --config {args.config} --view {args.view} "
            f"--variant {args.variant} --bench-args \"{args.bench_args}\" --out {args.out}`:\n",
            "```"]
     extra = "" if args.view == "group" or "--view" in args.bench_args else " --no-group-view"
     b = f"python3 $R/bench.py {args.bench_args}".rstrip()
-    out.append(f"rocprofv3 --kernel-trace --stats --output-format csv -d $R/{args.dir}/kt -o kt -- {b} --no-cpu-baseline{extra}")
+    out.append(f"rocprofv3 --kernel-trace --stats --output-format csv -d $R/{shown}/kt -o kt -- {b} --no-cpu-baseline{extra}")
     have_pmc = os.path.isdir(os.path.join(args.dir, "fetch")) and os.path.isdir(os.path.join(args.dir, "write"))
     if have_pmc:
         for c, tag in (("FETCH_SIZE", "fetch"), ("WRITE_SIZE", "write")):
-            out.append(f"rocprofv3 --pmc {c} --output-format csv -d $R/{args.dir}/{tag} -o {tag} -- {b} --steps 2 "
+            out.append(f"rocprofv3 --pmc {c} --output-format csv -d $R/{shown}/{tag} -o {tag} -- {b} --steps 2 "
                        f"--warmup 0 --no-cpu-baseline{extra} --calibration-copy")
     out.append("```\n")
 
