@@ -6,6 +6,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -16,6 +17,7 @@
 namespace {
 
 thread_local char g_error[512] = "";
+std::atomic<int> g_blocks_per_cu{0};
 
 int fail(int code, const char* fmt, ...)
 {
@@ -97,6 +99,7 @@ int mics_set_blocks_per_cu(int blocks_per_cu)
 {
     if (blocks_per_cu < 0 || blocks_per_cu > 4096)
         return fail(MICS_ERR_INVALID_ARG, "mics_set_blocks_per_cu: %d not in [0, 4096]", blocks_per_cu);
+    g_blocks_per_cu.store(blocks_per_cu);
     mics::set_blocks_per_cu(blocks_per_cu);
     return MICS_OK;
 }
@@ -347,6 +350,7 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
     const size_t eb = (size_t)elem_bytes;
     if (!aligned(dst_flat, eb))
         return fail(MICS_ERR_ALIGNMENT, "%s: dst_flat not aligned to %d bytes", fn, elem_bytes);
+    int used = 0;                                    // tensors that are not empty
     const size_t limit = SIZE_MAX / 8 / (size_t)p;   // keeps every byte offset below SIZE_MAX / 2
     size_t dst_lo = SIZE_MAX, dst_hi = 0, src_lo = SIZE_MAX, src_hi = 0, total = 0;
     for (int t = 0; t < n_segs; ++t) {
@@ -357,6 +361,7 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
             return fail(MICS_ERR_INVALID_ARG, "%s: segment %d: numel = %zu exceeds p * shard_elems = %zu",
                         fn, t, sg.numel, (size_t)p * sg.shard_elems);
         if (sg.numel == 0) continue;
+        ++used;
         total += sg.numel;
         if (sg.dst_offset < dst_lo) dst_lo = sg.dst_offset;
         if (sg.dst_offset + sg.numel > dst_hi) dst_hi = sg.dst_offset + sg.numel;
@@ -386,14 +391,17 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
                              fn, bad_a, bad_b);
 
     // Tensors whose bases, shard size and offsets are 16-byte clean go to the vector kernel, all
-    // others to the kernel for any alignment: one launch per kMaxSegPerLaunch tensors of either kind.
-    mics::Segment clean[mics::kMaxSegPerLaunch], other[mics::kMaxSegPerLaunch];
+    // others to the kernel for any alignment: one launch per kMaxSegPerLaunch tensors of either kind.  A small
+    // call is not split by kind (unless grids are capped, which its kernel does not do).
+    const bool small = used > 1 && 2 * total * eb < mics::small_gather_bytes(used) && g_blocks_per_cu.load() == 0;
+    mics::Segment clean[mics::kMaxSegPerLaunch], other[mics::kMaxSegSmall];
+    const int most = small ? mics::kMaxSegSmall : mics::kMaxSegPerLaunch;
     int nc = 0, no = 0;
     for (int t = 0; t <= n_segs; ++t) {
         const bool last = (t == n_segs);
         if (!last && segs[t].numel) {
             const mics_segment& sg = segs[t];
-            const bool vec16 = bases16 && (sg.shard_elems * eb) % 16 == 0 && (sg.src_offset * eb) % 16 == 0 &&
+            const bool vec16 = !small && bases16 && (sg.shard_elems * eb) % 16 == 0 && (sg.src_offset * eb) % 16 == 0 &&
                                (sg.dst_offset * eb) % 16 == 0;
             mics::Segment& slot = vec16 ? clean[nc++] : other[no++];
             slot.numel = sg.numel; slot.shard_elems = sg.shard_elems;
@@ -404,7 +412,7 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
             if (err) return hip_fail(fn, err);
             nc = 0;
         }
-        if (no == mics::kMaxSegPerLaunch || (last && no)) {
+        if (no == most || (last && no)) {
             int err = mics::launch_reorder_coalesced(dst_flat, tab, other, no, p, k, elem_bytes, false, stream);
             if (err) return hip_fail(fn, err);
             no = 0;

@@ -52,6 +52,11 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
 // Segment records travel in the kernel-argument segment: at most this many per launch.
 constexpr int kMaxSegPerLaunch = 48;
 
+// Small coalesced calls carry twice as many per launch.  A gather of n tensors is small if it moves (reads and writes)
+// less than this; it takes all its tensors, whatever their alignment, through one kernel (limits: kernels.hip, flat_vectors).
+constexpr int kMaxSegSmall = 2 * kMaxSegPerLaunch;
+constexpr size_t small_gather_bytes(int n) { return (n > kMaxSegPerLaunch ? size_t{64} : size_t{36}) << 20; }
+
 // One separately sharded tensor of a coalesced call (mirrors mics_segment; elements).
 struct Segment {
     size_t numel, shard_elems, src_offset, dst_offset;

@@ -491,6 +491,123 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
     else move(std::false_type{});
 }
 
+// Small calls.  What bounds them is latency: of dependent reads of the kernel arguments (0.15 to 0.25 us each; the
+// kernels above make three or four before their first load), and, with many tensors, of workgroups that have
+// nothing to do (one workgroup per chunk is p of them for every bias).  Here a tensor's destination is cut into
+// tiles whatever its chunks are, and every lane finds the chunk of its own 16 bytes: a multiplication by a host-made
+// reciprocal for the chunk, another for its node, and the stage-1 buffer's address from the lane that holds it.  Up to
+// 64 tensors all of the arguments come in one round of loads: lane i takes entry i of each table, and the tile's
+// tensor is the number of entries at or below it.  Any alignment: 16 bytes that cross the border of a chunk or an
+// end of the tensor go in 2-byte units.  us, one workgroup per chunk / so: 1 MB in one tensor, p = 16 2.45 / 2.06;
+// p = 16, 40 tensors, 1 MB 7.3 / 3.2; p = 128, 90 tensors, 5 MB 42.6 / 8.6, 40 tensors, 1 MB 20.9 / 3.4.
+struct FlatSeg {
+    unsigned long long src_byte, dst_byte;
+    unsigned shard_bytes, valid_bytes;             // below 2^31
+    unsigned recip, shift;                         // b / shard_bytes = mulhi(b, recip) >> shift for even b below 2^32
+};
+template <int SEGS>
+struct FlatTable {
+    unsigned tile_begin[SEGS];                     // ascending; kNoTile behind the last
+    FlatSeg seg[SEGS];
+};
+
+// Lane `from`'s value, for a lane index that may differ from lane to lane.
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, unsigned from)
+{
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4 * from), (int)v);
+}
+__device__ __forceinline__ uint32_t uniform_lane(uint32_t v, unsigned from)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)from);
+}
+
+template <int U, int SEGS, bool MANY>
+__global__ __launch_bounds__(kMaxBlock) void reorder_flat_kernel(
+    unsigned char* __restrict__ dst, PtrTable src, FlatTable<SEGS> tab, unsigned k, unsigned k_recip)
+{
+    const unsigned lane = threadIdx.x & 63u, x = blockIdx.x;
+    const uint64_t p0 = (uint64_t)src.ptr[MANY ? lane : lane & 15], p1 = (uint64_t)src.ptr[MANY ? 64 + lane : 0];
+    FlatSeg sg;
+    unsigned first = 0;                                        // tile of the tensor
+    if constexpr (SEGS == 1) {
+        sg = tab.seg[0];
+    } else if constexpr (SEGS <= 64) {
+        const unsigned begin = tab.tile_begin[lane];
+        sg = tab.seg[lane];
+        const unsigned t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1;
+        first = uniform_lane(begin, t);
+        auto entry = [&](unsigned v) { return uniform_lane(v, t); };
+        auto wide = [&](unsigned long long v) { return (unsigned long long)entry((uint32_t)(v >> 32)) << 32 | entry((uint32_t)v); };
+        sg = FlatSeg{wide(sg.src_byte), wide(sg.dst_byte), entry(sg.shard_bytes), entry(sg.valid_bytes), entry(sg.recip), entry(sg.shift)};
+    } else {
+        // the second read overlaps the first: its last SEGS - 64 entries count
+        const unsigned begin = tab.tile_begin[lane], later = tab.tile_begin[SEGS - 64 + lane];
+        const unsigned t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1 +
+                           (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane >= 128 - SEGS && later <= x));
+        first = t < 64 ? uniform_lane(begin, t) : uniform_lane(later, t - (SEGS - 64));
+        sg = tab.seg[t];
+    }
+    const unsigned tile = x - first, shard = sg.shard_bytes, valid = sg.valid_bytes;
+    const uintptr_t d_lo = (uintptr_t)dst + sg.dst_byte;
+    const uintptr_t d_line = d_lo & ~(uintptr_t)127;           // tiles begin on the destination's lines
+
+    // every lane takes part in the exchange, whatever it moves
+    auto buffer = [&](unsigned l) {
+        const uint64_t a = (uint64_t)lane_value((uint32_t)(p0 >> 32), l & 63u) << 32 | lane_value((uint32_t)p0, l & 63u);
+        if (!MANY) return a;
+        const uint64_t b = (uint64_t)lane_value((uint32_t)(p1 >> 32), l & 63u) << 32 | lane_value((uint32_t)p1, l & 63u);
+        return l < 64 ? a : b;
+    };
+    int off[U];                                                // the lane's first byte, in the tensor
+    unsigned j[U], l[U], rest[U];                              // where it is (byte 0 if that lies in front of the tensor)
+    uintptr_t s[U];
+    u32x4 v[U];
+    bool whole[U];
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        off[u] = (int)((tile * U + u) * blockDim.x * 16 + threadIdx.x * 16) - (int)(d_lo - d_line);
+        const unsigned b = off[u] < 0 ? 0 : (unsigned)off[u], g = __umulhi(b, sg.recip) >> sg.shift;
+        rest[u] = b - g * shard;
+        j[u] = g * k_recip >> 16;
+        l[u] = g - j[u] * k;
+        s[u] = buffer(l[u]) + sg.src_byte + j[u] * shard + rest[u];
+        whole[u] = off[u] >= 0 && b + 16 <= valid && rest[u] + 16 <= shard;
+        if (whole[u]) v[u] = MICS_LD(true, (const u32x4_a2*)s[u]);
+    }
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool parts = !whole[u] && off[u] + 16 > 0 && off[u] < (int)valid;
+        if (__builtin_amdgcn_ballot_w64(parts)) {
+            const unsigned from = off[u] < 0 ? 0 : (unsigned)off[u];
+            const unsigned n = !parts ? 0 : ((unsigned)(off[u] + 16) < valid ? (unsigned)(off[u] + 16) : valid) - from;
+            uint16_t h[8];
+            if (shard >= 16) {                                 // one border at most
+                const unsigned here = shard - rest[u];
+                const unsigned l1 = l[u] + 1 == k ? 0 : l[u] + 1, j1 = l[u] + 1 == k ? j[u] + 1 : j[u];
+                const uintptr_t s1 = buffer(l1) + sg.src_byte + j1 * shard - here;
+                #pragma unroll
+                for (unsigned i = 0; i < 8; ++i)
+                    if (2 * i < n) h[i] = *(const uint16_t*)((2 * i < here ? s[u] : s1) + 2 * i);
+            } else {
+                #pragma unroll
+                for (unsigned i = 0; i < 8; ++i) {
+                    const uintptr_t a = buffer(l[u]) + sg.src_byte + j[u] * shard + rest[u];
+                    if (2 * i < n) h[i] = *(const uint16_t*)a;
+                    rest[u] += 2;
+                    if (rest[u] == shard) {
+                        rest[u] = 0;
+                        if (++l[u] == k) l[u] = 0, ++j[u];
+                    }
+                }
+            }
+            #pragma unroll
+            for (unsigned i = 0; i < 8; ++i)
+                if (2 * i < n) *(uint16_t*)(d_lo + from + 2 * i) = h[i];
+        }
+        if (whole[u]) *(u32x4*)(d_lo + off[u]) = v[u];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Step 2a: reduction of the partition-group reduce-scatter, accumulated over
 // micro-steps (Section 3.4).
@@ -1387,10 +1504,83 @@ static size_t off_line(const void* dst, size_t dst_byte, size_t shard_bytes)
     return (((uintptr_t)dst + dst_byte) | shard_bytes) % 128 ? 7 : 0;
 }
 
+namespace {
+
+// Vectors per lane (1 or 2) of a call that moves `moved` bytes through reorder_flat_kernel, 0: not its work.  us, flat /
+// the kernels with a workgroup per chunk:
+//   one tensor, 16-byte aligned, p = 16: 0.3 MB 1.82 / 2.22, 8 MB 3.04 / 3.47, 20 MB (two vectors) 5.08 / 5.97, 28 MB 6.6 /
+//   6.9, 36 MB 8.9 / 8.2; not aligned, whose wavefronts at the borders of chunks make a second round trip: 0.1 MB 2.7 / 2.7,
+//   1 MB 2.8 / 3.2, 8 MB 3.0 / 3.4, 11 MB 4.7 / 4.6, 14 MB 5.3 / 5.1
+//   up to 48 tensors, geometric means of the speed over p = 4, 16, 96 and 3, 16 tensors: aligned 8 MB 2.4, 28 MB 1.7, 44 MB
+//   1.4; not aligned 8 MB 1.8, 28 MB 1.4, 44 MB 0.95 at worst; more tensors, where the other kernels are launched
+//   twice, 60 MB 1.14 at worst
+int flat_vectors(int n, size_t moved, bool vec16)
+{
+    const size_t mb = moved >> 20;
+    if (g_blocks_per_cu.load() > 0) return 0;                  // its grid has no cap
+    if (n == 1) {
+        if (vec16 ? mb >= 27 : mb >= 10 || moved < (512u << 10)) return 0;
+        return mb < 16 ? 1 : 2;
+    }
+    return moved >= small_gather_bytes(n) ? 0 : mb < 18 ? 1 : 2;
+}
+
+template <int U, int SEGS>
+int launch_reorder_flat(void* dst, const PtrTable& src, const Segment* segs, int n, size_t moved, int k, size_t eb, hipStream_t st)
+{
+    // us, one tensor, 64 / 128 / 512 lanes: 1 MB 2.08 / 2.06 / 2.14, 8 MB 3.58 / 3.40 / 3.04; two vectors: 256.  Many, speed against
+    // 64 lanes of 256: 0.3 MB 0.93, 2 MB 1.00, 8 MB 1.11
+    const int lanes = U == 2 ? 256 : n == 1 ? (moved < (3u << 20) ? 128 : kMaxBlock) : moved < (3u << 19) ? 64 : 256;
+    const Shape sh = with_knobs(kFamReorder, Shape{lanes, 0});
+    const size_t tile_bytes = (size_t)sh.lanes * U * 16;
+    FlatTable<SEGS> tab;
+    size_t tiles = 0;
+    for (int t = 0; t < n; ++t) {
+        const size_t valid = segs[t].numel * eb, shard = segs[t].shard_elems * eb;
+        FlatSeg& f = tab.seg[t];
+        tab.tile_begin[t] = (unsigned)tiles;
+        f.src_byte = segs[t].src_offset * eb;
+        f.dst_byte = segs[t].dst_offset * eb;
+        f.valid_bytes = (unsigned)valid;
+        f.shard_bytes = (unsigned)(shard < valid ? shard : valid);
+        // n / d for n < 2^31: with 2^shift >= d the rounded-up 2^(31 + shift) / d is too large by less than 2^shift / d
+        const unsigned d = f.shard_bytes / 2;
+        f.shift = 0;
+        while ((1ull << f.shift) < d) ++f.shift;
+        f.recip = (unsigned)(((1ull << (31 + f.shift)) + d - 1) / d);
+        tiles += (valid + (((uintptr_t)dst + f.dst_byte) & 127) + tile_bytes - 1) / tile_bytes;
+    }
+    for (int t = n; t < SEGS; ++t) tab.tile_begin[t] = kNoTile;
+    return launch(k <= 16 ? reorder_flat_kernel<U, SEGS, false> : reorder_flat_kernel<U, SEGS, true>, dim3((unsigned)tiles), dim3(sh.lanes),
+                  lds_for(sh), st, (unsigned char*)dst, src, tab, (unsigned)k, 65536u / (unsigned)k + 1);
+}
+
+// Tensors of at least one byte.
+int launch_reorder_small(void* dst, const PtrTable& src, const Segment* segs, int n, int vectors, size_t moved, int k, size_t eb,
+                         hipStream_t st)
+{
+    for (int first = 0; first < n; first += kMaxSegSmall) {
+        const int nt = n - first < kMaxSegSmall ? n - first : kMaxSegSmall;
+        const int err = dispatch_bool(vectors == 2, [&](auto TWO) {
+            constexpr int U = TWO.value ? 2 : 1;
+            if (nt == 1) return launch_reorder_flat<U, 1>(dst, src, segs + first, nt, moved, k, eb, st);
+            if (nt <= 64) return launch_reorder_flat<U, 64>(dst, src, segs + first, nt, moved, k, eb, st);
+            return launch_reorder_flat<U, kMaxSegSmall>(dst, src, segs + first, nt, moved, k, eb, st);
+        });
+        if (err) return err;
+    }
+    return 0;
+}
+
+}  // namespace
+
 int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t shard_bytes, int p,
                    int k, bool vec16, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
+    const Segment one = {n_valid_bytes, shard_bytes, 0, 0};
+    if (const int vectors = flat_vectors(1, 2 * n_valid_bytes, vec16))
+        return launch_reorder_small(dst, src, &one, 1, vectors, 2 * n_valid_bytes, k, 1, st);
     if (vec16) {
         // spread the block budget over the p chunks
         unsigned total = 0;
@@ -1400,7 +1590,6 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
         return launch(reorder_vec_kernel, dim3(bx, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st, (u32x4*)dst, src,
                       shard_bytes / 16, n_valid_bytes, k);
     }
-    const Segment one = {n_valid_bytes, shard_bytes, 0, 0};
     return launch_reorder_coalesced(dst, src, &one, 1, p, k, 1, false, stream);
 }
 
@@ -1600,6 +1789,9 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
 {
     hipStream_t st = (hipStream_t)stream;
     const size_t eb = (size_t)elem_bytes;
+    size_t all = 0;
+    for (int t = 0; t < n; ++t) all += 2 * segs[t].numel * eb;
+    if (const int vectors = flat_vectors(n, all, vec16)) return launch_reorder_small(dst, src, segs, n, vectors, all, k, eb, st);
     for (int first = 0; first < n; first += kMaxSeg) {
         const int nt = n - first < kMaxSeg ? n - first : kMaxSeg;
         size_t tiles = 0;

@@ -272,3 +272,40 @@ def test_aligned_gather_off_the_128_byte_lines(orc, gen, dst_vecs, unit):
         got = one.numpy()
         assert np.array_equal(got[:n], orc.hier_gather_reorder([t[at:at + p // k * S] for t in T], n, S, p)), S
         assert np.array_equal(got[n:], before[n:]) and one.guards_intact(), S
+
+
+@pytest.mark.parametrize("p,k,eb,sizes", [
+    (4, 2, 2, [3, 1, 17, 40, 130]), (128, 128, 2, [191, 127, 900, 70000, 33]), (96, 48, 4, [95, 4097, 130000]),
+    (6, 3, 2, [5] * 64), (24, 8, 2, list(range(1, 700, 11))), (12, 4, 4, list(range(7, 20000, 199))),
+    (48, 8, 2, [3_000_017, 1_500_001, 12_345]), (2, 2, 2, [100_003] * 70), (8, 8, 2, [9_000_000, 2_000_001])])
+@pytest.mark.parametrize("align,skew", [(1, 0), (1, 3), (8, 0), (8, 5)])
+@pytest.mark.parametrize("cap", [0, 4096])
+def test_gather_of_small_tensors(orc, gen, p, k, eb, sizes, align, skew, cap):
+    """Small calls find the chunk of every 16 bytes by a reciprocal: chunks from one element to megabytes, more tensors
+    than a wavefront has lanes and than a launch carries, more stage-1 buffers than 16 and than 64, one and two
+    vectors per lane.  A capped grid takes the kernels of larger calls."""
+    dtype = np.uint16 if eb == 2 else np.uint32
+    tab = gen.normal_table(1.0, "bf16") if eb == 2 else gen.normal_table(1.0, "f32").view(np.uint32)
+    segs, src, dst_at = [], 0, 0
+    for n in sizes:
+        S = -(-(-(-n // p)) // align) * align
+        segs.append((n, S, src, dst_at))
+        src, dst_at = src + p // k * S, dst_at + n
+    T = [gen.fill_host(gen.stream_key(4600 + l, gen.ROLE_PARAM), 0, src, tab) for l in range(k)]
+    T_dev = [Guarded(src, dtype, skew=skew, fill=t) for t in T]
+    dst = Guarded(dst_at, dtype, skew=skew)
+    want = dst.numpy().copy()
+    orc.hier_gather_reorder_coalesced(T, segs, p, want)
+    try:
+        mics.mics_set_blocks_per_cu(cap)
+        mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, eb)
+        torch.cuda.synchronize()
+        assert np.array_equal(dst.numpy(), want) and dst.guards_intact()
+        for n, S, at, _ in (segs[0], segs[-1]):
+            one = Guarded(n, dtype, skew=skew)
+            mics.mics_hier_gather_reorder(one.t, [t.t[at:] for t in T_dev], n, S, p, k, eb)
+            torch.cuda.synchronize()
+            assert np.array_equal(one.numpy(), orc.hier_gather_reorder([t[at:at + p // k * S] for t in T], n, S, p)), n
+            assert one.guards_intact()
+    finally:
+        mics.mics_set_blocks_per_cu(0)
