@@ -470,7 +470,7 @@ int reduce_scatter_accum_coalesced(const char* fn, const char* table, float* acc
                              fn, bad_a, bad_b);
 
     // every tensor, whatever its alignment, shares the launch of its batch
-    mics::Segment batch[mics::kMaxSegPerLaunch];
+    mics::Segment batch[mics::kMaxSegSmall];
     int nb = 0;
     for (int t = 0; t <= n_segs; ++t) {
         const bool last = (t == n_segs);
@@ -480,7 +480,7 @@ int reduce_scatter_accum_coalesced(const char* fn, const char* table, float* acc
             batch[nb].src_offset = sg.src_offset; batch[nb].dst_offset = sg.dst_offset;
             ++nb;
         }
-        if (nb == mics::kMaxSegPerLaunch || (last && nb)) {
+        if (nb == mics::kMaxSegSmall || (last && nb)) {
             int err = mics::launch_reduce_coalesced(acc, tab, batch, nb, p, accumulate != 0, kind, stream);
             if (err) return hip_fail(fn, err);
             nb = 0;

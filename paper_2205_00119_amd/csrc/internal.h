@@ -17,8 +17,8 @@ struct PtrTable {
 
 // Launchers: arguments are already validated.  Each returns 0 or the hipError_t
 // of the failed launch call (as int) and enqueues on `stream` without waiting.
-// Every launcher issues exactly one kernel launch, the coalesced ones one per
-// kMaxSegPerLaunch segments.
+// Every launcher issues exactly one kernel launch, the coalesced ones one per kMaxSegPerLaunch segments at most
+// (large gathers), 64 (reductions) or kMaxSegSmall (small calls).
 
 // vec16: every source, the destination and the shard size are multiples of 16
 // bytes -> direct 128-bit copy; otherwise the kernel that re-phases through a lane shift.

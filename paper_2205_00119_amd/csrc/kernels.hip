@@ -491,13 +491,54 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
     else move(std::false_type{});
 }
 
+// Table of up to SEGS (1, or 64 to 128) tensors in the kernel arguments, and the look-up of the tensor whose tiles
+// hold workgroup x: lane i takes entry i, the tensor's index is the number of entries at or below x.  Small calls
+// (ONE_ROUND, 64 entries) have every lane take entry i's record too, so that nothing waits for the index, and so do
+// the large reductions but those of few two-byte buffers, whose wavefronts move too little for 2 KiB of table (16
+// tensors, bf16, p = 4, 79 M elements: 194 us, without 190).  Looked up with scalar instructions, as the large gathers
+// do, in three dependent rounds, reductions take 1 to 4 % longer (p = 32, 16 tensors, 3.8 M elements 7 %).
+template <typename Seg, int SEGS>
+struct TileTable {
+    unsigned tile_begin[SEGS];                     // ascending; kNoTile behind the last
+    Seg seg[SEGS];
+};
+__device__ __forceinline__ uint32_t uniform_lane(uint32_t v, unsigned from)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)from);
+}
+template <bool ONE_ROUND, typename Seg, int SEGS>
+__device__ __forceinline__ Seg segment_at(const TileTable<Seg, SEGS>& tab, unsigned x, unsigned* tile)
+{
+    const unsigned lane = threadIdx.x & 63u;
+    const unsigned begin = tab.tile_begin[lane];
+    unsigned t;
+    if constexpr (SEGS == 64) {
+        constexpr int W = sizeof(Seg) / 4;
+        struct Words { uint32_t w[W]; } sg;
+        if constexpr (ONE_ROUND) sg = __builtin_bit_cast(Words, tab.seg[lane]);
+        t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1;
+        *tile = x - uniform_lane(begin, t);
+        if constexpr (ONE_ROUND) {
+            #pragma unroll
+            for (int i = 0; i < W; ++i) sg.w[i] = uniform_lane(sg.w[i], t);
+            return __builtin_bit_cast(Seg, sg);
+        }
+    } else {
+        // the second read overlaps the first: its last SEGS - 64 entries count
+        const unsigned later = tab.tile_begin[SEGS - 64 + lane];
+        t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1 +
+            (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane >= 128 - SEGS && later <= x));
+        *tile = x - (t < 64 ? uniform_lane(begin, t) : uniform_lane(later, t - (SEGS - 64)));
+    }
+    return tab.seg[t];
+}
+
 // Small calls.  What bounds them is latency: of dependent reads of the kernel arguments (0.15 to 0.25 us each; the
 // kernels above make three or four before their first load), and, with many tensors, of workgroups that have
 // nothing to do (one workgroup per chunk is p of them for every bias).  Here a tensor's destination is cut into
 // tiles whatever its chunks are, and every lane finds the chunk of its own 16 bytes: a multiplication by a host-made
 // reciprocal for the chunk, another for its node, and the stage-1 buffer's address from the lane that holds it.  Up to
-// 64 tensors all of the arguments come in one round of loads: lane i takes entry i of each table, and the tile's
-// tensor is the number of entries at or below it.  Any alignment: 16 bytes that cross the border of a chunk or an
+// 64 tensors all of the arguments come in one round of loads.  Any alignment: 16 bytes that cross the border of a chunk or an
 // end of the tensor go in 2-byte units.  us, one workgroup per chunk / so: 1 MB in one tensor, p = 16 2.45 / 2.06;
 // p = 16, 40 tensors, 1 MB 7.3 / 3.2; p = 128, 90 tensors, 5 MB 42.6 / 8.6, 40 tensors, 1 MB 20.9 / 3.4.
 struct FlatSeg {
@@ -505,20 +546,12 @@ struct FlatSeg {
     unsigned shard_bytes, valid_bytes;             // below 2^31
     unsigned recip, shift;                         // b / shard_bytes = mulhi(b, recip) >> shift for even b below 2^32
 };
-template <int SEGS>
-struct FlatTable {
-    unsigned tile_begin[SEGS];                     // ascending; kNoTile behind the last
-    FlatSeg seg[SEGS];
-};
+template <int SEGS> using FlatTable = TileTable<FlatSeg, SEGS>;
 
 // Lane `from`'s value, for a lane index that may differ from lane to lane.
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, unsigned from)
 {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(4 * from), (int)v);
-}
-__device__ __forceinline__ uint32_t uniform_lane(uint32_t v, unsigned from)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)from);
 }
 
 template <int U, int SEGS, bool MANY>
@@ -527,27 +560,11 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_flat_kernel(
 {
     const unsigned lane = threadIdx.x & 63u, x = blockIdx.x;
     const uint64_t p0 = (uint64_t)src.ptr[MANY ? lane : lane & 15], p1 = (uint64_t)src.ptr[MANY ? 64 + lane : 0];
+    unsigned tile = x;                                         // of the tensor
     FlatSeg sg;
-    unsigned first = 0;                                        // tile of the tensor
-    if constexpr (SEGS == 1) {
-        sg = tab.seg[0];
-    } else if constexpr (SEGS <= 64) {
-        const unsigned begin = tab.tile_begin[lane];
-        sg = tab.seg[lane];
-        const unsigned t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1;
-        first = uniform_lane(begin, t);
-        auto entry = [&](unsigned v) { return uniform_lane(v, t); };
-        auto wide = [&](unsigned long long v) { return (unsigned long long)entry((uint32_t)(v >> 32)) << 32 | entry((uint32_t)v); };
-        sg = FlatSeg{wide(sg.src_byte), wide(sg.dst_byte), entry(sg.shard_bytes), entry(sg.valid_bytes), entry(sg.recip), entry(sg.shift)};
-    } else {
-        // the second read overlaps the first: its last SEGS - 64 entries count
-        const unsigned begin = tab.tile_begin[lane], later = tab.tile_begin[SEGS - 64 + lane];
-        const unsigned t = (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= x)) - 1 +
-                           (unsigned)__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane >= 128 - SEGS && later <= x));
-        first = t < 64 ? uniform_lane(begin, t) : uniform_lane(later, t - (SEGS - 64));
-        sg = tab.seg[t];
-    }
-    const unsigned tile = x - first, shard = sg.shard_bytes, valid = sg.valid_bytes;
+    if constexpr (SEGS == 1) sg = tab.seg[0];
+    else sg = segment_at<true>(tab, x, &tile);
+    const unsigned shard = sg.shard_bytes, valid = sg.valid_bytes;
     const uintptr_t d_lo = (uintptr_t)dst + sg.dst_byte;
     const uintptr_t d_line = d_lo & ~(uintptr_t)127;           // tiles begin on the destination's lines
 
@@ -834,6 +851,11 @@ __device__ __forceinline__ void wave_lds_order()
 // find nothing to do).  A lane whose elements are not all inside the range does nothing:
 // those elements -- fewer than EPL at either end -- are rsa_edges' work.
 //
+// PARTS (small segments, of at least EPL elements): such a lane sums the first or the last EPL elements of the
+// range instead and keeps those that are its own.  A workgroup that has a segment's ends would otherwise wait for
+// a second chain of loads, 16 at a time.  (In the flat kernels, where a workgroup of its own does that, the
+// additional instructions cost more: p = 4, 0.1 M elements 2.2 / 2.4 us.)
+//
 // CACHED (kAccCached): plain accesses, straight from the lane.  A kernel of its own, because in small calls
 // every instruction in front of the loads and between sum and store counts (bf16, p = 8, 125 k elements: 2.4
 // us; with the choice made at run time, or through LDS, 2.7).
@@ -843,7 +865,7 @@ __device__ __forceinline__ void wave_lds_order()
 // cache lines, which leave the L2 between the two halves.  Passing the results through 2 KiB of LDS
 // per wavefront lets every store instruction cover one contiguous KiB.  Vector j of the wavefront's
 // 128 holds half of the elements of lane j / 2.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, bool FIRST, typename Tab>
+template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, bool FIRST, bool PARTS, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
                                          size_t lead, size_t end, int how)
 {
@@ -852,7 +874,31 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
     float a[EPL];
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = 0.0f;
-    if constexpr (CACHED) {
+    if constexpr (PARTS) {
+        static_assert(CACHED, "");
+        if (v0 >= end || v0 + EPL <= lead) return;
+        const size_t w0 = full ? v0 : v0 < lead ? lead : end - EPL;
+        float* const at = acc + (w0 - lead);
+        auto own = [&](int e) { return w0 + e >= v0 && w0 + e < v0 + EPL; };
+        rsa_sum<KIND, VEC, P, BATCH, VEC == 4, false>(a, g, p, src0 + w0, [&] {
+            if constexpr (ACCUM) {
+                if (full) {
+                    ld_f32<EPL, false>(a, at);
+                } else {
+                    #pragma unroll
+                    for (int e = 0; e < EPL; ++e)
+                        if (own(e)) a[e] = at[e];
+                }
+            }
+        });
+        if (full) {
+            st_f32<EPL, false>(at, a);
+        } else {
+            #pragma unroll
+            for (int e = 0; e < EPL; ++e)
+                if (own(e)) at[e] = a[e];
+        }
+    } else if constexpr (CACHED) {
         if (full) {
             rsa_sum<KIND, VEC, P, BATCH, VEC == 4, false>(a, g, p, src0 + v0, [&] {
                 if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
@@ -907,6 +953,15 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
     }
 }
 
+// A segment of fewer than EPL elements: one per lane of the calling workgroup.
+template <int KIND, int P, bool ACCUM, typename Tab>
+__device__ __forceinline__ void rsa_short(float* acc, const Tab& g, int p, size_t src0, size_t lead, size_t end)
+{
+    if (threadIdx.x >= end - lead) return;
+    if constexpr (P <= 16) rsa_element<KIND, P, ACCUM>(acc + threadIdx.x, g, p, src0 + lead + threadIdx.x);
+    else rsa_element<KIND, P, ACCUM>(acc + threadIdx.x, kernarg_table(), P, src0 + lead + threadIdx.x);
+}
+
 // The elements that no lane holds as a full vector: virtual [lead, head) with head = lead
 // rounded up to EPL (or `end`), and [tail, end) with tail = `end` rounded down to EPL (or
 // head).  One element per lane, lanes 0 .. 2*EPL-1 of the calling workgroup.
@@ -945,7 +1000,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8)>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8), false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -957,25 +1012,29 @@ struct ReduceSeg {
     unsigned long long end, src0, dst;
     unsigned lead, pad;
 };
-struct ReduceSegTable {
-    int n;
-    unsigned tile_begin[kMaxSeg + 1];
-    ReduceSeg seg[kMaxSeg];
-};
+template <int SEGS> using ReduceTable = TileTable<ReduceSeg, SEGS>;
 
-template <int KIND, int P, bool ACCUM, bool CACHED, typename Tab>
-__global__ __launch_bounds__(kMaxBlock) void rsa_seg_kernel(
-    Tab gtab, float* __restrict__ acc, int p, ReduceSegTable tab, int how)
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, int SEGS, typename Tab>
+__global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_kernel(
+    Tab gtab, float* __restrict__ acc, int p, ReduceTable<SEGS> tab, int how)
 {
     const auto& g = table_view(gtab);
-    constexpr int EPL = 4 * GradFormat<KIND>::kPerDword;
-    const unsigned x = blockIdx.x;
-    const int t = segment_of(tab.tile_begin, x);
-    const size_t end = tab.seg[t].end, lead = tab.seg[t].lead;
-    const size_t v0 = ((size_t)(x - tab.tile_begin[t]) * blockDim.x + threadIdx.x) * EPL;
-    if (x == tab.tile_begin[t]) rsa_edges<KIND, EPL, P, ACCUM>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, lead, end);
-    rsa_lane<KIND, 4, P, MICS_RSA_BATCH, ACCUM, CACHED, false>(acc + tab.seg[t].dst, g, p, tab.seg[t].src0, v0, lead,
-                                                               end, how);
+    constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
+    constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
+    unsigned tile;
+    const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 4)>(tab, blockIdx.x, &tile);
+    const size_t end = sg.end, lead = sg.lead;
+    float* const dst = acc + sg.dst;
+    if constexpr (CACHED) {
+        if (end - lead < EPL) {
+            rsa_short<KIND, P, ACCUM>(dst, g, p, sg.src0, lead, end);
+            return;
+        }
+    } else if (tile == 0) {
+        rsa_edges<KIND, EPL, P, ACCUM>(dst, g, p, sg.src0, lead, end);
+    }
+    const size_t v0 = ((size_t)tile * blockDim.x + threadIdx.x) * EPL;
+    rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, false, CACHED>(dst, g, p, sg.src0, v0, lead, end, how);
 }
 
 // ---------------------------------------------------------------------------
@@ -1638,10 +1697,12 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
 //     grid, because the partial lines between two wavefronts then meet in one workgroup (2 M for p < 16;
 //     p = 8, 9.8 M: 64 x 10 40.7, 512 x 32 39.2; 30 M: 114, 119).  Gradients off 16 bytes: 512 x 16
 //     (p = 16, 50 M: 344, 64 x 8 350).  Up to 3 two-byte buffers with either off: 256 lanes, uncapped (p = 2,
-//     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5).
+//     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5); as segments of a coalesced call, 256 lanes in any
+//     case, from two buffers on 256 x 16 (16 tensors, 64 lanes / so: p = 2, 39 M elements 79.5 / 76.3, p = 3, 67 M 1.08
+//     times the speed).
 //   - Below, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
 //     uncapped 28.7).
-Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, size_t units)
+Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool segments, size_t units)
 {
     const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
     Shape sh;
@@ -1650,7 +1711,8 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
     } else if (grads16) {
         const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
-        sh = Shape{p < 4 && elem_bytes == 2 && !acc16 ? 256 : 64, p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
+        const bool few = p < 4 && elem_bytes == 2;
+        sh = Shape{few && (segments || !acc16) ? 256 : 64, few && segments && p > 1 ? 16 : p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
                        p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
     } else {
         sh = p < 4 && elem_bytes == 2 ? Shape{256, 0} : Shape{kMaxBlock, 16};
@@ -1658,8 +1720,8 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
     return with_knobs(kFamReduce, sh);
 }
 
-// Small messages on large groups take the one-dword-per-lane kernel (VEC = 1), MB of gradients up to which it
-// wins.  us per call, one dword / 128 bits per lane:
+// Small messages on large groups take the one-dword-per-lane kernels (VEC = 1; of a coalesced call all its segments
+// together), MB of gradients up to which they win.  us per call, one dword / 128 bits per lane:
 //   bf16, p = 20 5 MB 3.4 / 3.9, 19 MB 6.0 / 6.0, 32 MB 8.9 / 8.2      p = 32 13 MB 4.3 / 4.7, 24 MB 6.4 / 6.3
 //         p = 48 13 MB 4.5 / 5.8, 49 MB 10.7 / 12.2, 63 MB 13.7 / 12.9  p = 40 49 MB 10.9 / 11.6, 62 MB 13.6 / 12.9
 //         p = 64 1 MB 3.0 / 6.4, 50 MB 10.7 / 11.6, 65 MB 13.5 / 14.6   p = 128 3 MB 4.3 / 11.2, 67 MB 12.7 / 15.9
@@ -1708,7 +1770,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     if (int e = compute_units(&units)) return e;
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
-    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, units);
+    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, false, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     const int how = accum_policy(count, p, GB);
     return dispatch_bool(accumulate, [&](auto A) {
@@ -1873,6 +1935,53 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
 
 namespace {
 
+// `n` segments in one launch, with lanes of VEC dwords.
+template <int KIND, int VEC, int SEGS>
+int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit, const Segment* segs, int n, int p,
+                    bool accumulate, const Shape& sh, int how, hipStream_t st)
+{
+    constexpr size_t EPL = VEC * GradFormat<KIND>::kPerDword;
+    ReduceTable<SEGS> tab;
+    const size_t tile_elems = (size_t)sh.lanes * EPL;
+    size_t tiles = 0;
+    for (int t = 0; t < n; ++t) {
+        const Segment& sg = segs[t];
+        // position of the segment's first element in the rounded-down buffers; its virtual
+        // element 0 is the one on a line (of 128, 16 or 4 bytes: see align_gradient_pointers) at or below it
+        const size_t src = sg.src_offset + base_lead;
+        const unsigned lead = (unsigned)(src % unit);
+        tab.tile_begin[t] = (unsigned)tiles;
+        tab.seg[t].lead = lead;
+        tab.seg[t].pad = 0;
+        tab.seg[t].end = lead + sg.numel;
+        tab.seg[t].src0 = src - lead;
+        tab.seg[t].dst = sg.dst_offset;
+        if (sg.numel) tiles += (lead + sg.numel + tile_elems - 1) / tile_elems;
+        if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
+    }
+    for (int t = n; t < SEGS; ++t) tab.tile_begin[t] = kNoTile;
+    if (tiles == 0) return 0;
+    auto run = [&](auto P, auto A, auto C) {
+        // lanes of 8 elements pass their results through 32 bytes of LDS
+        const size_t lds = lds_for(sh, !C.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
+        const dim3 gr((unsigned)tiles), bl(sh.lanes);
+        if constexpr (P.value > 0)
+            return launch(rsa_seg_kernel<KIND, VEC, P.value, A.value, C.value, SEGS, SmallTable<P.value>>, gr, bl, lds, st,
+                          small<P.value>(g), acc, p, tab, how);
+        else
+            return launch(rsa_seg_kernel<KIND, VEC, 0, A.value, C.value, SEGS, PtrTable>, gr, bl, lds, st, g, acc, p, tab, how);
+    };
+    return dispatch_bool(accumulate, [&](auto A) {
+        if constexpr (VEC == 1) {
+            return run(std::integral_constant<int, 0>{}, A, std::true_type{});
+        } else {
+            return dispatch_bool(how == kAccCached, [&](auto C) {
+                return dispatch_group(p, [&](auto P) { return run(P, A, C); });
+            });
+        }
+    });
+}
+
 template <int KIND>
 int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, int p, bool accumulate,
                           hipStream_t st)
@@ -1883,53 +1992,29 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
     const size_t unit = line >= 16 ? line / GB : 4 / GB;             // elements that a segment's lead is counted in
-    for (int first = 0; first < n; first += kMaxSeg) {
-        ReduceSegTable tab;
-        tab.n = n - first < kMaxSeg ? n - first : kMaxSeg;
+    size_t all = 0;
+    for (int t = 0; t < n; ++t) all += segs[t].numel;
+    const bool narrow = narrow_call(p, GB, all, line >= 16);
+    for (int first = 0, nt; first < n; first += nt) {
+        nt = n - first < 64 ? n - first : 64;
         size_t elements = 0;
-        for (int t = 0; t < tab.n; ++t) elements += segs[first + t].numel;
-        bool acc16 = true;
-        for (int t = 0; t < tab.n; ++t) {
-            const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
-            acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
+        for (int t = 0; t < nt; ++t) elements += segs[first + t].numel;
+        int err;
+        if (narrow) {
+            nt = n - first < kMaxSegSmall ? n - first : kMaxSegSmall;
+            const Shape sh = {kNarrowBlock, 0};
+            err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st)
+                           : reduce_segments<KIND, 1, kMaxSegSmall>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st);
+        } else {
+            bool acc16 = true;
+            for (int t = 0; t < nt; ++t) {
+                const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
+                acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
+            }
+            const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
+            err = reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh,
+                                               accum_policy(elements, p, (int)GB), st);
         }
-        const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, units);
-        const size_t tile_elems = (size_t)sh.lanes * EPL;
-        size_t tiles = 0;
-        for (int t = 0; t < tab.n; ++t) {
-            const Segment& sg = segs[first + t];
-            // position of the segment's first element in the rounded-down buffers; its virtual
-            // element 0 is the one on a line (of 128, 16 or 4 bytes: see align_gradient_pointers) at or below it
-            const size_t src = sg.src_offset + base_lead;
-            const unsigned lead = (unsigned)(src % unit);
-            tab.tile_begin[t] = (unsigned)tiles;
-            tab.seg[t].lead = lead;
-            tab.seg[t].pad = 0;
-            tab.seg[t].end = lead + sg.numel;
-            tab.seg[t].src0 = src - lead;
-            tab.seg[t].dst = sg.dst_offset;
-            if (sg.numel) tiles += (lead + sg.numel + tile_elems - 1) / tile_elems;
-            else tab.seg[t].end = 0;
-            if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
-        }
-        for (int t = tab.n; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
-        if (tiles == 0) continue;
-        const int how = accum_policy(elements, p, (int)GB);
-        const int err = dispatch_bool(accumulate, [&](auto A) {
-            return dispatch_bool(how == kAccCached, [&](auto C) {
-                // lanes of 8 elements pass their results through 32 bytes of LDS
-                const size_t lds = lds_for(sh, !C.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
-                const dim3 gr((unsigned)tiles), bl(sh.lanes);
-                return dispatch_group(p, [&](auto P) {
-                    if constexpr (P.value > 0)
-                        return launch(rsa_seg_kernel<KIND, P.value, A.value, C.value, SmallTable<P.value>>, gr, bl, lds,
-                                      st, small<P.value>(g), acc, p, tab, how);
-                    else
-                        return launch(rsa_seg_kernel<KIND, 0, A.value, C.value, PtrTable>, gr, bl, lds, st, g, acc, p,
-                                      tab, how);
-                });
-            });
-        });
         if (err) return err;
     }
     return 0;

@@ -309,3 +309,29 @@ def test_gather_of_small_tensors(orc, gen, p, k, eb, sizes, align, skew, cap):
             assert one.guards_intact()
     finally:
         mics.mics_set_blocks_per_cu(0)
+
+
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [1, 3, 4, 8, 12, 24, 32, 48, 100])
+@pytest.mark.parametrize("n_segs,threshold", [(64, 0), (65, 0), (150, 0), (70, 1)])
+def test_reduce_of_many_small_segments(orc, gen, name, p, n_segs, threshold):
+    """More segments than a wavefront has lanes and than a launch carries, down to one element, at changing positions
+    inside a lane's elements; with a threshold, through the kernels of large accumulators."""
+    code = FORMATS[name][0]
+    segs, src, dst = [], 1, 0
+    for t in range(n_segs):
+        n = (1, 2, 7, 8, 9, 63, 130, 600)[t % 8]
+        src += t % 5
+        segs.append((n, 0, src, dst))
+        src, dst = src + n, dst + n
+    host, dev = rank_buffers(gen, name, p, src + 3, [0])
+    try:
+        mics.mics_set_stream_threshold_bytes(threshold)
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, dst, skew=1)
+            mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+            orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), accumulate
+    finally:
+        mics.mics_set_stream_threshold_bytes(0)
