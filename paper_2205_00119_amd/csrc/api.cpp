@@ -350,7 +350,6 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
     const size_t eb = (size_t)elem_bytes;
     if (!aligned(dst_flat, eb))
         return fail(MICS_ERR_ALIGNMENT, "%s: dst_flat not aligned to %d bytes", fn, elem_bytes);
-    int used = 0;                                    // tensors that are not empty
     const size_t limit = SIZE_MAX / 8 / (size_t)p;   // keeps every byte offset below SIZE_MAX / 2
     size_t dst_lo = SIZE_MAX, dst_hi = 0, src_lo = SIZE_MAX, src_hi = 0, total = 0;
     for (int t = 0; t < n_segs; ++t) {
@@ -361,7 +360,6 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
             return fail(MICS_ERR_INVALID_ARG, "%s: segment %d: numel = %zu exceeds p * shard_elems = %zu",
                         fn, t, sg.numel, (size_t)p * sg.shard_elems);
         if (sg.numel == 0) continue;
-        ++used;
         total += sg.numel;
         if (sg.dst_offset < dst_lo) dst_lo = sg.dst_offset;
         if (sg.dst_offset + sg.numel > dst_hi) dst_hi = sg.dst_offset + sg.numel;
@@ -390,32 +388,27 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
                       : fail(MICS_ERR_INVALID_ARG, "%s: the destination regions of segments %d and %d overlap",
                              fn, bad_a, bad_b);
 
-    // Tensors whose bases, shard size and offsets are 16-byte clean go to the vector kernel, all
-    // others to the kernel for any alignment: one launch per kMaxSegPerLaunch tensors of either kind.  A small
-    // call is not split by kind (unless grids are capped, which its kernel does not do).
-    const bool small = used > 1 && 2 * total * eb < mics::small_gather_bytes(used) && g_blocks_per_cu.load() == 0;
-    mics::Segment clean[mics::kMaxSegPerLaunch], other[mics::kMaxSegSmall];
-    const int most = small ? mics::kMaxSegSmall : mics::kMaxSegPerLaunch;
-    int nc = 0, no = 0;
+    // Calls whose bases, shard sizes and offsets are all 16-byte clean go to the vector kernel, all
+    // others to the kernel for any alignment: one launch per gather_batch tensors.
+    bool vec16 = bases16;
+    for (int t = 0; t < n_segs; ++t) {
+        const mics_segment& sg = segs[t];
+        if (sg.numel)
+            vec16 = vec16 && (sg.shard_elems * eb) % 16 == 0 && (sg.src_offset * eb) % 16 == 0 && (sg.dst_offset * eb) % 16 == 0;
+    }
+    const int most = mics::gather_batch(2 * total * eb);
+    mics::Segment batch[mics::kMaxSegMany];
+    int nb = 0;
     for (int t = 0; t <= n_segs; ++t) {
         const bool last = (t == n_segs);
         if (!last && segs[t].numel) {
             const mics_segment& sg = segs[t];
-            const bool vec16 = !small && bases16 && (sg.shard_elems * eb) % 16 == 0 && (sg.src_offset * eb) % 16 == 0 &&
-                               (sg.dst_offset * eb) % 16 == 0;
-            mics::Segment& slot = vec16 ? clean[nc++] : other[no++];
-            slot.numel = sg.numel; slot.shard_elems = sg.shard_elems;
-            slot.src_offset = sg.src_offset; slot.dst_offset = sg.dst_offset;
+            batch[nb++] = {sg.numel, sg.shard_elems, sg.src_offset, sg.dst_offset};
         }
-        if (nc == mics::kMaxSegPerLaunch || (last && nc)) {
-            int err = mics::launch_reorder_coalesced(dst_flat, tab, clean, nc, p, k, elem_bytes, true, stream);
+        if (nb == most || (last && nb)) {
+            int err = mics::launch_reorder_coalesced(dst_flat, tab, batch, nb, p, k, elem_bytes, vec16, stream);
             if (err) return hip_fail(fn, err);
-            nc = 0;
-        }
-        if (no == most || (last && no)) {
-            int err = mics::launch_reorder_coalesced(dst_flat, tab, other, no, p, k, elem_bytes, false, stream);
-            if (err) return hip_fail(fn, err);
-            no = 0;
+            nb = 0;
         }
     }
     return MICS_OK;
@@ -470,7 +463,7 @@ int reduce_scatter_accum_coalesced(const char* fn, const char* table, float* acc
                              fn, bad_a, bad_b);
 
     // every tensor, whatever its alignment, shares the launch of its batch
-    mics::Segment batch[mics::kMaxSegSmall];
+    mics::Segment batch[mics::kMaxSegMany];
     int nb = 0;
     for (int t = 0; t <= n_segs; ++t) {
         const bool last = (t == n_segs);
@@ -480,7 +473,7 @@ int reduce_scatter_accum_coalesced(const char* fn, const char* table, float* acc
             batch[nb].src_offset = sg.src_offset; batch[nb].dst_offset = sg.dst_offset;
             ++nb;
         }
-        if (nb == mics::kMaxSegSmall || (last && nb)) {
+        if (nb == mics::kMaxSegMany || (last && nb)) {
             int err = mics::launch_reduce_coalesced(acc, tab, batch, nb, p, accumulate != 0, kind, stream);
             if (err) return hip_fail(fn, err);
             nb = 0;

@@ -17,8 +17,8 @@ struct PtrTable {
 
 // Launchers: arguments are already validated.  Each returns 0 or the hipError_t
 // of the failed launch call (as int) and enqueues on `stream` without waiting.
-// Every launcher issues exactly one kernel launch, the coalesced ones one per kMaxSegPerLaunch segments at most
-// (large gathers), 64 (reductions) or kMaxSegSmall (small calls).
+// Every launcher issues exactly one kernel launch, the coalesced reductions one per 64 segments, or kMaxSegMany in
+// small calls.
 
 // vec16: every source, the destination and the shard size are multiples of 16
 // bytes -> direct 128-bit copy; otherwise the kernel that re-phases through a lane shift.
@@ -49,22 +49,23 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
                     const PtrTable& copies, int r, float scale, size_t count, const AdamScalars& hp,
                     void* stream);
 
-// Segment records travel in the kernel-argument segment: at most this many per launch.
-constexpr int kMaxSegPerLaunch = 48;
+// Segment records travel in the kernel-argument segment: at most kMaxSegMany per launch; up to kMaxSegPerLaunch the
+// gathers have kernels with a smaller table.
+constexpr int kMaxSegPerLaunch = 48, kMaxSegMany = 96;
 
-// Small coalesced calls carry twice as many per launch.  A gather of n tensors is small if it moves (reads and writes)
-// less than this; it takes all its tensors, whatever their alignment, through one kernel (limits: kernels.hip, flat_vectors).
-constexpr int kMaxSegSmall = 2 * kMaxSegPerLaunch;
-constexpr size_t small_gather_bytes(int n) { return (n > kMaxSegPerLaunch ? size_t{64} : size_t{36}) << 20; }
+// Tensors per launch of a gather that moves (reads and writes) `moved` bytes: the look-up among 96 costs more than a
+// second launch from there on (us, 48 / 96 per launch, p = 16: 400 MB, 95 tensors 73.4 / 72.2, 50 tensors 72.5 / 71.8; 1 GB
+// 172.5 / 175.7, 166.5 / 169.5).
+constexpr int gather_batch(size_t moved) { return moved < (size_t{640} << 20) ? kMaxSegMany : kMaxSegPerLaunch; }
 
 // One separately sharded tensor of a coalesced call (mirrors mics_segment; elements).
 struct Segment {
     size_t numel, shard_elems, src_offset, dst_offset;
 };
 
-// vec16: every segment satisfies the 16-byte conditions of the vector kernel (bases, shard
-// size and both offsets); otherwise the segments go through the lane-shift kernel, which
-// takes any element-aligned geometry.
+// At most kMaxSegMany tensors, none of them empty: one launch.  vec16: every segment satisfies the 16-byte
+// conditions of the vector kernel (bases, shard size and both offsets); otherwise they go through the lane-shift
+// kernel, which takes any element-aligned geometry.
 int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs, int n, int p,
                              int k, int elem_bytes, bool vec16, void* stream);
 // numel = elements to reduce; any element-aligned geometry.  kind: 0 bf16, 1 binary16, 2 binary32.

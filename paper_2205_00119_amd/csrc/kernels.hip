@@ -275,8 +275,10 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_vec_kernel(
     }
 }
 
-// Coalesced form (many separately sharded tensors in one launch, all 16-byte aligned):
-// blockIdx.y and .z = chunk, blockIdx.x = tile x - tile_begin[t] of tensor t's chunk.  A tile is
+// Coalesced form (many separately sharded tensors in one launch): blockIdx.y and .z = chunk, blockIdx.x = tile
+// x - tile_begin[t] of tensor t's chunk.  reorder_seg_kernel is for calls whose tensors are all 16-byte aligned,
+// reorder_shift_kernel for all others, which moves the aligned ones among them the same way (move_tile): one launch, us,
+// split by kind / so: 16 tensors with odd shards p = 16, 60 MB 16.1 / 12.8, 200 MB 38.1 / 35.5, 800 MB 131 / 129.  A tile is
 // MICS_SEG_U runs of blockDim.x vectors: the table look-up in every wavefront's prologue has to
 // be paid for by two vectors per lane (one: -15 %), more spreads the window (four: -3 %).
 // Measured on the h = 8192 layer with two vectors per lane (GB/s): 64 lanes 6470, 128: 6540,
@@ -288,49 +290,56 @@ constexpr int kSegLanes = MICS_SEG_BLOCK;
 #ifndef MICS_SEG_U
 #define MICS_SEG_U 2
 #endif
-constexpr int kMaxSeg = kMaxSegPerLaunch;
 
-// Index of the segment whose tile range holds workgroup x (x < 2^31 - 1): tile_begin is
-// ascending, unused entries hold kNoTile.  Counting instead of walking keeps the table reads
+// Where the tiles of up to SEGS tensors begin, and the index of the tensor whose tiles hold workgroup x (x < 2^31 - 1):
+// begin is ascending, unused entries hold kNoTile.  Counting instead of walking keeps the table reads
 // independent of one another (a few wide scalar loads), which matters for workgroups that move
 // only a few KiB.  The count is written as integer arithmetic on the sign bit so that it stays
 // on the scalar unit: as a sum of comparisons it was compiled into some 300 vector
 // instructions per wavefront (-18 % on a layer of 16 unaligned tensors).  Counting only the
 // entries in use would need the entry count first, and that dependent load costs more than
-// the additions it saves (h = 8192 layer: 6.25 against 6.45 TB/s).
+// the additions it saves (h = 8192 layer: 6.25 against 6.45 TB/s).  Up to 48 tensors all entries are counted; above, every
+// eighth and then the eight from there: with 16 tensors at 400 MB that round costs 1.3 us, with more than 48 a second launch
+// costs more (us, 48 / 96 per launch: 95 tensors, p = 2 80 MB 20.8 / 17.2, 400 MB 69.2 / 66.0, p = 96 80 MB 34.5 / 19.7, 1 GB
+// equal; all 96 entries counted: 62 tensors 200 MB 28.2 / 26.5).
 constexpr unsigned kNoTile = 0x7FFFFFFFu;
-__device__ __forceinline__ int segment_of(const unsigned (&tile_begin)[kMaxSeg + 1], unsigned x)
-{
-    unsigned t = 0;
-    #pragma unroll
-    for (int i = 1; i < kMaxSeg; ++i) t += (tile_begin[i] - 1u - x) >> 31;      // 1 iff tile_begin[i] <= x
-    return (int)t;
-}
+template <int SEGS>
+struct TileBegin {
+    static constexpr int kStep = SEGS <= kMaxSegPerLaunch ? SEGS : 8;
+    unsigned coarse[SEGS / kStep];                 // every kStep-th entry
+    unsigned begin[SEGS];
+    __device__ __forceinline__ unsigned find(unsigned x) const
+    {
+        unsigned t = 0;
+        #pragma unroll
+        for (int i = 1; i < SEGS / kStep; ++i) t += (coarse[i] - 1u - x) >> 31;       // 1 iff coarse[i] <= x
+        t *= kStep;
+        unsigned u = 0;
+        #pragma unroll
+        for (int i = 1; i < kStep; ++i) u += (begin[t + i] - 1u - x) >> 31;
+        return t + u;
+    }
+    void close(int n)                              // behind the n entries in use
+    {
+        for (int t = n; t < SEGS; ++t) begin[t] = kNoTile;
+        for (int t = 0; t < SEGS; t += kStep) coarse[t / kStep] = begin[t];
+    }
+};
 struct ReorderSeg {
     unsigned long long shard_vecs, valid_bytes, src_vec, dst_vec;
 };
+template <int SEGS>
 struct ReorderSegTable {
-    int n;
-    unsigned tile_begin[kMaxSeg + 1];
-    ReorderSeg seg[kMaxSeg];
+    TileBegin<SEGS> tiles;
+    ReorderSeg seg[SEGS];
 };
 
-__global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
-    u32x4* __restrict__ dst, PtrTable src, ReorderSegTable tab, int k)
+// Tile `tile` of an aligned chunk of `valid` bytes.
+__device__ __forceinline__ void move_tile(size_t tile, const u32x4* __restrict__ s, u32x4* __restrict__ d, size_t valid)
 {
-    const unsigned x = blockIdx.x;
-    const int t = segment_of(tab.tile_begin, x);
-    const size_t shard_vecs = tab.seg[t].shard_vecs, valid_bytes = tab.seg[t].valid_bytes;
-    const size_t l = blockIdx.y, j = blockIdx.z, g = j * (size_t)k + l;
-    const size_t chunk_begin = g * shard_vecs * 16;
-    if (chunk_begin >= valid_bytes) return;
-    size_t valid = valid_bytes - chunk_begin;
-    if (valid > shard_vecs * 16) valid = shard_vecs * 16;
     const size_t nfull = valid / 16;
-    const u32x4* __restrict__ s = (const u32x4*)src.ptr[l] + tab.seg[t].src_vec + j * shard_vecs;
-    u32x4* __restrict__ d = dst + tab.seg[t].dst_vec + g * shard_vecs;
     const size_t tile_vecs = (size_t)blockDim.x * MICS_SEG_U;
-    const size_t tile0 = (size_t)(x - tab.tile_begin[t]) * tile_vecs;
+    const size_t tile0 = tile * tile_vecs;
     const unsigned lead = (unsigned)((uintptr_t)d / 16 & 7);          // as in reorder_vec_kernel
     u32x4 v[MICS_SEG_U];
     #pragma unroll
@@ -345,11 +354,27 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
     }
     // ragged end of the tensor: the tile that holds vector index nfull moves the last bytes
     const size_t tail_halves = (valid - nfull * 16) / 2;
-    if (tail_halves && (nfull + lead) / tile_vecs == x - tab.tile_begin[t] && threadIdx.x < tail_halves) {
+    if (tail_halves && (nfull + lead) / tile_vecs == tile && threadIdx.x < tail_halves) {
         const uint16_t* sh = (const uint16_t*)(s + nfull);
         uint16_t* dh = (uint16_t*)(d + nfull);
         dh[threadIdx.x] = sh[threadIdx.x];
     }
+}
+
+template <int SEGS>
+__global__ __launch_bounds__(kMaxBlock) void reorder_seg_kernel(
+    u32x4* __restrict__ dst, PtrTable src, ReorderSegTable<SEGS> tab, int k)
+{
+    const unsigned x = blockIdx.x;
+    const unsigned t = tab.tiles.find(x);
+    const size_t shard_vecs = tab.seg[t].shard_vecs, valid_bytes = tab.seg[t].valid_bytes;
+    const size_t l = blockIdx.y, j = blockIdx.z, g = j * (size_t)k + l;
+    const size_t chunk_begin = g * shard_vecs * 16;
+    if (chunk_begin >= valid_bytes) return;
+    size_t valid = valid_bytes - chunk_begin;
+    if (valid > shard_vecs * 16) valid = shard_vecs * 16;
+    move_tile(x - tab.tiles.begin[t], (const u32x4*)src.ptr[l] + tab.seg[t].src_vec + j * shard_vecs,
+              dst + tab.seg[t].dst_vec + g * shard_vecs, valid);
 }
 
 // General case: source and destination of a chunk sit at different offsets
@@ -361,19 +386,21 @@ struct ByteSeg {
     unsigned long long shard_bytes, valid_bytes, src_byte, dst_byte;
 };
 // Where workgroup x works: many tensors (table in the kernel arguments) ...
+template <int SEGS>
 struct ByteSegTable {
-    int n;
-    unsigned tile_begin[kMaxSeg + 1];
-    ByteSeg seg[kMaxSeg];
+    static constexpr bool kAligned = true;         // aligned tensors may be among them
+    TileBegin<SEGS> tiles;
+    ByteSeg seg[SEGS];
     __device__ __forceinline__ const ByteSeg& locate(unsigned x, size_t* tile) const
     {
-        const int t = segment_of(tile_begin, x);
-        *tile = x - tile_begin[t];
+        const unsigned t = tiles.find(x);
+        *tile = x - tiles.begin[t];
         return seg[t];
     }
 };
 // ... or a single tensor: no table, no look-up (4 % faster than a table of one entry).
 struct OneTensor {
+    static constexpr bool kAligned = false;
     ByteSeg seg;
     __device__ __forceinline__ const ByteSeg& locate(unsigned x, size_t* tile) const
     {
@@ -427,6 +454,14 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
     size_t valid = n_valid_bytes - chunk_begin;
     if (valid > shard_bytes) valid = shard_bytes;
 
+    if constexpr (Where::kAligned) {
+        static_assert(U == MICS_SEG_U, "move_tile's tiles");
+        const uintptr_t s0 = (uintptr_t)src.ptr[l] + sg.src_byte, d0 = (uintptr_t)dst + sg.dst_byte;
+        if (((s0 | d0 | shard_bytes) & 15) == 0) {
+            move_tile(tile, (const u32x4*)(s0 + j * shard_bytes), (u32x4*)(d0 + chunk_begin), valid);
+            return;
+        }
+    }
     const uintptr_t d_lo = (uintptr_t)dst + sg.dst_byte + chunk_begin;      // chunk in dst
     const uintptr_t d_hi = d_lo + valid;
     const uintptr_t s_chunk = (uintptr_t)src.ptr[l] + sg.src_byte + j * shard_bytes;
@@ -1570,10 +1605,10 @@ namespace {
 //   one tensor, 16-byte aligned, p = 16: 0.3 MB 1.82 / 2.22, 8 MB 3.04 / 3.47, 20 MB (two vectors) 5.08 / 5.97, 28 MB 6.6 /
 //   6.9, 36 MB 8.9 / 8.2; not aligned, whose wavefronts at the borders of chunks make a second round trip: 0.1 MB 2.7 / 2.7,
 //   1 MB 2.8 / 3.2, 8 MB 3.0 / 3.4, 11 MB 4.7 / 4.6, 14 MB 5.3 / 5.1
-//   up to 48 tensors, geometric means of the speed over p = 4, 16, 96 and 3, 16 tensors: aligned 8 MB 2.4, 28 MB 1.7, 44 MB
-//   1.4; not aligned 8 MB 1.8, 28 MB 1.4, 44 MB 0.95 at worst; more tensors, where the other kernels are launched
-//   twice, 60 MB 1.14 at worst
-int flat_vectors(int n, size_t moved, bool vec16)
+//   several tensors: not all aligned, p = 16, 4 tensors 27 MiB 9.1 / 7.5, 16 tensors 10.3 / 8.4, 20 MiB equal; all aligned
+//   27 MiB 6.4 / 7.6, 38 MiB equal; large groups, whose tensors are a workgroup per chunk there, p = 96 27 MiB 8.2 / 11.4
+//   and 6.4 / 9.9; more than 48, p = 16, 95 tensors 19 MiB 7.6 / 8.4, 27 MiB 10.9 / 9.6, p = 96 38 MiB 14.7 / 24, 57 MiB 18.4 / 16.8
+int flat_vectors(int n, size_t moved, int p, bool vec16)
 {
     const size_t mb = moved >> 20;
     if (g_blocks_per_cu.load() > 0) return 0;                  // its grid has no cap
@@ -1581,7 +1616,8 @@ int flat_vectors(int n, size_t moved, bool vec16)
         if (vec16 ? mb >= 27 : mb >= 10 || moved < (512u << 10)) return 0;
         return mb < 16 ? 1 : 2;
     }
-    return moved >= small_gather_bytes(n) ? 0 : mb < 18 ? 1 : 2;
+    const size_t most = p >= 48 ? (n > kMaxSegPerLaunch ? 52 : 36) : n > kMaxSegPerLaunch || !vec16 ? 24 : 36;
+    return mb >= most ? 0 : mb < 18 ? 1 : 2;
 }
 
 template <int U, int SEGS>
@@ -1618,17 +1654,12 @@ int launch_reorder_flat(void* dst, const PtrTable& src, const Segment* segs, int
 int launch_reorder_small(void* dst, const PtrTable& src, const Segment* segs, int n, int vectors, size_t moved, int k, size_t eb,
                          hipStream_t st)
 {
-    for (int first = 0; first < n; first += kMaxSegSmall) {
-        const int nt = n - first < kMaxSegSmall ? n - first : kMaxSegSmall;
-        const int err = dispatch_bool(vectors == 2, [&](auto TWO) {
-            constexpr int U = TWO.value ? 2 : 1;
-            if (nt == 1) return launch_reorder_flat<U, 1>(dst, src, segs + first, nt, moved, k, eb, st);
-            if (nt <= 64) return launch_reorder_flat<U, 64>(dst, src, segs + first, nt, moved, k, eb, st);
-            return launch_reorder_flat<U, kMaxSegSmall>(dst, src, segs + first, nt, moved, k, eb, st);
-        });
-        if (err) return err;
-    }
-    return 0;
+    return dispatch_bool(vectors == 2, [&](auto TWO) {
+        constexpr int U = TWO.value ? 2 : 1;
+        if (n == 1) return launch_reorder_flat<U, 1>(dst, src, segs, n, moved, k, eb, st);
+        if (n <= 64) return launch_reorder_flat<U, 64>(dst, src, segs, n, moved, k, eb, st);
+        return launch_reorder_flat<U, kMaxSegMany>(dst, src, segs, n, moved, k, eb, st);
+    });
 }
 
 }  // namespace
@@ -1638,7 +1669,7 @@ int launch_reorder(void* dst, const PtrTable& src, size_t n_valid_bytes, size_t 
 {
     hipStream_t st = (hipStream_t)stream;
     const Segment one = {n_valid_bytes, shard_bytes, 0, 0};
-    if (const int vectors = flat_vectors(1, 2 * n_valid_bytes, vec16))
+    if (const int vectors = flat_vectors(1, 2 * n_valid_bytes, p, vec16))
         return launch_reorder_small(dst, src, &one, 1, vectors, 2 * n_valid_bytes, k, 1, st);
     if (vec16) {
         // spread the block budget over the p chunks
@@ -1846,91 +1877,91 @@ int launch_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* para
     });
 }
 
+namespace {
+
+// A launch of SEGS tensors at most, none of them empty.
+template <int SEGS>
+int launch_reorder_seg(void* dst, const PtrTable& src, const Segment* segs, int n, size_t moved, int p, int k, size_t eb, hipStream_t st)
+{
+    const Shape sh = reorder_shape(moved, kSegLanes);
+    const size_t tile_vecs = (size_t)sh.lanes * MICS_SEG_U;
+    size_t tiles = 0;
+    ReorderSegTable<SEGS> tab;
+    for (int t = 0; t < n; ++t) {
+        const Segment& sg = segs[t];
+        tab.tiles.begin[t] = (unsigned)tiles;
+        tab.seg[t].shard_vecs = sg.shard_elems * eb / 16;
+        tab.seg[t].valid_bytes = sg.numel * eb;
+        tab.seg[t].src_vec = sg.src_offset * eb / 16;
+        tab.seg[t].dst_vec = sg.dst_offset * eb / 16;
+        tiles += (tab.seg[t].shard_vecs + off_line(dst, sg.dst_offset * eb, sg.shard_elems * eb) + tile_vecs - 1) / tile_vecs;
+        if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
+    }
+    tab.tiles.close(n);
+    return launch(reorder_seg_kernel<SEGS>, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
+                  (u32x4*)dst, src, tab, k);
+}
+
+ByteSeg byte_seg(const Segment& sg, size_t eb)
+{
+    return ByteSeg{sg.shard_elems * eb, sg.numel * eb, sg.src_offset * eb, sg.dst_offset * eb};
+}
+
+// Tiles start on a 128-byte line of the destination; at least one per tensor, for the chunk ends.
+size_t shift_tiles(const ByteSeg& sg, size_t tile_bytes) { return (sg.shard_bytes + 127 + tile_bytes - 1) / tile_bytes; }
+
+// Vectors per lane of reorder_shift_kernel: more of them, fewer wavefronts that share a source line at their ends;
+// fewer, a call that is spread further.  Speed against loads off 16 bytes, one tensor, 512
+// lanes x 1 / 64 x 4: 39 MB 1.15 / 1.11, 134 MB 1.11 / 1.12 and (p = 48) 1.08 / 1.05, 268 MB 1.04 / 1.10,
+// 1.26 GB 1.05 / 1.07; many tensors per launch, whose tile has to be found first, 128 x 2 / 64 x 4 /
+// 512 x 1: 315 MB 1.12 / 1.08 / 0.83, 3.2 GB 1.13 / 1.07 / 0.81.
+template <int SEGS>
+int launch_reorder_shift(void* dst, const PtrTable& src, const Segment* segs, int n, size_t moved, int p, int k, size_t eb, hipStream_t st)
+{
+    const Shape sh = reorder_shape(moved, kSegLanes);
+    const size_t tile_bytes = (size_t)sh.lanes * MICS_SEG_U * 16;
+    size_t tiles = 0;
+    ByteSegTable<SEGS> tab;
+    for (int t = 0; t < n; ++t) {
+        tab.tiles.begin[t] = (unsigned)tiles;
+        tab.seg[t] = byte_seg(segs[t], eb);
+        tiles += shift_tiles(tab.seg[t], tile_bytes);
+        if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
+    }
+    tab.tiles.close(n);
+    return launch(reorder_shift_kernel<ByteSegTable<SEGS>, MICS_SEG_U>, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)),
+                  dim3(sh.lanes), lds_for(sh), st, (unsigned char*)dst, src, tab, k);
+}
+
+int launch_reorder_shift_one(void* dst, const PtrTable& src, const Segment& one, size_t moved, int p, int k, size_t eb, hipStream_t st)
+{
+    const bool spread = moved < (160u << 20);
+    const Shape sh = reorder_shape(moved, spread ? kMaxBlock : 64);
+    const OneTensor where{byte_seg(one, eb)};
+    const size_t tiles = shift_tiles(where.seg, (size_t)sh.lanes * (spread ? 1 : 4) * 16);
+    if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
+    return launch(spread ? reorder_shift_kernel<OneTensor, 1> : reorder_shift_kernel<OneTensor, 4>,
+                  dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
+                  (unsigned char*)dst, src, where, k);
+}
+
+}  // namespace
+
 int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs, int n, int p, int k,
                              int elem_bytes, bool vec16, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
     const size_t eb = (size_t)elem_bytes;
-    size_t all = 0;
-    for (int t = 0; t < n; ++t) all += 2 * segs[t].numel * eb;
-    if (const int vectors = flat_vectors(n, all, vec16)) return launch_reorder_small(dst, src, segs, n, vectors, all, k, eb, st);
-    for (int first = 0; first < n; first += kMaxSeg) {
-        const int nt = n - first < kMaxSeg ? n - first : kMaxSeg;
-        size_t tiles = 0;
-        if (vec16) {
-            size_t moved = 0;
-            for (int t = 0; t < nt; ++t) moved += 2 * segs[first + t].numel * eb;
-            const Shape sh = reorder_shape(moved, kSegLanes);
-            const size_t tile_vecs = (size_t)sh.lanes * MICS_SEG_U;
-            ReorderSegTable tab;
-            tab.n = nt;
-            for (int t = 0; t < nt; ++t) {
-                const Segment& sg = segs[first + t];
-                tab.tile_begin[t] = (unsigned)tiles;
-                tab.seg[t].shard_vecs = sg.shard_elems * eb / 16;
-                tab.seg[t].valid_bytes = sg.numel * eb;
-                tab.seg[t].src_vec = sg.src_offset * eb / 16;
-                tab.seg[t].dst_vec = sg.dst_offset * eb / 16;
-                tiles += sg.shard_elems ? (tab.seg[t].shard_vecs + off_line(dst, sg.dst_offset * eb, sg.shard_elems * eb) + tile_vecs - 1) / tile_vecs : 0;
-                if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
-            }
-            for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
-            if (tiles == 0) continue;
-            if (int e = launch(reorder_seg_kernel, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
-                               (u32x4*)dst, src, tab, k))
-                return e;
-        } else {
-            size_t moved = 0;
-            for (int t = 0; t < nt; ++t) moved += 2 * segs[first + t].numel * eb;
-            // Vectors per lane: more of them, fewer wavefronts that share a source line at their ends;
-            // fewer, a call that is spread further.  Speed against loads off 16 bytes, one tensor, 512
-            // lanes x 1 / 64 x 4: 39 MB 1.15 / 1.11, 134 MB 1.11 / 1.12 and (p = 48) 1.08 / 1.05, 268 MB 1.04 / 1.10,
-            // 1.26 GB 1.05 / 1.07; many tensors per launch, whose tile has to be found first, 128 x 2 / 64 x 4 /
-            // 512 x 1: 315 MB 1.12 / 1.08 / 0.83, 3.2 GB 1.13 / 1.07 / 0.81.
-            const bool spread = nt == 1 && moved < (160u << 20);
-            const int u = nt > 1 ? 2 : spread ? 1 : 4;
-            const Shape sh = reorder_shape(moved, nt > 1 ? 128 : spread ? kMaxBlock : 64);
-            const size_t tile_bytes = (size_t)sh.lanes * u * 16;
-            // tiles start on a 128-byte line of the destination; at least one per tensor, for the chunk ends
-            auto tiles_of = [&](const ByteSeg& sg) {
-                return sg.valid_bytes ? (sg.shard_bytes + 127 + tile_bytes - 1) / tile_bytes : 0;
-            };
-            if (nt == 1) {
-                const Segment& sg = segs[first];
-                OneTensor one;
-                one.seg.shard_bytes = sg.shard_elems * eb;
-                one.seg.valid_bytes = sg.numel * eb;
-                one.seg.src_byte = sg.src_offset * eb;
-                one.seg.dst_byte = sg.dst_offset * eb;
-                tiles = tiles_of(one.seg);
-                if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
-                if (tiles == 0) continue;
-                if (int e = launch(spread ? reorder_shift_kernel<OneTensor, 1> : reorder_shift_kernel<OneTensor, 4>,
-                                   dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes), lds_for(sh), st,
-                                   (unsigned char*)dst, src, one, k))
-                    return e;
-                continue;
-            }
-            ByteSegTable tab;
-            tab.n = nt;
-            for (int t = 0; t < nt; ++t) {
-                const Segment& sg = segs[first + t];
-                tab.tile_begin[t] = (unsigned)tiles;
-                tab.seg[t].shard_bytes = sg.shard_elems * eb;
-                tab.seg[t].valid_bytes = sg.numel * eb;
-                tab.seg[t].src_byte = sg.src_offset * eb;
-                tab.seg[t].dst_byte = sg.dst_offset * eb;
-                tiles += tiles_of(tab.seg[t]);
-                if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
-            }
-            for (int t = nt; t <= kMaxSeg; ++t) tab.tile_begin[t] = kNoTile;
-            if (tiles == 0) continue;
-            if (int e = launch(reorder_shift_kernel<ByteSegTable, 2>, dim3((unsigned)tiles, (unsigned)k, (unsigned)(p / k)), dim3(sh.lanes),
-                               lds_for(sh), st, (unsigned char*)dst, src, tab, k))
-                return e;
-        }
-    }
-    return 0;
+    size_t moved = 0;
+    for (int t = 0; t < n; ++t) moved += 2 * segs[t].numel * eb;
+    if (moved == 0) return 0;
+    if (const int vectors = flat_vectors(n, moved, p, vec16)) return launch_reorder_small(dst, src, segs, n, vectors, moved, k, eb, st);
+    if (vec16)
+        return n <= kMaxSegPerLaunch ? launch_reorder_seg<kMaxSegPerLaunch>(dst, src, segs, n, moved, p, k, eb, st)
+                                     : launch_reorder_seg<kMaxSegMany>(dst, src, segs, n, moved, p, k, eb, st);
+    if (n == 1) return launch_reorder_shift_one(dst, src, segs[0], moved, p, k, eb, st);
+    return n <= kMaxSegPerLaunch ? launch_reorder_shift<kMaxSegPerLaunch>(dst, src, segs, n, moved, p, k, eb, st)
+                                 : launch_reorder_shift<kMaxSegMany>(dst, src, segs, n, moved, p, k, eb, st);
 }
 
 namespace {
@@ -2001,10 +2032,10 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         for (int t = 0; t < nt; ++t) elements += segs[first + t].numel;
         int err;
         if (narrow) {
-            nt = n - first < kMaxSegSmall ? n - first : kMaxSegSmall;
+            nt = n - first < kMaxSegMany ? n - first : kMaxSegMany;
             const Shape sh = {kNarrowBlock, 0};
             err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st)
-                           : reduce_segments<KIND, 1, kMaxSegSmall>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st);
+                           : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st);
         } else {
             bool acc16 = true;
             for (int t = 0; t < nt; ++t) {

@@ -335,3 +335,27 @@ def test_reduce_of_many_small_segments(orc, gen, name, p, n_segs, threshold):
             assert same_bits(acc, ref), accumulate
     finally:
         mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("p,k,n_tensors", [(2, 2, 2), (4, 4, 47), (16, 8, 48), (8, 8, 49), (6, 3, 96), (16, 8, 97), (64, 8, 96)])
+@pytest.mark.parametrize("kinds", ["aligned", "mixed", "odd"])
+def test_gather_of_tensors_of_two_kinds(orc, gen, p, k, n_tensors, kinds):
+    """Larger coalesced calls: 16-byte aligned tensors and others share a launch; the numbers of tensors around those of
+    the two tables.  Every other tensor is small, the first is too large for the kernel of small calls."""
+    segs, src, dst_at, align = [], 0, 0, 8 if kinds != "odd" else 1
+    for t in range(n_tensors):
+        n = 14_200_000 if t == 0 else (130_024 if t % 2 else 24 + 8 * t)
+        if kinds == "odd" or (kinds == "mixed" and t % 3 == 2):
+            n += 3
+        S = -(-(-(-n // p)) // align) * align
+        segs.append((n, S, src, dst_at))
+        src, dst_at = src + p // k * S, dst_at + (-(-n // 8) * 8 if kinds == "aligned" else n + t % 2)
+    tab = gen.normal_table(1.0, "bf16")
+    T = [gen.fill_host(gen.stream_key(4700 + l, gen.ROLE_PARAM), 0, src, tab) for l in range(k)]
+    T_dev = [Guarded(src, np.uint16, fill=t) for t in T]
+    dst = Guarded(dst_at, np.uint16)
+    want = dst.numpy().copy()
+    orc.hier_gather_reorder_coalesced(T, segs, p, want)
+    mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(dst.numpy(), want) and dst.guards_intact()
