@@ -790,7 +790,33 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 template <int KIND, int VEC, int P, int BATCH, bool HOLD, bool FIRST, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
-    if constexpr (P > 0) {
+    if constexpr (VEC == 4 && ((P == 32 && (KIND != 0 || HOLD)) || (P == 16 && KIND == 1 && !HOLD && !FIRST))) {
+        // A window of W loads that moves on by STEP buffers, held in this order.  Left to itself the compiler put as few as
+        // one load in flight here and more than enough there, from one change of the source to the next: us, f16, 16
+        // tensors, p = 16 900 MB 239 / so 139, 2 GB 524 / 324, p = 32 45 MB 20.5 / 10.6, 2 GB 752 / 313; f32, p = 32, 12 MB in two batches
+        // 3.95 / 3.69.  A window of 4 is 5 to 8 % slower at 2 GB, f32; of 8 to 16 equal at best (p = 32 45 MB 9.5 / 9.9).  Slower
+        // than the best that the compiler found by chance: f32, p = 32, 80 MB up to 8 %, f16 3 %.  The bf16 kernels, and p = 16 in one
+        // tensor, are better in the compiler's order (p = 16 300 MB 47.7, held 49.0; p = 32 300 MB 49.1 / 51).
+        constexpr int W = HOLD ? 16 : P == 16 ? 4 : 6, STEP = HOLD ? 4 : 2;
+        GradVec<KIND, VEC> v[W];
+        if (FIRST) accumulator();
+        #pragma unroll
+        for (int b = 0; b < W; ++b) v[b].load(g.ptr[b], elem);
+        if (!FIRST) accumulator();
+        __builtin_amdgcn_sched_barrier(0);
+        #pragma unroll
+        for (int q0 = 0; q0 < P; q0 += STEP) {
+            #pragma unroll
+            for (int b = q0; b < q0 + STEP; ++b) {
+                if (b == 0) rsa_add<KIND, VEC, true>(s, v[0]);
+                else rsa_add<KIND, VEC, false>(s, v[b % W]);
+            }
+            #pragma unroll
+            for (int b = q0; b < q0 + STEP; ++b)
+                if (b + W < P) v[b % W].load(g.ptr[b + W], elem);
+            if (q0 + W < P) __builtin_amdgcn_sched_barrier(0);
+        }
+    } else if constexpr (P > 0) {
         if (FIRST) accumulator();
         #pragma unroll
         for (int q0 = 0; q0 < P; q0 += BATCH) {
@@ -1015,6 +1041,17 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
     else rsa_element<KIND, P, ACCUM>(acc + (e - lead), kernarg_table(), P, src0 + e);
 }
 
+// The tile of workgroup x of n.  Workgroups go to the 8 XCDs in turn, so neighbouring tiles meet in no L2, and a line
+// that two of them share is fetched, or written in parts, twice.  IN_RUNS (reduction_in_runs): rounds of 128 workgroups in which every XCD
+// has a run of 16 neighbouring tiles.
+constexpr int kInRuns = 4;                         // in a kernel's `how`, beside the accumulator's policy
+__device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs)
+{
+    constexpr unsigned kXcds = 8, kRun = 16, kRound = kXcds * kRun;
+    const unsigned at = x % kRound, base = x - at;
+    return in_runs && base + kRound <= n ? base + at % kXcds * kRun + at / kXcds : x;
+}
+
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
@@ -1034,8 +1071,10 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
         return;
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
-    for (size_t base = (size_t)blockIdx.x * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8), false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how);
+    const unsigned tile = VEC == 1 ? blockIdx.x : tile_of(blockIdx.x, gridDim.x - 1, how & kInRuns);
+    for (size_t base = (size_t)tile * block; base < nlanes; base += stride)   // workgroup-uniform
+        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8), false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end,
+                                                                     how & ~kInRuns);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -1057,7 +1096,8 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
     constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     unsigned tile;
-    const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 4)>(tab, blockIdx.x, &tile);
+    const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 4)>(
+        tab, VEC == 1 ? blockIdx.x : tile_of(blockIdx.x, gridDim.x, how & kInRuns), &tile);
     const size_t end = sg.end, lead = sg.lead;
     float* const dst = acc + sg.dst;
     if constexpr (CACHED) {
@@ -1069,7 +1109,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
         rsa_edges<KIND, EPL, P, ACCUM>(dst, g, p, sg.src0, lead, end);
     }
     const size_t v0 = ((size_t)tile * blockDim.x + threadIdx.x) * EPL;
-    rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, false, CACHED>(dst, g, p, sg.src0, v0, lead, end, how);
+    rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, false, CACHED>(dst, g, p, sg.src0, v0, lead, end, how & ~kInRuns);
 }
 
 // ---------------------------------------------------------------------------
@@ -1751,6 +1791,53 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
     return with_knobs(kFamReduce, sh);
 }
 
+// Where the gradients are at one position inside their lines and the accumulator is at another, the lanes' vectors can be laid
+// on the lines of either.  The `lead` that lays them on the accumulator's, if the gradients' (`first` = address of the first
+// element) are then on 16 bytes, else -1.
+int lead_on_accumulator_lines(const float* acc, uintptr_t first, size_t elem_bytes)
+{
+    const uintptr_t lead = (uintptr_t)acc / 4 % 32;
+    return (first - lead * elem_bytes) % 16 ? -1 : (int)lead;
+}
+
+// Whether neighbouring tiles meet in one XCD (tile_of), and on whose lines the vectors lie.  Speed against the plain order on the
+// gradients' lines (where two times stand, us before / so):
+//   - Gradients off their lines, each buffer at another position or fewer than 4: in runs at any size (rows of one buffer, 16-byte positions, bf16 p = 6
+//     105 M elements 342 / 320, p = 24 45 MB .99, 90 MB 1.07, 1.1 GB 1.07, p = 48 45 MB 1.21; f32 p = 8 90 MB 1.05, 600 MB 1.10; p = 2
+//     90 MB 1.07, 1.1 GB 1.03).  At odd positions 1.00 to 1.13.
+//   - Gradients on lines, accumulator not: on the accumulator's lines and in runs, so that the gradients' shared lines are
+//     found in the L2 and no accumulator's line is written in parts (bf16 p = 4 300 MB 1.08, 2.2 GB 1.08, p = 8 600 MB 1.05, 2.2 GB 1.08, p = 16 600 MB 1.07, 1.1 GB
+//     .97; f32 p = 4 600 MB 1.00, p = 16 600 MB 1.08, 2.2 GB .96; bf16 p = 24 .98 to 1.02, p = 96 45 MB .94).  Not in runs this
+//     loses 1 to 20 %, and runs alone lose 3 to 14 % with few buffers, whose accumulator is most of the traffic.
+//   - Everything on lines, or many buffers: in runs in the middle of the range (bf16 p = 2 45 MB 1.00, 90 MB 1.05, 600 MB 1.03, 2.2 GB 1.00; p = 16 90 MB
+//     1.03, 300 MB 1.05, 1.1 GB .96; p = 24 300 MB 1.06, 1.1 GB .99; f32 p = 12 150 MB 1.06, 600 MB .98, 2.2 GB .88; first micro-steps p = 6 600 MB
+//     .97, p = 16 300 MB 1.05).
+//   - Segments, whose ends lie anywhere: p = 4 to 31 as in the second case at any size (bf16 p = 8 400 MB 1.09, p = 16 45 MB 1.10, 200 MB
+//     1.00, 800 MB 1.06; f32 p = 8 45 MB 1.04, 400 MB .99), from 32 on in runs only (bf16 p = 32 400 MB 1.14; p = 64 1.00), up to 3 only below
+//     64 MB (bf16 p = 2 45 MB 1.07, 400 MB .93; f32 400 MB .90), float32 below 1 GB (p = 16 2 GB .93).
+struct ReduceOrder {
+    bool in_runs, acc_lines;
+};
+ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, bool grads_on_lines, bool acc_on_lines, bool alignable)
+{
+    const size_t mb = count * ((size_t)p * elem_bytes + (accumulate ? 8 : 4)) >> 20;
+    const bool two = elem_bytes == 2;
+    if (!grads_on_lines || (p < 4 && !acc_on_lines)) return {true, false};
+    if (!acc_on_lines && p <= 16) {
+        const bool gains = two && p <= 8 ? mb >= 60 : mb >= 20 && mb < 700;
+        if (alignable && gains) return {true, true};
+        if (p < 12) return {false, false};
+    }
+    const bool few = accumulate ? !two && p < 8 : p < 12;
+    return {!few && mb >= (two ? 80 : 120) && mb < (two && accumulate ? 700 : 500), false};
+}
+ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb)
+{
+    if (p < 4) return {mb < 64, false};
+    const bool gains = elem_bytes == 2 || mb < 1000;
+    return {gains && p < 48, gains && p < 32};
+}
+
 // Small messages on large groups take the one-dword-per-lane kernels (VEC = 1; of a coalesced call all its segments
 // together), MB of gradients up to which they win.  us per call, one dword / 128 bits per lane:
 //   bf16, p = 20 5 MB 3.4 / 3.9, 19 MB 6.0 / 6.0, 32 MB 8.9 / 8.2      p = 32 13 MB 4.3 / 4.7, 24 MB 6.4 / 6.3
@@ -1785,7 +1872,7 @@ template <int KIND>
 int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate, hipStream_t st)
 {
     unsigned line = 0;
-    const unsigned lead = align_gradient_pointers(g, p, GradFormat<KIND>::kElemBytes, &line);
+    unsigned lead = align_gradient_pointers(g, p, GradFormat<KIND>::kElemBytes, &line);
     constexpr size_t PD = GradFormat<KIND>::kPerDword;
     unsigned blocks = 0;
     // small message on a large group: one dword per lane and buffer
@@ -1799,13 +1886,23 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     }
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
+    const uintptr_t first = (uintptr_t)g.ptr[0] + lead * GB;
+    const int other = lead_on_accumulator_lines(acc, first, GB);
+    const ReduceOrder order = reduce_order(p, GB, count, accumulate, line == 128 || on_lines(g, p),
+                                           ((uintptr_t)acc - 4 * (uintptr_t)lead) % 128 == 0, other >= 0);
+    if (order.acc_lines) {
+        for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] + ((ptrdiff_t)lead - other) * GB;
+        pad_table(g, p);
+        lead = (unsigned)other;
+        line = 16;
+    }
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, false, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
-    const int how = accum_policy(count, p, GB);
+    const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     return dispatch_bool(accumulate, [&](auto A) {
-        return dispatch_bool(how == kAccCached, [&](auto C) {
+        return dispatch_bool(policy == kAccCached, [&](auto C) {
             return dispatch_group(p, [&](auto P) {
                 return rsa_launch<KIND, 4, P.value, A.value, C.value>(acc, g, p, lead, count, blocks, sh, how, st);
             });
@@ -1966,11 +2063,24 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
 
 namespace {
 
+// Virtual index of the first element of a segment that is element `src` of the rounded-down buffers.
+template <int KIND>
+unsigned segment_lead(const float* acc, const PtrTable& g, size_t src, size_t dst, size_t unit, ReduceOrder order)
+{
+    constexpr size_t GB = GradFormat<KIND>::kElemBytes;
+    if (order.acc_lines && unit * GB == 128) {
+        const int lead = lead_on_accumulator_lines(acc + dst, (uintptr_t)g.ptr[0] + src * GB, GB);
+        if (lead >= 0) return (unsigned)lead;
+    }
+    return (unsigned)(src % unit);
+}
+
 // `n` segments in one launch, with lanes of VEC dwords.
 template <int KIND, int VEC, int SEGS>
 int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit, const Segment* segs, int n, int p,
-                    bool accumulate, const Shape& sh, int how, hipStream_t st)
+                    bool accumulate, const Shape& sh, int policy, ReduceOrder order, hipStream_t st)
 {
+    const int how = policy | (order.in_runs ? kInRuns : 0);
     constexpr size_t EPL = VEC * GradFormat<KIND>::kPerDword;
     ReduceTable<SEGS> tab;
     const size_t tile_elems = (size_t)sh.lanes * EPL;
@@ -1980,7 +2090,7 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
         // position of the segment's first element in the rounded-down buffers; its virtual
         // element 0 is the one on a line (of 128, 16 or 4 bytes: see align_gradient_pointers) at or below it
         const size_t src = sg.src_offset + base_lead;
-        const unsigned lead = (unsigned)(src % unit);
+        const unsigned lead = segment_lead<KIND>(acc, g, src, sg.dst_offset, unit, order);
         tab.tile_begin[t] = (unsigned)tiles;
         tab.seg[t].lead = lead;
         tab.seg[t].pad = 0;
@@ -2006,7 +2116,7 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
         if constexpr (VEC == 1) {
             return run(std::integral_constant<int, 0>{}, A, std::true_type{});
         } else {
-            return dispatch_bool(how == kAccCached, [&](auto C) {
+            return dispatch_bool(policy == kAccCached, [&](auto C) {
                 return dispatch_group(p, [&](auto P) { return run(P, A, C); });
             });
         }
@@ -2034,17 +2144,18 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         if (narrow) {
             nt = n - first < kMaxSegMany ? n - first : kMaxSegMany;
             const Shape sh = {kNarrowBlock, 0};
-            err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st)
-                           : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, st);
+            err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st)
+                           : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st);
         } else {
+            const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20);
             bool acc16 = true;
             for (int t = 0; t < nt; ++t) {
-                const size_t lead = (segs[first + t].src_offset + base_lead) % unit;
+                const size_t lead = segment_lead<KIND>(acc, g, segs[first + t].src_offset + base_lead, segs[first + t].dst_offset, unit, order);
                 acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
             }
             const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
             err = reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh,
-                                               accum_policy(elements, p, (int)GB), st);
+                                               accum_policy(elements, p, (int)GB), order, st);
         }
         if (err) return err;
     }

@@ -359,3 +359,46 @@ def test_gather_of_tensors_of_two_kinds(orc, gen, p, k, n_tensors, kinds):
     mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, 2)
     torch.cuda.synchronize()
     assert np.array_equal(dst.numpy(), want) and dst.guards_intact()
+
+
+@pytest.mark.parametrize("name,p,count", [
+    ("bf16", 2, 66_003), ("f32", 3, 40_001), ("f16", 6, 131_077), ("bf16", 8, 2_700_011), ("f16", 16, 560_003), ("f32", 5, 1_000_003),
+    ("bf16", 24, 1_600_007), ("f32", 32, 70_001), ("f32", 32, 300_017), ("f16", 32, 300_017)])
+@pytest.mark.parametrize("skews", [[0], [0, 8, 16], [3, 0, 5]])
+def test_reduce_in_runs_of_tiles(orc, gen, name, p, count, skews):
+    """Calls of more than a round of workgroups, whose tiles are dealt to the XCDs in runs: buffers at one position and at
+    several inside their lines, vectors on the gradients' lines and on the accumulator's; the last round is partial."""
+    code = FORMATS[name][0]
+    host, dev = rank_buffers(gen, name, p, count + 40, skews)
+    for offset, acc_skew in ((0, 0), (24, 0), (24, 8), (5, 1)):
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, count, skew=acc_skew)
+            mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], offset, count, accumulate, code)
+            orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), (offset, acc_skew, accumulate)
+
+
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [2, 4, 16, 24, 32])
+@pytest.mark.parametrize("threshold", [0, 1])
+def test_reduce_segments_in_runs_of_tiles(orc, gen, name, p, threshold):
+    """Segments whose vectors lie on the accumulator's lines where the gradients then are on 16 bytes, the first of them
+    at the very start of the buffers, others where they are not; more than a round of workgroups."""
+    code = FORMATS[name][0]
+    segs, src, dst = [], 0, 24
+    for n, gap in ((60_000, 0), (8, 8), (33_000, 24), (4_097, 1), (50_003, 3), (640, 16)):
+        src += gap
+        segs.append((n, 0, src, dst))
+        src, dst = src + n, dst + n
+    host, dev = rank_buffers(gen, name, p, src, [0])
+    try:
+        mics.mics_set_stream_threshold_bytes(threshold)
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, dst)
+            mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+            orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), accumulate
+    finally:
+        mics.mics_set_stream_threshold_bytes(0)
