@@ -142,6 +142,24 @@ def _stream(stream) -> Optional[int]:
     return stream.cuda_stream or None
 
 
+# Whole calls with plain arguments go past ctypes (csrc/marshal.cpp); what these functions answer with None, and the
+# message of an error, goes through it.
+_marshal.bind(tuple(ctypes.cast(getattr(lib, "mics_" + name), _vp).value for name in (
+    "hier_gather_reorder", "hier_gather_reorder_coalesced", "reduce_scatter_accum", "reduce_scatter_accum_typed",
+    "reduce_scatter_accum_coalesced", "reduce_scatter_accum_coalesced_typed", "replica_average", "adam_shard",
+    "adam_shard_typed", "replica_average_adam_shard", "replica_average_adam_shard_typed")),
+    _device, _raw_stream)
+
+
+def _done(rc) -> bool:
+    """True after a call that went past ctypes; raises its error."""
+    if rc is None:
+        return False
+    if rc:
+        _check(rc)
+    return True
+
+
 def mics_version() -> int:
     return lib.mics_version()
 
@@ -172,6 +190,8 @@ def mics_set_launch_shape(kernel_family: int, lanes: int = 0, waves_per_cu: int 
 def mics_hier_gather_reorder(dst_flat, stage1_bufs: Sequence, n_valid: int, shard_elems: int,
                              p: int, k: int, elem_bytes: int, stream=None) -> None:
     """Stage-1 buffers of the hierarchical all-gather -> contiguous flat parameter."""
+    if _done(_marshal.gather(dst_flat, stage1_bufs, n_valid, shard_elems, p, k, elem_bytes, stream)):
+        return
     if len(stage1_bufs) != k:
         raise ValueError(f"expected k = {k} stage-1 buffers, got {len(stage1_bufs)}")
     _check(lib.mics_hier_gather_reorder(_dev_ptr(dst_flat), _table(stage1_bufs), n_valid,
@@ -181,12 +201,16 @@ def mics_hier_gather_reorder(dst_flat, stage1_bufs: Sequence, n_valid: int, shar
 def mics_reduce_scatter_accum(acc, grads_bf16: Sequence, elem_offset: int, count: int,
                               accumulate: bool, stream=None) -> None:
     """acc[0:count] (+)= sum over the p rank buffers of elements [elem_offset, +count)."""
+    if _done(_marshal.reduce(acc, grads_bf16, elem_offset, count, accumulate, stream)):
+        return
     _check(lib.mics_reduce_scatter_accum(_dev_ptr(acc), _table(grads_bf16), elem_offset, count,
                                          len(grads_bf16), int(bool(accumulate)), _stream(stream)))
 
 
 def mics_replica_average(out, acc_copies: Sequence, count: int, scale: float, stream=None) -> None:
     """out = (sum over the r replica copies) * scale."""
+    if _done(_marshal.average(out, acc_copies, count, scale, stream)):
+        return
     _check(lib.mics_replica_average(_dev_ptr(out), _table(acc_copies), count, len(acc_copies),
                                     scale, _stream(stream)))
 
@@ -195,6 +219,8 @@ def mics_adam_shard(master, exp_avg, exp_avg_sq, param_bf16, grad, count: int, *
                     beta1: float, beta2: float, eps: float, weight_decay: float, step: int,
                     stream=None) -> None:
     """Mixed-precision Adam step in place on the fp32 shard; writes the bf16 parameter."""
+    if _done(_marshal.adam(master, exp_avg, exp_avg_sq, param_bf16, grad, count, lr, beta1, beta2, eps, weight_decay, step, stream)):
+        return
     _check(lib.mics_adam_shard(_dev_ptr(master), _dev_ptr(exp_avg), _dev_ptr(exp_avg_sq),
                                _dev_ptr(param_bf16), _dev_ptr(grad), count, lr, beta1, beta2, eps,
                                weight_decay, step, _stream(stream)))
@@ -204,6 +230,8 @@ def mics_hier_gather_reorder_coalesced(dst_flat, stage1_bufs: Sequence, segs, p:
                                        elem_bytes: int, stream=None) -> None:
     """The gather reorder for many separately sharded tensors in one call; ``segs`` holds
     (numel, shard_elems, src_offset, dst_offset) per tensor."""
+    if _done(_marshal.gather_coalesced(dst_flat, stage1_bufs, segs, p, k, elem_bytes, stream)):
+        return
     if len(stage1_bufs) != k:
         raise ValueError(f"expected k = {k} stage-1 buffers, got {len(stage1_bufs)}")
     arr = segs if isinstance(segs, ctypes.Array) else _segments(segs)
@@ -215,6 +243,8 @@ def mics_reduce_scatter_accum_coalesced(acc, grads_bf16: Sequence, segs, accumul
                                         stream=None) -> None:
     """Reduce-scatter-accumulate for many tensors in one call; ``segs`` holds
     (count, 0, src_offset, dst_offset) per tensor."""
+    if _done(_marshal.reduce_coalesced(acc, grads_bf16, segs, accumulate, stream)):
+        return
     arr = segs if isinstance(segs, ctypes.Array) else _segments(segs)
     _check(lib.mics_reduce_scatter_accum_coalesced(_dev_ptr(acc), _table(grads_bf16), arr, len(arr),
                                                    len(grads_bf16), int(bool(accumulate)),
@@ -225,6 +255,9 @@ def mics_replica_average_adam_shard(master, exp_avg, exp_avg_sq, param_bf16, acc
                                     count: int, scale: float, *, lr: float, beta1: float, beta2: float,
                                     eps: float, weight_decay: float, step: int, stream=None) -> None:
     """Replica average and Adam step in one pass; same results as the two separate calls."""
+    if _done(_marshal.update(master, exp_avg, exp_avg_sq, param_bf16, acc_copies, count, scale, lr, beta1, beta2, eps, weight_decay,
+                             step, stream)):
+        return
     _check(lib.mics_replica_average_adam_shard(
         _dev_ptr(master), _dev_ptr(exp_avg), _dev_ptr(exp_avg_sq), _dev_ptr(param_bf16),
         _table(acc_copies), count, len(acc_copies), scale, lr, beta1, beta2, eps, weight_decay, step,
@@ -234,6 +267,8 @@ def mics_replica_average_adam_shard(master, exp_avg, exp_avg_sq, param_bf16, acc
 def mics_reduce_scatter_accum_coalesced_typed(acc, grads: Sequence, segs, accumulate: bool, grad_dtype: int,
                                               stream=None) -> None:
     """mics_reduce_scatter_accum_coalesced for bf16 / fp16 / fp32 gradient buffers (MICS_DTYPE_*)."""
+    if _done(_marshal.reduce_coalesced_typed(acc, grads, segs, accumulate, grad_dtype, stream)):
+        return
     arr = segs if isinstance(segs, ctypes.Array) else _segments(segs)
     _check(lib.mics_reduce_scatter_accum_coalesced_typed(_dev_ptr(acc), _table(grads), arr, len(arr), len(grads),
                                                          int(bool(accumulate)), grad_dtype, _stream(stream)))
@@ -243,6 +278,9 @@ def mics_adam_shard_typed(master, exp_avg, exp_avg_sq, param_out, param_dtype: i
                           lr: float, beta1: float, beta2: float, eps: float, weight_decay: float, step: int,
                           stream=None) -> None:
     """mics_adam_shard writing the 16-bit parameter as bf16 or binary16 (MICS_DTYPE_*)."""
+    if _done(_marshal.adam_typed(master, exp_avg, exp_avg_sq, param_out, param_dtype, grad, count, lr, beta1, beta2, eps, weight_decay,
+                                 step, stream)):
+        return
     _check(lib.mics_adam_shard_typed(_dev_ptr(master), _dev_ptr(exp_avg), _dev_ptr(exp_avg_sq),
                                      _dev_ptr(param_out), param_dtype, _dev_ptr(grad), count, lr, beta1, beta2,
                                      eps, weight_decay, step, _stream(stream)))
@@ -253,6 +291,9 @@ def mics_replica_average_adam_shard_typed(master, exp_avg, exp_avg_sq, param_out
                                           beta1: float, beta2: float, eps: float, weight_decay: float,
                                           step: int, stream=None) -> None:
     """mics_replica_average_adam_shard writing the 16-bit parameter as bf16 or binary16."""
+    if _done(_marshal.update_typed(master, exp_avg, exp_avg_sq, param_out, param_dtype, acc_copies, count, scale, lr, beta1, beta2, eps,
+                                   weight_decay, step, stream)):
+        return
     _check(lib.mics_replica_average_adam_shard_typed(
         _dev_ptr(master), _dev_ptr(exp_avg), _dev_ptr(exp_avg_sq), _dev_ptr(param_out), param_dtype,
         _table(acc_copies), count, len(acc_copies), scale, lr, beta1, beta2, eps, weight_decay, step,
@@ -262,6 +303,8 @@ def mics_replica_average_adam_shard_typed(master, exp_avg, exp_avg_sq, param_out
 def mics_reduce_scatter_accum_typed(acc, grads: Sequence, elem_offset: int, count: int,
                                     accumulate: bool, grad_dtype: int, stream=None) -> None:
     """mics_reduce_scatter_accum for bf16 / fp16 / fp32 gradient buffers (MICS_DTYPE_*)."""
+    if _done(_marshal.reduce_typed(acc, grads, elem_offset, count, accumulate, grad_dtype, stream)):
+        return
     _check(lib.mics_reduce_scatter_accum_typed(_dev_ptr(acc), _table(grads), elem_offset, count,
                                                len(grads), int(bool(accumulate)), grad_dtype,
                                                _stream(stream)))

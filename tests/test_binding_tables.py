@@ -3,6 +3,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import types
 
 import numpy as np
 import pytest
@@ -142,3 +143,80 @@ def test_an_item_that_leaves_its_list_while_it_is_read():
     res = subprocess.run([sys.executable, "-c", DROPPED], cwd=root, env=dict(os.environ, PYTHONMALLOC="debug"),
                          capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+T = [torch.zeros(8) for _ in range(6)]
+HYPER = dict(lr=0.5, beta1=0.25, beta2=0.125, eps=1e-3, weight_decay=0.75, step=7)
+SEGS = [(5, 6, 7, 8), (1, 2), (2 ** 40, 0, -1, 3)]
+CALLS = {
+    "gather": ("hier_gather_reorder", (T[0], T[1:3], 11, 12, 4, 2, 2), {}),
+    "gather_coalesced": ("hier_gather_reorder_coalesced", (T[0], (T[1], 4096), SEGS, 4, 2, 4), {}),
+    "reduce": ("reduce_scatter_accum", (T[0], T, 3, 4, True), {}),
+    "reduce_typed": ("reduce_scatter_accum_typed", (T[0], T[2:], 3, -1, 0, 2), {}),
+    "reduce_coalesced": ("reduce_scatter_accum_coalesced", (None, T, tuple(SEGS), 5), {}),
+    "reduce_coalesced_typed": ("reduce_scatter_accum_coalesced_typed", (T[0], [None, 16], [], False, 1), {}),
+    "average": ("replica_average", (T[3], [T[1]] * 128, 9, 0.1), {}),
+    "adam": ("adam_shard", (T[0], T[1], T[2], T[3], T[4], 21), HYPER),
+    "adam_typed": ("adam_shard_typed", (T[0], T[1], T[2], None, 1, T[4], 2 ** 64 + 21), HYPER),
+    "update": ("replica_average_adam_shard", (T[0], T[1], T[2], T[3], T[4:], 21, 1e300), HYPER),
+    "update_typed": ("replica_average_adam_shard_typed", (T[0], T[1], T[2], T[3], 2 ** 32 + 1, T[4:], 21, 3e-42), HYPER),
+}
+LIKE = {"as it is": lambda x: x, "numpy's integers": lambda x: np.int64(x) if type(x) is int and abs(x) < 2 ** 40 else x,
+        "whole numbers": lambda x: int(x) if type(x) is float and x < 1e6 else x,
+        "tuples": lambda x: tuple(x) if type(x) is list else x, "parameters": lambda x: torch.nn.Parameter(x) if x is T[0] else x,
+        "not contiguous": lambda x: BASE.t() if x is T[0] else x, "text": lambda x: "7" if type(x) is int else x,
+        "too many": lambda x: x * 65 if type(x) is list and len(x) in (2, 3) else x}
+
+
+@pytest.mark.parametrize("like", list(LIKE))
+@pytest.mark.parametrize("call", list(CALLS))
+def test_whole_calls_hand_over_what_ctypes_does(monkeypatch, call, like):
+    """Both ways with the library's entry point replaced by one that records its arguments."""
+    name, args, kwargs = CALLS[call]
+    args, kwargs = [LIKE[like](x) for x in args], {k: LIKE[like](x) for k, x in kwargs.items()}
+    real, seen = getattr(mics.lib, "mics_" + name), []
+
+    def record(*got):
+        got = list(got)
+        ints = [x for x in args if isinstance(x, (list, tuple))]
+        for i, kind in enumerate(real.argtypes):
+            if kind is ctypes.POINTER(mics.mics_segment):
+                got[i] = [tuple(getattr(got[i][t], f) for f, _ in mics.mics_segment._fields_) for t in range(len(ints[1]))]
+            elif i == TABLE[name]:
+                got[i] = list((ctypes.c_void_p * len(ints[0])).from_address(got[i]))
+        seen.append(got)
+        return 0
+
+    stub = ctypes.CFUNCTYPE(ctypes.c_int, *real.argtypes)(record)
+    entries = ["mics_" + n for n in ENTRIES]
+    addresses = [ctypes.cast(getattr(mics.lib, n), ctypes.c_void_p).value for n in entries]
+    at = entries.index("mics_" + name)
+    fake = addresses[:at] + [ctypes.cast(stub, ctypes.c_void_p).value] + addresses[at + 1:]
+
+    def outcome():
+        try:
+            return getattr(mics, "mics_" + name)(*args, stream=64, **kwargs), seen.pop()
+        except Exception as e:                                      # noqa: BLE001
+            return type(e), str(e)
+
+    mics._marshal.bind(tuple(fake), mics._device, mics._raw_stream)
+    monkeypatch.setattr(mics, "lib", types.SimpleNamespace(**{"mics_" + name: stub}))
+    try:
+        fast = outcome()
+        asked = getattr(mics._marshal, call)
+        monkeypatch.setattr(mics, "_marshal", types.SimpleNamespace(**{**vars(mics._marshal), call: lambda *a: None}))
+        assert fast == outcome()
+        if like == "as it is":
+            positional = [*args, *[kwargs[k] for k in ("lr", "beta1", "beta2", "eps", "weight_decay", "step") if k in kwargs], 64]
+            assert asked(*positional) == 0                          # this one does go past ctypes
+    finally:
+        monkeypatch.undo()
+        mics._marshal.bind(tuple(addresses), mics._device, mics._raw_stream)
+
+
+ENTRIES = ("hier_gather_reorder", "hier_gather_reorder_coalesced", "reduce_scatter_accum", "reduce_scatter_accum_typed",
+           "reduce_scatter_accum_coalesced", "reduce_scatter_accum_coalesced_typed", "replica_average", "adam_shard",
+           "adam_shard_typed", "replica_average_adam_shard", "replica_average_adam_shard_typed")
+TABLE = dict(hier_gather_reorder=1, hier_gather_reorder_coalesced=1, reduce_scatter_accum=1, reduce_scatter_accum_typed=1,
+             reduce_scatter_accum_coalesced=1, reduce_scatter_accum_coalesced_typed=1, replica_average=1, adam_shard=None,
+             adam_shard_typed=None, replica_average_adam_shard=4, replica_average_adam_shard_typed=5)
