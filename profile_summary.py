@@ -75,7 +75,7 @@ def algorithmic_bytes(name: str, cfg, count: int, N: int, pb: int):
         return count * (gb * p + (8 if a[3] else 4))
     if name.startswith("rsa_seg_kernel"):
         gb = 4 if a[0] == 2 else 2
-        return count * (gb * p + (8 if a[2] else 4))
+        return count * (gb * p + (8 if a[3] else 4))
     if name.startswith("avg_kernel"):
         return count * (4 * r + 4)
     if name.startswith("adam_kernel"):
