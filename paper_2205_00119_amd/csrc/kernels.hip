@@ -2115,6 +2115,8 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
     return dispatch_bool(accumulate, [&](auto A) {
         if constexpr (VEC == 1) {
             return run(std::integral_constant<int, 0>{}, A, std::true_type{});
+        } else if constexpr (SEGS > 64) {
+            return dispatch_group(p, [&](auto P) { return run(P, A, std::true_type{}); });
         } else {
             return dispatch_bool(policy == kAccCached, [&](auto C) {
                 return dispatch_group(p, [&](auto P) { return run(P, A, C); });
@@ -2137,16 +2139,22 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     for (int t = 0; t < n; ++t) all += segs[t].numel;
     const bool narrow = narrow_call(p, GB, all, line >= 16);
     for (int first = 0, nt; first < n; first += nt) {
-        nt = n - first < 64 ? n - first : 64;
         size_t elements = 0;
-        for (int t = 0; t < nt; ++t) elements += segs[first + t].numel;
+        auto take = [&](int most) {
+            nt = n - first < most ? n - first : most;
+            elements = 0;
+            for (int t = 0; t < nt; ++t) elements += segs[first + t].numel;
+        };
+        // Small calls carry more than 64 segments, whose records then come in a second round: us, 64 / 96 per launch, f16, p = 12,
+        // 79 segments 7.3 / 4.0; larger ones keep to 64 and to half as many kernels.
+        take(kMaxSegMany);
         int err;
         if (narrow) {
-            nt = n - first < kMaxSegMany ? n - first : kMaxSegMany;
             const Shape sh = {kNarrowBlock, 0};
             err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st)
                            : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st);
         } else {
+            if (nt > 64 && accum_policy(elements, p, (int)GB) != kAccCached) take(64);
             const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20);
             bool acc16 = true;
             for (int t = 0; t < nt; ++t) {
@@ -2154,8 +2162,9 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
                 acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
             }
             const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
-            err = reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh,
-                                               accum_policy(elements, p, (int)GB), order, st);
+            const int policy = accum_policy(elements, p, (int)GB);
+            err = nt <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, policy, order, st)
+                           : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, policy, order, st);
         }
         if (err) return err;
     }
