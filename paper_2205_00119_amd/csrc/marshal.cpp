@@ -261,25 +261,28 @@ class Call {
         }
         return segs;
     }
-    // None: the current stream of the current device.  After everything else: this runs torch's Python code.
+    // None: the current stream of the current device.  After everything else: this runs torch's Python code, whose
+    // exceptions (an interrupt may arrive in it) are the call's.
     void* stream(int i)
     {
         if (!plain) return nullptr;
         if (PyLong_CheckExact(a[i])) return (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(a[i]);
         void* got = nullptr;
         plain = a[i] == Py_None && device_of_thread;
-        PyObject* dev = plain ? PyObject_CallNoArgs(device_of_thread) : nullptr;
+        if (!plain) return nullptr;
+        PyObject* dev = PyObject_CallNoArgs(device_of_thread);
         PyObject* raw = dev ? PyObject_CallOneArg(raw_stream, dev) : nullptr;
+        raised = !raw;
         plain = raw && PyLong_CheckExact(raw);
         if (plain) got = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(raw);
         Py_XDECREF(raw);
         Py_XDECREF(dev);
-        PyErr_Clear();
         return got;
     }
     template <typename F>
     PyObject* run(F&& f)
     {
+        if (raised) return nullptr;
         if (!plain) Py_RETURN_NONE;
         int rc;
         Py_BEGIN_ALLOW_THREADS
@@ -287,12 +290,13 @@ class Call {
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(rc);
     }
+    void expect_entries(int k) { plain = plain && entries == k; }
     int entries = 0, n_segments = 0;
 
   private:
     static constexpr int kMaxSegments = 128;
     PyObject* const* a;
-    bool plain;
+    bool plain, raised = false;
     void* pointers[MICS_MAX_GROUP];
     mics_segment segs[kMaxSegments];
 
@@ -323,8 +327,8 @@ MICS_CALL(gather)
     const auto bufs = c.table<void>(1);
     const size_t n_valid = c.size(2), shard = c.size(3);
     const int p = c.num(4), k = c.num(5), eb = c.num(6);
+    c.expect_entries(k);
     void* st = c.stream(7);
-    if (c.entries != k) Py_RETURN_NONE;
     return c.run([&] { return lib.hier_gather_reorder(dst, bufs, n_valid, shard, p, k, eb, st); });
 }
 
@@ -335,8 +339,8 @@ MICS_CALL(gather_coalesced)
     const auto bufs = c.table<void>(1);
     const auto segs = c.segments(2);
     const int p = c.num(3), k = c.num(4), eb = c.num(5);
+    c.expect_entries(k);
     void* st = c.stream(6);
-    if (c.entries != k) Py_RETURN_NONE;
     return c.run([&] { return lib.hier_gather_reorder_coalesced(dst, bufs, segs, c.n_segments, p, k, eb, st); });
 }
 

@@ -220,3 +220,32 @@ ENTRIES = ("hier_gather_reorder", "hier_gather_reorder_coalesced", "reduce_scatt
 TABLE = dict(hier_gather_reorder=1, hier_gather_reorder_coalesced=1, reduce_scatter_accum=1, reduce_scatter_accum_typed=1,
              reduce_scatter_accum_coalesced=1, reduce_scatter_accum_coalesced_typed=1, replica_average=1, adam_shard=None,
              adam_shard_typed=None, replica_average_adam_shard=4, replica_average_adam_shard_typed=5)
+
+
+def bound(device, raw_stream, entry=None):
+    """Binds the entry points with other callables for the current stream, every entry point being `entry` if given."""
+    addresses = [ctypes.cast(entry or getattr(mics.lib, "mics_" + n), ctypes.c_void_p).value for n in ENTRIES]
+    mics._marshal.bind(tuple(addresses), device, raw_stream)
+
+
+def positional(call, stream):
+    args, kwargs = CALLS[call][1:]
+    return [*args, *[kwargs[k] for k in ("lr", "beta1", "beta2", "eps", "weight_decay", "step") if k in kwargs], stream]
+
+
+@pytest.mark.parametrize("where", ["device", "raw stream"])
+@pytest.mark.parametrize("call", list(CALLS))
+def test_an_interrupt_while_the_current_stream_is_asked_for(call, where):
+    """Signals are handled in the Python code that names the current stream: what they raise leaves the call, nothing runs."""
+    def interrupted(*_):
+        raise KeyboardInterrupt("now")
+
+    ran = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: ran.append(1) or 0)
+    try:
+        bound(interrupted if where == "device" else (lambda: 0), interrupted, entry)
+        with pytest.raises(KeyboardInterrupt, match="now"):
+            getattr(mics._marshal, call)(*positional(call, None))
+        assert not ran
+    finally:
+        bound(mics._device, mics._raw_stream)
