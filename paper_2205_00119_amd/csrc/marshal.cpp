@@ -290,7 +290,13 @@ class Call {
         Py_END_ALLOW_THREADS
         return PyLong_FromLong(rc);
     }
-    void expect_entries(int k) { plain = plain && entries == k; }
+    // The table's number of entries, which argument i has to state exactly (num() would cut it to 32 bits).
+    int entries_as(int i)
+    {
+        int overflow;                                      // the value is -1 then
+        plain = plain && PyLong_CheckExact(a[i]) && PyLong_AsLongAndOverflow(a[i], &overflow) == entries;
+        return entries;
+    }
     int entries = 0, n_segments = 0;
 
   private:
@@ -326,8 +332,7 @@ MICS_CALL(gather)
     void* dst = c.ptr(0);
     const auto bufs = c.table<void>(1);
     const size_t n_valid = c.size(2), shard = c.size(3);
-    const int p = c.num(4), k = c.num(5), eb = c.num(6);
-    c.expect_entries(k);
+    const int p = c.num(4), k = c.entries_as(5), eb = c.num(6);
     void* st = c.stream(7);
     return c.run([&] { return lib.hier_gather_reorder(dst, bufs, n_valid, shard, p, k, eb, st); });
 }
@@ -338,8 +343,7 @@ MICS_CALL(gather_coalesced)
     void* dst = c.ptr(0);
     const auto bufs = c.table<void>(1);
     const auto segs = c.segments(2);
-    const int p = c.num(3), k = c.num(4), eb = c.num(5);
-    c.expect_entries(k);
+    const int p = c.num(3), k = c.entries_as(4), eb = c.num(5);
     void* st = c.stream(6);
     return c.run([&] { return lib.hier_gather_reorder_coalesced(dst, bufs, segs, c.n_segments, p, k, eb, st); });
 }

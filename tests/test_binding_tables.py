@@ -249,3 +249,22 @@ def test_an_interrupt_while_the_current_stream_is_asked_for(call, where):
         assert not ran
     finally:
         bound(mics._device, mics._raw_stream)
+
+
+@pytest.mark.parametrize("k", [1, 3, 2 ** 32 + 2, 2 ** 64 + 2, 2 - 2 ** 32, 2 - 2 ** 64])
+@pytest.mark.parametrize("call", ["gather", "gather_coalesced"])
+def test_the_number_of_stage1_buffers_is_compared_as_it_is(call, k):
+    """Two buffers and a k that is not 2, also one that is 2 in its low 32 or 64 bits."""
+    name, args, _ = CALLS[call]
+    at = 5 if call == "gather" else 4
+    assert args[at] == 2
+    wrong = [*args[:at], k, *args[at + 1:]]
+    ran = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: ran.append(1) or 0)
+    try:
+        bound(mics._device, mics._raw_stream, entry)
+        with pytest.raises(ValueError, match=f"expected k = {k} stage-1 buffers, got 2"):
+            getattr(mics, "mics_" + name)(*wrong, stream=64)
+        assert not ran
+    finally:
+        bound(mics._device, mics._raw_stream)
