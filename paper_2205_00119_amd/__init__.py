@@ -149,6 +149,7 @@ _marshal.bind(tuple(ctypes.cast(getattr(lib, "mics_" + name), _vp).value for nam
     "reduce_scatter_accum_coalesced", "reduce_scatter_accum_coalesced_typed", "replica_average", "adam_shard",
     "adam_shard_typed", "replica_average_adam_shard", "replica_average_adam_shard_typed")),
     _device, _raw_stream)
+_marshal.bind_segment(mics_segment)
 
 
 def _done(rc) -> bool:

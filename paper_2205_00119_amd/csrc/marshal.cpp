@@ -3,12 +3,12 @@
 // of 64 gradient buffers) took twice as long as the kernel of an 8 MB reduction.
 //
 // Whole calls as well: the functions from `gather` on take the arguments of a Python entry point that are of the plain
-// kinds (tensors, ints, floats, lists and tuples of them), make the tables on the stack and call the library without ctypes:
-// us per call from Python, ctypes / so: gather 1 MB 5.4 / 4.6, reduction of 64 buffers, 8 MB 5.7 / 4.9, of 76 segments 8.0 / 6.1,
-// Adam 5.9 / 5.1; the launch itself is 2.5 to 4 of them.
+// kinds (tensors, numbers, torch streams, lists and tuples of them, ctypes arrays of segments), make the tables on the
+// stack and call the library without ctypes: us per call from Python, ctypes / so: gather 1 MB 5.4 / 4.6, reduction of 64
+// buffers, 8 MB 5.7 / 4.9, of 76 segments 8.0 / 6.1, Adam 5.9 / 5.1; the launch itself is 2.5 to 4 of them.
 // Whatever they do not know they leave alone and return None; the entry point then goes through ctypes.
 //
-// No state but the addresses that bind() sets at import.  Everything is called with the GIL held, which is given up
+// No state but what bind() and bind_segment() set at import.  Everything is called with the GIL held, which is given up
 // while the library works; nothing outlives the call.
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -187,7 +187,8 @@ struct {
     decltype(&mics_replica_average_adam_shard_typed) replica_average_adam_shard_typed;
 } lib;
 constexpr Py_ssize_t kEntries = sizeof lib / sizeof(void*);
-PyObject *device_of_thread, *raw_stream;
+PyObject *device_of_thread, *raw_stream, *segment_type;
+PyObject *stream_attr, *item_attr;                 // "cuda_stream", "_type_"
 
 // bind(addresses in the order above, current device, raw stream of a device)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n)
@@ -201,6 +202,9 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n)
         at[i] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(args[0], i));
         if (!at[i] && PyErr_Occurred()) return nullptr;
     }
+    if (!stream_attr) stream_attr = PyUnicode_InternFromString("cuda_stream");
+    if (!item_attr) item_attr = PyUnicode_InternFromString("_type_");
+    if (!stream_attr || !item_attr) return nullptr;
     std::memcpy((void*)&lib, at, sizeof at);
     Py_INCREF(args[1]);
     Py_INCREF(args[2]);
@@ -209,33 +213,45 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n)
     Py_RETURN_NONE;
 }
 
+// bind_segment(mics_segment, the ctypes structure)
+PyObject* bind_segment(PyObject*, PyObject* type)
+{
+    Py_INCREF(type);
+    Py_XSETREF(segment_type, type);
+    Py_RETURN_NONE;
+}
+
 // The arguments of one call.  `plain` turns false at the first that is not of a plain kind; no Python code of an
-// argument runs, so the lists cannot change meanwhile.
+// argument runs before the stream's, so the lists cannot change meanwhile.
 class Call {
   public:
-    Call(PyObject* const* args, Py_ssize_t n, Py_ssize_t want) : a(args), plain(n == want) {}
+    // kinds: a letter for each argument (of_kind).  They are looked at before any table is made, because a call that goes
+    // through ctypes after all has this in front of it (us without it / tables first / so: 64 buffers, a count of numpy's
+    // 2.3 / 3.0 / 2.45).  What programs pass in earnest is taken as it is: through ctypes, with that in front / past it, a
+    // torch stream 3.0 / 0.8, a weight decay of 0 2.7 / 0.85, segments in a ctypes array 3.2 / 0.85.
+    Call(PyObject* const* args, Py_ssize_t n, const char* kinds) : a(args), plain(n == (Py_ssize_t)std::strlen(kinds))
+    {
+        for (Py_ssize_t i = 0; plain && i < n; ++i) plain = of_kind(args[i], kinds[i]);
+    }
 
     void* ptr(int i) { return plain ? address(a[i]) : nullptr; }
-    size_t size(int i)
-    {
-        if (!plain || !PyLong_CheckExact(a[i])) return (size_t)(plain = false);
-        return PyLong_AsUnsignedLongLongMask(a[i]);
-    }
+    size_t size(int i) { return plain ? PyLong_AsUnsignedLongLongMask(a[i]) : 0; }
     int num(int i) { return (int)size(i); }
-    int flag(int i)
-    {
-        if (!plain || !(PyBool_Check(a[i]) || PyLong_CheckExact(a[i]))) return plain = false;
-        return PyObject_IsTrue(a[i]);
-    }
+    int flag(int i) { return plain && PyObject_IsTrue(a[i]); }
     float real(int i)
     {
-        if (!plain || !PyFloat_CheckExact(a[i])) return (float)(plain = false);
-        return (float)PyFloat_AS_DOUBLE(a[i]);
+        if (!plain) return 0;
+        if (PyFloat_Check(a[i])) return (float)PyFloat_AS_DOUBLE(a[i]);
+        const double v = PyLong_AsDouble(a[i]);
+        if (v == -1 && PyErr_Occurred()) {                 // too large
+            PyErr_Clear();
+            plain = false;
+        }
+        return (float)v;
     }
     template <typename T>
     const T* const* table(int i)
     {
-        if (!plain || !sequence(a[i]) || PySequence_Fast_GET_SIZE(a[i]) > MICS_MAX_GROUP) plain = false;
         if (!plain) return nullptr;
         entries = (int)PySequence_Fast_GET_SIZE(a[i]);
         for (int q = 0; plain && q < entries; ++q) pointers[q] = address(PySequence_Fast_GET_ITEM(a[i], q));
@@ -243,40 +259,52 @@ class Call {
     }
     const mics_segment* segments(int i)
     {
-        if (!plain || !sequence(a[i]) || PySequence_Fast_GET_SIZE(a[i]) > kMaxSegments) plain = false;
         if (!plain) return nullptr;
+        if (!sequence(a[i])) {                             // a ctypes array of them
+            Py_buffer buf;
+            plain = PyObject_GetBuffer(a[i], &buf, PyBUF_SIMPLE) == 0;
+            if (!plain) {
+                PyErr_Clear();
+                return nullptr;
+            }
+            const void* at = buf.buf;
+            n_segments = (int)(buf.len / (Py_ssize_t)sizeof(mics_segment));
+            PyBuffer_Release(&buf);                        // the array stays where it is
+            return (const mics_segment*)at;
+        }
         n_segments = (int)PySequence_Fast_GET_SIZE(a[i]);
         for (int t = 0; t < n_segments; ++t) {
             PyObject* sg = PySequence_Fast_GET_ITEM(a[i], t);
-            const Py_ssize_t m = PyTuple_CheckExact(sg) ? PyTuple_GET_SIZE(sg) : 5;
-            size_t f[4] = {0, 0, 0, 0};
-            if (m > 4) plain = false;
-            for (Py_ssize_t k = 0; plain && k < m; ++k) {
-                PyObject* v = PyTuple_GET_ITEM(sg, k);
-                if (PyLong_CheckExact(v)) f[k] = PyLong_AsUnsignedLongLongMask(v);
-                else plain = false;
-            }
+            plain = segment(sg);
             if (!plain) return nullptr;
+            size_t f[4] = {0, 0, 0, 0};
+            for (Py_ssize_t k = 0; k < PySequence_Fast_GET_SIZE(sg); ++k)
+                f[k] = PyLong_AsUnsignedLongLongMask(PySequence_Fast_GET_ITEM(sg, k));
             segs[t] = mics_segment{f[0], f[1], f[2], f[3]};
         }
         return segs;
     }
-    // None: the current stream of the current device.  After everything else: this runs torch's Python code, whose
-    // exceptions (an interrupt may arrive in it) are the call's.
+    // An integer, a torch stream, or None: the current stream of the current device.  After everything else: this runs
+    // Python code, whose exceptions (an interrupt may arrive in it) are the call's.
     void* stream(int i)
     {
         if (!plain) return nullptr;
-        if (PyLong_CheckExact(a[i])) return (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(a[i]);
-        void* got = nullptr;
-        plain = a[i] == Py_None && device_of_thread;
-        if (!plain) return nullptr;
-        PyObject* dev = PyObject_CallNoArgs(device_of_thread);
-        PyObject* raw = dev ? PyObject_CallOneArg(raw_stream, dev) : nullptr;
-        raised = !raw;
+        PyObject* raw = nullptr;
+        if (PyLong_Check(a[i])) {
+            raw = a[i];
+            Py_INCREF(raw);
+        } else if (a[i] != Py_None) {
+            raw = PyObject_GetAttr(a[i], stream_attr);
+            raised = !raw;
+        } else if (device_of_thread) {
+            PyObject* dev = PyObject_CallNoArgs(device_of_thread);
+            raw = dev ? PyObject_CallOneArg(raw_stream, dev) : nullptr;
+            raised = !raw;
+            Py_XDECREF(dev);
+        }
         plain = raw && PyLong_CheckExact(raw);
-        if (plain) got = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(raw);
+        void* const got = plain ? (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(raw) : nullptr;
         Py_XDECREF(raw);
-        Py_XDECREF(dev);
         return got;
     }
     template <typename F>
@@ -294,7 +322,7 @@ class Call {
     int entries_as(int i)
     {
         int overflow;                                      // the value is -1 then
-        plain = plain && PyLong_CheckExact(a[i]) && PyLong_AsLongAndOverflow(a[i], &overflow) == entries;
+        plain = plain && PyLong_AsLongAndOverflow(a[i], &overflow) == entries;
         return entries;
     }
     int entries = 0, n_segments = 0;
@@ -307,6 +335,35 @@ class Call {
     mics_segment segs[kMaxSegments];
 
     static bool sequence(PyObject* x) { return PyList_CheckExact(x) || PyTuple_CheckExact(x); }
+    static bool segment(PyObject* x)
+    {
+        if (!sequence(x) || PySequence_Fast_GET_SIZE(x) > 4) return false;
+        for (Py_ssize_t k = 0; k < PySequence_Fast_GET_SIZE(x); ++k)
+            if (!PyLong_CheckExact(PySequence_Fast_GET_ITEM(x, k))) return false;
+        return true;
+    }
+    static bool segment_list(PyObject* x)                  // as far as its first item
+    {
+        if (sequence(x)) {
+            const Py_ssize_t m = PySequence_Fast_GET_SIZE(x);
+            return m <= kMaxSegments && (!m || segment(PySequence_Fast_GET_ITEM(x, 0)));
+        }
+        PyObject* const names = Py_TYPE(x)->tp_dict;       // of a ctypes array's type: _type_ is its items' type
+        return names && segment_type && PyDict_GetItem(names, item_attr) == segment_type;
+    }
+    // p pointer, t table of them, g segments, i integer, b flag, f number, s stream
+    static bool of_kind(PyObject* x, char kind)
+    {
+        switch (kind) {
+            case 'p': return x == Py_None || PyLong_CheckExact(x) || THPVariable_CheckExact(x);
+            case 't': return sequence(x) && PySequence_Fast_GET_SIZE(x) <= MICS_MAX_GROUP;
+            case 'g': return segment_list(x);
+            case 'i': return PyLong_CheckExact(x);
+            case 'b': return PyBool_Check(x) || PyLong_CheckExact(x);
+            case 'f': return PyFloat_Check(x) || PyLong_CheckExact(x);
+            default: return true;
+        }
+    }
     void* address(PyObject* x)
     {
         if (x == Py_None) return nullptr;
@@ -328,7 +385,7 @@ class Call {
 
 MICS_CALL(gather)
 {
-    Call c(args, n, 8);
+    Call c(args, n, "ptiiiiis");
     void* dst = c.ptr(0);
     const auto bufs = c.table<void>(1);
     const size_t n_valid = c.size(2), shard = c.size(3);
@@ -339,7 +396,7 @@ MICS_CALL(gather)
 
 MICS_CALL(gather_coalesced)
 {
-    Call c(args, n, 7);
+    Call c(args, n, "ptgiiis");
     void* dst = c.ptr(0);
     const auto bufs = c.table<void>(1);
     const auto segs = c.segments(2);
@@ -350,7 +407,7 @@ MICS_CALL(gather_coalesced)
 
 MICS_CALL(reduce)
 {
-    Call c(args, n, 6);
+    Call c(args, n, "ptiibs");
     float* acc = (float*)c.ptr(0);
     const auto g = c.table<uint16_t>(1);
     const size_t offset = c.size(2), count = c.size(3);
@@ -361,7 +418,7 @@ MICS_CALL(reduce)
 
 MICS_CALL(reduce_typed)
 {
-    Call c(args, n, 7);
+    Call c(args, n, "ptiibis");
     float* acc = (float*)c.ptr(0);
     const auto g = c.table<void>(1);
     const size_t offset = c.size(2), count = c.size(3);
@@ -372,7 +429,7 @@ MICS_CALL(reduce_typed)
 
 MICS_CALL(reduce_coalesced)
 {
-    Call c(args, n, 5);
+    Call c(args, n, "ptgbs");
     float* acc = (float*)c.ptr(0);
     const auto g = c.table<uint16_t>(1);
     const auto segs = c.segments(2);
@@ -383,7 +440,7 @@ MICS_CALL(reduce_coalesced)
 
 MICS_CALL(reduce_coalesced_typed)
 {
-    Call c(args, n, 6);
+    Call c(args, n, "ptgbis");
     float* acc = (float*)c.ptr(0);
     const auto g = c.table<void>(1);
     const auto segs = c.segments(2);
@@ -396,7 +453,7 @@ MICS_CALL(reduce_coalesced_typed)
 
 MICS_CALL(average)
 {
-    Call c(args, n, 5);
+    Call c(args, n, "ptifs");
     float* out = (float*)c.ptr(0);
     const auto copies = c.table<float>(1);
     const size_t count = c.size(2);
@@ -421,7 +478,7 @@ struct States {
 
 MICS_CALL(adam)
 {
-    Call c(args, n, 13);
+    Call c(args, n, "pppppifffffis");
     const States s(c);
     const float* grad = (const float*)c.ptr(4);
     const size_t count = c.size(5);
@@ -435,7 +492,7 @@ MICS_CALL(adam)
 
 MICS_CALL(adam_typed)
 {
-    Call c(args, n, 14);
+    Call c(args, n, "ppppipifffffis");
     const States s(c);
     const int dtype = c.num(4);
     const float* grad = (const float*)c.ptr(5);
@@ -450,7 +507,7 @@ MICS_CALL(adam_typed)
 
 MICS_CALL(update)
 {
-    Call c(args, n, 14);
+    Call c(args, n, "pppptiffffffis");
     const States s(c);
     const auto copies = c.table<float>(4);
     const size_t count = c.size(5);
@@ -465,7 +522,7 @@ MICS_CALL(update)
 
 MICS_CALL(update_typed)
 {
-    Call c(args, n, 15);
+    Call c(args, n, "ppppitiffffffis");
     const States s(c);
     const int dtype = c.num(4);
     const auto copies = c.table<float>(5);
@@ -486,6 +543,7 @@ PyMethodDef methods[] = {
     {"addresses", (PyCFunction)(void (*)())addresses, METH_FASTCALL, "Fills an array of pointers from a sequence."},
     {"segments", (PyCFunction)(void (*)())segments, METH_FASTCALL, "Fills an array of mics_segment from a sequence."},
     {"bind", (PyCFunction)(void (*)())bind, METH_FASTCALL, "Sets the library's entry points."},
+    {"bind_segment", bind_segment, METH_O, "Sets the type whose ctypes arrays are tables of segments."},
     MICS_METHOD(gather), MICS_METHOD(gather_coalesced), MICS_METHOD(reduce), MICS_METHOD(reduce_typed),
     MICS_METHOD(reduce_coalesced), MICS_METHOD(reduce_coalesced_typed), MICS_METHOD(average), MICS_METHOD(adam),
     MICS_METHOD(adam_typed), MICS_METHOD(update), MICS_METHOD(update_typed),

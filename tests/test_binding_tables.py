@@ -268,3 +268,82 @@ def test_the_number_of_stage1_buffers_is_compared_as_it_is(call, k):
         assert not ran
     finally:
         bound(mics._device, mics._raw_stream)
+
+
+class Stream:
+    def __init__(self, handle):
+        self.handle = handle
+
+    @property
+    def cuda_stream(self):
+        if isinstance(self.handle, BaseException):
+            raise self.handle
+        return self.handle
+
+
+def as_array(segs):
+    arr = (mics.mics_segment * len(segs))()
+    for a, sg in zip(arr, segs):
+        for (field, _), x in zip(mics.mics_segment._fields_, sg):
+            setattr(a, field, x % 2 ** 64)
+    return arr
+
+
+def is_segments(x):
+    return isinstance(x, (list, tuple)) and len(x) == len(SEGS) and all(a is b for a, b in zip(x, SEGS))
+
+
+FORMS = {"a stream object": lambda x: Stream(x) if type(x) is int and x == 64 else x,
+         "segments as lists": lambda x: [list(s) for s in x] if is_segments(x) else x,
+         "an array of segments": lambda x: as_array(x) if is_segments(x) else x,
+         "numpy's floats": lambda x: np.float64(x) if type(x) is float else x,
+         "whole numbers": lambda x: int(x) if type(x) is float and x == int(x) and x < 1e6 else x}
+
+
+@pytest.mark.parametrize("form", list(FORMS))
+@pytest.mark.parametrize("call", list(CALLS))
+def test_forms_of_arguments_that_go_past_ctypes(call, form):
+    """What a call made without ctypes hands over does not depend on the form; the plain ones are compared with ctypes above."""
+    name = CALLS[call][0]
+    real, seen = getattr(mics.lib, "mics_" + name), []
+
+    def record(*got):
+        got = list(got)
+        for i, kind in enumerate(real.argtypes):
+            if kind is ctypes.POINTER(mics.mics_segment):
+                got[i] = [tuple(getattr(got[i][t], f) for f, _ in mics.mics_segment._fields_) for t in range(got[i + 1])]
+            elif i == TABLE[name]:
+                got[i] = list((ctypes.c_void_p * len(CALLS[call][1][i])).from_address(got[i]))
+        seen.append(got)
+        return 0
+
+    plain = [1.0 if type(x) is float and x == 1e300 else x for x in positional(call, 64)]
+    if "weight_decay" in CALLS[call][2]:
+        plain[-3] = 0.0                                             # a whole number among them
+    stub = ctypes.CFUNCTYPE(ctypes.c_int, *real.argtypes)(record)
+    try:
+        bound(mics._device, mics._raw_stream, stub)
+        for args in (plain, [FORMS[form](x) for x in plain]):
+            assert getattr(mics._marshal, call)(*args) == 0
+        assert seen[0] == seen[1]
+    finally:
+        bound(mics._device, mics._raw_stream)
+
+
+def test_a_stream_object_that_raises_or_has_no_handle():
+    ran = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: ran.append(1) or 0)
+    try:
+        bound(mics._device, mics._raw_stream, entry)
+        for raised in (KeyboardInterrupt("now"), ZeroDivisionError("x")):
+            with pytest.raises(type(raised)):
+                mics.mics_replica_average(T[0], T[1:3], 4, 1.0, Stream(raised))
+        with pytest.raises(AttributeError, match="cuda_stream"):
+            mics.mics_replica_average(T[0], T[1:3], 4, 1.0, "7")
+        assert mics._marshal.average(T[0], T[1:3], 4, 1.0, True) is None         # ctypes' to judge
+        assert mics._marshal.average(T[0], T[1:3], 4, 1.0, Stream(None)) is None
+        assert mics._marshal.reduce_coalesced(T[0], T, (ctypes.c_size_t * 4)(), True, 64) is None
+        assert mics._marshal.average(T[0], T[1:3], 4, 10 ** 400, 64) is None
+        assert not ran
+    finally:
+        bound(mics._device, mics._raw_stream)
