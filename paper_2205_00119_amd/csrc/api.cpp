@@ -462,22 +462,18 @@ int reduce_scatter_accum_coalesced(const char* fn, const char* table, float* acc
                       : fail(MICS_ERR_INVALID_ARG, "%s: the accumulator regions of segments %d and %d overlap",
                              fn, bad_a, bad_b);
 
-    // every tensor, whatever its alignment, shares the launch of its batch
+    // every tensor, whatever its alignment, shares the launch of its batch; what a launch leaves begins the next batch
     mics::Segment batch[mics::kMaxSegMany];
     int nb = 0;
-    for (int t = 0; t <= n_segs; ++t) {
-        const bool last = (t == n_segs);
-        if (!last && segs[t].numel) {
-            const mics_segment& sg = segs[t];
-            batch[nb].numel = sg.numel; batch[nb].shard_elems = 0;
-            batch[nb].src_offset = sg.src_offset; batch[nb].dst_offset = sg.dst_offset;
-            ++nb;
-        }
-        if (nb == mics::kMaxSegMany || (last && nb)) {
-            int err = mics::launch_reduce_coalesced(acc, tab, batch, nb, p, accumulate != 0, kind, stream);
-            if (err) return hip_fail(fn, err);
-            nb = 0;
-        }
+    for (int t = 0; t < n_segs || nb > 0;) {
+        for (; t < n_segs && nb < mics::kMaxSegMany; ++t)
+            if (segs[t].numel) batch[nb++] = {segs[t].numel, 0, segs[t].src_offset, segs[t].dst_offset};
+        if (nb == 0) break;
+        int taken = 0;
+        int err = mics::launch_reduce_coalesced(acc, tab, batch, nb, p, accumulate != 0, kind, &taken, stream);
+        if (err) return hip_fail(fn, err);
+        nb -= taken;
+        std::copy(batch + taken, batch + taken + nb, batch);
     }
     return MICS_OK;
 }

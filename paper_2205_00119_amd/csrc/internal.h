@@ -17,8 +17,7 @@ struct PtrTable {
 
 // Launchers: arguments are already validated.  Each returns 0 or the hipError_t
 // of the failed launch call (as int) and enqueues on `stream` without waiting.
-// Every launcher issues exactly one kernel launch, the coalesced reductions one per 64 segments, or kMaxSegMany in
-// small calls.
+// Every launcher issues exactly one kernel launch.
 
 // vec16: every source, the destination and the shard size are multiples of 16
 // bytes -> direct 128-bit copy; otherwise the kernel that re-phases through a lane shift.
@@ -68,9 +67,10 @@ struct Segment {
 // kernel, which takes any element-aligned geometry.
 int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs, int n, int p,
                              int k, int elem_bytes, bool vec16, void* stream);
-// numel = elements to reduce; any element-aligned geometry.  kind: 0 bf16, 1 binary16, 2 binary32.
+// numel = elements to reduce; any element-aligned geometry.  kind: 0 bf16, 1 binary16, 2 binary32.  One launch of the
+// first *taken segments: all (at most kMaxSegMany) in small calls, 64 of them in others.
 int launch_reduce_coalesced(float* acc, const PtrTable& grads, const Segment* segs, int n, int p,
-                            bool accumulate, int kind, void* stream);
+                            bool accumulate, int kind, int* taken, void* stream);
 
 // Kernel families whose launch shape can be set (mics_tuning.h).
 enum { kFamReorder = 0, kFamReduce = 1, kFamAverage = 2, kFamAdam = 3, kFamFused = 4, kFamilies = 5 };

@@ -1838,8 +1838,8 @@ ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb)
     return {gains && p < 48, gains && p < 32};
 }
 
-// Small messages on large groups take the one-dword-per-lane kernels (VEC = 1; of a coalesced call all its segments
-// together), MB of gradients up to which they win.  us per call, one dword / 128 bits per lane:
+// Small messages on large groups take the one-dword-per-lane kernels (VEC = 1; of a coalesced call up to kMaxSegMany
+// segments together), MB of gradients up to which they win.  us per call, one dword / 128 bits per lane:
 //   bf16, p = 20 5 MB 3.4 / 3.9, 19 MB 6.0 / 6.0, 32 MB 8.9 / 8.2      p = 32 13 MB 4.3 / 4.7, 24 MB 6.4 / 6.3
 //         p = 48 13 MB 4.5 / 5.8, 49 MB 10.7 / 12.2, 63 MB 13.7 / 12.9  p = 40 49 MB 10.9 / 11.6, 62 MB 13.6 / 12.9
 //         p = 64 1 MB 3.0 / 6.4, 50 MB 10.7 / 11.6, 65 MB 13.5 / 14.6   p = 128 3 MB 4.3 / 11.2, 67 MB 12.7 / 15.9
@@ -2126,7 +2126,7 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
 }
 
 template <int KIND>
-int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, int p, bool accumulate,
+int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, int p, bool accumulate, int* taken,
                           hipStream_t st)
 {
     constexpr size_t GB = GradFormat<KIND>::kElemBytes, EPL = 4 * GradFormat<KIND>::kPerDword;
@@ -2135,52 +2135,46 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     size_t units = 0;
     if (int e = compute_units(&units)) return e;
     const size_t unit = line >= 16 ? line / GB : 4 / GB;             // elements that a segment's lead is counted in
-    size_t all = 0;
-    for (int t = 0; t < n; ++t) all += segs[t].numel;
-    const bool narrow = narrow_call(p, GB, all, line >= 16);
-    for (int first = 0, nt; first < n; first += nt) {
-        size_t elements = 0;
-        auto take = [&](int most) {
-            nt = n - first < most ? n - first : most;
-            elements = 0;
-            for (int t = 0; t < nt; ++t) elements += segs[first + t].numel;
-        };
-        // Small calls carry more than 64 segments, whose records then come in a second round: us, 64 / 96 per launch, f16, p = 12,
-        // 79 segments 7.3 / 4.0; larger ones keep to 64 and to half as many kernels.
-        take(kMaxSegMany);
-        int err;
-        if (narrow) {
-            const Shape sh = {kNarrowBlock, 0};
-            err = nt <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st)
-                           : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, kAccCached, {false, false}, st);
-        } else {
-            if (nt > 64 && accum_policy(elements, p, (int)GB) != kAccCached) take(64);
-            const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20);
-            bool acc16 = true;
-            for (int t = 0; t < nt; ++t) {
-                const size_t lead = segment_lead<KIND>(acc, g, segs[first + t].src_offset + base_lead, segs[first + t].dst_offset, unit, order);
-                acc16 = acc16 && ((uintptr_t)(acc + segs[first + t].dst_offset) - 4 * lead) % 16 == 0;
-            }
-            const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
-            const int policy = accum_policy(elements, p, (int)GB);
-            err = nt <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, policy, order, st)
-                           : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs + first, nt, p, accumulate, sh, policy, order, st);
-        }
-        if (err) return err;
+    auto elements_of = [&](int m) {
+        size_t sum = 0;
+        for (int t = 0; t < m; ++t) sum += segs[t].numel;
+        return sum;
+    };
+    size_t elements = elements_of(n);
+    *taken = n;
+    if (narrow_call(p, GB, elements, line >= 16)) {
+        const Shape sh = {kNarrowBlock, 0};
+        return n <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st)
+                       : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st);
     }
-    return 0;
+    // Small calls carry more than 64 segments, whose records then come in a second round: us, 64 / 96 per launch, f16, p = 12,
+    // 79 segments 7.3 / 4.0; larger ones keep to 64 and to half as many kernels.
+    if (n > 64 && accum_policy(elements, p, (int)GB) != kAccCached) {
+        *taken = n = 64;
+        elements = elements_of(n);
+    }
+    const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20);
+    bool acc16 = true;
+    for (int t = 0; t < n; ++t) {
+        const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
+        acc16 = acc16 && ((uintptr_t)(acc + segs[t].dst_offset) - 4 * lead) % 16 == 0;
+    }
+    const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
+    const int policy = accum_policy(elements, p, (int)GB);
+    return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st)
+                   : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st);
 }
 
 }  // namespace
 
 int launch_reduce_coalesced(float* acc, const PtrTable& grads, const Segment* segs, int n, int p,
-                            bool accumulate, int kind, void* stream)
+                            bool accumulate, int kind, int* taken, void* stream)
 {
     hipStream_t st = (hipStream_t)stream;
     switch (kind) {
-        case 0: return reduce_coalesced_kind<0>(acc, grads, segs, n, p, accumulate, st);
-        case 1: return reduce_coalesced_kind<1>(acc, grads, segs, n, p, accumulate, st);
-        default: return reduce_coalesced_kind<2>(acc, grads, segs, n, p, accumulate, st);
+        case 0: return reduce_coalesced_kind<0>(acc, grads, segs, n, p, accumulate, taken, st);
+        case 1: return reduce_coalesced_kind<1>(acc, grads, segs, n, p, accumulate, taken, st);
+        default: return reduce_coalesced_kind<2>(acc, grads, segs, n, p, accumulate, taken, st);
     }
 }
 

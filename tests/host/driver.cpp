@@ -4,10 +4,14 @@
 #include <cstring>
 #include <vector>
 
+#include "internal.h"
 #include "mics.h"
 #include "mics_tuning.h"
 
-namespace mics { extern int g_launches; }
+namespace mics {
+extern int g_launches;
+extern std::vector<Segment> g_reduced;
+}
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "%s:%d: %s [%s]\n", __FILE__, __LINE__, #cond, mics_last_error()); std::exit(1); } } while (0)
 
@@ -74,6 +78,23 @@ int main()
     CHECK(mics_reduce_scatter_accum_coalesced((float*)A, (const uint16_t* const*)tab.data(), segs.data(),
                                               (int)segs.size(), 16, 1, nullptr) == MICS_OK);
     CHECK(mics::g_launches == before + 3);
+    // 64 segments a launch, each of them once and in their order, the empty ones left out
+    for (int n : {1, 63, 64, 65, 96, 97, 128, 129, 192, 193, 300}) {
+        std::vector<mics_segment> many;
+        for (int t = 0; t < n; ++t) {
+            many.push_back({(size_t)t % 7 + 1, 9, (size_t)t * 3, (size_t)t * 8});
+            if (t % 5 == 2) many.push_back({0, 1, 2, 3});
+        }
+        before = mics::g_launches;
+        mics::g_reduced.clear();
+        CHECK(mics_reduce_scatter_accum_coalesced((float*)A, (const uint16_t* const*)tab.data(), many.data(), (int)many.size(), 16, 1, nullptr) == MICS_OK);
+        CHECK(mics::g_launches - before == (n + 63) / 64);
+        CHECK((int)mics::g_reduced.size() == n);
+        for (int t = 0; t < n; ++t) {
+            const mics::Segment& sg = mics::g_reduced[(size_t)t];
+            CHECK(sg.numel == (size_t)t % 7 + 1 && sg.src_offset == (size_t)t * 3 && sg.dst_offset == (size_t)t * 8);
+        }
+    }
     // a transformer layer's 16 tensors sharded with odd sizes (nothing 16-byte clean): at most
     // two launches for the gather, one for the reduction
     {

@@ -1,5 +1,8 @@
 """Edges of the kernels' tiles, lines and dispatch rules, against the oracle (bit for bit: the
 contract fixes the order and the rounding of every operation)."""
+import ctypes
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -402,3 +405,25 @@ def test_reduce_segments_in_runs_of_tiles(orc, gen, name, p, threshold):
             assert same_bits(acc, ref), accumulate
     finally:
         mics.mics_set_stream_threshold_bytes(0)
+
+
+def kernels_of(call):
+    """Kernel launches of a call, from its capture (never replayed)."""
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    graph, side = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    n = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("n_segs", [1, 64, 65, 96, 97, 128, 129, 192, 193])
+@pytest.mark.parametrize("numel,per_launch", [(64, 96), (100_000, 64)])
+def test_launches_of_coalesced_reductions(n_segs, numel, per_launch):
+    """64 tensors in a launch, 96 in small calls (accumulators up to 12 MiB); the last launch takes what is left."""
+    segs = [(numel, 0, t * numel, t * numel) for t in range(n_segs)]
+    grads = [torch.zeros(n_segs * numel, dtype=torch.int16, device="cuda:0") for _ in range(4)]
+    acc = torch.zeros(n_segs * numel, device="cuda:0")
+    assert kernels_of(lambda: mics.mics_reduce_scatter_accum_coalesced(acc, grads, segs, True)) == -(-n_segs // per_launch)
