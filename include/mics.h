@@ -40,7 +40,7 @@
  *     enqueued.  MICS_ERR_HIP reports the status of the failed launch call
  *     itself (an earlier, unrelated HIP error of the thread is neither reported
  *     nor cleared); every entry point issues a single launch, except the
- *     coalesced ones, which issue one launch per 48 tensors and may have
+ *     coalesced ones, which issue one per 48 to 96 tensors and may have
  *     enqueued earlier launches when a later one fails.
  *   - Return value: MICS_OK or a negative MICS_ERR_*; mics_last_error() gives
  *     the text for the calling thread's most recent failure.
@@ -240,9 +240,9 @@ typedef struct mics_segment {
  *     dst_flat[dst_offset_t + x] = stage1_bufs[l][src_offset_t + j*S_t + i].
  * Tensor t occupies (p/k)*S_t elements from src_offset_t in every stage-1 buffer and numel_t
  * elements from dst_offset_t in dst_flat; the destination regions of different tensors must not
- * overlap (checked: MICS_ERR_INVALID_ARG).  segs is a HOST array.  Tensors whose addresses and
- * shard sizes are multiples of 16 bytes share one launch per 48 of them, all other tensors
- * another launch per 48: a layer of 16 tensors is moved by at most two launches.
+ * overlap (checked: MICS_ERR_INVALID_ARG).  segs is a HOST array.  One launch per 96 tensors,
+ * whatever their alignment, or per 48 in calls that move (read and write) 640 MiB and more; if
+ * every tensor's address and shard size is a multiple of 16 bytes, through the faster kernel.
  */
 int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1_bufs,
                                        const mics_segment* segs, int n_segs, int p, int k,
@@ -256,7 +256,7 @@ int mics_hier_gather_reorder_coalesced(void* dst_flat, const void* const* stage1
  * whose gradient buffers hold tensor t at offset o_t (p*S_t elements) and whose shard buffer
  * holds it at offset a_t: numel = S_t, src_offset = o_t + g*S_t, dst_offset = a_t.
  * The accumulator regions of different tensors must not overlap (checked).  One launch per
- * 48 tensors, whatever their alignment.
+ * 64 tensors, whatever their alignment, or per 96 in small calls.
  */
 int mics_reduce_scatter_accum_coalesced(float* acc, const uint16_t* const* grads_bf16,
                                         const mics_segment* segs, int n_segs, int p,

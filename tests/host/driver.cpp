@@ -62,7 +62,8 @@ int main()
     CHECK(mics::g_launches == before + 4);
     for (int i = 0; i < MICS_MAX_GROUP; ++i) tab[i] = fake(i + 8);
 
-    // coalesced calls: one launch per 48 tensors of a kind
+    // coalesced calls: one launch per 96 tensors of a gather, whatever their alignment, per 64 of a reduction (96 in
+    // small calls, see the launchers)
     std::vector<mics_segment> segs;
     size_t s_off = 0, d_off = 0;
     for (int t = 0; t < 131; ++t) {        // more than one launch's worth, some not 16-byte clean
@@ -72,7 +73,7 @@ int main()
     }
     before = mics::g_launches;
     CHECK(mics_hier_gather_reorder_coalesced(A, tab.data(), segs.data(), (int)segs.size(), 4, 2, 2, nullptr) == MICS_OK);
-    CHECK(mics::g_launches - before >= 3 && mics::g_launches - before <= 4);   // 131 tensors of two kinds
+    CHECK(mics::g_launches == before + 2);
     for (auto& sg : segs) sg.shard_elems = 0;
     before = mics::g_launches;
     CHECK(mics_reduce_scatter_accum_coalesced((float*)A, (const uint16_t* const*)tab.data(), segs.data(),
@@ -95,8 +96,27 @@ int main()
             CHECK(sg.numel == (size_t)t % 7 + 1 && sg.src_offset == (size_t)t * 3 && sg.dst_offset == (size_t)t * 8);
         }
     }
-    // a transformer layer's 16 tensors sharded with odd sizes (nothing 16-byte clean): at most
-    // two launches for the gather, one for the reduction
+    // a gather's launches by its tensors, and from 640 MiB moved on 48 of them each; aligned, not aligned, and both
+    for (size_t odd : {0, 1, 2}) {
+        auto gathers = [&](int n, size_t shard) {
+            std::vector<mics_segment> many;
+            size_t so = 0, dn = 0;
+            for (int t = 0; t < n; ++t) {
+                const size_t S = shard + (odd == 2 ? (size_t)t % 2 : odd);
+                many.push_back({2 * S, S, so, dn});
+                so += S; dn += 2 * S;
+            }
+            const int at = mics::g_launches;
+            CHECK(mics_hier_gather_reorder_coalesced(A, tab.data(), many.data(), n, 2, 2, 2, nullptr) == MICS_OK);
+            return mics::g_launches - at;
+        };
+        CHECK(gathers(16, 64) == 1 && gathers(96, 64) == 1 && gathers(97, 64) == 2 && gathers(192, 64) == 2 && gathers(193, 64) == 3);
+        // 8 bytes moved per element of a shard
+        const size_t below = ((size_t{640} << 20) / 8 / 96 - 2) / 8 * 8, above = ((size_t{640} << 20) / 8 / 96 + 8) / 8 * 8;
+        CHECK(gathers(96, below) == 1 && gathers(96, above) == 2 && gathers(97, above) == 3);
+        CHECK(gathers(48, 2 * above) == 1 && gathers(49, 2 * above) == 2);
+    }
+    // a transformer layer's 16 tensors sharded with odd sizes (nothing 16-byte clean): one launch
     {
         const size_t h = 130;              // hidden size; tensor sizes as in a transformer layer
         const size_t numels[16] = {3 * h * h, 3 * h, h * h, h, h, h, 4 * h * h, 4 * h, 4 * h * h, h, h, h, h + 1, 7, h, 3};
@@ -109,7 +129,7 @@ int main()
         }
         before = mics::g_launches;
         CHECK(mics_hier_gather_reorder_coalesced(A, tab.data(), layer.data(), 16, 8, 8, 2, nullptr) == MICS_OK);
-        CHECK(mics::g_launches - before >= 1 && mics::g_launches - before <= 2);
+        CHECK(mics::g_launches == before + 1);
         std::vector<mics_segment> red;
         size_t go = 5, ao = 1;
         for (auto& sg : layer) { red.push_back({sg.shard_elems, 0, go + 3 * sg.shard_elems, ao}); go += 8 * sg.shard_elems; ao += sg.shard_elems; }

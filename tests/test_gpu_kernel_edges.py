@@ -427,3 +427,17 @@ def test_launches_of_coalesced_reductions(n_segs, numel, per_launch):
     grads = [torch.zeros(n_segs * numel, dtype=torch.int16, device="cuda:0") for _ in range(4)]
     acc = torch.zeros(n_segs * numel, device="cuda:0")
     assert kernels_of(lambda: mics.mics_reduce_scatter_accum_coalesced(acc, grads, segs, True)) == -(-n_segs // per_launch)
+
+
+@pytest.mark.parametrize("n_tensors,shard,launches", [(16, 64, 1), (96, 64, 1), (97, 64, 2), (60, 500_000, 1), (60, 1_500_000, 2), (2, 64, 1)])
+@pytest.mark.parametrize("odd", [0, 1, 2])
+def test_launches_of_coalesced_gathers(n_tensors, shard, launches, odd):
+    """96 tensors in a launch and 48 from 640 MiB moved on, aligned, not aligned, or both in turn."""
+    segs, src, dst_at = [], 0, 0
+    for t in range(n_tensors):
+        S = shard + (t % 2 if odd == 2 else odd)
+        segs.append((2 * S, S, src, dst_at))
+        src, dst_at = src + S, dst_at + 2 * S
+    T = [torch.zeros(src, dtype=torch.int16, device="cuda:0") for _ in range(2)]
+    dst = torch.zeros(dst_at, dtype=torch.int16, device="cuda:0")
+    assert kernels_of(lambda: mics.mics_hier_gather_reorder_coalesced(dst, T, segs, 2, 2, 2)) == launches
