@@ -6,7 +6,6 @@
 #include "internal.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -17,7 +16,6 @@
 namespace {
 
 thread_local char g_error[512] = "";
-std::atomic<int> g_blocks_per_cu{0};
 
 int fail(int code, const char* fmt, ...)
 {
@@ -99,7 +97,6 @@ int mics_set_blocks_per_cu(int blocks_per_cu)
 {
     if (blocks_per_cu < 0 || blocks_per_cu > 4096)
         return fail(MICS_ERR_INVALID_ARG, "mics_set_blocks_per_cu: %d not in [0, 4096]", blocks_per_cu);
-    g_blocks_per_cu.store(blocks_per_cu);
     mics::set_blocks_per_cu(blocks_per_cu);
     return MICS_OK;
 }

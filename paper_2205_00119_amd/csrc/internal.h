@@ -62,13 +62,13 @@ struct Segment {
     size_t numel, shard_elems, src_offset, dst_offset;
 };
 
-// At most kMaxSegMany tensors, none of them empty: one launch.  vec16: every segment satisfies the 16-byte
+// 1 to kMaxSegMany tensors, none of them empty: one launch.  vec16: every segment satisfies the 16-byte
 // conditions of the vector kernel (bases, shard size and both offsets); otherwise they go through the lane-shift
 // kernel, which takes any element-aligned geometry.
 int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs, int n, int p,
                              int k, int elem_bytes, bool vec16, void* stream);
-// numel = elements to reduce; any element-aligned geometry.  kind: 0 bf16, 1 binary16, 2 binary32.  One launch of the
-// first *taken segments: all (at most kMaxSegMany) in small calls, 64 of them in others.
+// 1 to kMaxSegMany segments, none of them empty, in any element-aligned geometry; numel = elements to reduce.  kind: 0
+// bf16, 1 binary16, 2 binary32.  One launch of the first *taken segments: all of them in small calls, else up to 64.
 int launch_reduce_coalesced(float* acc, const PtrTable& grads, const Segment* segs, int n, int p,
                             bool accumulate, int kind, int* taken, void* stream);
 

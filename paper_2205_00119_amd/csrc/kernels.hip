@@ -2051,7 +2051,6 @@ int launch_reorder_coalesced(void* dst, const PtrTable& src, const Segment* segs
     const size_t eb = (size_t)elem_bytes;
     size_t moved = 0;
     for (int t = 0; t < n; ++t) moved += 2 * segs[t].numel * eb;
-    if (moved == 0) return 0;
     if (const int vectors = flat_vectors(n, moved, p, vec16)) return launch_reorder_small(dst, src, segs, n, vectors, moved, k, eb, st);
     if (vec16)
         return n <= kMaxSegPerLaunch ? launch_reorder_seg<kMaxSegPerLaunch>(dst, src, segs, n, moved, p, k, eb, st)
@@ -2097,11 +2096,10 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
         tab.seg[t].end = lead + sg.numel;
         tab.seg[t].src0 = src - lead;
         tab.seg[t].dst = sg.dst_offset;
-        if (sg.numel) tiles += (lead + sg.numel + tile_elems - 1) / tile_elems;
+        tiles += (lead + sg.numel + tile_elems - 1) / tile_elems;
         if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
     }
     for (int t = n; t < SEGS; ++t) tab.tile_begin[t] = kNoTile;
-    if (tiles == 0) return 0;
     auto run = [&](auto P, auto A, auto C) {
         // lanes of 8 elements pass their results through 32 bytes of LDS
         const size_t lds = lds_for(sh, !C.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
