@@ -794,15 +794,19 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         // A window of W loads that moves on by STEP buffers, held in this order.  Left to itself the compiler put as few as
         // one load in flight here and more than enough there, from one change of the source to the next: us, f16, 16
         // tensors, p = 16 900 MB 239 / so 139, 2 GB 524 / 324, p = 32 45 MB 20.5 / 10.6, 2 GB 752 / 313; f32, p = 32, 12 MB in two batches
-        // 3.95 / 3.69.  A window of 4 is 5 to 8 % slower at 2 GB, f32; of 8 to 16 equal at best (p = 32 45 MB 9.5 / 9.9).  Slower
-        // than the best that the compiler found by chance: f32, p = 32, 80 MB up to 8 %, f16 3 %.  The bf16 kernels, and p = 16 in one
-        // tensor, are better in the compiler's order (p = 16 300 MB 47.7, held 49.0; p = 32 300 MB 49.1 / 51).
-        constexpr int W = HOLD ? 16 : P == 16 ? 4 : 6, STEP = HOLD ? 4 : 2;
+        // 3.95 / 3.69.  The bf16 kernels, and p = 16 in one tensor, are better in the compiler's order (p = 16 300 MB 47.7, held
+        // 49.0; p = 32 300 MB 49.1 / 51).
+        // The accumulator's loads go out behind the last gradients: in front, or behind the first window, they are one of the
+        // few in flight while nothing needs them (us, p = 32, in front / behind the first / behind the last: f32 45 MB 9.0 / 9.2 /
+        // 8.6, 2 GB 302 / 302 / 295; f16 45 MB 9.9 / 9.9 / 9.2, 200 MB 34.7 / 34.7 / 32.6, 900 MB 142.7 / 142.8 / 138.5).
+        // W = 4 where BATCH asks for it (short_window) and for 16 buffers, else 6: us, f32, p = 32, 4 / 6, 75 MB 12.7 / 13.5, 900 MB
+        // 141.7 / 138, first micro-step 75 MB 12.5 / 13.4, 900 MB 150 / 138; f16 75 MB 12.35 / 12.3, 2 GB 316 / 309.
+        constexpr int W = HOLD ? 16 : P == 16 || BATCH == 4 ? 4 : 6, STEP = HOLD ? 4 : 2;
+        static_assert((P - W) % STEP == 0, "");
         GradVec<KIND, VEC> v[W];
-        if (FIRST) accumulator();
         #pragma unroll
         for (int b = 0; b < W; ++b) v[b].load(g.ptr[b], elem);
-        if (!FIRST) accumulator();
+        if (HOLD) accumulator();
         __builtin_amdgcn_sched_barrier(0);
         #pragma unroll
         for (int q0 = 0; q0 < P; q0 += STEP) {
@@ -814,6 +818,7 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             #pragma unroll
             for (int b = q0; b < q0 + STEP; ++b)
                 if (b + W < P) v[b % W].load(g.ptr[b + W], elem);
+            if (!HOLD && q0 + STEP + W == P) accumulator();
             if (q0 + W < P) __builtin_amdgcn_sched_barrier(0);
         }
     } else if constexpr (P > 0) {
@@ -1055,12 +1060,13 @@ __device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
-template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, typename Tab>
+// SHORT: the window of 4 (short_window).
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHORT, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
     Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
     const auto& g = table_view(tab);
-    constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
+    constexpr int BATCH = SHORT ? 4 : VEC == 4 ? MICS_RSA_BATCH : 64;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const size_t end = (size_t)lead + count;
     const size_t nlanes = (end + EPL - 1) / EPL;
@@ -1854,18 +1860,26 @@ inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line)
     return count <= ((size_t)most << 20) / ((size_t)p * elem_bytes);
 }
 
-template <int KIND, int VEC, int P, bool ACCUM, bool CACHED>
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHORT = false>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
                const Shape& sh, int how, hipStream_t st)
 {
     // lanes of 8 elements pass their results through 32 bytes of LDS (rsa_lane)
     const size_t lds = lds_for(sh, !CACHED && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
     if constexpr (P > 0)
-        return launch(rsa_kernel<KIND, VEC, P, ACCUM, CACHED, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
+        return launch(rsa_kernel<KIND, VEC, P, ACCUM, CACHED, SHORT, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
                       small<P>(g), acc, p, lead, count, how);
     else
-        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, CACHED, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
+        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, CACHED, SHORT, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
                       acc, p, lead, count, how);
+}
+
+// Whether 32 binary32 buffers are read with 4 instead of 6 loads in flight.  us, 4 / 6 (accumulating, first micro-step): 45 MB 8.6 /
+// 8.7, 8.45 / 8.55; 75 MB 12.7 / 13.5, 12.5 / 13.4; 90 MB 15.3 / 15.8, 15.2 / 15.8; 110 MB 19.3 / 18.7; 200 MB 31.7 / 31.7, 33.5 / 32.4; 900
+// MB 141.7 / 138, 150 / 138.
+bool short_window(int kind, int p, size_t count, bool accumulate)
+{
+    return kind == 2 && p == 32 && count * (accumulate ? 136 : 132) < (size_t{100} << 20);
 }
 
 template <int KIND>
@@ -1902,6 +1916,9 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     return dispatch_bool(accumulate, [&](auto A) {
+        if constexpr (KIND == 2)
+            if (policy != kAccCached && short_window(KIND, p, count, accumulate))
+                return rsa_launch<KIND, 4, 32, A.value, false, true>(acc, g, p, lead, count, blocks, sh, how, st);
         return dispatch_bool(policy == kAccCached, [&](auto C) {
             return dispatch_group(p, [&](auto P) {
                 return rsa_launch<KIND, 4, P.value, A.value, C.value>(acc, g, p, lead, count, blocks, sh, how, st);

@@ -441,3 +441,17 @@ def test_launches_of_coalesced_gathers(n_tensors, shard, launches, odd):
     T = [torch.zeros(src, dtype=torch.int16, device="cuda:0") for _ in range(2)]
     dst = torch.zeros(dst_at, dtype=torch.int16, device="cuda:0")
     assert kernels_of(lambda: mics.mics_hier_gather_reorder_coalesced(dst, T, segs, 2, 2, 2)) == launches
+
+
+@pytest.mark.parametrize("name,count", [("f32", 262_147), ("f32", 771_011), ("f32", 771_012), ("f32", 794_376), ("f32", 794_377), ("f16", 794_377)])
+def test_reduce_of_32_buffers_through_either_window(orc, gen, name, count):
+    """Both sides of the line between 4 and 6 loads in flight (100 MiB moved), the accumulator on the lanes' lines and off them."""
+    code = FORMATS[name][0]
+    host, dev = rank_buffers(gen, name, 32, count + 8, [0])
+    for offset, skew in ((0, 0), (5, 3)):
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, count, skew=skew)
+            mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], offset, count, accumulate, code)
+            orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), (offset, skew, accumulate)
