@@ -1060,13 +1060,14 @@ __device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs
 // Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
-// SHORT: the window of 4 (short_window).
-template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHORT, typename Tab>
+// OTHER: a kernel's other form, with CACHED tiles in runs (of the others `how` says whether: tile_of's few instructions are
+// 1 % of a small call), else the window of 4 (short_window).
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool OTHER, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
     Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
     const auto& g = table_view(tab);
-    constexpr int BATCH = SHORT ? 4 : VEC == 4 ? MICS_RSA_BATCH : 64;
+    constexpr int BATCH = VEC == 1 ? 64 : OTHER && !CACHED ? 4 : MICS_RSA_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const size_t end = (size_t)lead + count;
     const size_t nlanes = (end + EPL - 1) / EPL;
@@ -1077,7 +1078,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
         return;
     }
     const size_t stride = (size_t)(gridDim.x - 1) * block;
-    const unsigned tile = VEC == 1 ? blockIdx.x : tile_of(blockIdx.x, gridDim.x - 1, how & kInRuns);
+    const unsigned tile = CACHED && !OTHER ? blockIdx.x : tile_of(blockIdx.x, gridDim.x - 1, CACHED || (how & kInRuns));
     for (size_t base = (size_t)tile * block; base < nlanes; base += stride)   // workgroup-uniform
         rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8), false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end,
                                                                      how & ~kInRuns);
@@ -1860,17 +1861,17 @@ inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line)
     return count <= ((size_t)most << 20) / ((size_t)p * elem_bytes);
 }
 
-template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHORT = false>
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool OTHER = false>
 int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count, unsigned blocks,
                const Shape& sh, int how, hipStream_t st)
 {
     // lanes of 8 elements pass their results through 32 bytes of LDS (rsa_lane)
     const size_t lds = lds_for(sh, !CACHED && KIND != 2 ? (size_t)sh.lanes * 32 : 0);
     if constexpr (P > 0)
-        return launch(rsa_kernel<KIND, VEC, P, ACCUM, CACHED, SHORT, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
+        return launch(rsa_kernel<KIND, VEC, P, ACCUM, CACHED, OTHER, SmallTable<P>>, dim3(blocks + 1), dim3(sh.lanes), lds, st,
                       small<P>(g), acc, p, lead, count, how);
     else
-        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, CACHED, SHORT, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
+        return launch(rsa_kernel<KIND, VEC, 0, ACCUM, CACHED, OTHER, PtrTable>, dim3(blocks + 1), dim3(sh.lanes), lds, st, g,
                       acc, p, lead, count, how);
 }
 
@@ -1916,13 +1917,17 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     return dispatch_bool(accumulate, [&](auto A) {
-        if constexpr (KIND == 2)
-            if (policy != kAccCached && short_window(KIND, p, count, accumulate))
-                return rsa_launch<KIND, 4, 32, A.value, false, true>(acc, g, p, lead, count, blocks, sh, how, st);
-        return dispatch_bool(policy == kAccCached, [&](auto C) {
-            return dispatch_group(p, [&](auto P) {
-                return rsa_launch<KIND, 4, P.value, A.value, C.value>(acc, g, p, lead, count, blocks, sh, how, st);
+        if (policy == kAccCached)
+            return dispatch_bool(order.in_runs, [&](auto R) {
+                return dispatch_group(p, [&](auto P) {                 // one buffer is never in runs there
+                    return rsa_launch<KIND, 4, P.value, A.value, true, (R.value && P.value != 1)>(acc, g, p, lead, count, blocks, sh, how, st);
+                });
             });
+        if constexpr (KIND == 2)
+            if (short_window(KIND, p, count, accumulate))
+                return rsa_launch<KIND, 4, 32, A.value, false, true>(acc, g, p, lead, count, blocks, sh, how, st);
+        return dispatch_group(p, [&](auto P) {
+            return rsa_launch<KIND, 4, P.value, A.value, false>(acc, g, p, lead, count, blocks, sh, how, st);
         });
     });
 }

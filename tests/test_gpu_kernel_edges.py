@@ -455,3 +455,23 @@ def test_reduce_of_32_buffers_through_either_window(orc, gen, name, count):
             orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
             torch.cuda.synchronize()
             assert same_bits(acc, ref), (offset, skew, accumulate)
+
+
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [2, 3, 4, 5, 6, 7, 8, 12, 16, 32])
+@pytest.mark.parametrize("skews", [[0, 8, 16], [3, 0, 5]])
+def test_small_accumulators_in_runs_of_tiles(orc, gen, name, p, skews):
+    """Just above and below the 12 MiB moved from which calls with gradients off their lines are dealt out in runs; the accumulator
+    is small enough to stay in the L2 up to 16 buffers.  (32: held loads as well, see the next test.)"""
+    code, dtype = FORMATS[name]
+    per_element = p * np.dtype(dtype).itemsize + 8
+    above = -(-(12 << 20) // per_element) + 5
+    host, dev = rank_buffers(gen, name, p, above + 40, skews)
+    for count in (above - 5000, above):
+        for offset, acc_skew in ((0, 0), (24, 8), (5, 1)):
+            for accumulate in (False, True):
+                ref, acc = start_acc(gen, count, skew=acc_skew)
+                mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], offset, count, accumulate, code)
+                orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
+                torch.cuda.synchronize()
+                assert same_bits(acc, ref), (count, offset, acc_skew, accumulate)
