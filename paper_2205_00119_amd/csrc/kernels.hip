@@ -1047,7 +1047,7 @@ __device__ __forceinline__ void rsa_edges(float* acc, const Tab& g, int p, size_
 }
 
 // The tile of workgroup x of n.  Workgroups go to the 8 XCDs in turn, so neighbouring tiles meet in no L2, and a line
-// that two of them share is fetched, or written in parts, twice.  IN_RUNS (reduction_in_runs): rounds of 128 workgroups in which every XCD
+// that two of them share is fetched, or written in parts, twice.  IN_RUNS (reduce_order): rounds of 128 workgroups in which every XCD
 // has a run of 16 neighbouring tiles.
 constexpr int kInRuns = 4;                         // in a kernel's `how`, beside the accumulator's policy
 __device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs)
@@ -1807,42 +1807,48 @@ int lead_on_accumulator_lines(const float* acc, uintptr_t first, size_t elem_byt
     return (first - lead * elem_bytes) % 16 ? -1 : (int)lead;
 }
 
-// Whether neighbouring tiles meet in one XCD (tile_of), and on whose lines the vectors lie.  Speed against the plain order on the
-// gradients' lines (where two times stand, us before / so):
-//   - Gradients off their lines, each buffer at another position or fewer than 4: in runs at any size (rows of one buffer, 16-byte positions, bf16 p = 6
-//     105 M elements 342 / 320, p = 24 45 MB .99, 90 MB 1.07, 1.1 GB 1.07, p = 48 45 MB 1.21; f32 p = 8 90 MB 1.05, 600 MB 1.10; p = 2
-//     90 MB 1.07, 1.1 GB 1.03).  At odd positions 1.00 to 1.13.
-//   - Gradients on lines, accumulator not: on the accumulator's lines and in runs, so that the gradients' shared lines are
-//     found in the L2 and no accumulator's line is written in parts (bf16 p = 4 300 MB 1.08, 2.2 GB 1.08, p = 8 600 MB 1.05, 2.2 GB 1.08, p = 16 600 MB 1.07, 1.1 GB
-//     .97; f32 p = 4 600 MB 1.00, p = 16 600 MB 1.08, 2.2 GB .96; bf16 p = 24 .98 to 1.02, p = 96 45 MB .94).  Not in runs this
-//     loses 1 to 20 %, and runs alone lose 3 to 14 % with few buffers, whose accumulator is most of the traffic.
-//   - Everything on lines, or many buffers: in runs in the middle of the range (bf16 p = 2 45 MB 1.00, 90 MB 1.05, 600 MB 1.03, 2.2 GB 1.00; p = 16 90 MB
-//     1.03, 300 MB 1.05, 1.1 GB .96; p = 24 300 MB 1.06, 1.1 GB .99; f32 p = 12 150 MB 1.06, 600 MB .98, 2.2 GB .88; first micro-steps p = 6 600 MB
-//     .97, p = 16 300 MB 1.05).
-//   - Segments, whose ends lie anywhere: p = 4 to 31 as in the second case at any size (bf16 p = 8 400 MB 1.09, p = 16 45 MB 1.10, 200 MB
-//     1.00, 800 MB 1.06; f32 p = 8 45 MB 1.04, 400 MB .99), from 32 on in runs only (bf16 p = 32 400 MB 1.14; p = 64 1.00), up to 3 only below
-//     64 MB (bf16 p = 2 45 MB 1.07, 400 MB .93; f32 400 MB .90), float32 below 1 GB (p = 16 2 GB .93).
+// Whether neighbouring tiles meet in one XCD (tile_of), and on whose lines the vectors lie.  From 640 calls and 400 of segments drawn
+// over p = 1 .. 96, 12 MB .. 2.2 GB, the formats, positions and both kinds of micro-step; speed against the plain order on the
+// gradients' lines:
+//   - Gradients off their lines, each buffer at another position: in runs (bf16, p = 8 64 MB 1.06, 411 MB 1.15; p = 12..16 25..60 MB 1.07;
+//     p = 32 60..120 MB 1.09; p = 96 1.04; f32, p = 8 54 MB 1.23, 436 MB 1.09); below 12 MB the few instructions cost 1 to 2 %.  Not with few
+//     buffers, where the accumulator is most of the traffic: one (bf16, 24 MB .77; f32, 160 MB .81), two and three of f32 off 16
+//     bytes (p = 3 666 MB .88; on 16 bytes p = 2, 3 1.01 to 1.09).
+//   - Gradients on lines, accumulator not: on the accumulator's lines and in runs, so that the gradients' shared lines are found in the
+//     L2 and no accumulator's line is written in parts (bf16, p = 5 321 MB 1.09, runs alone 1.04, 1.2 GB 1.07, .97; p = 8 416 MB 1.10, 1.04;
+//     p = 12..16 300..700 MB 1.06, 1.03, above 700 MB .97, 1.00; f32, p = 8 250 MB 1.03, .92, 1.8 GB .98, .94; p = 24 and more up to 5 % slower).  Not in
+//     runs this loses 1 to 10 %.  If the gradients are then off 16 bytes: p = 12 to 16 runs alone (bf16 120..700 MB 1.01 to 1.03, f32 p = 12 200..450
+//     MB 1.05 to 1.08, p = 16 1.04; above 700 MB 1.00, first micro-steps .96), fewer buffers neither (bf16, p = 8 120 MB and more .97 to 1.00).
+//   - Everything on lines, or many buffers: in runs in the middle of the range (bf16, p = 4 209 MB 1.06, p = 8 231 MB 1.05, p = 12..16 120..300
+//     MB 1.05, 300..700 MB 1.03, above .98; below 60 MB .99 to 1.00; f32, p = 8 124 MB 1.06, p = 12..16 60..120 MB .96, 120..300 MB 1.03, above 700 MB
+//     .97; first micro-steps 120..700 MB 1.01 to 1.03, above .95 to .96).
+//   - Segments, whose ends lie anywhere: in runs, up to 3 buffers below 60 MB only (bf16, p = 2 45 MB 1.07, 150 MB .97, 600 MB .94; f32, p = 3
+//     300..700 MB .84), f32 up to 11 below 300 MB (p = 8 45 MB 1.04, 450 MB .88), from 32 on above 24 MB (f32, p = 32 14 MB .83).  Accumulating, on
+//     the accumulator's lines where that can be (lines / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB 1.02 / 1.00; f32, p = 8
+//     120..300 MB 1.04 / .93), with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05, above 700 MB .98 / 1.03), with more
+//     never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (p = 8 1.00 / 1.03, p = 12..16 .99 / 1.01, p = 24 .97 / 1.00).
 struct ReduceOrder {
     bool in_runs, acc_lines;
 };
-ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, bool grads_on_lines, bool acc_on_lines, bool alignable)
+ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, bool grads_on_lines, bool grads16, const float* lane_acc, bool alignable)
 {
     const size_t mb = count * ((size_t)p * elem_bytes + (accumulate ? 8 : 4)) >> 20;
-    const bool two = elem_bytes == 2;
-    if (!grads_on_lines || (p < 4 && !acc_on_lines)) return {true, false};
+    const bool two = elem_bytes == 2, acc_on_lines = (uintptr_t)lane_acc % 128 == 0;
+    if (!grads_on_lines || (p < 4 && !acc_on_lines))
+        return {mb >= 12 && (p >= 4 || (p > 1 && (two || (grads16 && (uintptr_t)lane_acc % 16 == 0)))), false};
+    const bool below = mb < (two && accumulate ? 700 : 500);
     if (!acc_on_lines && p <= 16) {
-        const bool gains = two && p <= 8 ? mb >= 60 : mb >= 20 && mb < 700;
-        if (alignable && gains) return {true, true};
+        if (alignable && (two && p <= 8 ? mb >= 60 : mb >= 20 && mb < (accumulate ? 700 : 600))) return {true, true};
         if (p < 12) return {false, false};
     }
     const bool few = accumulate ? !two && p < 8 : p < 12;
-    return {!few && mb >= (two ? 80 : 120) && mb < (two && accumulate ? 700 : 500), false};
+    return {!few && mb >= (two ? 80 : 120) && below, false};
 }
-ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb)
+ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb, bool accumulate)
 {
-    if (p < 4) return {mb < 64, false};
-    const bool gains = elem_bytes == 2 || mb < 1000;
-    return {gains && p < 48, gains && p < 32};
+    if (p < 4) return {p > 1 && mb < 60, false};
+    if (elem_bytes == 4 && p < 12 && accumulate && mb >= 300) return {false, false};
+    return {p < 32 || (p < 48 && mb >= 24), accumulate && (p < 12 || (p < 20 && mb >= 60 && mb < 700))};
 }
 
 // Small messages on large groups take the one-dword-per-lane kernels (VEC = 1; of a coalesced call up to kMaxSegMany
@@ -1903,8 +1909,8 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     if (int e = compute_units(&units)) return e;
     const uintptr_t first = (uintptr_t)g.ptr[0] + lead * GB;
     const int other = lead_on_accumulator_lines(acc, first, GB);
-    const ReduceOrder order = reduce_order(p, GB, count, accumulate, line == 128 || on_lines(g, p),
-                                           ((uintptr_t)acc - 4 * (uintptr_t)lead) % 128 == 0, other >= 0);
+    const bool lines = line == 128 || on_lines(g, p);
+    const ReduceOrder order = reduce_order(p, GB, count, accumulate, lines, lines || line >= 16, acc - lead, other >= 0);
     if (order.acc_lines) {
         for (int q = 0; q < p; ++q) g.ptr[q] = (const char*)g.ptr[q] + ((ptrdiff_t)lead - other) * GB;
         pad_table(g, p);
@@ -2173,7 +2179,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         *taken = n = 64;
         elements = elements_of(n);
     }
-    const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20);
+    const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20, accumulate);
     bool acc16 = true;
     for (int t = 0; t < n; ++t) {
         const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
