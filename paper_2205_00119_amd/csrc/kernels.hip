@@ -24,6 +24,7 @@
 //   - fp32 denormals are kept.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <initializer_list>
 #include <type_traits>
@@ -1860,10 +1861,19 @@ ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb, bool accumul
 // and about half of that where the buffers sit at different positions inside their lines, which costs every dword
 // load (bf16, p = 24 12 MB 5.4 / 5.5, 23 MB 8.3 / 7.2; p = 48 21 MB 7.1 / 7.1, 35 MB 10.6 / 9.3; p = 64 31 MB 9.2 / 8.9;
 // p = 128 52 MB 14.5 / 15.2, 67 MB 18.4 / 17.7; f16, p = 128 59 MB 15.6 / 16.6).
-inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line)
+// Few segments change sooner, many as one tensor does (from 32 buffers on): speed against 128 bits a lane, 16 tensors of a layer / 60 of 1 k
+// elements and more: bf16, p = 20 10 MB 1.07 / 1.08, 18 MB .97 / .92, 23 MB .91 / .88; p = 32 10 MB 1.06 / 1.15, 18 MB .88 / 1.13; p = 40 23 MB
+// 1.02 / 1.09, 30 MB .72 / 1.13; p = 48 30 MB 1.18 / 1.22, 50 MB .94 / .95; p = 64 30 MB 1.09 / 1.34, 40 MB .86 / 1.22; p = 128 50 MB 1.01 / 1.34, 60 MB
+// .89 / 1.17; f32, p = 40 18 MB 1.13 / 1.20, 30 MB .92 / 1.00; p = 48 50 MB .87 / 1.04; p = 96 50 MB .96 / 1.19.  22 tensors go with the 60 (p = 32 20 MB 1.25).
+// segments: their number, 0 for one tensor.
+inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line, int segments)
 {
-    const int most = p >= 56 ? (same_line ? (p >= 96 ? 72 : 68) : p / 2) : p >= 48 ? (same_line ? 60 : 25)
-                     : p >= 40 ? (same_line ? 54 : 22) : p >= 20 && elem_bytes == 2 ? (same_line ? 24 : 12) : 0;
+    int most = p >= 56 ? (same_line ? (p >= 96 ? 72 : 68) : p / 2) : p >= 48 ? (same_line ? 60 : 25)
+               : p >= 40 ? (same_line ? 54 : 22) : p >= 20 && elem_bytes == 2 ? (same_line ? 24 : 12) : 0;
+    if (segments && (p < 32 || segments <= 20)) {
+        const int line = p >= 96 ? 50 : p >= 48 ? 31 : p >= 40 ? 24 : p >= 32 ? 12 : 14;
+        most = std::min(most, same_line ? line : line / 2);
+    }
     return count <= ((size_t)most << 20) / ((size_t)p * elem_bytes);
 }
 
@@ -1898,7 +1908,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     unsigned blocks = 0;
     // small message on a large group: one dword per lane and buffer
     constexpr int GB = GradFormat<KIND>::kElemBytes;
-    if (narrow_call(p, GB, count, line >= 16)) {
+    if (narrow_call(p, GB, count, line >= 16, 0)) {
         const Shape narrow = {kNarrowBlock, 0};
         const size_t nlanes = (lead + count + PD - 1) / PD;
         if (int e = grid_for(nlanes, kNarrowBlock, MICS_RSA_BPC, &blocks)) return e;
@@ -2168,7 +2178,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     };
     size_t elements = elements_of(n);
     *taken = n;
-    if (narrow_call(p, GB, elements, line >= 16)) {
+    if (narrow_call(p, GB, elements, line >= 16, n)) {
         const Shape sh = {kNarrowBlock, 0};
         return n <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st)
                        : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st);

@@ -475,3 +475,25 @@ def test_small_accumulators_in_runs_of_tiles(orc, gen, name, p, skews):
                 orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
                 torch.cuda.synchronize()
                 assert same_bits(acc, ref), (count, offset, acc_skew, accumulate)
+
+
+@pytest.mark.parametrize("name,p,mb", [("bf16", 20, 14), ("f16", 32, 12), ("f16", 32, 24), ("f32", 40, 24), ("bf16", 48, 31), ("bf16", 40, 54), ("f32", 96, 50)])
+@pytest.mark.parametrize("n_segs", [5, 20, 21, 70])
+def test_segments_around_the_limit_of_one_dword_per_lane(orc, gen, name, p, mb, n_segs):
+    """MiB of gradients up to which a lane takes one dword of each buffer, for few and for many segments: both sides of each limit,
+    ends anywhere, the segments of unequal sizes."""
+    code, dtype = FORMATS[name]
+    limit = (mb << 20) // (p * np.dtype(dtype).itemsize)
+    small = [3 + t % 40 for t in range(n_segs - 1)]
+    for total in (limit, limit + 1):
+        segs, src, dst = [], 0, 0
+        for n in (*small, total - sum(small)):
+            segs.append((n, 0, src, dst))
+            src, dst = src + n + 1, dst + n
+        host, dev = rank_buffers(gen, name, p, src, [0])
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, dst, skew=1)
+            mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+            orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), (total, accumulate)
