@@ -530,8 +530,8 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
 // Table of up to SEGS (1, or 64 to 128) tensors in the kernel arguments, and the look-up of the tensor whose tiles
 // hold workgroup x: lane i takes entry i, the tensor's index is the number of entries at or below x.  Small calls
 // (ONE_ROUND, 64 entries) have every lane take entry i's record too, so that nothing waits for the index, and so do
-// the large reductions but those of few two-byte buffers, whose wavefronts move too little for 2 KiB of table (16
-// tensors, bf16, p = 4, 79 M elements: 194 us, without 190).  Looked up with scalar instructions, as the large gathers
+// the large reductions but those of up to 8 two-byte buffers, whose wavefronts move too little for 2 KiB of table (16
+// tensors, bf16, p = 4, 79 M elements: 194 us, without 190; p = 6, 335 MB 52.3, 50.7).  Looked up with scalar instructions, as the large gathers
 // do, in three dependent rounds, reductions take 1 to 4 % longer (p = 32, 16 tensors, 3.8 M elements 7 %).
 template <typename Seg, int SEGS>
 struct TileTable {
@@ -1104,7 +1104,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
     constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     unsigned tile;
-    const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 4)>(
+    const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 8)>(
         tab, VEC == 1 ? blockIdx.x : tile_of(blockIdx.x, gridDim.x, how & kInRuns), &tile);
     const size_t end = sg.end, lead = sg.lead;
     float* const dst = acc + sg.dst;
@@ -1778,12 +1778,15 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
 //     (p = 16, 50 M: 344, 64 x 8 350).  Up to 3 two-byte buffers with either off: 256 lanes, uncapped (p = 2,
 //     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5); as segments of a coalesced call, 256 lanes in any
 //     case, from two buffers on 256 x 16 (16 tensors, 64 lanes / so: p = 2, 39 M elements 79.5 / 76.3, p = 3, 67 M 1.08
-//     times the speed).
+//     times the speed), but for the first micro-step of two (p = 2, 19 M elements 23.3 / 26.0).
+//   - Segments with the accumulator off 16 bytes take the shapes of the others, from 4 two-byte and 9 binary32 buffers on: a workgroup of 512
+//     lanes looks its tensor up eight times (16 tensors with odd shards, 512 lanes / so: bf16, p = 5 280 MB 46.7 / 45.1, p = 8 335 MB 54.2 / 52.5; f32,
+//     p = 12 335 MB 57.4 / 53.6; p = 4 100 MB 16.4 / 17.0).
 //   - Below, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
 //     uncapped 28.7).
-Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool segments, size_t units)
+Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, bool segments, size_t units)
 {
-    const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
+    const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 && !(segments && (elem_bytes == 2 ? p >= 4 : p > 8)) ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
     Shape sh;
     if (nlanes < units * many) {
         sh = small_call(nlanes, units);
@@ -1791,6 +1794,7 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
     } else if (grads16) {
         const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
         const bool few = p < 4 && elem_bytes == 2;
+        segments = segments && (accumulate || p != 2);
         sh = Shape{few && (segments || !acc16) ? 256 : 64, few && segments && p > 1 ? 16 : p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
                        p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
     } else {
@@ -1929,7 +1933,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     }
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
-    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, false, units);
+    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, false, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     return dispatch_bool(accumulate, [&](auto A) {
@@ -2195,7 +2199,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
         acc16 = acc16 && ((uintptr_t)(acc + segs[t].dst_offset) - 4 * lead) % 16 == 0;
     }
-    const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, true, units);
+    const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, accumulate, true, units);
     const int policy = accum_policy(elements, p, (int)GB);
     return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st)
                    : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st);
