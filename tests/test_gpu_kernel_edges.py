@@ -477,6 +477,43 @@ def test_small_accumulators_in_runs_of_tiles(orc, gen, name, p, skews):
                 assert same_bits(acc, ref), (count, offset, acc_skew, accumulate)
 
 
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("count", [150_001, 196_608, 196_609, 230_003, 262_144, 262_145])
+@pytest.mark.parametrize("skews", [[0], [0, 8, 16], [3, 0, 5]])
+def test_reduce_of_32_buffers_into_a_small_accumulator(orc, gen, name, count, skews):
+    """Between the calls that take one dword per lane (two-byte buffers at different positions: up to 196608 elements) and the
+    accumulators that do not stay in the L2 (from 262145 on): the loads of a window of 16, held."""
+    code = FORMATS[name][0]
+    host, dev = rank_buffers(gen, name, 32, count + 24, skews)
+    for accumulate in (False, True):
+        ref, acc = start_acc(gen, count)
+        mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], 8, count, accumulate, code)
+        orc.reduce_scatter_accum_typed(ref, host, 8, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
+
+
+@pytest.mark.parametrize("name", list(FORMATS))
+@pytest.mark.parametrize("p", [2, 5, 6, 7, 16])
+@pytest.mark.parametrize("n_segs", [65, 96, 97])
+def test_reduce_of_up_to_96_segments_unrolled(orc, gen, name, p, n_segs):
+    """The unrolled kernels that the any-p ones and those of 1, 3, 4, 8 and 32 buffers above leave out."""
+    code = FORMATS[name][0]
+    segs, src, dst = [], 3, 0
+    for t in range(n_segs):
+        n = (1, 2, 7, 8, 9, 63, 130, 2_000)[(t + 1) % 8]
+        src += t % 5
+        segs.append((n, 0, src, dst))
+        src, dst = src + n, dst + n
+    host, dev = rank_buffers(gen, name, p, src + 3, [0])
+    for accumulate in (False, True):
+        ref, acc = start_acc(gen, dst, skew=1)
+        mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+        orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
+
+
 @pytest.mark.parametrize("name,p,mb", [("bf16", 20, 14), ("f16", 32, 12), ("f16", 32, 24), ("f32", 40, 24), ("bf16", 48, 31), ("bf16", 40, 54), ("f32", 96, 50)])
 @pytest.mark.parametrize("n_segs", [5, 20, 21, 70])
 def test_segments_around_the_limit_of_one_dword_per_lane(orc, gen, name, p, mb, n_segs):
