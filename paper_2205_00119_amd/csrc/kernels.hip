@@ -1651,20 +1651,17 @@ namespace {
 // Vectors per lane (1 or 2) of a call that moves `moved` bytes through reorder_flat_kernel, 0: not its work.  us, flat /
 // the kernels with a workgroup per chunk:
 //   one tensor, 16-byte aligned, p = 16: 0.3 MB 1.82 / 2.22, 8 MB 3.04 / 3.47, 20 MB (two vectors) 5.08 / 5.97, 28 MB 6.6 /
-//   6.9, 36 MB 8.9 / 8.2; not aligned, whose wavefronts at the borders of chunks make a second round trip: 0.1 MB 2.7 / 2.7,
-//   1 MB 2.8 / 3.2, 8 MB 3.0 / 3.4, 11 MB 4.7 / 4.6, 14 MB 5.3 / 5.1
-//   several tensors: not all aligned, p = 16, 4 tensors 27 MiB 9.1 / 7.5, 16 tensors 10.3 / 8.4, 20 MiB equal; all aligned
-//   27 MiB 6.4 / 7.6, 38 MiB equal; large groups, whose tensors are a workgroup per chunk there, p = 96 27 MiB 8.2 / 11.4
-//   and 6.4 / 9.9; more than 48, p = 16, 95 tensors 19 MiB 7.6 / 8.4, 27 MiB 10.9 / 9.6, p = 96 38 MiB 14.7 / 24, 57 MiB 18.4 / 16.8
+//   6.9, 36 MB 8.9 / 8.2 (buffers in the L2: 10 MB 3.0 / 2.75); not aligned, whose wavefronts at the borders of chunks make a second
+//   round trip, never: 0.6 MB 2.35 / 2.05, 4 MB 3.75 / 3.3, 8 MB 4.3 / 4.0
+//   several tensors, not all aligned: 4 of them p = 16 10 MB 1.1 times the speed, 16 MB 1.0, 22 MB 9.0 / 7.1, p = 64 36 MB 13.3 / 9.7; 16 of a
+//   layer p = 16 22 MB 6.5 / 7.3, p = 64 7.4 / 8.4; 40 p = 16 22 MB 1.3, 27 MiB 10.3 / 8.4, p = 64 30 MB 1.55, 36 MB 1.1; all aligned 27 MiB 6.4 / 7.6, 38 MiB equal; more than 48, p = 16, 95
+//   tensors 19 MiB 7.6 / 8.4, 27 MiB 10.9 / 9.6, p = 96 38 MiB 14.7 / 24, 57 MiB 18.4 / 16.8
 int flat_vectors(int n, size_t moved, int p, bool vec16)
 {
     const size_t mb = moved >> 20;
     if (g_blocks_per_cu.load() > 0) return 0;                  // its grid has no cap
-    if (n == 1) {
-        if (vec16 ? mb >= 27 : mb >= 10 || moved < (512u << 10)) return 0;
-        return mb < 16 ? 1 : 2;
-    }
-    const size_t most = p >= 48 ? (n > kMaxSegPerLaunch ? 52 : 36) : n > kMaxSegPerLaunch || !vec16 ? 24 : 36;
+    if (n == 1) return !vec16 || mb >= 27 ? 0 : mb < 16 ? 1 : 2;
+    const size_t most = n > kMaxSegPerLaunch ? (p >= 48 ? 52 : 24) : vec16 ? 36 : n < 16 ? 18 : p >= 48 ? 36 : 24;
     return mb >= most ? 0 : mb < 18 ? 1 : 2;
 }
 

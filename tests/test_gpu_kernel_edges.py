@@ -534,3 +534,27 @@ def test_segments_around_the_limit_of_one_dword_per_lane(orc, gen, name, p, mb, 
             orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
             torch.cuda.synchronize()
             assert same_bits(acc, ref), (total, accumulate)
+
+
+@pytest.mark.parametrize("p,k", [(4, 4), (64, 8)])
+@pytest.mark.parametrize("n_tensors,mb", [(1, 27), (2, 18), (15, 18), (16, 24), (16, 36), (49, 24), (49, 52)])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_gather_on_both_sides_of_the_small_calls(orc, gen, p, k, n_tensors, mb, odd):
+    """MiB moved up to which a gather finds the chunk of every 16 bytes, by the number of tensors, aligned or not: the last ones
+    below each limit and the first above it."""
+    for total in ((mb << 20) // 4 - 8 * n_tensors, (mb << 20) // 4 + 8 * p * n_tensors):
+        each = total // n_tensors // (8 * p) * (8 * p) + odd
+        segs, src, dst_at = [], 0, 0
+        for n in (*[each] * (n_tensors - 1), total - each * (n_tensors - 1) | odd):
+            S = -(-n // p) if odd else -(-n // (8 * p)) * 8
+            segs.append((n, S, src, dst_at))
+            src, dst_at = src + p // k * S, dst_at + n
+        tab = gen.normal_table(1.0, "bf16")
+        T = [gen.fill_host(gen.stream_key(4800 + l, gen.ROLE_PARAM), 0, src, tab) for l in range(k)]
+        T_dev = [Guarded(src, np.uint16, fill=t) for t in T]
+        dst = Guarded(dst_at, np.uint16)
+        want = dst.numpy().copy()
+        orc.hier_gather_reorder_coalesced(T, segs, p, want)
+        mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, 2)
+        torch.cuda.synchronize()
+        assert np.array_equal(dst.numpy(), want) and dst.guards_intact(), total
