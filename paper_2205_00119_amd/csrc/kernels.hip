@@ -1825,7 +1825,9 @@ int lead_on_accumulator_lines(const float* acc, uintptr_t first, size_t elem_byt
 //     MB 1.05, 300..700 MB 1.03, above .98; below 60 MB .99 to 1.00; f32, p = 8 124 MB 1.06, p = 12..16 60..120 MB .96, 120..300 MB 1.03, above 700 MB
 //     .97; first micro-steps 120..700 MB 1.01 to 1.03, above .95 to .96).
 //   - Segments, whose ends lie anywhere: in runs, up to 3 buffers below 60 MB only (bf16, p = 2 45 MB 1.07, 150 MB .97, 600 MB .94; f32, p = 3
-//     300..700 MB .84), f32 up to 11 below 300 MB (p = 8 45 MB 1.04, 450 MB .88), from 32 on above 24 MB (f32, p = 32 14 MB .83).  Accumulating, on
+//     300..700 MB .84), f32 below 1 GB (p = 16 2 GB .93), up to 8 of
+//     them not from 300 to 700 MB if they cannot all be on the accumulator's lines (p = 8 335 MB .93, 447 MB .88, 760 MB 1.09; if they can 335
+//     MB 1.04), from 32 on above 24 MB (f32, p = 32 14 MB .83).  Accumulating, on
 //     the accumulator's lines where that can be (lines / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB 1.02 / 1.00; f32, p = 8
 //     120..300 MB 1.04 / .93), with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05, above 700 MB .98 / 1.03), with more
 //     never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (p = 8 1.00 / 1.03, p = 12..16 .99 / 1.01, p = 24 .97 / 1.00).
@@ -1846,10 +1848,11 @@ ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, b
     const bool few = accumulate ? !two && p < 8 : p < 12;
     return {!few && mb >= (two ? 80 : 120) && below, false};
 }
-ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb, bool accumulate)
+// alignable: all segments can be laid on the accumulator's lines.
+ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb, bool accumulate, bool alignable)
 {
     if (p < 4) return {p > 1 && mb < 60, false};
-    if (elem_bytes == 4 && p < 12 && accumulate && mb >= 300) return {false, false};
+    if (elem_bytes == 4 && (mb >= 1000 || (accumulate && !alignable && p <= 8 && mb >= 300 && mb < 700))) return {false, false};
     return {p < 32 || (p < 48 && mb >= 24), accumulate && (p < 12 || (p < 20 && mb >= 60 && mb < 700))};
 }
 
@@ -2190,7 +2193,10 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         *taken = n = 64;
         elements = elements_of(n);
     }
-    const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20, accumulate);
+    bool alignable = unit * GB == 128;
+    for (int t = 0; t < n; ++t)
+        alignable = alignable && lead_on_accumulator_lines(acc + segs[t].dst_offset, (uintptr_t)g.ptr[0] + (segs[t].src_offset + base_lead) * GB, GB) >= 0;
+    const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20, accumulate, alignable);
     bool acc16 = true;
     for (int t = 0; t < n; ++t) {
         const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
