@@ -783,7 +783,7 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 // `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more instructions,
 // and a small call is over in a few times the latency of what stands in front of its loads.  FIRST: in front of them,
 // in the flat kernels of large calls, where the order is worth a little either way (us, first / behind: flat, p = 16,
-// 50 M elements 303.0 / 304.5; 16 tensors, p = 16, 50 M 309 / 303).
+// 50 M elements 303.0 / 304.5; 16 tensors, p = 16, 50 M 309 / 303).  Windows of loads have it behind the last buffers.
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
 // batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
@@ -1825,16 +1825,18 @@ int lead_on_accumulator_lines(const float* acc, uintptr_t first, size_t elem_byt
 //     MB 1.05, 300..700 MB 1.03, above .98; below 60 MB .99 to 1.00; f32, p = 8 124 MB 1.06, p = 12..16 60..120 MB .96, 120..300 MB 1.03, above 700 MB
 //     .97; first micro-steps 120..700 MB 1.01 to 1.03, above .95 to .96).
 //   - Segments, whose ends lie anywhere: in runs, up to 3 buffers below 60 MB only (bf16, p = 2 45 MB 1.07, 150 MB .97, 600 MB .94; f32, p = 3
-//     300..700 MB .84), f32 below 1 GB (p = 16 2 GB .93), up to 8 of
-//     them not from 300 to 700 MB if they cannot all be on the accumulator's lines (p = 8 335 MB .93, 447 MB .88, 760 MB 1.09; if they can 335
-//     MB 1.04), from 32 on above 24 MB (f32, p = 32 14 MB .83).  Accumulating, on
-//     the accumulator's lines where that can be (lines / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB 1.02 / 1.00; f32, p = 8
-//     120..300 MB 1.04 / .93), with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05, above 700 MB .98 / 1.03), with more
-//     never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (p = 8 1.00 / 1.03, p = 12..16 .99 / 1.01, p = 24 .97 / 1.00).
+//     300..700 MB .84), from 32 on above 24 MB (f32, p = 32 14 MB .83), f32 below 1 GB (p = 16 2 GB .93), up to 8 buffers of f32 not from 300 to
+//     700 MB unless all can be on the accumulator's lines (p = 8 335 MB .93, 447 MB .88, 760 MB 1.09; if they can 335 MB 1.04).
+//     Accumulating, on the accumulator's lines where that can be (lines / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB
+//     1.02 / 1.00; f32, p = 8 120..300 MB 1.04 / .93), with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05,
+//     above 700 MB .98 / 1.03), with more never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (lines / so: p = 8 1.00 /
+//     1.03, p = 12..16 .99 / 1.01, p = 24 .97 / 1.00).
 struct ReduceOrder {
     bool in_runs, acc_lines;
 };
-ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, bool grads_on_lines, bool grads16, const float* lane_acc, bool alignable)
+// lane_acc: the accumulator at the lanes' virtual element 0; alignable: the vectors can be laid on its lines.
+ReduceOrder reduce_order(int p, int elem_bytes, size_t count, bool accumulate, bool grads_on_lines, bool grads16, const float* lane_acc,
+                         bool alignable)
 {
     const size_t mb = count * ((size_t)p * elem_bytes + (accumulate ? 8 : 4)) >> 20;
     const bool two = elem_bytes == 2, acc_on_lines = (uintptr_t)lane_acc % 128 == 0;

@@ -105,9 +105,10 @@ int main()
                 const size_t S = shard + (odd == 2 ? (size_t)t % 2 : odd);
                 many.push_back({2 * S, S, so, dn});
                 so += S; dn += 2 * S;
+                if (t % 7 == 3) many.push_back({0, 8, so, dn});
             }
             const int at = mics::g_launches;
-            CHECK(mics_hier_gather_reorder_coalesced(A, tab.data(), many.data(), n, 2, 2, 2, nullptr) == MICS_OK);
+            CHECK(mics_hier_gather_reorder_coalesced(A, tab.data(), many.data(), (int)many.size(), 2, 2, 2, nullptr) == MICS_OK);
             return mics::g_launches - at;
         };
         CHECK(gathers(16, 64) == 1 && gathers(96, 64) == 1 && gathers(97, 64) == 2 && gathers(192, 64) == 2 && gathers(193, 64) == 3);

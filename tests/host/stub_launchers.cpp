@@ -12,9 +12,15 @@ int launch_reduce_scatter_accum(float*, const PtrTable&, size_t, int, bool, int,
 int launch_replica_average(float*, const PtrTable&, size_t, int, float, void*) { ++g_launches; return 0; }
 int launch_adam(float*, float*, float*, uint16_t*, bool, const float*, size_t, const AdamScalars&, void*) { ++g_launches; return 0; }
 int launch_avg_adam(float*, float*, float*, uint16_t*, bool, const PtrTable&, int, float, size_t, const AdamScalars&, void*) { ++g_launches; return 0; }
-int launch_reorder_coalesced(void*, const PtrTable&, const Segment*, int n, int, int, int, bool, void*)
+bool in_bounds(const Segment* segs, int n)          // the coalesced launchers' precondition
 {
-    if (n < 1 || n > kMaxSegMany) return -1;
+    bool ok = n >= 1 && n <= kMaxSegMany;
+    for (int t = 0; ok && t < n; ++t) ok = segs[t].numel > 0;
+    return ok;
+}
+int launch_reorder_coalesced(void*, const PtrTable&, const Segment* segs, int n, int, int, int, bool, void*)
+{
+    if (!in_bounds(segs, n)) return -1;
     ++g_launches;
     return 0;
 }
@@ -22,7 +28,7 @@ int launch_reorder_coalesced(void*, const PtrTable&, const Segment*, int n, int,
 std::vector<Segment> g_reduced;
 int launch_reduce_coalesced(float*, const PtrTable&, const Segment* segs, int n, int, bool, int, int* taken, void*)
 {
-    if (n < 1 || n > kMaxSegMany) return -1;
+    if (!in_bounds(segs, n)) return -1;
     *taken = n < 64 ? n : 64;
     g_reduced.insert(g_reduced.end(), segs, segs + *taken);
     ++g_launches;
