@@ -340,7 +340,7 @@ def test_a_stream_object_that_raises_or_has_no_handle():
                 mics.mics_replica_average(T[0], T[1:3], 4, 1.0, Stream(raised))
         with pytest.raises(AttributeError, match="cuda_stream"):
             mics.mics_replica_average(T[0], T[1:3], 4, 1.0, "7")
-        assert mics._marshal.average(T[0], T[1:3], 4, 1.0, True) is None         # ctypes' to judge
+        assert mics._marshal.average(T[0], T[1:3], 4, 1.0, True) is None         # left to ctypes
         assert mics._marshal.average(T[0], T[1:3], 4, 1.0, Stream(None)) is None
         assert mics._marshal.reduce_coalesced(T[0], T, (ctypes.c_size_t * 4)(), True, 64) is None
         assert mics._marshal.average(T[0], T[1:3], 4, 10 ** 400, 64) is None
