@@ -26,6 +26,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <initializer_list>
 #include <type_traits>
 
@@ -779,6 +780,49 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
     }
 }
 
+// As rsa_batch for any p, in batches of kShallow (large calls of 16 and more buffers, `shallow_call`).  What counts there is
+// what all wavefronts of a compute unit have in flight together, 8 x 2 to 4 KiB: deeper batches in fewer wavefronts end at the same rate,
+// but a wavefront then lives longer, and with it the end of the call, where units run dry.  The next pointers come while
+// these loads are out.  us, bf16, the best cap for each of 3 / 4 / 6 / 8 / 16 loads: p = 24 350 MB 53.3 / 52.7 / 53.3 / 54.0 / 55.6, 730 MB
+// 109.3 / 107.4 / 109.6 / 111.3 / 115.9; p = 32 159 MB 24.8 / 24.9 / 25.3 / 26.0 / 25.8; p = 64 301 MB 44.6 / 45.5 / 46.0 / 47.8 / 50.1; p = 128 482 MB
+// 73.1 / 71.1 / 76.3 / 76.9 / 80.2; f32, p = 24 325 MB 49.1 / 49.4 / 49.6 / 50.2 / 51.4, p = 64 430 MB 63.0 / 65.1 / 65.8 / 66.7 / 68.6.  A ring of 6 or 8
+// loads that moves on by two is 1 % slower.  The accumulator's loads go out with the last batch.
+constexpr int kShallow = 4;
+template <int KIND, int N, typename Issue>
+__device__ __forceinline__ void rsa_last_batch(float* s, const void* const (&g)[kShallow], int n, size_t elem, Issue&& accumulator)
+{
+    if constexpr (N > 1)
+        if (n < N) return rsa_last_batch<KIND, N - 1>(s, g, n, elem, accumulator);
+    GradVec<KIND, 4> v[N];
+    #pragma unroll
+    for (int b = 0; b < N; ++b) v[b].load(g[b], elem);
+    accumulator();
+    __builtin_amdgcn_sched_barrier(0);
+    #pragma unroll
+    for (int b = 0; b < N; ++b) rsa_add<KIND, 4, false>(s, v[b]);
+}
+template <int KIND, typename Tab, typename Issue>
+__device__ __forceinline__ void rsa_shallow(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
+{
+    static_assert(kMaxGroup % kShallow == 0, "a batch of pointers is inside the table");
+    const void* next[kShallow];
+    #pragma unroll
+    for (int b = 0; b < kShallow; ++b) next[b] = g.ptr[b];
+    int q0 = 0;
+    #pragma unroll 1
+    for (; q0 + kShallow < p; q0 += kShallow) {
+        GradVec<KIND, 4> v[kShallow];
+        #pragma unroll
+        for (int b = 0; b < kShallow; ++b) v[b].load(next[b], elem);
+        #pragma unroll
+        for (int b = 0; b < kShallow; ++b) next[b] = g.ptr[q0 + kShallow + b];
+        __builtin_amdgcn_sched_barrier(0);
+        #pragma unroll
+        for (int b = 0; b < kShallow; ++b) rsa_add<KIND, 4, false>(s, v[b]);
+    }
+    rsa_last_batch<KIND, kShallow>(s, next, p - q0, elem, accumulator);
+}
+
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
 // `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more instructions,
 // and a small call is over in a few times the latency of what stands in front of its loads.  FIRST: in front of them,
@@ -800,9 +844,7 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         // The accumulator's loads go out behind the last gradients: in front, or behind the first window, they are one of the
         // few in flight while nothing needs them (us, p = 32, in front / behind the first / behind the last: f32 45 MB 9.0 / 9.2 /
         // 8.6, 2 GB 302 / 302 / 295; f16 45 MB 9.9 / 9.9 / 9.2, 200 MB 34.7 / 34.7 / 32.6, 900 MB 142.7 / 142.8 / 138.5).
-        // W = 4 where BATCH asks for it (short_window) and for 16 buffers, else 6: us, f32, p = 32, 4 / 6, 75 MB 12.7 / 13.5, 900 MB
-        // 141.7 / 138, first micro-step 75 MB 12.5 / 13.4, 900 MB 150 / 138; f16 75 MB 12.35 / 12.3, 2 GB 316 / 309.
-        constexpr int W = HOLD ? 16 : P == 16 || BATCH == 4 ? 4 : 6, STEP = HOLD ? 4 : 2;
+        constexpr int W = HOLD ? 16 : P == 16 ? 4 : 6, STEP = HOLD ? 4 : 2;
         static_assert((P - W) % STEP == 0, "");
         GradVec<KIND, VEC> v[W];
         #pragma unroll
@@ -851,6 +893,7 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         constexpr int PAD = VEC == 1 ? 8 : 1;
         #pragma unroll
         for (int e = 0; e < VEC * GradFormat<KIND>::kPerDword; ++e) s[e] = -0.0f;
+        if constexpr (BATCH == kShallow) return rsa_shallow<KIND>(s, g, p, elem, accumulator);
         accumulator();
         int q0 = 0;
         for (; q0 + BATCH <= p; q0 += BATCH) rsa_batch<KIND, VEC, BATCH, 1>(s, g, q0, BATCH, elem);
@@ -1062,13 +1105,13 @@ __device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
 // OTHER: a kernel's other form, with CACHED tiles in runs (of the others `how` says whether: tile_of's few instructions are
-// 1 % of a small call), else the window of 4 (short_window).
+// 1 % of a small call), else shallow batches (shallow_call).
 template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool OTHER, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kernel(
     Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
     const auto& g = table_view(tab);
-    constexpr int BATCH = VEC == 1 ? 64 : OTHER && !CACHED ? 4 : MICS_RSA_BATCH;
+    constexpr int BATCH = VEC == 1 ? 64 : OTHER && !CACHED ? kShallow : MICS_RSA_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const size_t end = (size_t)lead + count;
     const size_t nlanes = (end + EPL - 1) / EPL;
@@ -1457,10 +1500,10 @@ int launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStrea
 // request streams at the memory controllers.  Measured on MI355X (GB/s of algorithmic bytes; lanes
 // x wavefronts per compute unit, 32 = no cap; 50 M elements):
 //   reorder (3.2 GB)  256x32 6335  64x32 6580  64x16 5990  64x8  3860
-//   average r = 2                  64x32 6540  64x16 6470  64x12 6200
-//   average r = 8     512x32 5935  64x32 6325  64x10 6580  64x8  6650
-//   Adam              128x32 6040  64x32 5965  64x12 6670  64x10 6630
-//   average + Adam, r = 8          64x12 6290  64x8  6530  64x6  6740
+//   average r = 2                  64x32 6540  64x16 6470  64x11 6200
+//   average r = 8     512x32 5935  64x32 6325  64x9 6580  64x8  6650
+//   Adam              128x32 6040  64x32 5965  64x11 6670  64x9 6630
+//   average + Adam, r = 8          64x11 6290  64x8  6530  64x5  6740
 // The cap is enforced with otherwise unused dynamic LDS: a workgroup that asks for 1/n of a
 // compute unit's LDS shares the unit with at most n - 1 others.
 struct Shape {
@@ -1541,8 +1584,8 @@ int average_store(int r, size_t count, bool streamed)
 }
 
 // The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
-// 64x16 14.9, r = 8 at 151 MB 27.3, 64x10 26.1; average + Adam at 143 MB 25.5, 64x10 26.1, at 334 MB
-// 55.8, 52.9, r = 8 at 122 MB 22.3, 64x10 22.9, at 243 MB 48.3, 45.3; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
+// 64x16 14.9, r = 8 at 151 MB 27.3, 64x9 26.1; average + Adam at 143 MB 25.5, 64x9 26.1, at 334 MB
+// 55.8, 52.9, r = 8 at 122 MB 22.3, 64x9 22.9, at 243 MB 48.3, 45.3; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
 Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 4), nlanes = (count + 3) / 4;
@@ -1551,25 +1594,25 @@ Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units
     // few copies, few loads in flight per lane: every wavefront that fits
     if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
     if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call(nlanes, units));
-    // 4 copies, caps of 16 / 12: 450 MB 67 / 68 us, 600 MB 97 / 93, 1.1 GB 176 / 165, streamed 1.5 GB 232 / 254; 5 copies:
+    // 4 copies, caps of 16 / 11: 450 MB 67 / 68 us, 600 MB 97 / 93, 1.1 GB 176 / 165, streamed 1.5 GB 232 / 254; 5 copies:
     // 150 MB 24.4 / 25.1, 300 MB 46.8 / 46.0, 1.1 GB 174 / 165, streamed 2.5 GB 389 / 367
     const bool wide = r < 5 ? traffic < (500u << 20) || streamed : traffic < (250u << 20);
-    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 10 : wide ? 16 : 12});
+    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 9 : wide ? 16 : 11});
 }
 
-Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 12}); }
+Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 11}); }
 
 Shape fused_shape(int r, size_t count, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 26);
     if (!lines) return with_knobs(kFamFused, off_lines((count + 3) / 4, units));
-    if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 10});
+    if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 9});
     if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
-    if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 7 : 5});
-    // us at 50 M elements with caps of 7 / 8 / 10 / 12: r = 3 386 / 317 / 297 / 284, r = 4 322 / 319 / 324 / 327, r = 5 408 / 349 /
+    if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 6 : 4});
+    // us at 50 M elements with caps of 6 / 8 / 9 / 11: r = 3 386 / 317 / 297 / 284, r = 4 322 / 319 / 324 / 327, r = 5 408 / 349 /
     // 342 / 358, r = 6 422 / 372 / 379 / 392, r = 7 436 / 406 / 419 / 430; within 1 % of that order from 10 to 100 M
-    constexpr int kCap[8] = {0, 12, 10, 12, 8, 10, 8, 8};
-    return with_knobs(kFamFused, Shape{64, r < 8 ? kCap[r] : 6});
+    constexpr int kCap[8] = {0, 11, 9, 11, 8, 9, 8, 8};
+    return with_knobs(kFamFused, Shape{64, r < 8 ? kCap[r] : 5});
 }
 
 Shape reorder_shape(size_t traffic, int lanes)
@@ -1578,16 +1621,17 @@ Shape reorder_shape(size_t traffic, int lanes)
 }
 
 // Dynamic LDS that keeps the wavefronts of `sh` on a compute unit at or below its cap, at least
-// `needed` bytes (what the kernel itself uses).  Without an opt-in a workgroup gets at most
-// 64 KiB, so the cap cannot go below 3 workgroups per compute unit.
+// `needed` bytes (what the kernel itself uses).  A workgroup's LDS is handed out in pieces of 1280 bytes (counted on the
+// chip: 16384 bytes a workgroup leave room for 9, 14848 for 10), so that 13, 15, 17, 19 and 20 workgroups cannot be had.  Without
+// an opt-in a workgroup gets at most 64 KiB, so the cap cannot go below 2 workgroups per compute unit.
 size_t lds_for(const Shape& sh, size_t needed = 0)
 {
-    constexpr size_t kLdsPerCu = 160u << 10, kMaxDynamic = 64u << 10;
+    constexpr size_t kLdsPerCu = 160u << 10, kPiece = 1280, kMaxDynamic = (64u << 10) / kPiece * kPiece;
     const int waves_per_wg = sh.lanes / 64;
     if (sh.waves_per_cu <= 0 || sh.waves_per_cu / waves_per_wg >= 32) return needed;
     size_t wgs = (size_t)sh.waves_per_cu / (size_t)waves_per_wg;
     if (wgs < 1) wgs = 1;
-    size_t bytes = (kLdsPerCu / wgs) & ~(size_t)255;
+    size_t bytes = kLdsPerCu / wgs / kPiece * kPiece;
     if (bytes > kMaxDynamic) bytes = kMaxDynamic;
     return bytes > needed ? bytes : needed;
 }
@@ -1761,43 +1805,90 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
     return (unsigned)(back / (uintptr_t)elem_bytes);
 }
 
-// Launch shape of a reduction over p buffers with `nlanes` lanes of work.  Measured per call on
-// buffers that rotate through 1 GB, p = 1 .. 128, 16 MB .. 1.6 GB of traffic, three formats; the lines
+// Launch shape of a reduction over p buffers with `nlanes` lanes of work that is not read in shallow batches.  Measured per call on
+// buffers that rotate through 1 GB, p = 1 .. 128, 16 MB .. 2.4 GB of traffic, three formats; the lines
 // below lie where the best shape changes, and the shapes next to the chosen one lose 1 to 3 %.
-//   - From some 0.8 M lanes on, single-wavefront workgroups with a cap on the wavefronts of a compute
-//     unit that falls with the buffers a lane reads: what counts is the number of request streams
-//     (p = 8, 33 M elements: 64 x 10 121 us, 512 x 32 129; p = 32, 11 M: 64 x 6 132, 64 x 16 143,
-//     512 x 32 149).  The line moves down for 32 and more buffers (0.6 M; p = 32, 5.6 M elements: 64 x 6
-//     71, 512 x 32 74), up for 12 to 24 buffers of 2-byte elements (1.2 M; p = 12, 7.8 M elements:
-//     64 x 10 44.5, 512 x 32 42.9), and up again where the accumulator is off 16 bytes in the lanes'
-//     grid, because the partial lines between two wavefronts then meet in one workgroup (2 M for p < 16;
-//     p = 8, 9.8 M: 64 x 10 40.7, 512 x 32 39.2; 30 M: 114, 119).  Gradients off 16 bytes: 512 x 16
-//     (p = 16, 50 M: 344, 64 x 8 350).  Up to 3 two-byte buffers with either off: 256 lanes, uncapped (p = 2,
+//   - Small calls, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
+//     uncapped 28.7).
+//   - One tensor, 4 buffers and more: from 25 wavefronts per compute unit on, single-wavefront workgroups with a cap on the
+//     wavefronts of a unit that falls with the buffers a lane reads: what counts is the number of request streams.  Wherever the
+//     buffers lie: us, 512 lanes uncapped (gradients off 16 bytes: capped at 16) / so: bf16, p = 4, odd rows 59 MB 11.1 / 10.8, 179 MB 29.5 / 26.9; p = 5, odd
+//     rows 99 MB 17.3 / 16.6; p = 6, odd rows 218 MB 34.3 / 32.1; p = 8, 99 MB 16.9 / 16.1, odd rows 218 MB 34.3 / 32.2; p = 12, 149 MB 24.8 / 23.9, accumulator
+//     off 348 MB 54.5 / 52.1; f32, p = 5, 54 MB 10.0 / 9.1; p = 8, 82 MB 14.7 / 13.6, accumulator off 290 MB 46.5 / 44.8; p = 10, accumulator off
+//     153 MB 27.3 / 25.4.  (17 to 25 wavefronts per unit: f32, p = 8, accumulator off 58 MB 9.8 / 10.6.)  Four two-byte buffers on their lines with the
+//     accumulator off need more of them, because the partial lines between two wavefronts then meet in one workgroup (bf16, 99 MB 16.8 / 17.4,
+//     497 MB 82.4 / 82.2).  First micro-steps take more wavefronts (bf16, p = 4, 129 MB caps of 14 / 16 17.0 / 16.7; p = 8, 149 MB 10 / 11 21.1 / 20.6), and fewer again
+//     from 200 per unit on (p = 8, 995 MB 10 / 7 135.5 / 128.2; p = 12, 2.2 GB 9 / 6 299 / 292; f32, p = 12, 1.9 GB 276 / 269.5), as do long calls that
+//     accumulate (f32, p = 4, 1.1 GB 14 / 11 176.5 / 171.6; p = 6, 1.2 GB 12 / 10 184.8 / 180.7; p = 8, 1.2 GB 10 / 8 191.4 / 187.5).
+//   - Up to 3 two-byte buffers with either off 16 bytes: 256 lanes, uncapped (p = 2,
 //     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5); as segments of a coalesced call, 256 lanes in any
 //     case, from two buffers on 256 x 16 (16 tensors, 64 lanes / so: p = 2, 39 M elements 79.5 / 76.3, p = 3, 67 M 1.08
 //     times the speed), but for the first micro-step of two (p = 2, 19 M elements 23.3 / 26.0).
-//   - Segments with the accumulator off 16 bytes take the shapes of the others, from 4 two-byte and 9 binary32 buffers on: a workgroup of 512
-//     lanes looks its tensor up eight times (16 tensors with odd shards, 512 lanes / so: bf16, p = 5 280 MB 46.7 / 45.1, p = 8 335 MB 54.2 / 52.5; f32,
+//   - Segments change to single wavefronts later: from some 0.8 M lanes, 0.6 M from 32 buffers on (p = 32, 5.6 M elements: 64 x 5
+//     71, 512 x 32 74), 1.2 M for 12 to 24 buffers of 2-byte elements, 2 M with the accumulator off 16 bytes below 4 two-byte and 9 binary32 buffers: a workgroup
+//     of 512 lanes looks its tensor up eight times (16 tensors with odd shards, 512 lanes / 64: bf16, p = 5 280 MB 46.7 / 45.1, p = 8 335 MB 54.2 / 52.5; f32,
 //     p = 12 335 MB 57.4 / 53.6; p = 4 100 MB 16.4 / 17.0).
-//   - Below, see small_call; single-wavefront workgroups are capped at 16 here (p = 24, 2.7 M: 28.2 us,
-//     uncapped 28.7).
+int reduce_cap(int p, bool two, size_t nlanes, bool accumulate, size_t units)
+{
+    const size_t per_unit = nlanes / (64 * units);
+    const bool many = per_unit >= (!accumulate ? 200 : two ? 1500 : 350);
+    if (p < 6) return accumulate ? (many ? 11 : two ? 14 : 16) : p > 4 ? 16 : many && !two ? 14 : 0;
+    if (p < 8) return accumulate ? (many ? 10 : 12) : many ? 11 : 14;
+    if (p < 12) return accumulate ? (many ? 8 : 10) : many ? (two ? 7 : 9) : 11;
+    return accumulate ? (many ? 7 : 8) : many ? (two ? 6 : 7) : 10;
+}
 Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, bool segments, size_t units)
 {
-    const size_t many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 && !(segments && (elem_bytes == 2 ? p >= 4 : p > 8)) ? 8000 : p >= 12 && elem_bytes == 2 ? 4700 : 3200;
+    const bool two = elem_bytes == 2;
+    size_t many = p < 6 ? 1600 : 1800;
+    if (segments || p < 4 || (p == 4 && two && grads16 && !acc16))
+        many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 && !(segments && (two ? p >= 4 : p > 8)) ? 8000 : p >= 12 && two ? 4700 : 3200;
     Shape sh;
     if (nlanes < units * many) {
         sh = small_call(nlanes, units);
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
+    } else if (!segments && p >= 4) {
+        sh = !two && !grads16 && p > 4 && p < 8 && nlanes >= units * 9600 ? Shape{kMaxBlock, 16} : Shape{64, reduce_cap(p, two, nlanes, accumulate, units)};
     } else if (grads16) {
         const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
-        const bool few = p < 4 && elem_bytes == 2;
+        const bool few = p < 4 && two;
         segments = segments && (accumulate || p != 2);
-        sh = Shape{few && (segments || !acc16) ? 256 : 64, few && segments && p > 1 ? 16 : p < 4 ? 0 : p < 6 ? (huge ? 12 : 16) : p < 8 ? 14 :
-                       p < 16 ? (huge ? 8 : 10) : p < 32 ? (huge ? 5 : 8) : 6};
+        sh = Shape{few && (segments || !acc16) ? 256 : 64, few && segments && p > 1 ? 16 : p < 4 ? 0 : p < 6 ? (huge ? 11 : 16) : p < 8 ? 14 :
+                       p < 16 ? (huge ? 8 : 9) : p < 32 ? (huge ? 4 : 8) : 5};
     } else {
-        sh = p < 4 && elem_bytes == 2 ? Shape{256, 0} : Shape{kMaxBlock, 16};
+        sh = p < 4 && two ? Shape{256, 0} : Shape{kMaxBlock, 16};
     }
     return with_knobs(kFamReduce, sh);
+}
+
+// Whether a reduction past the L2 reads its buffers in shallow batches (rsa_shallow): from 16 buffers on, if a compute unit gets wavefronts
+// enough, as it does wherever the accumulator of up to 31 does not stay in the L2.
+// us, batches of 16 / so, wavefronts per unit in front: p = 32 7 11.7 / 12.2, 8 13.1 / 12.9, f32 7 11.2 / 11.4, 9 13.1 / 12.9; p = 48 5.2 13.2 / 13.3,
+// 6.3 15.2 / 14.1; p = 64 5.2 16.5 / 16.3; p = 128 4.2 27.3 / 27.6, 5.2 29.5 / 29.4, 6.3 34.8 / 32.1.
+bool shallow_call(int p, size_t nlanes, size_t units) { return p >= 16 && (p < 32 || nlanes >= units * (p < 48 ? 512 : 352)); }
+
+// A call's wavefronts start together and read the same number of bytes, so they end together too: a compute unit goes through
+// them in rounds of as many as it holds, and a last round that is half empty costs almost as much as a full one.  So the cap
+// is the one that leaves the least of the last round empty, beside what a cap costs in calls of many rounds.  us, bf16, p = 128, 17 wavefronts per unit
+// (585 MB), caps of 6 / 7 / 8 / 9 / 10 / 12 / 16: 89.7 / 93.7 / 101.8 / 87.8 / 90.1 / 97.9 / 101.9; p = 64, 20 per unit (354 MB) 60.0 / 53.5 / 56.3 / 60.1 /
+// 54.6 / 56.2 / 57.4; p = 24, 70 per unit (511 MB) 82.8 / 79.3 / 75.9 / 79.3 / 79.2 / 79.7 / 78.6.  An empty round costs about 0.4 of a full one.
+// All in one round is as good up to 12 per unit (p = 64, 11: 30.3, two rounds 31.3; 14: 38.9, two 37.8; odd rows, 13: 39.5, 36.5).
+Shape shallow_shape(int p, size_t nlanes, size_t units)
+{
+    // {waves, cost up to 48 buffers, from 64 on, from 64 on in calls of 46 and more wavefronts per unit}
+    static constexpr struct { int waves; double cost[3]; } kCaps[] = {
+        {6, {.06, .02, 0}}, {7, {.04, 0, .01}}, {8, {0, 0, .025}}, {9, {.04, .012, .035}}, {10, {.035, .025, .05}}, {11, {.04, .03, .06}},
+        {12, {.035, .035, .06}}, {14, {.035, .04, .07}}, {16, {.03, .04, .07}}};
+    const double per_unit = (double)((nlanes + 63) / 64) / (double)units;
+    const int column = p < 64 ? 0 : per_unit < 46 ? 1 : 2;
+    int best = 8;
+    double least = 1e9;
+    for (const auto& c : kCaps) {
+        const double rounds = per_unit / c.waves;
+        const double cost = rounds > 1 ? .4 * (std::ceil(rounds) / rounds - 1) + c.cost[column] : per_unit <= 12 ? .03 : .085;
+        if (cost < least) least = cost, best = c.waves;
+    }
+    return with_knobs(kFamReduce, Shape{64, best});
 }
 
 // Where the gradients are at one position inside their lines and the accumulator is at another, the lanes' vectors can be laid
@@ -1897,14 +1988,6 @@ int rsa_launch(float* acc, const PtrTable& g, int p, unsigned lead, size_t count
                       acc, p, lead, count, how);
 }
 
-// Whether 32 binary32 buffers are read with 4 instead of 6 loads in flight.  us, 4 / 6 (accumulating, first micro-step): 45 MB 8.6 /
-// 8.7, 8.45 / 8.55; 75 MB 12.7 / 13.5, 12.5 / 13.4; 90 MB 15.3 / 15.8, 15.2 / 15.8; 110 MB 19.3 / 18.7; 200 MB 31.7 / 31.7, 33.5 / 32.4; 900
-// MB 141.7 / 138, 150 / 138.
-bool short_window(int kind, int p, size_t count, bool accumulate)
-{
-    return kind == 2 && p == 32 && count * (accumulate ? 136 : 132) < (size_t{100} << 20);
-}
-
 template <int KIND>
 int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate, hipStream_t st)
 {
@@ -1935,9 +2018,10 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     }
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
-    const Shape sh = reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, false, units);
-    if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
+    const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units);
+    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, false, units);
+    if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         if (policy == kAccCached)
             return dispatch_bool(order.in_runs, [&](auto R) {
@@ -1945,11 +2029,10 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
                     return rsa_launch<KIND, 4, P.value, A.value, true, (R.value && P.value != 1)>(acc, g, p, lead, count, blocks, sh, how, st);
                 });
             });
-        if constexpr (KIND == 2)
-            if (short_window(KIND, p, count, accumulate))
-                return rsa_launch<KIND, 4, 32, A.value, false, true>(acc, g, p, lead, count, blocks, sh, how, st);
+        if (shallow) return rsa_launch<KIND, 4, 0, A.value, false, true>(acc, g, p, lead, count, blocks, sh, how, st);
         return dispatch_group(p, [&](auto P) {
-            return rsa_launch<KIND, 4, P.value, A.value, false>(acc, g, p, lead, count, blocks, sh, how, st);
+            constexpr int N = P.value == 16 ? 0 : P.value;             // 16 are always read in shallow batches
+            return rsa_launch<KIND, 4, N, A.value, false>(acc, g, p, lead, count, blocks, sh, how, st);
         });
     });
 }

@@ -445,7 +445,7 @@ def test_launches_of_coalesced_gathers(n_tensors, shard, launches, odd):
 
 @pytest.mark.parametrize("name,count", [("f32", 262_147), ("f32", 771_011), ("f32", 771_012), ("f32", 794_376), ("f32", 794_377), ("f16", 794_377)])
 def test_reduce_of_32_buffers_through_either_window(orc, gen, name, count):
-    """Both sides of the line between 4 and 6 loads in flight (100 MiB moved), the accumulator on the lanes' lines and off them."""
+    """The window of 6 loads in flight and, from 8 wavefronts per compute unit on, batches of 4; the accumulator on the lanes' lines and off them."""
     code = FORMATS[name][0]
     host, dev = rank_buffers(gen, name, 32, count + 8, [0])
     for offset, skew in ((0, 0), (5, 3)):
@@ -558,3 +558,25 @@ def test_gather_on_both_sides_of_the_small_calls(orc, gen, p, k, n_tensors, mb, 
         mics.mics_hier_gather_reorder_coalesced(dst.t, [t.t for t in T_dev], segs, p, k, 2)
         torch.cuda.synchronize()
         assert np.array_equal(dst.numpy(), want) and dst.guards_intact(), total
+
+
+@pytest.mark.parametrize("name,p,count", [
+    ("bf16", 16, 5_003), ("f16", 16, 2_097_153), ("f32", 17, 3_001), ("bf16", 18, 2_100_011), ("f16", 19, 1_033), ("f32", 24, 70_001), ("bf16", 31, 20_011),
+    ("bf16", 32, 1_048_513), ("bf16", 32, 1_048_577), ("f32", 33, 524_289), ("bf16", 47, 1_048_577), ("bf16", 48, 720_961), ("f16", 50, 720_897),
+    ("f32", 67, 360_449), ("f16", 127, 720_905), ("bf16", 128, 720_897)])
+def test_reduce_in_shallow_batches(orc, gen, name, p, count):
+    """Every remainder of the batches of 4, the largest group, and both sides of the number of wavefronts from which they are taken
+    (up to 31 buffers: any number, where the accumulator passes the L2); gradients on one line, on several and odd, accumulator off."""
+    code = FORMATS[name][0]
+    for skews, acc_skew in (([0], 0), ([5], 3), ([0, 8], 1), ([3, 0, 6], 0)):
+        host, dev = rank_buffers(gen, name, p, count + 6, skews)
+        for threshold, offset, accumulate in ((1, 0, True), (0, 6, False)):
+            try:
+                mics.mics_set_stream_threshold_bytes(threshold)
+                ref, acc = start_acc(gen, count, skew=acc_skew)
+                mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], offset, count, accumulate, code)
+                orc.reduce_scatter_accum_typed(ref, host, offset, accumulate, code)
+                torch.cuda.synchronize()
+                assert same_bits(acc, ref), (skews, acc_skew, accumulate)
+            finally:
+                mics.mics_set_stream_threshold_bytes(0)
