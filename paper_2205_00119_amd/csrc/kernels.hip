@@ -1139,16 +1139,28 @@ struct ReduceSeg {
 };
 template <int SEGS> using ReduceTable = TileTable<ReduceSeg, SEGS>;
 
-template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, int SEGS, typename Tab>
+// Whether a segment's ends get a workgroup of their own in front of the tiles, because a tile would wait for too many of its loads one
+// after another: 16 tensors, p = 96, 64 MB 18.5 / 15.9 us, f32 68 tensors 194 MB 45.2 / 40.9.  Not with up to 8 buffers, where the additional
+// branch costs more (p = 2, 75 MB 13.9 / 14.4; f32, p = 4, 75 MB 2.5 %), nor with 32 (28 MB 3 %).
+template <int P, bool CACHED> constexpr bool kEdgeGroups = !CACHED && P == 0;
+template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHALLOW, int SEGS, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_kernel(
-    Tab gtab, float* __restrict__ acc, int p, ReduceTable<SEGS> tab, int how)
+    Tab gtab, float* __restrict__ acc, int p, ReduceTable<SEGS> tab, int how, unsigned edges)
 {
     const auto& g = table_view(gtab);
-    constexpr int BATCH = VEC == 4 ? MICS_RSA_BATCH : 64;
+    constexpr int BATCH = VEC == 1 ? 64 : SHALLOW ? kShallow : MICS_RSA_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
-    unsigned tile;
+    unsigned tile, x = blockIdx.x;
+    if constexpr (kEdgeGroups<P, CACHED>) {
+        if (x < edges) {                               // workgroup x does nothing but the ends of segment x
+            const ReduceSeg& sg = tab.seg[x];
+            rsa_edges<KIND, EPL, P, ACCUM>(acc + sg.dst, g, p, sg.src0, sg.lead, sg.end);
+            return;
+        }
+        x -= edges;
+    }
     const ReduceSeg sg = segment_at<(CACHED || KIND == 2 || P == 0 || P > 8)>(
-        tab, VEC == 1 ? blockIdx.x : tile_of(blockIdx.x, gridDim.x, how & kInRuns), &tile);
+        tab, VEC == 1 ? x : tile_of(x, kEdgeGroups<P, CACHED> ? gridDim.x - edges : gridDim.x, how & kInRuns), &tile);
     const size_t end = sg.end, lead = sg.lead;
     float* const dst = acc + sg.dst;
     if constexpr (CACHED) {
@@ -1156,8 +1168,8 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
             rsa_short<KIND, P, ACCUM>(dst, g, p, sg.src0, lead, end);
             return;
         }
-    } else if (tile == 0) {
-        rsa_edges<KIND, EPL, P, ACCUM>(dst, g, p, sg.src0, lead, end);
+    } else if constexpr (!kEdgeGroups<P, CACHED>) {
+        if (tile == 0) rsa_edges<KIND, EPL, P, ACCUM>(dst, g, p, sg.src0, lead, end);
     }
     const size_t v0 = ((size_t)tile * blockDim.x + threadIdx.x) * EPL;
     rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, false, CACHED>(dst, g, p, sg.src0, v0, lead, end, how & ~kInRuns);
@@ -1431,7 +1443,7 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 int accum_policy(size_t count, int p, int elem_bytes)
 {
     constexpr size_t kSmall = 64u << 20;
-    const size_t cached = p < 4 && elem_bytes == 2 ? 7u << 20 : p < 12 ? 12u << 20 : p < 32 ? 8u << 20 : 1u << 20;
+    const size_t cached = p < 4 && elem_bytes == 2 ? 7u << 20 : p < 12 ? 12u << 20 : p < 16 ? 8u << 20 : p < 32 ? (elem_bytes == 2 ? 8u : 4u) << 20 : 1u << 20;
     if (stream_acc(count)) return kAccStreamed;
     if (count * 4 <= cached) return kAccCached;
     if (g_stream_bytes.load() == 0 && p >= 32 && count * 4 > kSmall) return kAccStreamed;
@@ -1821,13 +1833,7 @@ unsigned align_gradient_pointers(PtrTable& g, int p, int elem_bytes, unsigned* l
 //     from 200 per unit on (p = 8, 995 MB 10 / 7 135.5 / 128.2; p = 12, 2.2 GB 9 / 6 299 / 292; f32, p = 12, 1.9 GB 276 / 269.5), as do long calls that
 //     accumulate (f32, p = 4, 1.1 GB 14 / 11 176.5 / 171.6; p = 6, 1.2 GB 12 / 10 184.8 / 180.7; p = 8, 1.2 GB 10 / 8 191.4 / 187.5).
 //   - Up to 3 two-byte buffers with either off 16 bytes: 256 lanes, uncapped (p = 2,
-//     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5); as segments of a coalesced call, 256 lanes in any
-//     case, from two buffers on 256 x 16 (16 tensors, 64 lanes / so: p = 2, 39 M elements 79.5 / 76.3, p = 3, 67 M 1.08
-//     times the speed), but for the first micro-step of two (p = 2, 19 M elements 23.3 / 26.0).
-//   - Segments change to single wavefronts later: from some 0.8 M lanes, 0.6 M from 32 buffers on (p = 32, 5.6 M elements: 64 x 5
-//     71, 512 x 32 74), 1.2 M for 12 to 24 buffers of 2-byte elements, 2 M with the accumulator off 16 bytes below 4 two-byte and 9 binary32 buffers: a workgroup
-//     of 512 lanes looks its tensor up eight times (16 tensors with odd shards, 512 lanes / 64: bf16, p = 5 280 MB 46.7 / 45.1, p = 8 335 MB 54.2 / 52.5; f32,
-//     p = 12 335 MB 57.4 / 53.6; p = 4 100 MB 16.4 / 17.0).
+//     67 M: 127, 512 x 16 136; accumulator 4 bytes off, 17 M: 33.3, 64 lanes 34.5).
 int reduce_cap(int p, bool two, size_t nlanes, bool accumulate, size_t units)
 {
     const size_t per_unit = nlanes / (64 * units);
@@ -1837,26 +1843,50 @@ int reduce_cap(int p, bool two, size_t nlanes, bool accumulate, size_t units)
     if (p < 12) return accumulate ? (many ? 8 : 10) : many ? (two ? 7 : 9) : 11;
     return accumulate ? (many ? 7 : 8) : many ? (two ? 6 : 7) : 10;
 }
-Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, bool segments, size_t units)
+Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, size_t units)
 {
     const bool two = elem_bytes == 2;
     size_t many = p < 6 ? 1600 : 1800;
-    if (segments || p < 4 || (p == 4 && two && grads16 && !acc16))
-        many = p >= 64 ? 2000 : p >= 32 ? 2400 : !acc16 && p < 16 && !(segments && (two ? p >= 4 : p > 8)) ? 8000 : p >= 12 && two ? 4700 : 3200;
+    if (p < 4 || (p == 4 && two && grads16 && !acc16)) many = !acc16 ? 8000 : 3200;
     Shape sh;
     if (nlanes < units * many) {
         sh = small_call(nlanes, units);
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
-    } else if (!segments && p >= 4) {
+    } else if (p >= 4) {
         sh = !two && !grads16 && p > 4 && p < 8 && nlanes >= units * 9600 ? Shape{kMaxBlock, 16} : Shape{64, reduce_cap(p, two, nlanes, accumulate, units)};
     } else if (grads16) {
-        const bool huge = nlanes * (16 / (size_t)elem_bytes) >= kHugeElements;
-        const bool few = p < 4 && two;
-        segments = segments && (accumulate || p != 2);
-        sh = Shape{few && (segments || !acc16) ? 256 : 64, few && segments && p > 1 ? 16 : p < 4 ? 0 : p < 6 ? (huge ? 11 : 16) : p < 8 ? 14 :
-                       p < 16 ? (huge ? 8 : 9) : p < 32 ? (huge ? 4 : 8) : 5};
+        sh = Shape{two && !acc16 ? 256 : 64, 0};
     } else {
+        sh = two ? Shape{256, 0} : Shape{kMaxBlock, 16};
+    }
+    return with_knobs(kFamReduce, sh);
+}
+
+// The same for the segments of a coalesced call, whose last tiles are partial ones: workgroups of 512 lanes that would just fill the compute units no
+// longer do (16 tensors, bf16, p = 8, 49 MB 11.9 us, of 256 lanes 9.6; p = 4, 99 MB 17.6, 16.7), and wherever single wavefronts do not pay yet 256 lanes
+// are faster (p = 6, 99 MB 18.1 / 17.2, f32 18.3 / 17.3).  Single wavefronts, us: p = 8, 279 MB caps of 9 / 12 42.7 / 41.4, f32 478 MB 73.8 / 71.1, 899
+// MB 141 / 135.5; p = 12, 169 MB 512 lanes 28.8, caps of 8 / 10 / 12 27.6 / 27.6 / 27.5, f32 477 MB 8 / 9 / 10 74.0 / 73.2 / 73.0, 899 MB 137.0 / 136.2 / 137.1; p =
+// 16, 169 MB 512 lanes 30.6, caps of 8 / 10 / 12 28.6 / 28.1 / 28.1, f32 478 MB 75.2 / 75.8 / 76.5.
+// Two two-byte buffers take 256 lanes, capped at 16 wavefronts but in first micro-steps (318 MB 64 lanes 55.5, 256 53.2, 805 MB 122 / 126), 2 and 3 of f32 below 300
+// wavefronts per unit (p = 3, 278 MB 43.7 / 42.1, 479 MB 74.4 / 74.3, 899 MB 152 / 157).
+Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, size_t units)
+{
+    const bool two = elem_bytes == 2;
+    const size_t per_unit = nlanes / (64 * units);
+    Shape sh;
+    if (p >= 32 ? per_unit < 37 : p >= 12 ? per_unit < 30 : per_unit < 16) {
+        sh = small_call(nlanes, units);
+        if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
+    } else if (!grads16) {
         sh = p < 4 && two ? Shape{256, 0} : Shape{kMaxBlock, 16};
+    } else if (p < 4) {
+        const bool small = per_unit < (acc16 ? 50 : 125);
+        if (two) sh = !accumulate && p == 2 && per_unit >= 650 ? Shape{64, 0} : Shape{256, !small && p > 1 && (p == 3 || accumulate) ? 16 : 0};
+        else sh = Shape{per_unit < 300 ? 256 : 64, 0};
+    } else if (p < 12) {
+        sh = per_unit < 50 ? Shape{256, 0} : Shape{64, p < 6 ? 16 : p < 8 ? 14 : 12};
+    } else {
+        sh = Shape{64, p >= 32 ? 8 : two ? 10 : p < 16 ? 9 : 8};
     }
     return with_knobs(kFamReduce, sh);
 }
@@ -1866,6 +1896,14 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
 // us, batches of 16 / so, wavefronts per unit in front: p = 32 7 11.7 / 12.2, 8 13.1 / 12.9, f32 7 11.2 / 11.4, 9 13.1 / 12.9; p = 48 5.2 13.2 / 13.3,
 // 6.3 15.2 / 14.1; p = 64 5.2 16.5 / 16.3; p = 128 4.2 27.3 / 27.6, 5.2 29.5 / 29.4, 6.3 34.8 / 32.1.
 bool shallow_call(int p, size_t nlanes, size_t units) { return p >= 16 && (p < 32 || nlanes >= units * (p < 48 ? 512 : 352)); }
+
+// The same for segments.  16 buffers stay with the unrolled kernel (us, the best cap of each, unrolled / shallow: 172 MB 28.4 / 29.2, 307 MB 49.4 / 49.6,
+// f32 906 MB 138.5 / 139.0), 32 two-byte ones in long calls (453 MB 71.6 / 72.0, first micro-step 69.0 / 69.7; 276 MB 45.8 / 45.6); below 64
+// buffers it takes 12 wavefronts per unit (p = 48, odd shards 149 MB, 11 per unit 27.5 / 28.2; p = 64, 146 MB, 8.4 per unit 26.7 / 25.0).
+bool shallow_segments(int p, int elem_bytes, size_t nlanes, size_t units)
+{
+    return p > 16 && nlanes >= units * (p < 64 ? 768 : 352) && !(p == 32 && elem_bytes == 2 && nlanes >= units * 2560);
+}
 
 // A call's wavefronts start together and read the same number of bytes, so they end together too: a compute unit goes through
 // them in rounds of as many as it holds, and a last round that is half empty costs almost as much as a full one.  So the cap
@@ -2020,7 +2058,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units);
-    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, false, units);
+    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         if (policy == kAccCached)
@@ -2204,13 +2242,14 @@ unsigned segment_lead(const float* acc, const PtrTable& g, size_t src, size_t ds
 // `n` segments in one launch, with lanes of VEC dwords.
 template <int KIND, int VEC, int SEGS>
 int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit, const Segment* segs, int n, int p,
-                    bool accumulate, const Shape& sh, int policy, ReduceOrder order, hipStream_t st)
+                    bool accumulate, const Shape& sh, int policy, ReduceOrder order, bool shallow, hipStream_t st)
 {
     const int how = policy | (order.in_runs ? kInRuns : 0);
     constexpr size_t EPL = VEC * GradFormat<KIND>::kPerDword;
     ReduceTable<SEGS> tab;
     const size_t tile_elems = (size_t)sh.lanes * EPL;
     size_t tiles = 0;
+    bool ends = false;                             // elements that no lane holds as a full vector
     for (int t = 0; t < n; ++t) {
         const Segment& sg = segs[t];
         // position of the segment's first element in the rounded-down buffers; its virtual
@@ -2221,30 +2260,33 @@ int reduce_segments(float* acc, const PtrTable& g, size_t base_lead, size_t unit
         tab.seg[t].lead = lead;
         tab.seg[t].pad = 0;
         tab.seg[t].end = lead + sg.numel;
+        ends = ends || lead % EPL || tab.seg[t].end % EPL;
         tab.seg[t].src0 = src - lead;
         tab.seg[t].dst = sg.dst_offset;
         tiles += (lead + sg.numel + tile_elems - 1) / tile_elems;
         if (tiles > 0x7FFFFFFFull) return (int)hipErrorInvalidValue;
     }
     for (int t = n; t < SEGS; ++t) tab.tile_begin[t] = kNoTile;
-    auto run = [&](auto P, auto A, auto C) {
+    auto run = [&](auto P, auto A, auto C, auto S) {
         // lanes of 8 elements pass their results through 32 bytes of LDS
         const size_t lds = lds_for(sh, !C.value && EPL == 8 ? (size_t)sh.lanes * 32 : 0);
-        const dim3 gr((unsigned)tiles), bl(sh.lanes);
+        const unsigned edges = kEdgeGroups<P.value, C.value> && ends ? (unsigned)n : 0;
+        const dim3 gr((unsigned)tiles + edges), bl(sh.lanes);
         if constexpr (P.value > 0)
-            return launch(rsa_seg_kernel<KIND, VEC, P.value, A.value, C.value, SEGS, SmallTable<P.value>>, gr, bl, lds, st,
-                          small<P.value>(g), acc, p, tab, how);
+            return launch(rsa_seg_kernel<KIND, VEC, P.value, A.value, C.value, S.value, SEGS, SmallTable<P.value>>, gr, bl, lds, st,
+                          small<P.value>(g), acc, p, tab, how, edges);
         else
-            return launch(rsa_seg_kernel<KIND, VEC, 0, A.value, C.value, SEGS, PtrTable>, gr, bl, lds, st, g, acc, p, tab, how);
+            return launch(rsa_seg_kernel<KIND, VEC, 0, A.value, C.value, S.value, SEGS, PtrTable>, gr, bl, lds, st, g, acc, p, tab, how, edges);
     };
     return dispatch_bool(accumulate, [&](auto A) {
         if constexpr (VEC == 1) {
-            return run(std::integral_constant<int, 0>{}, A, std::true_type{});
+            return run(std::integral_constant<int, 0>{}, A, std::true_type{}, std::false_type{});
         } else if constexpr (SEGS > 64) {
-            return dispatch_group(p, [&](auto P) { return run(P, A, std::true_type{}); });
+            return dispatch_group(p, [&](auto P) { return run(P, A, std::true_type{}, std::false_type{}); });
         } else {
+            if (shallow) return run(std::integral_constant<int, 0>{}, A, std::false_type{}, std::true_type{});
             return dispatch_bool(policy == kAccCached, [&](auto C) {
-                return dispatch_group(p, [&](auto P) { return run(P, A, C); });
+                return dispatch_group(p, [&](auto P) { return run(P, A, C, std::false_type{}); });
             });
         }
     });
@@ -2269,8 +2311,8 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     *taken = n;
     if (narrow_call(p, GB, elements, line >= 16, n)) {
         const Shape sh = {kNarrowBlock, 0};
-        return n <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st)
-                       : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, st);
+        return n <= 64 ? reduce_segments<KIND, 1, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, false, st)
+                       : reduce_segments<KIND, 1, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, kAccCached, {false, false}, false, st);
     }
     // Small calls carry more than 64 segments, whose records then come in a second round: us, 64 / 96 per launch, f16, p = 12,
     // 79 segments 7.3 / 4.0; larger ones keep to 64 and to half as many kernels.
@@ -2283,14 +2325,18 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         alignable = alignable && lead_on_accumulator_lines(acc + segs[t].dst_offset, (uintptr_t)g.ptr[0] + (segs[t].src_offset + base_lead) * GB, GB) >= 0;
     const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20, accumulate, alignable);
     bool acc16 = true;
+    size_t waves = 0;                                                // in single-wavefront workgroups
     for (int t = 0; t < n; ++t) {
         const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
+        waves += (lead + segs[t].numel + 64 * EPL - 1) / (64 * EPL);
         acc16 = acc16 && ((uintptr_t)(acc + segs[t].dst_offset) - 4 * lead) % 16 == 0;
     }
-    const Shape sh = reduce_shape(p, (int)GB, (elements + EPL - 1) / EPL, line >= 16, acc16, accumulate, true, units);
     const int policy = accum_policy(elements, p, (int)GB);
-    return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st)
-                   : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, st);
+    const size_t nlanes = (elements + EPL - 1) / EPL;
+    const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units);
+    const Shape sh = shallow ? shallow_shape(p, 64 * waves, units) : reduce_shape_segments(p, (int)GB, nlanes, line >= 16, acc16, accumulate, units);
+    return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st)
+                   : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st);
 }
 
 }  // namespace

@@ -580,3 +580,30 @@ def test_reduce_in_shallow_batches(orc, gen, name, p, count):
                 assert same_bits(acc, ref), (skews, acc_skew, accumulate)
             finally:
                 mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("name,p,numel", [
+    ("bf16", 17, 1_600_003), ("f32", 24, 800_011), ("f16", 32, 1_600_009), ("bf16", 33, 1_580_001), ("f32", 48, 790_003), ("bf16", 64, 725_005),
+    ("f16", 96, 730_001), ("f32", 128, 362_003), ("bf16", 12, 2_100_003), ("f16", 40, 300_007)])
+@pytest.mark.parametrize("threshold", [0, 1])
+def test_reduce_segments_in_shallow_batches(orc, gen, name, p, numel, threshold):
+    """Segments that are read in batches of 4, and any-p ones that are not: their ends in workgroups of their own, a segment shorter than
+    a lane's vector and one without ends among them."""
+    code = FORMATS[name][0]
+    segs, src, dst = [], 3, 0
+    for n in (5, numel - 90_000, 64, 40_001, 50_017, 1):
+        segs.append((n, 0, src, dst))
+        src, dst = src + n + 2, dst + n
+    segs.append((4096, 0, -(-src // 64) * 64, dst))
+    src, dst = -(-src // 64) * 64 + 4096, dst + 4096
+    host, dev = rank_buffers(gen, name, p, src, [0])
+    try:
+        mics.mics_set_stream_threshold_bytes(threshold)
+        for accumulate in (False, True):
+            ref, acc = start_acc(gen, dst, skew=threshold)
+            mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+            orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+            torch.cuda.synchronize()
+            assert same_bits(acc, ref), accumulate
+    finally:
+        mics.mics_set_stream_threshold_bytes(0)
