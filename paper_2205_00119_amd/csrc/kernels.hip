@@ -1053,10 +1053,17 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
                 mine[2 * lane + 1] = f32x4{a[4], a[5], a[6], a[7]};
             }
             wave_lds_order();
+            // a workgroup's last wavefront may be a partial one (even_call), in the kernels that such calls reach
+            unsigned half = 64;
+            if constexpr ((P == 0 || P == 32) && BATCH != kShallow) {   // even_least
+                const unsigned left = blockDim.x - __builtin_amdgcn_readfirstlane(threadIdx.x);
+                if (left < 64) half = left;
+            }
             #pragma unroll
             for (unsigned h = 0; h < 2; ++h) {
-                const size_t owner = wave_v0 + 256 * h + 8 * (lane / 2);
-                if (owner >= lead && owner + 8 <= end) store(64 * h + lane, mine[64 * h + lane]);
+                const unsigned i = half * h + lane;
+                const size_t owner = wave_v0 + 8 * (i / 2);
+                if (owner >= lead && owner + 8 <= end) store(i, mine[i]);
             }
             wave_lds_order();                                    // the next pass writes there again
         }
@@ -1101,7 +1108,7 @@ __device__ __forceinline__ unsigned tile_of(unsigned x, unsigned n, bool in_runs
     return in_runs && base + kRound <= n ? base + at % kXcds * kRun + at / kXcds : x;
 }
 
-// Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4: the launcher takes small ones for
+// Workgroups of blockDim.x lanes (64 .. 512 for VEC = 4, a multiple of 8: the launcher takes small ones for
 // calls that would otherwise occupy a fraction of the compute units), plus one more workgroup
 // for the edge elements, so that their load chains run beside the vector work.
 // OTHER: a kernel's other form, with CACHED tiles in runs (of the others `how` says whether: tile_of's few instructions are
@@ -1552,6 +1559,30 @@ Shape small_call(size_t nlanes, size_t units)
     return Shape{waste(512) <= 1.12 ? 512 : waste(256) <= 1.12 ? 256 : 64, 0};
 }
 
+// A reduction with more than half of and less than seven eighths of a full-size workgroup for every compute unit (from 16 buffers on, more than a
+// quarter, f32 up to 31 a third): one workgroup per unit, of as many lanes as that takes, so that no unit idles and none has more than
+// another.  Tiles begin on the gradients' lines (8 lanes).  us, full-size workgroups or single wavefronts / so, wavefronts per unit in front: bf16, p = 4 4.3
+// 8 % faster, p = 8 10, p = 12 11, 5.5 5 to 7; p = 16 2.3 3.9 / 3.4, 4.2 5.45 / 4.77, 6.3 6.15 / 6.1; p = 32 4.2 9.1 / 7.5; p = 64 5.2 16.5 / 15.3; p = 128 2.3 17.8 / 15.0, 4.2
+// 27.3 / 23.4; f32, p = 12 4.3 4.3 / 3.8, p = 16 2.4 3.4 / 3.6, p = 32 2.3 16 % faster, 4.2 8.0 / 6.9, p = 128 4.2 26.3 / 22.3.  With few buffers single wavefronts are 2 to 6 %
+// faster below; two or more such workgroups per unit are faster or slower by 5 %, from one size to the next.
+// With n segments, so many workgroups less as may have a partial tile; every wavefront, the last and partial one too, needs n lanes to look
+// its segment up (segment_at).  us, 512 lanes / so: bf16, 16 tensors, p = 8 4.2 wavefronts per unit 13 % faster, p = 48 4.2 54 MB 14.2 / 11.3, p = 64 4.2 72 MB f32 16.5 /
+// 13.6, p = 96 4.2 107 MB f32 24.0 / 19.7.
+Shape even_call(size_t nlanes, size_t units, size_t least = 256, size_t most = 448, size_t n = 0)
+{
+    const size_t groups = units - n;
+    if (n >= 64 || units <= n || nlanes > groups * most || nlanes <= units * least) return small_call(nlanes, units);
+    size_t lanes = ((nlanes + groups - 1) / groups + 7) / 8 * 8;
+    if (lanes % 64 && lanes % 64 < n) lanes += (n + 7) / 8 * 8 - lanes % 64;
+    return Shape{(int)lanes, 0};
+}
+// The line from which a reduction does so; never where its kernel passes stores through LDS and knows whole wavefronts only (rsa_lane).
+size_t even_least(int p, int elem_bytes, bool cached)
+{
+    if (!cached && elem_bytes == 2 && (p <= 8 || p == 16)) return (size_t)1 << 40;
+    return p < 16 ? 256 : p < 32 && elem_bytes == 4 ? 170 : 128;
+}
+
 // True if the buffers begin on 128-byte lines.
 bool on_lines(std::initializer_list<const void*> buffers)
 {
@@ -1605,7 +1636,7 @@ Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units
     if (!lines || (r < 2 && traffic < (18u << 20))) return with_knobs(kFamAverage, off_lines(nlanes, units));
     // few copies, few loads in flight per lane: every wavefront that fits
     if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
-    if (traffic < (96u << 20)) return with_knobs(kFamAverage, small_call(nlanes, units));
+    if (traffic < (96u << 20)) return with_knobs(kFamAverage, r < 5 ? small_call(nlanes, units) : even_call(nlanes, units, 256, r < 12 ? 384 : 448));
     // 4 copies, caps of 16 / 11: 450 MB 67 / 68 us, 600 MB 97 / 93, 1.1 GB 176 / 165, streamed 1.5 GB 232 / 254; 5 copies:
     // 150 MB 24.4 / 25.1, 300 MB 46.8 / 46.0, 1.1 GB 174 / 165, streamed 2.5 GB 389 / 367
     const bool wide = r < 5 ? traffic < (500u << 20) || streamed : traffic < (250u << 20);
@@ -1619,7 +1650,7 @@ Shape fused_shape(int r, size_t count, bool lines, size_t units)
     const size_t traffic = count * (4 * (size_t)r + 26);
     if (!lines) return with_knobs(kFamFused, off_lines((count + 3) / 4, units));
     if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 9});
-    if (traffic < (200u << 20)) return with_knobs(kFamFused, small_call((count + 3) / 4, units));
+    if (traffic < (200u << 20)) return with_knobs(kFamFused, r < 12 ? small_call((count + 3) / 4, units) : even_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 6 : 4});
     // us at 50 M elements with caps of 6 / 8 / 9 / 11: r = 3 386 / 317 / 297 / 284, r = 4 322 / 319 / 324 / 327, r = 5 408 / 349 /
     // 342 / 358, r = 6 422 / 372 / 379 / 392, r = 7 436 / 406 / 419 / 430; within 1 % of that order from 10 to 100 M
@@ -1843,14 +1874,14 @@ int reduce_cap(int p, bool two, size_t nlanes, bool accumulate, size_t units)
     if (p < 12) return accumulate ? (many ? 8 : 10) : many ? (two ? 7 : 9) : 11;
     return accumulate ? (many ? 7 : 8) : many ? (two ? 6 : 7) : 10;
 }
-Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, size_t units)
+Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, bool cached, size_t units)
 {
     const bool two = elem_bytes == 2;
     size_t many = p < 6 ? 1600 : 1800;
     if (p < 4 || (p == 4 && two && grads16 && !acc16)) many = !acc16 ? 8000 : 3200;
     Shape sh;
     if (nlanes < units * many) {
-        sh = small_call(nlanes, units);
+        sh = even_call(nlanes, units, even_least(p, elem_bytes, cached));
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
     } else if (p >= 4) {
         sh = !two && !grads16 && p > 4 && p < 8 && nlanes >= units * 9600 ? Shape{kMaxBlock, 16} : Shape{64, reduce_cap(p, two, nlanes, accumulate, units)};
@@ -1869,13 +1900,13 @@ Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc1
 // 16, 169 MB 512 lanes 30.6, caps of 8 / 10 / 12 28.6 / 28.1 / 28.1, f32 478 MB 75.2 / 75.8 / 76.5.
 // Two two-byte buffers take 256 lanes, capped at 16 wavefronts but in first micro-steps (318 MB 64 lanes 55.5, 256 53.2, 805 MB 122 / 126), 2 and 3 of f32 below 300
 // wavefronts per unit (p = 3, 278 MB 43.7 / 42.1, 479 MB 74.4 / 74.3, 899 MB 152 / 157).
-Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, size_t units)
+Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, bool grads16, bool acc16, bool accumulate, bool cached, size_t units)
 {
     const bool two = elem_bytes == 2;
     const size_t per_unit = nlanes / (64 * units);
     Shape sh;
     if (p >= 32 ? per_unit < 37 : p >= 12 ? per_unit < 30 : per_unit < 16) {
-        sh = small_call(nlanes, units);
+        sh = n > 32 ? small_call(nlanes, units) : even_call(nlanes, units, even_least(p, elem_bytes, cached), 448, (size_t)n);
         if (sh.lanes == 64 && p >= 6 && nlanes * 2 > (size_t)kMaxBlock * units) sh.waves_per_cu = 16;
     } else if (!grads16) {
         sh = p < 4 && two ? Shape{256, 0} : Shape{kMaxBlock, 16};
@@ -2058,7 +2089,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units);
-    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, units);
+    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, policy == kAccCached, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         if (policy == kAccCached)
@@ -2334,7 +2365,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     const int policy = accum_policy(elements, p, (int)GB);
     const size_t nlanes = (elements + EPL - 1) / EPL;
     const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units);
-    const Shape sh = shallow ? shallow_shape(p, 64 * waves, units) : reduce_shape_segments(p, (int)GB, nlanes, line >= 16, acc16, accumulate, units);
+    const Shape sh = shallow ? shallow_shape(p, 64 * waves, units) : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
     return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st)
                    : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st);
 }

@@ -607,3 +607,36 @@ def test_reduce_segments_in_shallow_batches(orc, gen, name, p, numel, threshold)
             assert same_bits(acc, ref), accumulate
     finally:
         mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("name,p,per_unit", [
+    ("bf16", 4, 4.1), ("f16", 8, 5.2), ("f32", 12, 6.9), ("bf16", 16, 2.1), ("f32", 24, 3.0), ("bf16", 24, 6.3), ("f16", 32, 2.3), ("bf16", 32, 5.4),
+    ("f32", 33, 4.7), ("bf16", 48, 5.1), ("f16", 72, 4.4), ("f32", 128, 2.6)])
+@pytest.mark.parametrize("tensors", [0, 3, 16, 31, 33])
+def test_reduce_in_one_even_workgroup_per_unit(orc, gen, name, p, per_unit, tensors):
+    """Workgroups of a multiple of 8 lanes whose last wavefront is a partial one: as one tensor, and as segments, of which that wavefront
+    has to find its own; accumulators in the L2 and past it, gradients on and off their lines."""
+    code, dtype = FORMATS[name]
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    total = int(per_unit * 64 * units) * (16 // np.dtype(dtype).itemsize) + 3
+    segs, src, dst = [], 0, 0
+    for t in range(tensors):
+        n = 17 + 900 * (t % 5) if t else total - sum(17 + 900 * (i % 5) for i in range(1, tensors))
+        segs.append((n, 0, src, dst))
+        src, dst = src + n + t % 3, dst + n
+    for skews, threshold in (([0], 0), ([5], 1), ([3, 0, 8], 1)):
+        host, dev = rank_buffers(gen, name, p, (src if tensors else total) + 1, skews)
+        try:
+            mics.mics_set_stream_threshold_bytes(threshold)
+            for accumulate in (True, False):
+                ref, acc = start_acc(gen, dst if tensors else total)
+                if tensors:
+                    mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+                    orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+                else:
+                    mics.mics_reduce_scatter_accum_typed(acc.t, [d.t for d in dev], 1, total, accumulate, code)
+                    orc.reduce_scatter_accum_typed(ref, host, 1, accumulate, code)
+                torch.cuda.synchronize()
+                assert same_bits(acc, ref), (skews, accumulate)
+        finally:
+            mics.mics_set_stream_threshold_bytes(0)
