@@ -1626,21 +1626,41 @@ int average_store(int r, size_t count, bool streamed)
     return middle ? kOutPlain : kOutThrough;
 }
 
-// The lines below which a call is small, us (buffers rotating): average r = 4 at 84 MB 512x32 14.7,
-// 64x16 14.9, r = 8 at 151 MB 27.3, 64x9 26.1; average + Adam at 143 MB 25.5, 64x9 26.1, at 334 MB
-// 55.8, 52.9, r = 8 at 122 MB 22.3, 64x9 22.9, at 243 MB 48.3, 45.3; reorder at 32 MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
+// The lines below which a call is small, us (buffers rotating), full-size workgroups / single wavefronts: average, r = 4 at 50 MB 8.6 / 8.6, 90 MB 15.7 / 15.0, r = 5
+// 90 MB 16.2 / 15.3, r = 6 90 MB 16.6 / 15.4, 150 MB 25.8 / 24.3, r = 12 50 MB 8.8 / 8.8, 90 MB 16.2 / 15.1; average + Adam, r = 1 40 MB 8.5 / 8.5, 80 MB 15.6 / 15.0, 180 MB
+// 31.4 / 30.1, r = 4 40 MB 8.4 / 8.7, 80 MB 15.4 / 15.0, 180 MB 32.2 / 30.2, r = 6 120 MB 21.6 / 20.5, r = 8 40 MB 8.3 / 8.3, 120 MB 21.7 / 20.8; reorder at 32
+// MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
+constexpr size_t kLargeAverage = 60u << 20;
+// Updates of more copies later (us, full-size workgroups / single wavefronts: r = 12 70 MB 12.9 / 13.3, 150 MB 5 % faster, r = 16 80 MB 13.9 / 14.9, 120 MB 21.2 / 21.6), without an
+// unrolled kernel latest (r = 9 150 MB 26.9 / 28.9).
+size_t large_update(int r) { return (r <= 8 ? size_t{76} : r == 12 ? size_t{100} : r == 16 ? size_t{130} : size_t{200}) << 20; }
+// Averages of 3, 5, 6 and 7 copies have unrolled kernels for all but the largest calls (us, any r / unrolled: r = 3 3 MB 2.63 / 2.29, 90 MB 15.3 / 14.7, r = 6 3 MB 2.7 /
+// 2.3, 90 MB 16.7 / 15.4, 800 MB 119.7 / 121.6, r = 5 800 MB 122.3 / 122.4), updates of so
+// many, and of 12 and 16, for calls that are all latency and for large ones (r = 3 5 MB 3.4 / 2.9, 40 MB 7.2 / 8.6, 180 MB 33.0 / 30.5; r = 5 5 MB 3.6 / 3.0, 40 MB 7.9 / 8.3, 180 MB 32.4 /
+// 30.6; r = 16 3 MB 3.6 / 2.8, 28 MB 10 % faster, 80 MB 14.0 / 14.3).
+bool unrolled_average(int r, size_t count, bool streamed) { return r == 3 ? !streamed : r >= 12 || count * (4 * (size_t)r + 4) < (500u << 20); }
+size_t unrolled_update(int r) { return (r < 12 ? 12u : 36u) << 20; }
+
 Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 4), nlanes = (count + 3) / 4;
     // a single copy below 18 MB: 1 M elements 2.94, 64x32 3.02; 1.7 M 3.8, 4.0
     if (!lines || (r < 2 && traffic < (18u << 20))) return with_knobs(kFamAverage, off_lines(nlanes, units));
-    // few copies, few loads in flight per lane: every wavefront that fits
-    if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : 0});
-    if (traffic < (96u << 20)) return with_knobs(kFamAverage, r < 5 ? small_call(nlanes, units) : even_call(nlanes, units, 256, r < 12 ? 384 : 448));
-    // 4 copies, caps of 16 / 11: 450 MB 67 / 68 us, 600 MB 97 / 93, 1.1 GB 176 / 165, streamed 1.5 GB 232 / 254; 5 copies:
-    // 150 MB 24.4 / 25.1, 300 MB 46.8 / 46.0, 1.1 GB 174 / 165, streamed 2.5 GB 389 / 367
-    const bool wide = r < 5 ? traffic < (500u << 20) || streamed : traffic < (250u << 20);
-    return with_knobs(kFamAverage, Shape{64, r >= 6 ? 9 : wide ? 16 : 11});
+    // few copies, few loads in flight per lane: every wavefront that fits (3 copies 300 MB 42.3, a cap of 14 46.1, but 800 MB 127.3, 120.6, streamed 2.1 GB 328, 345)
+    if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : r == 3 && !streamed && traffic >= (600u << 20) ? 14 : 0});
+    if (traffic < kLargeAverage) return with_knobs(kFamAverage, r < 5 ? small_call(nlanes, units) : even_call(nlanes, units, 256, r < 12 ? 384 : 448));
+    // us, caps of 9 / 10 / 11 / 12 / 14 / 16 / 18: 4 copies 90 MB 17.1 / 16.6 / 16.4 / 16.0 / 15.7 / 15.3 / 15.0, 300 MB 48.9 / 47.4 / 46.4 / 45.8 / 45.0 / 44.6 / 44.6,
+    // 800 MB 127.6 / 124.5 / 121.3 / 122.4 / 125.2 / 126.7 / 127.7, streamed 1.5 GB a cap of 16 232, 11 254; 5 copies 90 MB 16.8 / 16.2 / 16.4 / 16.1 / 15.4 / 15.3 / 15.3, 300
+    // MB 46.5 / 45.7 / 45.6 / 45.5 / 45.1 / 45.6 / 45.8, 800 MB 123.2 / 122.4 / 123.3 / 125.3; 6 copies 90 MB 16.6 / 16.2 / 16.1 / 15.7 / 15.4, 300 MB 46.8 / 46.2 /
+    // 45.9 / 46.0 / 46.4; 8 copies 90 MB 15.7 / 15.4 / 15.3 / 15.4, 300 MB 46.2 / 46.3 / 46.3; 12 copies, caps of 7 / 8 / 9 300 MB 48.2 / 48.5 / 48.3, 800 MB 117.8 /
+    // 118.0 / 118.3; 16 copies 800 MB 120.2 / 120.7 / 121.1
+    const bool wide = traffic < (500u << 20) || (r < 5 && streamed);
+    int cap = 0;
+    if (r < 5) cap = traffic < (200u << 20) ? 18 : wide ? 16 : 11;
+    else if (r < 6) cap = wide ? 14 : 11;
+    else if (r < 8) cap = traffic < (120u << 20) ? 14 : wide ? 11 : 9;
+    else cap = r < 12 ? (traffic < (200u << 20) ? 10 : 9) : traffic < (200u << 20) ? 9 : 7;
+    return with_knobs(kFamAverage, Shape{64, cap});
 }
 
 Shape adam_shape(size_t count) { return with_knobs(kFamAdam, Shape{64, count >= kHugeElements ? 8 : 11}); }
@@ -1649,13 +1669,15 @@ Shape fused_shape(int r, size_t count, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 26);
     if (!lines) return with_knobs(kFamFused, off_lines((count + 3) / 4, units));
-    if (r >= 6 && traffic >= (160u << 20) && traffic < (300u << 20)) return with_knobs(kFamFused, Shape{64, 9});
-    if (traffic < (200u << 20)) return with_knobs(kFamFused, r < 12 ? small_call((count + 3) / 4, units) : even_call((count + 3) / 4, units));
+    if (traffic < large_update(r)) return with_knobs(kFamFused, r < 12 ? small_call((count + 3) / 4, units) : even_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 6 : 4});
-    // us at 50 M elements with caps of 6 / 8 / 9 / 11: r = 3 386 / 317 / 297 / 284, r = 4 322 / 319 / 324 / 327, r = 5 408 / 349 /
-    // 342 / 358, r = 6 422 / 372 / 379 / 392, r = 7 436 / 406 / 419 / 430; within 1 % of that order from 10 to 100 M
-    constexpr int kCap[8] = {0, 11, 9, 11, 8, 9, 8, 8};
-    return with_knobs(kFamFused, Shape{64, r < 8 ? kCap[r] : 5});
+    // us, caps of 4 / 5 / 6 / 7 / 8 / 9 / 10 / 11, at 120 MB: r = 1 .. / 25.4 / 23.9 / 22.7 / 21.7 / 21.1 / 20.9, r = 3 22.8 / 21.9 / 21.3 / 21.1 / 21.1 / 21.2 from 6 on, r = 4 22.0 /
+    // 21.2 / 21.0 / 21.0 / 21.1, r = 6 21.2 / 20.8 / 20.8 / 20.7 / 20.5, r = 8 22.9 / 21.4 / 21.0 / 21.1 / 21.2 / 20.8, r = 12 21.4 / 21.0 / 21.0 / 20.8 / 21.0; at 400 MB: r = 1 9 to 11 63.3 / 62.6 /
+    // 62.7, r = 2 62.5 at 9, r = 3 62.6 at 8, r = 4 61.6 at 7, r = 5 75.9 / 66.9 / 63.1 / 63.2 / 64.1, r = 6 71.9 / 64.2 / 62.2 / 62.9, r = 8 68.5 / 63.5 / 64.0 / 65.2, r = 12
+    // 66.2 / 66.8 / 67.9, r = 16 66.7 / 67.7 / 68.8; at 800 MB: r = 5 121.8 / 120.8 / 123.7 at 6 to 8, r = 6 140.9 / 124.8 / 120.3 / 122.6, r = 12 124.7 / 127.8, r = 16 125.8 / 128.8
+    constexpr int kCapSmall[9] = {0, 11, 10, 10, 9, 8, 8, 8, 9}, kCap[9] = {0, 10, 9, 8, 7, 7, 6, 6, 5};
+    const bool below = traffic < (220u << 20);
+    return with_knobs(kFamFused, Shape{64, r <= 8 ? (below ? kCapSmall[r] : kCap[r]) : r == 12 || r == 16 ? (below ? 6 : 4) : 5});
 }
 
 Shape reorder_shape(size_t traffic, int lanes)
@@ -1711,6 +1733,31 @@ int dispatch_group(int p, F&& f)
         case 32: return f(std::integral_constant<int, 32>{});
         default: return f(std::integral_constant<int, 0>{});
     }
+}
+
+// Calls f(std::integral_constant<int, R>, table) for an average of r copies: R = r where there is an unrolled kernel, those of 3, 5, 6, 7, 12 and 16
+// only if `all`, else R = 0 and the whole table.
+template <typename F>
+int dispatch_copies(const PtrTable& t, int r, bool all, F&& f)
+{
+    auto unrolled = [&](auto R) { return f(R, small<R.value>(t)); };
+    switch (r) {
+        case 1: return unrolled(std::integral_constant<int, 1>{});
+        case 2: return unrolled(std::integral_constant<int, 2>{});
+        case 4: return unrolled(std::integral_constant<int, 4>{});
+        case 8: return unrolled(std::integral_constant<int, 8>{});
+        default: break;
+    }
+    switch (all ? r : 0) {
+        case 3: return unrolled(std::integral_constant<int, 3>{});
+        case 5: return unrolled(std::integral_constant<int, 5>{});
+        case 6: return unrolled(std::integral_constant<int, 6>{});
+        case 7: return unrolled(std::integral_constant<int, 7>{});
+        case 12: return unrolled(std::integral_constant<int, 12>{});
+        case 16: return unrolled(std::integral_constant<int, 16>{});
+        default: break;
+    }
+    return f(std::integral_constant<int, 0>{}, t);
 }
 
 }  // namespace
@@ -2131,13 +2178,9 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_AVG_BPC, &blocks)) return e;
     const dim3 gr(blocks), bl(sh.lanes);
     auto run = [&](auto SO) {
-        switch (r) {
-            case 1: return launch(avg_kernel<1, SO.value, SmallTable<1>>, gr, bl, lds, st, out, small<1>(a), r, scale, count);
-            case 2: return launch(avg_kernel<2, SO.value, SmallTable<2>>, gr, bl, lds, st, out, small<2>(a), r, scale, count);
-            case 4: return launch(avg_kernel<4, SO.value, SmallTable<4>>, gr, bl, lds, st, out, small<4>(a), r, scale, count);
-            case 8: return launch(avg_kernel<8, SO.value, SmallTable<8>>, gr, bl, lds, st, out, small<8>(a), r, scale, count);
-            default: return launch(avg_kernel<0, SO.value, PtrTable>, gr, bl, lds, st, out, a, r, scale, count);
-        }
+        return dispatch_copies(a, r, unrolled_average(r, count, streamed), [&](auto R, const auto& tab) {
+            return launch(avg_kernel<R.value, SO.value, std::decay_t<decltype(tab)>>, gr, bl, lds, st, out, tab, r, scale, count);
+        });
     };
     switch (average_store(r, count, streamed)) {
         case kOutPlain: return run(std::integral_constant<int, kOutPlain>{});
@@ -2394,18 +2437,16 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
     const bool lines = on_lines(copies, r) && on_lines({master, exp_avg, exp_avg_sq});
     const Shape sh = fused_shape(r, count, lines, units);
     // off the lines: 17.6 M elements, r = 2, 110 us, through the L2 124
-    const bool through = lines && states_through(count * (4 * (size_t)r + 26));
+    const size_t traffic = count * (4 * (size_t)r + 26);
+    const bool through = lines && states_through(traffic);
     const size_t lds = lds_for(sh);
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto BF) {
         const dim3 gr(blocks), bl(sh.lanes);
-        switch (r) {
-            case 1: return launch(avg_adam_kernel<1, BF.value, SmallTable<1>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<1>(copies), r, scale, count, hp, through);
-            case 2: return launch(avg_adam_kernel<2, BF.value, SmallTable<2>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<2>(copies), r, scale, count, hp, through);
-            case 4: return launch(avg_adam_kernel<4, BF.value, SmallTable<4>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<4>(copies), r, scale, count, hp, through);
-            case 8: return launch(avg_adam_kernel<8, BF.value, SmallTable<8>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, small<8>(copies), r, scale, count, hp, through);
-            default: return launch(avg_adam_kernel<0, BF.value, PtrTable>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16, copies, r, scale, count, hp, through);
-        }
+        return dispatch_copies(copies, r, traffic >= large_update(r) || traffic < unrolled_update(r), [&](auto R, const auto& tab) {
+            return launch(avg_adam_kernel<R.value, BF.value, std::decay_t<decltype(tab)>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16,
+                          tab, r, scale, count, hp, through);
+        });
     });
 }
 

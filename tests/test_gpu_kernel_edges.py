@@ -640,3 +640,13 @@ def test_reduce_in_one_even_workgroup_per_unit(orc, gen, name, p, per_unit, tens
                 assert same_bits(acc, ref), (skews, accumulate)
         finally:
             mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("r,count", [
+    (3, 5), (3, 331_127), (3, 331_131), (3, 2_097_149), (3, 2_097_155), (5, 1_733_000), (5, 1_733_001), (6, 77_003), (6, 1_600_003), (7, 1_500_001), (7, 260_003),
+    (9, 1_048_579), (12, 510_103), (12, 510_104), (12, 1_416_993), (13, 40_001), (16, 420_003), (16, 1_515_002)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_average_and_update_of_numbers_of_copies(orc, gen, r, count, skew):
+    """Numbers of copies that have kernels of their own, for both ends of the range in updates, and ones that have none: both sides of
+    the lines between them and between full-size workgroups, even ones and single wavefronts."""
+    test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew)
