@@ -1787,15 +1787,17 @@ namespace {
 //   one tensor, 16-byte aligned, p = 16: 0.3 MB 1.82 / 2.22, 8 MB 3.04 / 3.47, 20 MB (two vectors) 5.08 / 5.97, 28 MB 6.6 /
 //   6.9, 36 MB 8.9 / 8.2 (buffers in the L2: 10 MB 3.0 / 2.75); not aligned, whose wavefronts at the borders of chunks make a second
 //   round trip, never: 0.6 MB 2.35 / 2.05, 4 MB 3.75 / 3.3, 8 MB 4.3 / 4.0
-//   several tensors, not all aligned: 4 of them p = 16 10 MB 1.1 times the speed, 16 MB 1.0, 22 MB 9.0 / 7.1, p = 64 36 MB 13.3 / 9.7; 16 of a
-//   layer p = 16 22 MB 6.5 / 7.3, p = 64 7.4 / 8.4; 40 p = 16 22 MB 1.3, 27 MiB 10.3 / 8.4, p = 64 30 MB 1.55, 36 MB 1.1; all aligned 27 MiB 6.4 / 7.6, 38 MiB equal; more than 48, p = 16, 95
-//   tensors 19 MiB 7.6 / 8.4, 27 MiB 10.9 / 9.6, p = 96 38 MiB 14.7 / 24, 57 MiB 18.4 / 16.8
+//   several tensors, all aligned: 16 of a layer, p = 4 33 MB 7.5 / 8.1, 40 MB 9.5 / 9.1, p = 128 33 MB 7.4 / 8.5, 40 MB 9.5 / 9.8
+//   not all aligned: 4 of them p = 4 23 MB 6.4 / 6.7, p = 16 22 MB 7.5 / 6.5, p = 64 19 MB 6.9 / 6.2; 16, 40, 60 and 93 of them p = 16 15 MB 5.5 / 6.1, 5.5 / 6.2, 5.7 / 6.0, 5.5 /
+//   6.2, 23 MB 7.5 / 7.3, 8.8 / 7.7, 8.4 / 7.3, 8.6 / 7.5; p = 32 19 MB 7.0 / 7.0, 7.3 / 7.6, 7.4 / 7.2, 7.9 / 7.7; p = 64 19 MB 7.2 / 7.4, 7.6 / 8.5, 7.9 / 8.1, 8.4 / 9.4, 27 MB 8.9 / 8.5,
+//   9.5 / 9.7, 10.9 / 9.5, 11.4 / 10.7; p = 128 27 MB 9.1 / 9.2, 9.9 / 12.0, 11.7 / 11.6, 12.3 / 13.6, 33 MB 13.1 / 10.3, 11.9 / 12.3, 12.2 / 12.5, 12.9 / 14.8
 int flat_vectors(int n, size_t moved, int p, bool vec16)
 {
     const size_t mb = moved >> 20;
     if (g_blocks_per_cu.load() > 0) return 0;                  // its grid has no cap
     if (n == 1) return !vec16 || mb >= 27 ? 0 : mb < 16 ? 1 : 2;
-    const size_t most = n > kMaxSegPerLaunch ? (p >= 48 ? 52 : 24) : vec16 ? 36 : n < 16 ? 18 : p >= 48 ? 36 : 24;
+    const size_t most = vec16 ? (n <= kMaxSegPerLaunch ? 36 : p >= 48 ? 52 : 24)
+                        : n < 16 ? 18 : p < 24 ? 17 : p < 48 ? 18 : p < 96 ? 20 : n <= 24 ? 27 : 34;
     return mb >= most ? 0 : mb < 18 ? 1 : 2;
 }
 
@@ -2216,10 +2218,19 @@ int launch_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* para
 namespace {
 
 // A launch of SEGS tensors at most, none of them empty.
+// Full-size workgroups take tiles of 16 KiB, which small chunks do not fill: below 48 MB they are for calls whose chunks do (us, full-size / 128 lanes: 41 MB, 40
+// tensors, p = 128 (chunks of 4 KB) 22.9 / 13.6, p = 64 (8 KB) 15.9 / 11.7, p = 16 (32 KB) 11.3 / 10.5; 16 tensors, p = 32 (40 KB) 11.0 / 10.4; 93 tensors, p = 8 (27 KB) 10.6 / 10.7; 60
+// tensors, p = 4, 28 MB (58 KB) 7.7 / 7.9).
+Shape reorder_tensors_shape(size_t moved, int n, int p)
+{
+    const size_t chunk = moved / 2 / ((size_t)n * (size_t)p);
+    return chunk < (size_t{48} << 10) ? with_knobs(kFamReorder, Shape{kSegLanes, 0}) : reorder_shape(moved, kSegLanes);
+}
+
 template <int SEGS>
 int launch_reorder_seg(void* dst, const PtrTable& src, const Segment* segs, int n, size_t moved, int p, int k, size_t eb, hipStream_t st)
 {
-    const Shape sh = reorder_shape(moved, kSegLanes);
+    const Shape sh = reorder_tensors_shape(moved, n, p);
     const size_t tile_vecs = (size_t)sh.lanes * MICS_SEG_U;
     size_t tiles = 0;
     ReorderSegTable<SEGS> tab;
@@ -2254,7 +2265,7 @@ size_t shift_tiles(const ByteSeg& sg, size_t tile_bytes) { return (sg.shard_byte
 template <int SEGS>
 int launch_reorder_shift(void* dst, const PtrTable& src, const Segment* segs, int n, size_t moved, int p, int k, size_t eb, hipStream_t st)
 {
-    const Shape sh = reorder_shape(moved, kSegLanes);
+    const Shape sh = reorder_tensors_shape(moved, n, p);
     const size_t tile_bytes = (size_t)sh.lanes * MICS_SEG_U * 16;
     size_t tiles = 0;
     ByteSegTable<SEGS> tab;

@@ -650,3 +650,10 @@ def test_average_and_update_of_numbers_of_copies(orc, gen, r, count, skew):
     """Numbers of copies that have kernels of their own, for both ends of the range in updates, and ones that have none: both sides of
     the lines between them and between full-size workgroups, even ones and single wavefronts."""
     test_average_and_update_in_every_launch_shape_and_store_kind(orc, gen, r, count, skew)
+
+
+@pytest.mark.parametrize("p,k,n_tensors,mb", [(8, 4, 20, 17), (32, 8, 17, 18), (64, 8, 60, 20), (96, 8, 24, 27), (128, 8, 25, 34), (32, 8, 40, 44), (8, 8, 16, 44), (128, 8, 12, 30)])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_gather_of_small_chunks(orc, gen, p, k, n_tensors, mb, odd):
+    """Both sides of the sizes from which several tensors go by chunks, and chunks that fill full-size workgroups' tiles and that do not."""
+    test_gather_on_both_sides_of_the_small_calls(orc, gen, p, k, n_tensors, mb, odd)
