@@ -1998,6 +1998,9 @@ Shape shallow_shape(int p, size_t nlanes, size_t units)
         {6, {.06, .02, 0}}, {7, {.04, 0, .01}}, {8, {0, 0, .025}}, {9, {.04, .012, .035}}, {10, {.035, .025, .05}}, {11, {.04, .03, .06}},
         {12, {.035, .035, .06}}, {14, {.035, .04, .07}}, {16, {.03, .04, .07}}};
     const double per_unit = (double)((nlanes + 63) / 64) / (double)units;
+    // between one round and the next, wavefronts of so few buffers need no cap (us, p = 16, 21 per unit caps of 8 / 10 / 12 / 16 / none 19.2 / 19.9 / 18.4 / 18.1 / 17.8, f32 17.1 /
+    // 18.1 / 16.7 / 17.1 / 16.4; 34 per unit 29.7 / 29.3 / 28.5 / 28.3 / 28.9)
+    if (p < 20 && per_unit >= 20 && per_unit < 26) return with_knobs(kFamReduce, Shape{64, 0});
     const int column = p < 64 ? 0 : per_unit < 46 ? 1 : 2;
     int best = 8;
     double least = 1e9;
