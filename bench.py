@@ -439,8 +439,10 @@ class Workload:
                 for name in names if not (a.fused and name == "a3")
             },
             "roofline": {
-                "kernel": (f"rsa_seg_kernel<{p}> (mics_reduce_scatter_accum_coalesced)" if a.coalesced
-                           else f"rsa_kernel<{kind}, 4, {p if p in (1, 2, 3, 4, 5, 6, 7, 8, 16, 32) else 0}> "
+                # large calls: from 16 buffers on (17 in segments) the any-p form with shallow batches
+                "kernel": (f"rsa_seg_kernel<{kind}, 4, {p if p <= 8 or p == 16 or (p == 32 and kind < 2) else 0}> "
+                           "(mics_reduce_scatter_accum_coalesced)" if a.coalesced
+                           else f"rsa_kernel<{kind}, 4, {p if p <= 8 else 0}> "
                                 f"({'mics_reduce_scatter_accum' if kind == 0 else 'mics_reduce_scatter_accum_typed'})"),
                 "bound": "hbm",
                 "achieved": round(a2_gbps, 1),

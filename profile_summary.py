@@ -156,7 +156,7 @@ def main():
                        f"{rf['avg_launch_ms']} (HIP events around the s launches of a step), median "
                        f"{rf['median_launch_ms']}, min {rf['min_launch_ms']}, achieved {rf['achieved']} GB/s, frac {rf['frac']}.")
             rsa = sorted(n for n in avg_ns if n.startswith(("rsa_kernel", "rsa_seg_kernel")))
-            acc = [n for n in rsa if template_args(n)[3 if n.startswith("rsa_kernel") else 2]]
+            acc = [n for n in rsa if template_args(n)[3]]
             ovw = [n for n in rsa if n not in acc]
             if len(acc) == 1 and len(ovw) == 1 and cfg.s > 1:
                 mix = ((cfg.s - 1) * avg_ns[acc[0]] + avg_ns[ovw[0]]) / cfg.s
@@ -202,7 +202,7 @@ def main():
         out.append(f"\nTraffic equals the algorithmic bytes to within {worst * 100:.2f} % for every kernel.  (FETCH_SIZE and "
                    "WRITE_SIZE sit between L2 and the fabric: bytes served by the Infinity Cache count as well.)")
         rsa = sorted(n for n in traffic if n.startswith(("rsa_kernel", "rsa_seg_kernel")))
-        acc = [n for n in rsa if template_args(n)[3 if n.startswith("rsa_kernel") else 2]]
+        acc = [n for n in rsa if template_args(n)[3]]
         ovw = [n for n in rsa if n not in acc]
         if len(acc) == 1 and len(ovw) == 1:
             per_launch = ((cfg.s - 1) * traffic[acc[0]] + traffic[ovw[0]]) / cfg.s
