@@ -33,8 +33,9 @@ int mics_set_stream_threshold_bytes(size_t bytes);
 
 /*
  * Launch shape of a kernel family for later calls: lanes per workgroup (64, 128, 256 or 512) and
- * the most wavefronts a compute unit may hold at a time (1 .. 32; 32 = as many as fit); 0 for
- * either restores the built-in choice, which depends on the size of the call and on the
+ * the most wavefronts a compute unit may hold at a time (1 .. 32; 32 = as many as fit; a number of
+ * workgroups that cannot be had, i.e. other than up to 12, 14, 16, 18, 21 and 25, is rounded down,
+ * but two always fit); 0 for either restores the built-in choice, which depends on the size of the call and on the
  * alignment of its buffers.  Streaming kernels on an MI355X run fastest in single-wavefront
  * workgroups with 8 to 16 wavefronts per compute unit; this knob is how that was measured.
  * Returns MICS_OK or MICS_ERR_INVALID_ARG.

@@ -251,19 +251,18 @@ inline Shape reorder_shape(size_t traffic, int lanes)
     return with_knobs(kFamReorder, traffic < (48u << 20) ? Shape{kMaxBlock, 0} : Shape{lanes, 0});
 }
 
-// Dynamic LDS that keeps the wavefronts of `sh` on a compute unit at or below its cap, at least
-// `needed` bytes (what the kernel itself uses).  A workgroup's LDS is handed out in pieces of 1280 bytes (counted on the
-// chip: 16384 bytes a workgroup leave room for 9, 14848 for 10), so that 13, 15, 17, 19 and 20 workgroups cannot be had.  Without
-// an opt-in a workgroup gets at most 64 KiB, so the cap cannot go below 2 workgroups per compute unit.
+// Dynamic LDS that keeps the wavefronts of `sh` on a compute unit at or below its cap, at least `needed` bytes (what the
+// kernel itself uses).  A workgroup's LDS is handed out in pieces of 1280 bytes (counted on the chip: 16384 bytes a workgroup leave room for
+// 9, 14848 for 10), and m pieces leave room for 128 / m workgroups: 12, 14, 16, 18, 21, 25 and every number below, not those between.  So a
+// workgroup asks for the fewest pieces that keep one more of them out.  A partial last wavefront counts as one.  Without an opt-in a
+// workgroup gets at most 64 KiB, which leaves room for 2.
 inline size_t lds_for(const Shape& sh, size_t needed = 0)
 {
-    constexpr size_t kLdsPerCu = 160u << 10, kPiece = 1280, kMaxDynamic = (64u << 10) / kPiece * kPiece;
-    const int waves_per_wg = sh.lanes / 64;
+    constexpr size_t kPiece = 1280, kPieces = (160u << 10) / kPiece, kMost = (64u << 10) / kPiece;
+    const int waves_per_wg = (sh.lanes + 63) / 64;
     if (sh.waves_per_cu <= 0 || sh.waves_per_cu / waves_per_wg >= 32) return needed;
-    size_t wgs = (size_t)sh.waves_per_cu / (size_t)waves_per_wg;
-    if (wgs < 1) wgs = 1;
-    size_t bytes = kLdsPerCu / wgs / kPiece * kPiece;
-    if (bytes > kMaxDynamic) bytes = kMaxDynamic;
+    const size_t wgs = std::max(sh.waves_per_cu / waves_per_wg, 1);
+    const size_t bytes = std::min(kPieces / (wgs + 1) + 1, kMost) * kPiece;
     return bytes > needed ? bytes : needed;
 }
 

@@ -1,0 +1,52 @@
+"""The launch rules (csrc/launch_rules.h), built with plain g++ and asked for their answers.  No GPU involved."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+UNITS = 256
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    lib = tmp_path_factory.mktemp("rules") / "rules.so"
+    csrc = os.path.join(ROOT, "paper_2205_00119_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", f"-I{csrc}", "-o", str(lib),
+                    os.path.join(ROOT, "tests", "host", "launch_rules_c.cpp")], check=True)
+    lib = ctypes.CDLL(str(lib))
+    lib.rules_lds.restype = ctypes.c_size_t
+    lib.rules_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    return lib
+
+
+PIECE, PIECES, MOST = 1280, 128, 65536       # LDS is handed out in pieces, 160 KiB of it a compute unit, 64 KiB a workgroup
+
+
+HAD = sorted({PIECES // m for m in range(1, MOST // PIECE + 1)})         # numbers of workgroups that a request can leave room for
+
+
+def workgroups(lds):
+    return PIECES // -(-lds // PIECE) if lds else 1 << 20
+
+
+@pytest.mark.parametrize("lanes", [64, 128, 136, 200, 256, 264, 384, 448, 512])
+def test_a_cap_on_wavefronts_is_one(rules, lanes):
+    """The dynamic LDS of a workgroup lets no more wavefronts on a compute unit than asked for (but one workgroup, and two where
+    64 KiB a workgroup allow no less), and no fewer than can be had."""
+    of_one = -(-lanes // 64)                 # a last wavefront that is a partial one counts
+    for cap in range(1, 32):
+        if cap // of_one >= 32:
+            continue
+        lds = rules.rules_lds(lanes, cap, 0)
+        assert lds <= MOST
+        at_most = [c for c in HAD if c <= max(cap // of_one, 1)]
+        assert workgroups(lds) == (max(at_most) if at_most else min(HAD)), (cap, lds)
+    assert rules.rules_lds(lanes, 0, 0) == 0 and rules.rules_lds(lanes, 0, 4096) == 4096
+    assert rules.rules_lds(lanes, 32, 20000) >= 20000
+
+
+
+def test_caps_that_can_be_had_exactly(rules):
+    assert [c for c in HAD if c < 32] == [2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 14, 16, 18, 21, 25]
