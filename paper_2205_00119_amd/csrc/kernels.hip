@@ -1481,7 +1481,7 @@ int dispatch_group(int p, F&& f)
     }
 }
 
-// Calls f(std::integral_constant<int, R>, table) for an average of r copies: R = r where there is an unrolled kernel, those of 3, 5, 6, 7, 12 and 16
+// Calls f(std::integral_constant<int, R>, table) for an average of r copies: R = r where there is an unrolled kernel, those of 3, 5, 6, 7 and 9 to 16
 // only if `all`, else R = 0 and the whole table.
 template <typename F>
 int dispatch_copies(const PtrTable& t, int r, bool all, F&& f)
@@ -1499,7 +1499,13 @@ int dispatch_copies(const PtrTable& t, int r, bool all, F&& f)
         case 5: return unrolled(std::integral_constant<int, 5>{});
         case 6: return unrolled(std::integral_constant<int, 6>{});
         case 7: return unrolled(std::integral_constant<int, 7>{});
+        case 9: return unrolled(std::integral_constant<int, 9>{});
+        case 10: return unrolled(std::integral_constant<int, 10>{});
+        case 11: return unrolled(std::integral_constant<int, 11>{});
         case 12: return unrolled(std::integral_constant<int, 12>{});
+        case 13: return unrolled(std::integral_constant<int, 13>{});
+        case 14: return unrolled(std::integral_constant<int, 14>{});
+        case 15: return unrolled(std::integral_constant<int, 15>{});
         case 16: return unrolled(std::integral_constant<int, 16>{});
         default: break;
     }
@@ -2088,7 +2094,7 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto BF) {
         const dim3 gr(blocks), bl(sh.lanes);
-        return dispatch_copies(copies, r, traffic >= large_update(r) || traffic < unrolled_update(r), [&](auto R, const auto& tab) {
+        return dispatch_copies(copies, r, unrolled_update(r, traffic), [&](auto R, const auto& tab) {
             return launch(avg_adam_kernel<R.value, BF.value, std::decay_t<decltype(tab)>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16,
                           tab, r, scale, count, hp, through);
         });

@@ -197,15 +197,22 @@ inline int average_store(int r, size_t count, bool streamed)
 // 31.4 / 30.1, r = 4 40 MB 8.4 / 8.7, 80 MB 15.4 / 15.0, 180 MB 32.2 / 30.2, r = 6 120 MB 21.6 / 20.5, r = 8 40 MB 8.3 / 8.3, 120 MB 21.7 / 20.8; reorder at 32
 // MB 7.7, 64x32 8.7, at 64 MB 13.1, 12.0.
 constexpr size_t kLargeAverage = 60u << 20;
-// Updates of more copies later (us, full-size workgroups / single wavefronts: r = 12 70 MB 12.9 / 13.3, 150 MB 5 % faster, r = 16 80 MB 13.9 / 14.9, 120 MB 21.2 / 21.6), without an
-// unrolled kernel latest (r = 9 150 MB 26.9 / 28.9).
-inline size_t large_update(int r) { return (r <= 8 ? size_t{76} : r == 12 ? size_t{100} : r == 16 ? size_t{130} : size_t{200}) << 20; }
-// Averages of 3, 5, 6 and 7 copies have unrolled kernels for all but the largest calls (us, any r / unrolled: r = 3 3 MB 2.63 / 2.29, 90 MB 15.3 / 14.7, r = 6 3 MB 2.7 /
-// 2.3, 90 MB 16.7 / 15.4, 800 MB 119.7 / 121.6, r = 5 800 MB 122.3 / 122.4), updates of so
-// many, and of 12 and 16, for calls that are all latency and for large ones (r = 3 5 MB 3.4 / 2.9, 40 MB 7.2 / 8.6, 180 MB 33.0 / 30.5; r = 5 5 MB 3.6 / 3.0, 40 MB 7.9 / 8.3, 180 MB 32.4 /
-// 30.6; r = 16 3 MB 3.6 / 2.8, 28 MB 10 % faster, 80 MB 14.0 / 14.3).
-inline bool unrolled_average(int r, size_t count, bool streamed) { return r == 3 ? !streamed : r >= 12 || count * (4 * (size_t)r + 4) < (500u << 20); }
-inline size_t unrolled_update(int r) { return (r < 12 ? 12u : 36u) << 20; }
+// Updates of more copies later: us, full-size workgroups, any r / single wavefronts, unrolled: r = 9 160 MB 27.5 / 31.5, 240 MB 44.8 / 40.6, r = 11 180 MB 30.6 / 32.5, 200 MB 36.5 / 35.2, r = 12 120 MB 23.1 /
+// 24.6, r = 13 180 MB 31.8 / 32.4, 240 MB 44.1 / 41.4, r = 16 140 MB 24.1 / 27.9, 240 MB 48.1 / 41.1; above 16, all of them any r: r = 20 180 MB 36.3 / 34.5, r = 24 200 MB 40.8 / 37.8.
+inline size_t large_update(int r) { return (r <= 8 ? size_t{76} : r < 12 ? size_t{180} : r <= 16 ? size_t{200} : size_t{160}) << 20; }
+// Copies in numbers other than 1, 2, 4 and 8 have unrolled kernels up to 16, whose loads need no pointer's load before each of them, and the one for any r, which
+// spaces its loads by that.  Averages, us, any r / unrolled: r = 3 3 MB 2.63 / 2.29, 90 MB 15.3 / 14.7, r = 6 3 MB 2.7 / 2.3, 90 MB 16.7 / 15.4, 800 MB
+// 119.7 / 121.6, r = 5 800 MB 122.3 / 122.4; r = 9 4 MB 2.9 / 2.5, 130 MB 22.9 / 22.2, 300 MB 46.8 / 45.7, r = 12 8 MB 3.4 / 3.1, 28 MB 6.5 / 7.2, 130 MB 22.8 / 24.2, 300 MB 47.1 / 46.4, r
+// = 13 500 MB 75.2 / 75.9, 1 GB 146.6 / 146.3, r = 16 12 MB 4.1 / 3.8, 40 MB 8.7 / 9.2, 250 MB 41.3 / 42.7.
+inline bool unrolled_average(int r, size_t count, bool streamed)
+{
+    const size_t traffic = count * (4 * (size_t)r + 4);
+    if (r > 8) return traffic < (16u << 20) || (r < 14 && traffic >= (200u << 20));
+    return r == 3 ? !streamed : traffic < (500u << 20);
+}
+// Updates: r = 3 5 MB 3.4 / 2.9, 40 MB 7.2 / 8.6, 180 MB 33.0 / 30.5; r = 5 5 MB 3.6 / 3.0, 40 MB 7.9 / 8.3, 180 MB 32.4 / 30.6; r = 9 4 MB 3.5 / 2.9, 20 MB 5.4 / 5.7, 300 MB 49.7 / 48.1, 900 MB
+// 152 / 135; r = 13 20 MB 5.35 / 4.9, 40 MB 8.1 / 8.15, 300 MB 53.7 / 50.3; r = 12 33 MB 7.0 / 7.4; r = 16 3 MB 3.6 / 2.8, 28 MB 10 % faster, 80 MB 15.7 / 16.9, 400 MB 69.9 / 66.9.
+inline bool unrolled_update(int r, size_t traffic) { return traffic >= large_update(r) || traffic < (r < 12 ? 12u << 20 : 30u << 20); }
 
 inline Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units)
 {
@@ -215,17 +222,26 @@ inline Shape average_shape(int r, size_t count, bool streamed, bool lines, size_
     // few copies, few loads in flight per lane: every wavefront that fits (3 copies 300 MB 42.3, a cap of 14 46.1, but 800 MB 127.3, 120.6, streamed 2.1 GB 328, 345)
     if (r < 4) return with_knobs(kFamAverage, Shape{64, count >= kHugeElements ? 16 : r == 3 && !streamed && traffic >= (600u << 20) ? 14 : 0});
     if (traffic < kLargeAverage) return with_knobs(kFamAverage, r < 5 ? small_call(nlanes, units) : even_call(nlanes, units, 256, r < 12 ? 384 : 448));
+    // more than 8 copies stay with full-size workgroups up to 96 MiB, if all that a unit gets run at once, up to three of them (25 wavefronts), or as many that their
+    // number no longer matters: us, full-size workgroups / single wavefronts, per unit in front, r = 11 22 12.5 / 13.5, r = 13 19 12.7 / 13.5, 27 20.1 / 18.3, r = 16 22 17.1 / 18.3, r = 14 25.4
+    // 20.6 / 18.4, r = 9 27 14.4 / 13.5, 38 17.1 / 18.0, r = 10 34 17.5 / 18.0, r = 64 6 17.5 / 19.2
+    const size_t waves = nlanes / (64 * units);
+    if (r > 8 && traffic < (96u << 20) && (waves < 25 || waves >= 32)) return with_knobs(kFamAverage, even_call(nlanes, units, 256, 448));
     // us, caps of 9 / 10 / 11 / 12 / 14 / 16 / 18: 4 copies 90 MB 17.1 / 16.6 / 16.4 / 16.0 / 15.7 / 15.3 / 15.0, 300 MB 48.9 / 47.4 / 46.4 / 45.8 / 45.0 / 44.6 / 44.6,
     // 800 MB 127.6 / 124.5 / 121.3 / 122.4 / 125.2 / 126.7 / 127.7, streamed 1.5 GB a cap of 16 232, 11 254; 5 copies 90 MB 16.8 / 16.2 / 16.4 / 16.1 / 15.4 / 15.3 / 15.3, 300
     // MB 46.5 / 45.7 / 45.6 / 45.5 / 45.1 / 45.6 / 45.8, 800 MB 123.2 / 122.4 / 123.3 / 125.3; 6 copies 90 MB 16.6 / 16.2 / 16.1 / 15.7 / 15.4, 300 MB 46.8 / 46.2 /
-    // 45.9 / 46.0 / 46.4; 8 copies 90 MB 15.7 / 15.4 / 15.3 / 15.4, 300 MB 46.2 / 46.3 / 46.3; 12 copies, caps of 7 / 8 / 9 300 MB 48.2 / 48.5 / 48.3, 800 MB 117.8 /
-    // 118.0 / 118.3; 16 copies 800 MB 120.2 / 120.7 / 121.1
+    // 45.9 / 46.0 / 46.4; 8 copies 90 MB 15.7 / 15.4 / 15.3 / 15.4, 300 MB 46.2 / 46.3 / 46.3.  Caps of 7 / 8 / 9 / 10, unrolled: 9 copies 300 MB 46.7 / 45.7 / 45.5 / 45.6, 1 GB 146.0 / 142.9 /
+    // 145.0 / 144.9, 11 copies 1 GB 145.1 / 145.6 / 146.0 / 146.8, 13 copies 1 GB 147.0 / 146.3 / 147.3 / 147.7; any r: 9 copies 130 MB 24.1 / 23.5 / 23.0 / 22.9, 12 copies 160 MB 28.0 / 28.1 / 27.3 / 27.4, 16
+    // copies 160 MB 28.2 / 28.7 / 27.9 / 28.1, 300 MB 47.7 / 48.3 / 48.1 / 48.4, 1 GB 147.2 / 148.9 / 150.0 / 151.0, 24 copies 250 MB 44.2 / 45.1 / 42.3 / 42.4, 64 copies 250 MB 47.8 / 49.0 / 47.2 / 45.0, 700
+    // MB 111.1 / 113.1 / 113.0 / 114.3
     const bool wide = traffic < (500u << 20) || (r < 5 && streamed);
     int cap = 0;
     if (r < 5) cap = traffic < (200u << 20) ? 18 : wide ? 16 : 11;
     else if (r < 6) cap = wide ? 14 : 11;
     else if (r < 8) cap = traffic < (120u << 20) ? 14 : wide ? 11 : 9;
-    else cap = r < 12 ? (traffic < (200u << 20) ? 10 : 9) : traffic < (200u << 20) ? 9 : 7;
+    else if (r < 9) cap = traffic < (200u << 20) ? 10 : 9;
+    else if (r < 14) cap = traffic >= (200u << 20) ? 8 : r < 12 ? 10 : 9;
+    else cap = traffic < (280u << 20) ? 9 : 7;
     return with_knobs(kFamAverage, Shape{64, cap});
 }
 
@@ -239,11 +255,13 @@ inline Shape fused_shape(int r, size_t count, bool lines, size_t units)
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 6 : 4});
     // us, caps of 4 / 5 / 6 / 7 / 8 / 9 / 10 / 11, at 120 MB: r = 1 .. / 25.4 / 23.9 / 22.7 / 21.7 / 21.1 / 20.9, r = 3 22.8 / 21.9 / 21.3 / 21.1 / 21.1 / 21.2 from 6 on, r = 4 22.0 /
     // 21.2 / 21.0 / 21.0 / 21.1, r = 6 21.2 / 20.8 / 20.8 / 20.7 / 20.5, r = 8 22.9 / 21.4 / 21.0 / 21.1 / 21.2 / 20.8, r = 12 21.4 / 21.0 / 21.0 / 20.8 / 21.0; at 400 MB: r = 1 9 to 11 63.3 / 62.6 /
-    // 62.7, r = 2 62.5 at 9, r = 3 62.6 at 8, r = 4 61.6 at 7, r = 5 75.9 / 66.9 / 63.1 / 63.2 / 64.1, r = 6 71.9 / 64.2 / 62.2 / 62.9, r = 8 68.5 / 63.5 / 64.0 / 65.2, r = 12
-    // 66.2 / 66.8 / 67.9, r = 16 66.7 / 67.7 / 68.8; at 800 MB: r = 5 121.8 / 120.8 / 123.7 at 6 to 8, r = 6 140.9 / 124.8 / 120.3 / 122.6, r = 12 124.7 / 127.8, r = 16 125.8 / 128.8
+    // 62.7, r = 2 62.5 at 9, r = 3 62.6 at 8, r = 4 61.6 at 7, r = 5 75.9 / 66.9 / 63.1 / 63.2 / 64.1, r = 6 71.9 / 64.2 / 62.2 / 62.9, r = 8 68.5 / 63.5 / 64.0 / 65.2, r = 9
+    // 65.4 / 62.6 / 63.7, r = 11 63.5 / 63.5 / 64.2, r = 13 64.4 / 65.2 / 65.7, r = 16 66.9 / 67.6 / 68.1; at 800 MB: r = 5 121.8 / 120.8 / 123.7 at 6 to 8, r = 6 140.9 / 124.8 / 120.3 / 122.6; at 2.2 GB:
+    // r = 9 350.8 / 340.1 / 344.2, r = 11 343.3 / 345.0 / 345.5, r = 13 333.3 / 341.6 / 342.9, r = 16 337.7 / 347.4 / 350.9.  Any r, caps of 5 / 8 or 9: r = 20 240 MB 47.0 / 43.0, 300 MB 56.0 / 52.3, r = 32 240 MB
+    // 47.5 / 43.9, 900 MB 148.8 / 154.6, r = 64 300 MB 58.0 / 54.6, 2.2 GB 374.5 / 377.6
     constexpr int kCapSmall[9] = {0, 11, 10, 10, 9, 8, 8, 8, 9}, kCap[9] = {0, 10, 9, 8, 7, 7, 6, 6, 5};
     const bool below = traffic < (220u << 20);
-    return with_knobs(kFamFused, Shape{64, r <= 8 ? (below ? kCapSmall[r] : kCap[r]) : r == 12 || r == 16 ? (below ? 6 : 4) : 5});
+    return with_knobs(kFamFused, Shape{64, r <= 8 ? (below ? kCapSmall[r] : kCap[r]) : r <= 16 ? (r < 12 ? 5 : 4) : traffic < (300u << 20) ? 9 : 5});
 }
 
 inline Shape reorder_shape(size_t traffic, int lanes)

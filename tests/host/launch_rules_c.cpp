@@ -3,6 +3,18 @@
 
 using namespace mics;
 
+static long long code(Shape sh) { return sh.lanes * 64 + sh.waves_per_cu; }
+
 extern "C" {
 size_t rules_lds(int lanes, int waves_per_cu, size_t needed) { return lds_for(Shape{lanes, waves_per_cu}, needed); }
+
+// Lanes and cap of an average's (fused = 0) or an update's shape as lanes * 64 + cap, buffers on their lines.
+long long rules_copies(int fused, int r, size_t count, size_t units)
+{
+    return code(fused ? fused_shape(r, count, true, units) : average_shape(r, count, stream_acc(count), true, units));
+}
+int rules_unrolled(int fused, int r, size_t count)
+{
+    return fused ? unrolled_update(r, count * (4 * (size_t)r + 26)) : unrolled_average(r, count, stream_acc(count));
+}
 }

@@ -18,6 +18,9 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(str(lib))
     lib.rules_lds.restype = ctypes.c_size_t
     lib.rules_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    lib.rules_copies.restype = ctypes.c_longlong
+    lib.rules_copies.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
+    lib.rules_unrolled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
     return lib
 
 
@@ -47,6 +50,36 @@ def test_a_cap_on_wavefronts_is_one(rules, lanes):
     assert rules.rules_lds(lanes, 32, 20000) >= 20000
 
 
-
 def test_caps_that_can_be_had_exactly(rules):
     assert [c for c in HAD if c < 32] == [2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 14, 16, 18, 21, 25]
+
+
+def shape(code):
+    return code // 64, code % 64
+
+
+@pytest.mark.parametrize("fused", [0, 1])
+@pytest.mark.parametrize("mb", [3, 8, 14, 20, 30, 40, 50, 120, 150, 180, 220, 250, 290, 320, 500, 900, 2000])
+def test_no_number_of_copies_stands_alone(rules, fused, mb):
+    """From 9 copies on a call of some size is launched as those of one copy less or one more are."""
+    def answer(r):
+        count = mb * 10**6 // (4 * r + (26 if fused else 4))
+        lanes, cap = shape(rules.rules_copies(fused, r, count, UNITS))
+        # how many lanes a small call takes follows its elements, not its copies
+        return rules.rules_unrolled(fused, r, count), (lanes, cap) if mb >= 220 else cap
+    answers = {r: answer(r) for r in range(9, 65)}
+    for r in range(10, 64):
+        assert answers[r] in (answers[r - 1], answers[r + 1]), (r, answers[r - 1], answers[r], answers[r + 1])
+
+
+@pytest.mark.parametrize("r", [9, 11, 12, 13, 16, 24, 64])
+def test_averages_of_many_copies_stay_with_full_size_workgroups_that_run_at_once(rules, r):
+    """60 to 96 MiB: up to 24 wavefronts a unit are three full-size workgroups, and from 32 on their number hardly matters."""
+    for mib in (61, 66, 72, 80, 88, 95):
+        count = mib * 2**20 // (4 * r + 4)
+        waves = count // 4 // (64 * UNITS)
+        lanes, cap = shape(rules.rules_copies(0, r, count, UNITS))
+        if 25 <= waves < 32:
+            assert lanes == 64 and cap > 0, (mib, lanes, cap)
+        else:
+            assert cap == 0, (mib, lanes, cap)
