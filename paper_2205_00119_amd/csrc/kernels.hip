@@ -1820,7 +1820,7 @@ int launch_replica_average(float* out, const PtrTable& a, size_t count, int r, f
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_AVG_BPC, &blocks)) return e;
     const dim3 gr(blocks), bl(sh.lanes);
     auto run = [&](auto SO) {
-        return dispatch_copies(a, r, unrolled_average(r, count, streamed), [&](auto R, const auto& tab) {
+        return dispatch_copies(a, r, unrolled_average(r, count, streamed, units), [&](auto R, const auto& tab) {
             return launch(avg_kernel<R.value, SO.value, std::decay_t<decltype(tab)>>, gr, bl, lds, st, out, tab, r, scale, count);
         });
     };
@@ -2094,7 +2094,7 @@ int launch_avg_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* 
     if (int e = grid_for((count + 3) / 4, sh.lanes, MICS_ADAM_BPC, &blocks)) return e;
     return dispatch_param(param_bf16, param_f16, [&](auto BF) {
         const dim3 gr(blocks), bl(sh.lanes);
-        return dispatch_copies(copies, r, unrolled_update(r, traffic), [&](auto R, const auto& tab) {
+        return dispatch_copies(copies, r, unrolled_update(r, count, units), [&](auto R, const auto& tab) {
             return launch(avg_adam_kernel<R.value, BF.value, std::decay_t<decltype(tab)>>, gr, bl, lds, st, master, exp_avg, exp_avg_sq, param_bf16,
                           tab, r, scale, count, hp, through);
         });

@@ -200,19 +200,30 @@ constexpr size_t kLargeAverage = 60u << 20;
 // Updates of more copies later: us, full-size workgroups, any r / single wavefronts, unrolled: r = 9 160 MB 27.5 / 31.5, 240 MB 44.8 / 40.6, r = 11 180 MB 30.6 / 32.5, 200 MB 36.5 / 35.2, r = 12 120 MB 23.1 /
 // 24.6, r = 13 180 MB 31.8 / 32.4, 240 MB 44.1 / 41.4, r = 16 140 MB 24.1 / 27.9, 240 MB 48.1 / 41.1; above 16, all of them any r: r = 20 180 MB 36.3 / 34.5, r = 24 200 MB 40.8 / 37.8.
 inline size_t large_update(int r) { return (r <= 8 ? size_t{76} : r < 12 ? size_t{180} : r <= 16 ? size_t{200} : size_t{160}) << 20; }
+// ... and up to 8 copies not below 25 wavefronts a unit, which all run at once as full-size workgroups: us, so / single wavefronts, r = 6 80 MB 15.5 / 16.3, r = 7 80 MB 14.8 / 16.1, 84 MB
+// 15.2 / 16.8, 88 MB 17.3 / 17.7, r = 8 88 MB 16.0 / 16.9, 92 MB 18.3 / 18.3.
+inline bool single_waves_update(int r, size_t count, size_t units)
+{
+    return count * (4 * (size_t)r + 26) >= large_update(r) && (r > 8 || (count + 3) / 4 >= units * 1600);
+}
 // Copies in numbers other than 1, 2, 4 and 8 have unrolled kernels up to 16, whose loads need no pointer's load before each of them, and the one for any r, which
-// spaces its loads by that.  Averages, us, any r / unrolled: r = 3 3 MB 2.63 / 2.29, 90 MB 15.3 / 14.7, r = 6 3 MB 2.7 / 2.3, 90 MB 16.7 / 15.4, 800 MB
-// 119.7 / 121.6, r = 5 800 MB 122.3 / 122.4; r = 9 4 MB 2.9 / 2.5, 130 MB 22.9 / 22.2, 300 MB 46.8 / 45.7, r = 12 8 MB 3.4 / 3.1, 28 MB 6.5 / 7.2, 130 MB 22.8 / 24.2, 300 MB 47.1 / 46.4, r
+// spaces its loads by that.  Averages, us, any r / unrolled: r = 3 3 MB 2.63 / 2.29, 90 MB 15.3 / 14.7, r = 6 3 MB 2.7 / 2.3, 11 MB 3.8 / 3.55, 20 MB 5.05 / 5.4, 38 MB 7.8 / 8.3, 90 MB 16.7 / 15.4, 800 MB
+// 119.7 / 121.6, r = 7 9 MB 3.5 / 3.1, 24 MB 5.7 / 6.3, 56 MB 11.3 / 12.2, r = 5 800 MB 122.3 / 122.4; r = 9 4 MB 2.9 / 2.5, 130 MB 22.9 / 22.2, 300 MB 46.8 / 45.7, r = 12 8 MB 3.4 / 3.1, 19 MB 5.35 / 4.9, 26 MB 5.85 / 5.5, 28 MB 6.5 / 7.2, 130 MB 22.8 / 24.2, 300 MB 47.1 / 46.4, r
 // = 13 500 MB 75.2 / 75.9, 1 GB 146.6 / 146.3, r = 16 12 MB 4.1 / 3.8, 40 MB 8.7 / 9.2, 250 MB 41.3 / 42.7.
-inline bool unrolled_average(int r, size_t count, bool streamed)
+// So from 6 copies on: unrolled in calls of up to one full-size workgroup a unit, which are all latency, and in large ones.
+inline bool unrolled_average(int r, size_t count, bool streamed, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 4);
-    if (r > 8) return traffic < (16u << 20) || (r < 14 && traffic >= (200u << 20));
-    return r == 3 ? !streamed : traffic < (500u << 20);
+    if (r > 5 && (count + 3) / 4 <= units * kMaxBlock) return true;
+    if (r > 8) return r < 14 && traffic >= (200u << 20);
+    return r == 3 ? !streamed : (r < 6 || traffic >= kLargeAverage) && traffic < (500u << 20);
 }
 // Updates: r = 3 5 MB 3.4 / 2.9, 40 MB 7.2 / 8.6, 180 MB 33.0 / 30.5; r = 5 5 MB 3.6 / 3.0, 40 MB 7.9 / 8.3, 180 MB 32.4 / 30.6; r = 9 4 MB 3.5 / 2.9, 20 MB 5.4 / 5.7, 300 MB 49.7 / 48.1, 900 MB
 // 152 / 135; r = 13 20 MB 5.35 / 4.9, 40 MB 8.1 / 8.15, 300 MB 53.7 / 50.3; r = 12 33 MB 7.0 / 7.4; r = 16 3 MB 3.6 / 2.8, 28 MB 10 % faster, 80 MB 15.7 / 16.9, 400 MB 69.9 / 66.9.
-inline bool unrolled_update(int r, size_t traffic) { return traffic >= large_update(r) || traffic < (r < 12 ? 12u << 20 : 30u << 20); }
+inline bool unrolled_update(int r, size_t count, size_t units)
+{
+    return single_waves_update(r, count, units) || count * (4 * (size_t)r + 26) < (r < 12 ? 12u << 20 : 30u << 20);
+}
 
 inline Shape average_shape(int r, size_t count, bool streamed, bool lines, size_t units)
 {
@@ -251,7 +262,7 @@ inline Shape fused_shape(int r, size_t count, bool lines, size_t units)
 {
     const size_t traffic = count * (4 * (size_t)r + 26);
     if (!lines) return with_knobs(kFamFused, off_lines((count + 3) / 4, units));
-    if (traffic < large_update(r)) return with_knobs(kFamFused, r < 12 ? small_call((count + 3) / 4, units) : even_call((count + 3) / 4, units));
+    if (!single_waves_update(r, count, units)) return with_knobs(kFamFused, r < 12 ? small_call((count + 3) / 4, units) : even_call((count + 3) / 4, units));
     if (count >= kHugeElements) return with_knobs(kFamFused, Shape{64, r < 4 ? 8 : r < 8 ? 6 : 4});
     // us, caps of 4 / 5 / 6 / 7 / 8 / 9 / 10 / 11, at 120 MB: r = 1 .. / 25.4 / 23.9 / 22.7 / 21.7 / 21.1 / 20.9, r = 3 22.8 / 21.9 / 21.3 / 21.1 / 21.1 / 21.2 from 6 on, r = 4 22.0 /
     // 21.2 / 21.0 / 21.0 / 21.1, r = 6 21.2 / 20.8 / 20.8 / 20.7 / 20.5, r = 8 22.9 / 21.4 / 21.0 / 21.1 / 21.2 / 20.8, r = 12 21.4 / 21.0 / 21.0 / 20.8 / 21.0; at 400 MB: r = 1 9 to 11 63.3 / 62.6 /

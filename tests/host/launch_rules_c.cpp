@@ -13,8 +13,8 @@ long long rules_copies(int fused, int r, size_t count, size_t units)
 {
     return code(fused ? fused_shape(r, count, true, units) : average_shape(r, count, stream_acc(count), true, units));
 }
-int rules_unrolled(int fused, int r, size_t count)
+int rules_unrolled(int fused, int r, size_t count, size_t units)
 {
-    return fused ? unrolled_update(r, count * (4 * (size_t)r + 26)) : unrolled_average(r, count, stream_acc(count));
+    return fused ? unrolled_update(r, count, units) : unrolled_average(r, count, stream_acc(count), units);
 }
 }

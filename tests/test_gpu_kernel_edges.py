@@ -643,7 +643,7 @@ def test_reduce_in_one_even_workgroup_per_unit(orc, gen, name, p, per_unit, tens
 
 
 @pytest.mark.parametrize("r,count", [
-    (3, 5), (3, 331_127), (3, 331_131), (3, 2_097_149), (3, 2_097_155), (5, 1_733_000), (5, 1_733_001), (6, 77_003), (6, 1_600_003), (7, 1_500_001), (7, 260_003),
+    (3, 5), (3, 331_127), (3, 331_131), (3, 2_097_149), (3, 2_097_155), (5, 1_733_000), (5, 1_733_001), (6, 77_003), (6, 1_600_003), (6, 524_288), (7, 524_289), (12, 524_285), (7, 1_500_001), (7, 260_003), (7, 1_610_003), (8, 1_500_003),
     (9, 1_048_579), (9, 140_003), (9, 419_431), (9, 5_242_883), (10, 262_147), (11, 300_003), (13, 349_531), (13, 3_744_923), (14, 280_003), (15, 4_191), (16, 246_727),
     (17, 1_783_003), (24, 700_001), (12, 510_103), (12, 510_104), (12, 1_416_993), (13, 40_001), (16, 420_003), (16, 1_515_002)])
 @pytest.mark.parametrize("skew", [0, 1])

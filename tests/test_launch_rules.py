@@ -20,7 +20,7 @@ def rules(tmp_path_factory):
     lib.rules_lds.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
     lib.rules_copies.restype = ctypes.c_longlong
     lib.rules_copies.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
-    lib.rules_unrolled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    lib.rules_unrolled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     return lib
 
 
@@ -66,7 +66,7 @@ def test_no_number_of_copies_stands_alone(rules, fused, mb):
         count = mb * 10**6 // (4 * r + (26 if fused else 4))
         lanes, cap = shape(rules.rules_copies(fused, r, count, UNITS))
         # how many lanes a small call takes follows its elements, not its copies
-        return rules.rules_unrolled(fused, r, count), (lanes, cap) if mb >= 220 else cap
+        return rules.rules_unrolled(fused, r, count, UNITS), (lanes, cap) if mb >= 220 else cap
     answers = {r: answer(r) for r in range(9, 65)}
     for r in range(10, 64):
         assert answers[r] in (answers[r - 1], answers[r + 1]), (r, answers[r - 1], answers[r], answers[r + 1])
@@ -83,3 +83,23 @@ def test_averages_of_many_copies_stay_with_full_size_workgroups_that_run_at_once
             assert lanes == 64 and cap > 0, (mib, lanes, cap)
         else:
             assert cap == 0, (mib, lanes, cap)
+
+
+@pytest.mark.parametrize("r", range(1, 9))
+def test_updates_go_to_single_wavefronts_where_full_size_workgroups_no_longer_run_at_once(rules, r):
+    """From 76 MiB on, but up to 8 copies not below 25 wavefronts a unit."""
+    for mib in (40, 60, 75, 77, 80, 83, 88, 92, 100):
+        count = mib * 2**20 // (4 * r + 26)
+        single = mib > 76 and count // 4 >= 1600 * UNITS
+        assert (shape(rules.rules_copies(1, r, count, UNITS))[1] > 0) == single, mib
+        if r in (3, 5, 6, 7):
+            assert rules.rules_unrolled(1, r, count, UNITS) == single, mib
+
+
+@pytest.mark.parametrize("r", [6, 7, 9, 12, 13, 14, 16])
+def test_averages_keep_the_kernel_for_any_number_of_copies_in_the_middle(rules, r):
+    """Unrolled up to one full-size workgroup a unit and, but for 14 and more copies, in large calls."""
+    one = 512 * 4 * UNITS
+    large = ((60 if r < 8 else 200) << 20) // (4 * r + 4) + 1
+    for count, unrolled in ((5, 1), (one, 1), (one + 1, 0), (large - 2, 0), (large, r < 14)):
+        assert rules.rules_unrolled(0, r, count, UNITS) == unrolled, count
