@@ -388,18 +388,20 @@ inline bool shallow_segments(int p, int elem_bytes, size_t nlanes, size_t units)
 // is the one that leaves the least of the last round empty, beside what a cap costs in calls of many rounds.  us, bf16, p = 128, 17 wavefronts per unit
 // (585 MB), caps of 6 / 7 / 8 / 9 / 10 / 12 / 16: 89.7 / 93.7 / 101.8 / 87.8 / 90.1 / 97.9 / 101.9; p = 64, 20 per unit (354 MB) 60.0 / 53.5 / 56.3 / 60.1 /
 // 54.6 / 56.2 / 57.4; p = 24, 70 per unit (511 MB) 82.8 / 79.3 / 75.9 / 79.3 / 79.2 / 79.7 / 78.6.  An empty round costs about 0.4 of a full one.
-// All in one round is as good up to 12 per unit (p = 64, 11: 30.3, two rounds 31.3; 14: 38.9, two 37.8; odd rows, 13: 39.5, 36.5).
+// All in one round is as good up to 12 per unit (p = 64, 11: 30.3, two rounds 31.3; 14: 38.9, two 37.8; odd rows, 13: 39.5, 36.5).  The workgroup for the ends
+// does not count: without one, calls of exactly full rounds take as long (p = 4 to 128, 2 to 24 per unit, 130 sizes within .5 %).
 inline Shape shallow_shape(int p, size_t nlanes, size_t units)
 {
-    // {waves, cost up to 48 buffers, from 64 on, from 64 on in calls of 46 and more wavefronts per unit}
-    static constexpr struct { int waves; double cost[3]; } kCaps[] = {
-        {6, {.06, .02, 0}}, {7, {.04, 0, .01}}, {8, {0, 0, .025}}, {9, {.04, .012, .035}}, {10, {.035, .025, .05}}, {11, {.04, .03, .06}},
-        {12, {.035, .035, .06}}, {14, {.035, .04, .07}}, {16, {.03, .04, .07}}};
+    // {waves, cost up to 19 buffers in calls of less than 46 wavefronts per unit, up to 48 otherwise, from 64 on, from 64 on in calls of 46 and more}
+    // Few buffers take more wavefronts in short calls: caps of 7 / 8 / 9 / 10 / 11 / 12 / 14 / none, speed against 16 in flight, p = 16 to 19, 21 per unit 1.04 / 1.04 / 1.01 / .98 / 1.07 / 1.05 /
+    // 1.02 / 1.07, 24 .99 / 1.04 / 1.04 / 1.01 / .98 / 1.05 / 1.02 / 1.05, 34 1.04 / 1.01 / 1.05 / 1.03 / 1.02 / 1.07 / 1.03 / 1.03.
+    // Long calls of many, us, caps of 6 / 7 / 8: p = 64 1.25 GB, first micro-step, 197.1 / 193.4 / 197.7, 2.1 GB 322.8 / 312.3 / 307.5, 2.5 GB, first, 387.4 / 368.6 / 380.3, p = 96 1.8 GB 274.7 / 267.9 / 271.4,
+    // 2.5 GB 372.1 / 377.2 / 377.4, p = 128 2.5 GB 379.1 / 378.5 / 389.7; f32, p = 64 2.5 GB 361.8 / 357.8 / 365.5.
+    static constexpr struct { int waves; double cost[4]; } kCaps[] = {
+        {6, {.06, .06, .02, .008}}, {7, {.045, .04, 0, 0}}, {8, {.02, 0, 0, .012}}, {9, {.015, .04, .012, .03}}, {10, {.01, .035, .025, .05}},
+        {11, {0, .04, .03, .06}}, {12, {.01, .035, .035, .06}}, {14, {.005, .035, .04, .07}}, {16, {.015, .03, .04, .07}}};
     const double per_unit = (double)((nlanes + 63) / 64) / (double)units;
-    // between one round and the next, wavefronts of so few buffers need no cap (us, p = 16, 21 per unit caps of 8 / 10 / 12 / 16 / none 19.2 / 19.9 / 18.4 / 18.1 / 17.8, f32 17.1 /
-    // 18.1 / 16.7 / 17.1 / 16.4; 34 per unit 29.7 / 29.3 / 28.5 / 28.3 / 28.9)
-    if (p < 20 && per_unit >= 20 && per_unit < 26) return with_knobs(kFamReduce, Shape{64, 0});
-    const int column = p < 64 ? 0 : per_unit < 46 ? 1 : 2;
+    const int column = p < 64 ? !(p < 20 && per_unit < 46) : per_unit < 46 ? 2 : 3;
     int best = 8;
     double least = 1e9;
     for (const auto& c : kCaps) {

@@ -17,4 +17,6 @@ int rules_unrolled(int fused, int r, size_t count, size_t units)
 {
     return fused ? unrolled_update(r, count, units) : unrolled_average(r, count, stream_acc(count), units);
 }
+
+long long rules_shallow(int p, size_t nlanes, size_t units) { return code(shallow_shape(p, nlanes, units)); }
 }

@@ -1,5 +1,6 @@
 """The launch rules (csrc/launch_rules.h), built with plain g++ and asked for their answers.  No GPU involved."""
 import ctypes
+import math
 import os
 import subprocess
 
@@ -21,6 +22,8 @@ def rules(tmp_path_factory):
     lib.rules_copies.restype = ctypes.c_longlong
     lib.rules_copies.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     lib.rules_unrolled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
+    lib.rules_shallow.restype = ctypes.c_longlong
+    lib.rules_shallow.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     return lib
 
 
@@ -103,3 +106,18 @@ def test_averages_keep_the_kernel_for_any_number_of_copies_in_the_middle(rules, 
     large = ((60 if r < 8 else 200) << 20) // (4 * r + 4) + 1
     for count, unrolled in ((5, 1), (one, 1), (one + 1, 0), (large - 2, 0), (large, r < 14)):
         assert rules.rules_unrolled(0, r, count, UNITS) == unrolled, count
+
+
+@pytest.mark.parametrize("p", [16, 19, 20, 24, 31, 32, 48, 64, 96, 128])
+def test_shallow_batches_leave_no_round_of_wavefronts_nearly_empty(rules, p):
+    """At every size the cap is one of those measured, and the last round is at least four fifths full on its share of the call."""
+    for quarter in range(4 * 7, 4 * 400):
+        lanes, cap = shape(rules.rules_shallow(p, quarter * 16 * UNITS, UNITS))
+        rounds = quarter / 4 / cap if cap else 0
+        assert lanes == 64 and cap in (6, 7, 8, 9, 10, 11, 12, 14, 16), (quarter / 4, cap)
+        assert rounds <= 1 or rounds / math.ceil(rounds) > .84, (quarter / 4, cap)
+
+
+@pytest.mark.parametrize("p,per_unit,cap", [(64, 118, 7), (64, 144.5, 7), (96, 68.7, 7), (64, 72.2, 7), (96, 57.2, 6), (96, 95.4, 6), (64, 39.3, 8), (48, 110, 8), (16, 384, 8)])
+def test_shallow_batches_of_long_calls(rules, p, per_unit, cap):
+    assert shape(rules.rules_shallow(p, int(per_unit * 64) * UNITS, UNITS)) == (64, cap)
