@@ -777,16 +777,18 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 // these loads are out.  us, bf16, the best cap for each of 3 / 4 / 6 / 8 / 16 loads: p = 24 350 MB 53.3 / 52.7 / 53.3 / 54.0 / 55.6, 730 MB
 // 109.3 / 107.4 / 109.6 / 111.3 / 115.9; p = 32 159 MB 24.8 / 24.9 / 25.3 / 26.0 / 25.8; p = 64 301 MB 44.6 / 45.5 / 46.0 / 47.8 / 50.1; p = 128 482 MB
 // 73.1 / 71.1 / 76.3 / 76.9 / 80.2; f32, p = 24 325 MB 49.1 / 49.4 / 49.6 / 50.2 / 51.4, p = 64 430 MB 63.0 / 65.1 / 65.8 / 66.7 / 68.6.  A ring of 6 or 8
-// loads that moves on by two is 1 % slower.  The accumulator's loads go out with the last batch.
+// loads that moves on by two is 1 % slower.  The accumulator's loads go out with the last batch, of 4 to 7: where it took what 4 left over, one load was
+// alone in flight (speed of this against that, means of 40 to 70 calls: p = 17 1.014, 18 1.008, 21 1.011, 25 1.010; f32, 16 tensors, p = 17 318 MB 53.2 / 51.5, 1.1 GB 173.4 / 166.9).
 constexpr int kShallow = 4;
-template <int KIND, int N, typename Issue>
-__device__ __forceinline__ void rsa_last_batch(float* s, const void* const (&g)[kShallow], int n, size_t elem, Issue&& accumulator)
+// The last kShallow to 2 kShallow - 1 of the n buffers from q0; the pointers of the first kShallow are there.
+template <int KIND, int N, typename Tab, typename Issue>
+__device__ __forceinline__ void rsa_last_batch(float* s, const void* const (&first)[kShallow], const Tab& g, int q0, int n, size_t elem, Issue&& accumulator)
 {
-    if constexpr (N > 1)
-        if (n < N) return rsa_last_batch<KIND, N - 1>(s, g, n, elem, accumulator);
+    if constexpr (N > kShallow)
+        if (n < N) return rsa_last_batch<KIND, N - 1>(s, first, g, q0, n, elem, accumulator);
     GradVec<KIND, 4> v[N];
     #pragma unroll
-    for (int b = 0; b < N; ++b) v[b].load(g[b], elem);
+    for (int b = 0; b < N; ++b) v[b].load(b < kShallow ? first[b] : g.ptr[q0 + b], elem);
     accumulator();
     __builtin_amdgcn_sched_barrier(0);
     #pragma unroll
@@ -795,13 +797,12 @@ __device__ __forceinline__ void rsa_last_batch(float* s, const void* const (&g)[
 template <int KIND, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_shallow(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
-    static_assert(kMaxGroup % kShallow == 0, "a batch of pointers is inside the table");
     const void* next[kShallow];
     #pragma unroll
     for (int b = 0; b < kShallow; ++b) next[b] = g.ptr[b];
     int q0 = 0;
     #pragma unroll 1
-    for (; q0 + kShallow < p; q0 += kShallow) {
+    for (; q0 + 2 * kShallow <= p; q0 += kShallow) {
         GradVec<KIND, 4> v[kShallow];
         #pragma unroll
         for (int b = 0; b < kShallow; ++b) v[b].load(next[b], elem);
@@ -811,7 +812,7 @@ __device__ __forceinline__ void rsa_shallow(float* s, const Tab& g, int p, size_
         #pragma unroll
         for (int b = 0; b < kShallow; ++b) rsa_add<KIND, 4, false>(s, v[b]);
     }
-    rsa_last_batch<KIND, kShallow>(s, next, p - q0, elem, accumulator);
+    rsa_last_batch<KIND, 2 * kShallow - 1>(s, next, g, q0, p - q0, elem, accumulator);
 }
 
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
