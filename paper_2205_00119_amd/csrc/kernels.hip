@@ -2051,16 +2051,18 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
         alignable = alignable && lead_on_accumulator_lines(acc + segs[t].dst_offset, (uintptr_t)g.ptr[0] + (segs[t].src_offset + base_lead) * GB, GB) >= 0;
     const ReduceOrder order = reduce_order_segments(p, (int)GB, elements * (p * GB + (accumulate ? 8 : 4)) >> 20, accumulate, alignable);
     bool acc16 = true;
-    size_t waves = 0;                                                // in single-wavefront workgroups
+    size_t waves = 0, full = 0, half = 0;                            // workgroups of 64 lanes, of kMaxBlock and of half as many
     for (int t = 0; t < n; ++t) {
         const size_t lead = segment_lead<KIND>(acc, g, segs[t].src_offset + base_lead, segs[t].dst_offset, unit, order);
         waves += (lead + segs[t].numel + 64 * EPL - 1) / (64 * EPL);
+        full += (lead + segs[t].numel + kMaxBlock * EPL - 1) / (kMaxBlock * EPL);
+        half += (lead + segs[t].numel + kMaxBlock / 2 * EPL - 1) / (kMaxBlock / 2 * EPL);
         acc16 = acc16 && ((uintptr_t)(acc + segs[t].dst_offset) - 4 * lead) % 16 == 0;
     }
     const int policy = accum_policy(elements, p, (int)GB);
     const size_t nlanes = (elements + EPL - 1) / EPL;
     const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units);
-    const Shape sh = shallow ? shallow_shape(p, 64 * waves, units) : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
+    const Shape sh = shallow ? shallow_shape_segments(p, waves, full, half, n, units) : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
     return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st)
                    : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st);
 }

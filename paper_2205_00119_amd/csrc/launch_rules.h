@@ -412,5 +412,19 @@ inline Shape shallow_shape(int p, size_t nlanes, size_t units)
     return with_knobs(kFamReduce, Shape{64, best});
 }
 
+// The same for n segments, whose partial tiles add wavefronts to an even number.  From 48 buffers on full-size workgroups (`full` of them for the whole call) where a unit
+// gets one at most, and from 8 segments on where they fill two or three a unit evenly: speed of single wavefronts / of these against 16 loads in flight, 64 to 128 buffers, wavefronts
+// per unit in front, mean and worst: 6 1.10, 1.06 / 1.19, 1.12 (bf16, p = 64, 16 tensors, 105 MB 23.2 / 18.8 us); 7 .96, .86 / 1.12, 1.07; 13.5 1.06, 1.02 / 1.10, 1.09; 14.5 1.05, .98 / 1.09, 1.03; 22 1.04,
+// 1.00 / 1.06, 1.03; 23.5 .99, .96 / 1.06, 1.04; not filled evenly 12.5 1.05 / 1.07, 17 1.11 / 1.02, 26 1.13 / 1.04, 30 1.10 / 1.05; 2 segments, p = 128 15.4 82.3 / 88.6 us.
+// From 16 segments on workgroups of 256 lanes, two, three or five of which fill a unit: speed against single wavefronts, means of 40 to 60 calls, 9.5 to 12 per unit 1.014, 17.5 to 20 1.024.
+inline Shape shallow_shape_segments(int p, size_t waves, size_t full, size_t half, int n, size_t units)
+{
+    // the wavefronts if all units get as many workgroups as the fullest one, by those that there are
+    auto waste = [&](size_t groups, size_t of) { return (double)((groups + units - 1) / units * units * of) / (double)waves; };
+    if (p >= 48 && (full <= units || (n >= 8 && full <= 3 * units && waste(full, 8) <= 1.2))) return with_knobs(kFamReduce, Shape{kMaxBlock, 0});
+    if (p >= 48 && n >= 16 && half <= 5 * units && waste(half, 4) <= 1.12) return with_knobs(kFamReduce, Shape{kMaxBlock / 2, 0});
+    return shallow_shape(p, 64 * waves, units);
+}
+
 }  // namespace
 }  // namespace mics

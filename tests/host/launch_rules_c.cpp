@@ -19,4 +19,9 @@ int rules_unrolled(int fused, int r, size_t count, size_t units)
 }
 
 long long rules_shallow(int p, size_t nlanes, size_t units) { return code(shallow_shape(p, nlanes, units)); }
+// n equal segments of `lanes` lanes each.
+long long rules_shallow_segments(int p, size_t lanes, size_t n, size_t units)
+{
+    return code(shallow_shape_segments(p, n * ((lanes + 63) / 64), n * ((lanes + 511) / 512), n * ((lanes + 255) / 256), (int)n, units));
+}
 }

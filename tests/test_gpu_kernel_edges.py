@@ -584,10 +584,11 @@ def test_reduce_in_shallow_batches(orc, gen, name, p, count):
 
 @pytest.mark.parametrize("name,p,numel", [
     ("bf16", 17, 1_600_003), ("f32", 24, 800_011), ("f16", 32, 1_600_009), ("bf16", 33, 1_580_001), ("f32", 48, 790_003), ("bf16", 64, 725_005),
-    ("f16", 96, 730_001), ("f32", 128, 362_003), ("bf16", 12, 2_100_003), ("f16", 40, 300_007)])
+    ("f16", 96, 730_001), ("f32", 128, 362_003), ("bf16", 12, 2_100_003), ("f16", 40, 300_007),
+    ("bf16", 64, 900_003), ("f32", 48, 983_003), ("f16", 49, 1_990_003), ("f32", 128, 458_003)])
 @pytest.mark.parametrize("threshold", [0, 1])
 def test_reduce_segments_in_shallow_batches(orc, gen, name, p, numel, threshold):
-    """Segments that are read in batches of 4, and any-p ones that are not: their ends in workgroups of their own, a segment shorter than
+    """Segments that are read in batches of 4, by single wavefronts, full-size workgroups and those of 256 lanes, and any-p ones that are not: their ends in workgroups of their own, a segment shorter than
     a lane's vector and one without ends among them."""
     code = FORMATS[name][0]
     segs, src, dst = [], 3, 0
@@ -607,6 +608,26 @@ def test_reduce_segments_in_shallow_batches(orc, gen, name, p, numel, threshold)
             assert same_bits(acc, ref), accumulate
     finally:
         mics.mics_set_stream_threshold_bytes(0)
+
+
+@pytest.mark.parametrize("name,p,per_unit", [("bf16", 64, 5.7), ("f16", 49, 12.6), ("f32", 48, 14.9), ("bf16", 50, 11.5), ("f32", 66, 11.7), ("f16", 48, 19.2)])
+def test_reduce_many_segments_in_shallow_batches(orc, gen, name, p, per_unit):
+    """17 segments by workgroups of 512 and 256 lanes and by single wavefronts, most of them with a partial last tile."""
+    code, dtype = FORMATS[name]
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    each = int(per_unit * 64 * units) * (16 // np.dtype(dtype).itemsize) // 17
+    segs, src, dst = [], 1, 0
+    for t in range(17):
+        n = each + (t - 8) * 333
+        segs.append((n, 0, src, dst))
+        src, dst = src + n + t % 3, dst + n
+    host, dev = rank_buffers(gen, name, p, src, [0])
+    for accumulate in (True, False):
+        ref, acc = start_acc(gen, dst)
+        mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, [d.t for d in dev], segs, accumulate, code)
+        orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
 
 
 @pytest.mark.parametrize("name,p,per_unit", [

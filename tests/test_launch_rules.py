@@ -24,6 +24,8 @@ def rules(tmp_path_factory):
     lib.rules_unrolled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     lib.rules_shallow.restype = ctypes.c_longlong
     lib.rules_shallow.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
+    lib.rules_shallow_segments.restype = ctypes.c_longlong
+    lib.rules_shallow_segments.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t]
     return lib
 
 
@@ -121,3 +123,13 @@ def test_shallow_batches_leave_no_round_of_wavefronts_nearly_empty(rules, p):
 @pytest.mark.parametrize("p,per_unit,cap", [(64, 118, 7), (64, 144.5, 7), (96, 68.7, 7), (64, 72.2, 7), (96, 57.2, 6), (96, 95.4, 6), (64, 39.3, 8), (48, 110, 8), (16, 384, 8)])
 def test_shallow_batches_of_long_calls(rules, p, per_unit, cap):
     assert shape(rules.rules_shallow(p, int(per_unit * 64) * UNITS, UNITS)) == (64, cap)
+
+
+@pytest.mark.parametrize("p,per_unit,n,lanes", [
+    (64, 5.6, 16, 512), (64, 5.6, 2, 512), (48, 7.7, 16, 512), (128, 7, 16, 512), (64, 15, 16, 512), (96, 23, 16, 512), (64, 8.5, 16, 64), (64, 12.5, 16, 64), (64, 17, 16, 64),
+    (64, 15, 4, 64), (128, 26, 16, 64), (64, 30, 16, 64), (47, 7, 16, 64), (64, 7.9, 40, 64), (64, 7.6, 30, 256), (64, 11.5, 16, 256), (64, 11.5, 8, 64),
+    (64, 19, 16, 256)])
+def test_segments_in_shallow_batches_fill_the_units_evenly(rules, p, per_unit, n, lanes):
+    """From 48 buffers on, full-size workgroups where a unit gets one, or a call of many segments two or three, nearly filled, and
+    workgroups of 256 lanes for two, three or five; 40 segments of 7.9 wavefronts a unit are more of them than two."""
+    assert shape(rules.rules_shallow_segments(p, int(per_unit * 64 * UNITS / n), n, UNITS))[0] == lanes
