@@ -345,8 +345,9 @@ inline Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bo
 // are faster (p = 6, 99 MB 18.1 / 17.2, f32 18.3 / 17.3).  Single wavefronts, us: p = 8, 279 MB caps of 9 / 12 42.7 / 41.4, f32 478 MB 73.8 / 71.1, 899
 // MB 141 / 135.5; p = 12, 169 MB 512 lanes 28.8, caps of 8 / 10 / 12 27.6 / 27.6 / 27.5, f32 477 MB 8 / 9 / 10 74.0 / 73.2 / 73.0, 899 MB 137.0 / 136.2 / 137.1; p =
 // 16, 169 MB 512 lanes 30.6, caps of 8 / 10 / 12 28.6 / 28.1 / 28.1, f32 478 MB 75.2 / 75.8 / 76.5.
-// Two two-byte buffers take 256 lanes, capped at 16 wavefronts but in first micro-steps (318 MB 64 lanes 55.5, 256 53.2, 805 MB 122 / 126), 2 and 3 of f32 below 300
-// wavefronts per unit (p = 3, 278 MB 43.7 / 42.1, 479 MB 74.4 / 74.3, 899 MB 152 / 157).
+// Two two-byte buffers take 256 lanes, capped at 16 wavefronts but in first micro-steps (318 MB 64 lanes 55.5, 256 53.2, 805 MB 122 / 126), up to 3 of f32 below 50
+// wavefronts per unit (speed of 256 lanes against 64, 200 calls, per unit in front: p = 1 to 25 1.10, 37 1.03, 50 .99, 75 .955, 100 .92, 300 .96; p = 2 25 1.03, 50 .98, 75 .96, 100 .96, 300 .98; p = 3
+// 25 1.00, 50 1.00, 75 1.00, 100 .99, 300 .985).
 inline Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, bool grads16, bool acc16, bool accumulate, bool cached, size_t units)
 {
     const bool two = elem_bytes == 2;
@@ -360,7 +361,7 @@ inline Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, 
     } else if (p < 4) {
         const bool small = per_unit < (acc16 ? 50 : 125);
         if (two) sh = !accumulate && p == 2 && per_unit >= 650 ? Shape{64, 0} : Shape{256, !small && p > 1 && (p == 3 || accumulate) ? 16 : 0};
-        else sh = Shape{per_unit < 300 ? 256 : 64, 0};
+        else sh = Shape{per_unit < 50 ? 256 : 64, 0};
     } else if (p < 12) {
         sh = per_unit < 50 ? Shape{256, 0} : Shape{64, p < 6 ? 16 : p < 8 ? 14 : 12};
     } else {

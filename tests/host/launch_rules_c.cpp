@@ -24,4 +24,8 @@ long long rules_shallow_segments(int p, size_t lanes, size_t n, size_t units)
 {
     return code(shallow_shape_segments(p, n * ((lanes + 63) / 64), n * ((lanes + 511) / 512), n * ((lanes + 255) / 256), (int)n, units));
 }
+long long rules_segments(int p, int elem_bytes, size_t nlanes, int n, int accumulate, size_t units)
+{
+    return code(reduce_shape_segments(p, elem_bytes, nlanes, n, true, true, accumulate, false, units));
+}
 }

@@ -26,6 +26,8 @@ def rules(tmp_path_factory):
     lib.rules_shallow.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     lib.rules_shallow_segments.restype = ctypes.c_longlong
     lib.rules_shallow_segments.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t]
+    lib.rules_segments.restype = ctypes.c_longlong
+    lib.rules_segments.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
     return lib
 
 
@@ -133,3 +135,10 @@ def test_segments_in_shallow_batches_fill_the_units_evenly(rules, p, per_unit, n
     """From 48 buffers on, full-size workgroups where a unit gets one, or a call of many segments two or three, nearly filled, and
     workgroups of 256 lanes for two, three or five; 40 segments of 7.9 wavefronts a unit are more of them than two."""
     assert shape(rules.rules_shallow_segments(p, int(per_unit * 64 * UNITS / n), n, UNITS))[0] == lanes
+
+
+@pytest.mark.parametrize("p", [1, 2, 3])
+def test_segments_of_few_f32_buffers(rules, p):
+    for per_unit, lanes in ((20, 256), (49, 256), (50, 64), (100, 64), (299, 64), (600, 64)):
+        for accumulate in (0, 1):
+            assert shape(rules.rules_segments(p, 4, per_unit * 64 * UNITS, 16, accumulate, UNITS)) == (lanes, 0), per_unit
