@@ -1778,7 +1778,7 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const size_t nlanes = (lead + count + 4 * PD - 1) / (4 * PD);
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
-    const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units);
+    const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units) && !long_call_in_step(g, p, nlanes, units);
     const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, policy == kAccCached, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
@@ -2061,7 +2061,7 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     }
     const int policy = accum_policy(elements, p, (int)GB);
     const size_t nlanes = (elements + EPL - 1) / EPL;
-    const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units);
+    const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units) && !long_call_in_step(g, p, nlanes, units);
     const Shape sh = shallow ? shallow_shape_segments(p, waves, full, half, n, units) : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
     return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st)
                    : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st);

@@ -319,6 +319,7 @@ inline int reduce_cap(int p, bool two, size_t nlanes, bool accumulate, size_t un
     if (p < 6) return accumulate ? (many ? 11 : two ? 14 : 16) : p > 4 ? 16 : many && !two ? 14 : 0;
     if (p < 8) return accumulate ? (many ? 10 : 12) : many ? 11 : 14;
     if (p < 12) return accumulate ? (many ? 8 : 10) : many ? (two ? 7 : 9) : 11;
+    if (p >= 32) return 5;                                 // long_call_in_step
     return accumulate ? (many ? 7 : 8) : many ? (two ? 6 : 7) : 10;
 }
 inline Shape reduce_shape(int p, int elem_bytes, size_t nlanes, bool grads16, bool acc16, bool accumulate, bool cached, size_t units)
@@ -365,7 +366,7 @@ inline Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, 
     } else if (p < 12) {
         sh = per_unit < 50 ? Shape{256, 0} : Shape{64, p < 6 ? 16 : p < 8 ? 14 : 12};
     } else {
-        sh = Shape{64, p >= 32 ? 8 : two ? 10 : p < 16 ? 9 : 8};
+        sh = Shape{64, p > 32 ? 5 : p == 32 ? 8 : two ? 10 : p < 16 ? 9 : 8};   // 33 and more: long_call_in_step
     }
     return with_knobs(kFamReduce, sh);
 }
@@ -375,6 +376,20 @@ inline Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, 
 // us, batches of 16 / so, wavefronts per unit in front: p = 32 7 11.7 / 12.2, 8 13.1 / 12.9, f32 7 11.2 / 11.4, 9 13.1 / 12.9; p = 48 5.2 13.2 / 13.3,
 // 6.3 15.2 / 14.1; p = 64 5.2 16.5 / 16.3; p = 128 4.2 27.3 / 27.6, 5.2 29.5 / 29.4, 6.3 34.8 / 32.1.
 inline bool shallow_call(int p, size_t nlanes, size_t units) { return p >= 16 && (p < 32 || nlanes >= units * (p < 48 ? 512 : 352)); }
+
+// Whether buffers lie 16 MiB (up to 63 of them also 32) from one to the next.  Four of them at a time meet in few memory channels, which long calls feel: us, 58 wavefronts per unit,
+// batches of 16 with 5 wavefronts / of 4, 16 MiB: p = 32 84.2 / 86.0, p = 48 122.5 / 140.8, f32 115.7 / 131.7, p = 64 162.9 / 167.3, f32 153.0 / 159.5, p = 96 237.1 / 244.0, p = 128 311.1 / 313.4; 32 MiB: p = 48
+// 119.6 / 125.3, p = 64 155.8 / 157.3, p = 96 231.5 / 228.9; 20 MiB: p = 64 160.4 / 157.7; 48 MiB 159.2 / 154.4; 64 MiB 158.5 / 150.9; 16 MiB, 29 per unit: p = 64 82.7 / 79.1.
+inline bool in_step(const PtrTable& g, int p)
+{
+    constexpr ptrdiff_t kStep = 16 << 20;
+    const ptrdiff_t step = (intptr_t)g.ptr[1] - (intptr_t)g.ptr[0];
+    if (step != kStep && step != -kStep && (p >= 64 || (step != 2 * kStep && step != -2 * kStep))) return false;
+    for (int q = 2; q < p; ++q)
+        if ((intptr_t)g.ptr[q] - (intptr_t)g.ptr[q - 1] != step) return false;
+    return true;
+}
+inline bool long_call_in_step(const PtrTable& g, int p, size_t nlanes, size_t units) { return p >= 32 && nlanes >= units * (46 * 64) && in_step(g, p); }
 
 // The same for segments.  16 buffers stay with the unrolled kernel (us, the best cap of each, unrolled / shallow: 172 MB 28.4 / 29.2, 307 MB 49.4 / 49.6,
 // f32 906 MB 138.5 / 139.0), 32 two-byte ones in long calls (453 MB 71.6 / 72.0, first micro-step 69.0 / 69.7; 276 MB 45.8 / 45.6); below 64

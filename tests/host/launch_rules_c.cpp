@@ -28,4 +28,10 @@ long long rules_segments(int p, int elem_bytes, size_t nlanes, int n, int accumu
 {
     return code(reduce_shape_segments(p, elem_bytes, nlanes, n, true, true, accumulate, false, units));
 }
+int rules_in_step(const size_t* addresses, int p, size_t nlanes, size_t units)
+{
+    PtrTable g = {};
+    for (int q = 0; q < p; ++q) g.ptr[q] = (const void*)addresses[q];
+    return long_call_in_step(g, p, nlanes, units);
+}
 }

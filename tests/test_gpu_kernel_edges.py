@@ -610,6 +610,36 @@ def test_reduce_segments_in_shallow_batches(orc, gen, name, p, numel, threshold)
         mics.mics_set_stream_threshold_bytes(0)
 
 
+@pytest.mark.parametrize("name,p,step,ends", [("bf16", 33, 16, 3), ("f32", 32, -16, 1), ("f16", 48, -32, 5), ("bf16", 64, 16, 0)])
+@pytest.mark.parametrize("segments", [False, True])
+def test_reduce_of_buffers_in_step(orc, gen, name, p, step, ends, segments):
+    """Long calls over buffers 16 and 32 MiB from one another, upwards and downwards, which are read in batches of 16."""
+    code, dtype = FORMATS[name]
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    size = np.dtype(dtype).itemsize
+    count, pitch = 46 * 64 * units * 16 // size + 8 * 17 + ends, abs(step) * 2**20 // size
+    if count + 64 > pitch:
+        pytest.skip("a call of this length does not fit between the buffers")
+    whole = torch.empty(p * pitch, dtype=torch.float32 if name == "f32" else torch.int16, device="cuda:0")
+    host, tab = [], grad_table(gen, name)
+    for q in range(p):
+        host.append(gen.fill_host(gen.stream_key(4400, gen.ROLE_GRAD, 0, 0, q), 0, count + 8, tab))
+    views = [whole[q * pitch:q * pitch + count + 8] for q in (range(p) if step > 0 else reversed(range(p)))]
+    for v, h in zip(views, host):
+        v.copy_(torch.from_numpy(h if name == "f32" else h.view(np.int16)))
+    segs = [(count // 3 + 1, 0, 2, 0), (count - count // 3 - 1, 0, count // 3 + 5, count // 3 + 1)]
+    for accumulate in (True, False):
+        ref, acc = start_acc(gen, count)
+        if segments:
+            mics.mics_reduce_scatter_accum_coalesced_typed(acc.t, views, segs, accumulate, code)
+            orc.reduce_scatter_accum_coalesced_typed(ref, host, segs, accumulate, code)
+        else:
+            mics.mics_reduce_scatter_accum_typed(acc.t, views, 1, count, accumulate, code)
+            orc.reduce_scatter_accum_typed(ref, host, 1, accumulate, code)
+        torch.cuda.synchronize()
+        assert same_bits(acc, ref), accumulate
+
+
 @pytest.mark.parametrize("name,p,per_unit", [("bf16", 64, 5.7), ("f16", 49, 12.6), ("f32", 48, 14.9), ("bf16", 50, 11.5), ("f32", 66, 11.7), ("f16", 48, 19.2)])
 def test_reduce_many_segments_in_shallow_batches(orc, gen, name, p, per_unit):
     """17 segments by workgroups of 512 and 256 lanes and by single wavefronts, most of them with a partial last tile."""

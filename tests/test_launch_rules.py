@@ -28,6 +28,7 @@ def rules(tmp_path_factory):
     lib.rules_shallow_segments.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t, ctypes.c_size_t]
     lib.rules_segments.restype = ctypes.c_longlong
     lib.rules_segments.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
+    lib.rules_in_step.argtypes = [ctypes.POINTER(ctypes.c_size_t), ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     return lib
 
 
@@ -142,3 +143,17 @@ def test_segments_of_few_f32_buffers(rules, p):
     for per_unit, lanes in ((20, 256), (49, 256), (50, 64), (100, 64), (299, 64), (600, 64)):
         for accumulate in (0, 1):
             assert shape(rules.rules_segments(p, 4, per_unit * 64 * UNITS, 16, accumulate, UNITS)) == (lanes, 0), per_unit
+
+
+def test_buffers_in_step(rules):
+    """16 MiB from one to the next, up or down, up to 63 of them also 32, in calls of 46 wavefronts a unit."""
+    def answer(p, mib, per_unit=58, moved=0):
+        at = [(1 << 40) + 12345 * 64 + int(q * mib * 2**20) for q in range(p)]
+        at[p // 2] += moved
+        return rules.rules_in_step((ctypes.c_size_t * p)(*at), p, per_unit * 64 * UNITS, UNITS)
+    for p in (32, 33, 63, 64, 96, 128):
+        assert answer(p, 16) and answer(p, -16)
+        assert bool(answer(p, 32)) == (p < 64) and bool(answer(p, -32)) == (p < 64)
+        assert not answer(p, 16, per_unit=45) and not answer(p, 16, moved=2) and not answer(p, 16, moved=2**21)
+        assert not any(answer(p, mib) for mib in (0, 4, 8, 14, 20, 24, 48, 64))
+    assert not answer(31, 16) and not answer(16, 16)
