@@ -98,8 +98,8 @@ struct SmallTable {
 // What a reduction indexes: a SmallTable itself (constant indices), or a table through the
 // kernel-argument segment, so that run-time indices stay scalar loads, of several pointers at once
 // where they are consecutive.  (Indexing the by-value parameter at run time makes one dependent
-// 8-byte load of every pointer, 64 of them 5 us; the averages of 3, 5, 6, 7 and more than 8 copies still do, because
-// large calls measured slower with whole batches: r = 6, 190 -> 197 us.)  Its kernels have their table as the
+// 8-byte load of every pointer, 64 of them 5 us; the averages' and updates' kernels for any number of copies still do, which
+// spaces their loads: in the middle of the range they are faster than unrolled ones, see unrolled_average.)  Its kernels have their table as the
 // first parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer repeat it
 // (pad_table).
 struct KernargTable {
@@ -817,25 +817,24 @@ __device__ __forceinline__ void rsa_shallow(float* s, const Tab& g, int p, size_
 
 // s = ((g_0 + g_1) + ...) + g_{p-1} for the lane's elements starting at virtual element `elem`.
 // `accumulator` issues the accumulator's loads, behind those of the first buffers: it needs more instructions,
-// and a small call is over in a few times the latency of what stands in front of its loads.  FIRST: in front of them,
-// in the flat kernels of large calls, where the order is worth a little either way (us, first / behind: flat, p = 16,
-// 50 M elements 303.0 / 304.5; 16 tensors, p = 16, 50 M 309 / 303).  Windows of loads have it behind the last buffers.
+// and a small call is over in a few times the latency of what stands in front of its loads (in front: 16 tensors, p = 16,
+// 50 M elements 309 / 303 us; bf16, p = 32, 0.3 to 1 M as fast).  Windows of loads have it behind the last buffers.
 // P > 0: p = P at compile time; P == 0: any p.  The loads go out in batches of BATCH, every
 // batch entirely in flight before its first addition (P <= BATCH: all of them at once; a
 // batch of 32 128-bit loads would leave room for 3 wavefronts per SIMD only).  -0 is the identity of
 // binary32 addition (-0 + x is x, also for x = -0 and x = +0).
-template <int KIND, int VEC, int P, int BATCH, bool HOLD, bool FIRST, typename Tab, typename Issue>
+template <int KIND, int VEC, int P, int BATCH, bool SHALLOW, bool HOLD, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_t elem, Issue&& accumulator)
 {
-    if constexpr (VEC == 4 && ((P == 32 && (KIND != 0 || HOLD)) || (P == 16 && KIND == 1 && !HOLD && !FIRST))) {
+    if constexpr (VEC == 4 && ((P == 32 && (KIND != 0 || HOLD)) || (P == 16 && KIND == 1 && !HOLD))) {
         // A window of W loads that moves on by STEP buffers, held in this order.  Left to itself the compiler put as few as
         // one load in flight here and more than enough there, from one change of the source to the next: us, f16, 16
         // tensors, p = 16 900 MB 239 / so 139, 2 GB 524 / 324, p = 32 45 MB 20.5 / 10.6, 2 GB 752 / 313; f32, p = 32, 12 MB in two batches
-        // 3.95 / 3.69.  The bf16 kernels, and p = 16 in one tensor, are better in the compiler's order (p = 16 300 MB 47.7, held
-        // 49.0; p = 32 300 MB 49.1 / 51).
+        // 3.95 / 3.69.  The bf16 kernels are better in the compiler's order (p = 32 300 MB 49.1, held 51).  (Of the calls past the L2, one tensor of 32 gets here below 8
+        // wavefronts per unit and segments of 32 below 12, of two-byte elements also from 40 on; long_call_in_step any.)
         // The accumulator's loads go out behind the last gradients: in front, or behind the first window, they are one of the
-        // few in flight while nothing needs them (us, p = 32, in front / behind the first / behind the last: f32 45 MB 9.0 / 9.2 /
-        // 8.6, 2 GB 302 / 302 / 295; f16 45 MB 9.9 / 9.9 / 9.2, 200 MB 34.7 / 34.7 / 32.6, 900 MB 142.7 / 142.8 / 138.5).
+        // few in flight while nothing needs them (us, p = 32, 45 MB, in front / behind the first / behind the last: f32 9.0 / 9.2 /
+        // 8.6; f16 9.9 / 9.9 / 9.2).
         constexpr int W = HOLD ? 16 : P == 16 ? 4 : 6, STEP = HOLD ? 4 : 2;
         static_assert((P - W) % STEP == 0, "");
         GradVec<KIND, VEC> v[W];
@@ -857,18 +856,17 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             if (q0 + W < P) __builtin_amdgcn_sched_barrier(0);
         }
     } else if constexpr (P > 0) {
-        if (FIRST) accumulator();
         #pragma unroll
         for (int q0 = 0; q0 < P; q0 += BATCH) {
             GradVec<KIND, VEC> v[BATCH];
             #pragma unroll
             for (int b = 0; b < BATCH; ++b)
                 if (q0 + b < P) v[b].load(g.ptr[q0 + b], elem);
-            if (q0 == 0 && !FIRST) accumulator();
+            if (q0 == 0) accumulator();
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
-            // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (p = 16, 7.5 M: 52.4
-            // against 50.7 us), except in the small calls that HOLD stands for, where latency counts (f32, p = 16,
+            // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (one tensor, p = 16, 7.5 M, which
+            // is read in shallow batches now: 52.4 against 50.7 us), except in the small calls that HOLD stands for, where latency counts (f32, p = 16,
             // 42 k elements: 2.4 us, not held 4.0; p = 32, 59 k: 3.7, 5.4; bf16, p = 16, 75 k: 2.7, 3.1).
             if constexpr (P <= 8 || HOLD) __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
@@ -885,7 +883,7 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         constexpr int PAD = VEC == 1 ? 8 : 1;
         #pragma unroll
         for (int e = 0; e < VEC * GradFormat<KIND>::kPerDword; ++e) s[e] = -0.0f;
-        if constexpr (BATCH == kShallow) return rsa_shallow<KIND>(s, g, p, elem, accumulator);
+        if constexpr (SHALLOW) return rsa_shallow<KIND>(s, g, p, elem, accumulator);
         accumulator();
         int q0 = 0;
         for (; q0 + BATCH <= p; q0 += BATCH) rsa_batch<KIND, VEC, BATCH, 1>(s, g, q0, BATCH, elem);
@@ -894,13 +892,13 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
 }
 
 // a[0 .. EPL) = a[0 .. EPL) + partial sum at virtual element `elem`.
-template <int KIND, int VEC, int P, int BATCH, bool HOLD, bool FIRST, typename Tab, typename Issue>
+template <int KIND, int VEC, int P, int BATCH, bool SHALLOW, bool HOLD, typename Tab, typename Issue>
 __device__ __forceinline__ void rsa_sum(float (&a)[VEC * GradFormat<KIND>::kPerDword], const Tab& g, int p, size_t elem,
                                         Issue&& accumulator)
 {
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     float s[EPL];
-    rsa_partial<KIND, VEC, P, BATCH, HOLD, FIRST>(s, g, p, elem, accumulator);
+    rsa_partial<KIND, VEC, P, BATCH, SHALLOW, HOLD>(s, g, p, elem, accumulator);
     #pragma unroll
     for (int e = 0; e < EPL; ++e) a[e] = a[e] + s[e];
 }
@@ -967,7 +965,7 @@ __device__ __forceinline__ void wave_lds_order()
 // cache lines, which leave the L2 between the two halves.  Passing the results through 2 KiB of LDS
 // per wavefront lets every store instruction cover one contiguous KiB.  Vector j of the wavefront's
 // 128 holds half of the elements of lane j / 2.
-template <int KIND, int VEC, int P, int BATCH, bool ACCUM, bool CACHED, bool FIRST, bool PARTS, typename Tab>
+template <int KIND, int VEC, int P, int BATCH, bool SHALLOW, bool ACCUM, bool CACHED, bool PARTS, typename Tab>
 __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t src0, size_t v0,
                                          size_t lead, size_t end, int how)
 {
@@ -982,7 +980,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
         const size_t w0 = full ? v0 : v0 < lead ? lead : end - EPL;
         float* const at = acc + (w0 - lead);
         auto own = [&](int e) { return w0 + e >= v0 && w0 + e < v0 + EPL; };
-        rsa_sum<KIND, VEC, P, BATCH, VEC == 4, false>(a, g, p, src0 + w0, [&] {
+        rsa_sum<KIND, VEC, P, BATCH, false, VEC == 4>(a, g, p, src0 + w0, [&] {
             if constexpr (ACCUM) {
                 if (full) {
                     ld_f32<EPL, false>(a, at);
@@ -1002,7 +1000,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
         }
     } else if constexpr (CACHED) {
         if (full) {
-            rsa_sum<KIND, VEC, P, BATCH, VEC == 4, false>(a, g, p, src0 + v0, [&] {
+            rsa_sum<KIND, VEC, P, BATCH, false, VEC == 4>(a, g, p, src0 + v0, [&] {
                 if (ACCUM) ld_f32<EPL, false>(a, acc + (v0 - lead));
             });
             st_f32<EPL, false>(acc + (v0 - lead), a);
@@ -1019,7 +1017,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             else MICS_ST(true, (f32x4_a4*)wave_acc + i, v);
         };
         if (full) {
-            rsa_sum<KIND, VEC, P, BATCH, false, FIRST>(a, g, p, src0 + v0, [&] {
+            rsa_sum<KIND, VEC, P, BATCH, SHALLOW, false>(a, g, p, src0 + v0, [&] {
                 // with more than 8 buffers the choice between two kinds of loads costs more registers than it
                 // gives (p = 32: 158 instead of 99)
                 if constexpr (ACCUM && P > 0 && P <= 8) {
@@ -1047,7 +1045,7 @@ __device__ __forceinline__ void rsa_lane(float* acc, const Tab& g, int p, size_t
             wave_lds_order();
             // a workgroup's last wavefront may be a partial one (even_call), in the kernels that such calls reach
             unsigned half = 64;
-            if constexpr ((P == 0 || P == 32) && BATCH != kShallow) {   // even_least
+            if constexpr (partial_waves(P, SHALLOW)) {
                 const unsigned left = blockDim.x - __builtin_amdgcn_readfirstlane(threadIdx.x);
                 if (left < 64) half = left;
             }
@@ -1110,7 +1108,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     Tab tab, float* __restrict__ acc, int p, unsigned lead, size_t count, int how)
 {
     const auto& g = table_view(tab);
-    constexpr int BATCH = VEC == 1 ? 64 : OTHER && !CACHED ? kShallow : MICS_RSA_BATCH;
+    constexpr int BATCH = VEC == 1 ? 64 : MICS_RSA_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     const size_t end = (size_t)lead + count;
     const size_t nlanes = (end + EPL - 1) / EPL;
@@ -1123,8 +1121,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_kerne
     const size_t stride = (size_t)(gridDim.x - 1) * block;
     const unsigned tile = CACHED && !OTHER ? blockIdx.x : tile_of(blockIdx.x, gridDim.x - 1, CACHED || (how & kInRuns));
     for (size_t base = (size_t)tile * block; base < nlanes; base += stride)   // workgroup-uniform
-        rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, (P > 8), false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end,
-                                                                     how & ~kInRuns);
+        rsa_lane<KIND, VEC, P, BATCH, OTHER && !CACHED, ACCUM, CACHED, false>(acc, g, p, 0, (base + threadIdx.x) * EPL, lead, end, how & ~kInRuns);
 }
 
 // Coalesced form (many separately sharded tensors in one launch): workgroup x works on
@@ -1147,7 +1144,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
     Tab gtab, float* __restrict__ acc, int p, ReduceTable<SEGS> tab, int how, unsigned edges)
 {
     const auto& g = table_view(gtab);
-    constexpr int BATCH = VEC == 1 ? 64 : SHALLOW ? kShallow : MICS_RSA_BATCH;
+    constexpr int BATCH = VEC == 1 ? 64 : MICS_RSA_BATCH;
     constexpr int EPL = VEC * GradFormat<KIND>::kPerDword;
     unsigned tile, x = blockIdx.x;
     if constexpr (kEdgeGroups<P, CACHED>) {
@@ -1171,7 +1168,7 @@ __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_k
         if (tile == 0) rsa_edges<KIND, EPL, P, ACCUM>(dst, g, p, sg.src0, lead, end);
     }
     const size_t v0 = ((size_t)tile * blockDim.x + threadIdx.x) * EPL;
-    rsa_lane<KIND, VEC, P, BATCH, ACCUM, CACHED, false, CACHED>(dst, g, p, sg.src0, v0, lead, end, how & ~kInRuns);
+    rsa_lane<KIND, VEC, P, BATCH, SHALLOW, ACCUM, CACHED, CACHED>(dst, g, p, sg.src0, v0, lead, end, how & ~kInRuns);
 }
 
 // ---------------------------------------------------------------------------
@@ -1467,7 +1464,7 @@ SmallTable<N> small(const PtrTable& t)
 template <typename F>
 int dispatch_group(int p, F&& f)
 {
-    switch (p) {
+    switch (unrolled_group(p)) {
         case 1: return f(std::integral_constant<int, 1>{});
         case 2: return f(std::integral_constant<int, 2>{});
         case 3: return f(std::integral_constant<int, 3>{});

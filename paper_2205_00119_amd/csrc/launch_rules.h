@@ -142,10 +142,14 @@ inline Shape even_call(size_t nlanes, size_t units, size_t least = 256, size_t m
     if (lanes % 64 && lanes % 64 < n) lanes += (n + 7) / 8 * 8 - lanes % 64;
     return Shape{(int)lanes, 0};
 }
-// The line from which a reduction does so; never where its kernel passes stores through LDS and knows whole wavefronts only (rsa_lane).
+// The P of a reduction's kernel: that of p buffers where there is an unrolled one, else 0.
+constexpr int unrolled_group(int p) { return p <= 8 || p == 16 || p == 32 ? p : 0; }
+// Whether a kernel that passes its stores through LDS (two-byte gradients, accumulator not left in the L2) knows a workgroup's partial last wavefront (rsa_lane).
+constexpr bool partial_waves(int P, bool shallow) { return (P == 0 || P == 32) && !shallow; }
+// The line from which a reduction does so.
 inline size_t even_least(int p, int elem_bytes, bool cached)
 {
-    if (!cached && elem_bytes == 2 && (p <= 8 || p == 16)) return (size_t)1 << 40;
+    if (!cached && elem_bytes == 2 && !partial_waves(unrolled_group(p), false)) return (size_t)1 << 40;
     return p < 16 ? 256 : p < 32 && elem_bytes == 4 ? 170 : 128;
 }
 
