@@ -34,4 +34,9 @@ int rules_in_step(const size_t* addresses, int p, size_t nlanes, size_t units)
     for (int q = 0; q < p; ++q) g.ptr[q] = (const void*)addresses[q];
     return long_call_in_step(g, p, nlanes, units);
 }
+long long rules_reduce(int p, int elem_bytes, size_t nlanes, int cached, size_t units)
+{
+    return code(reduce_shape(p, elem_bytes, nlanes, true, true, true, cached, units));
+}
+int rules_partial_waves(int p) { return partial_waves(unrolled_group(p), false); }
 }

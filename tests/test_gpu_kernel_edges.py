@@ -443,9 +443,10 @@ def test_launches_of_coalesced_gathers(n_tensors, shard, launches, odd):
     assert kernels_of(lambda: mics.mics_hier_gather_reorder_coalesced(dst, T, segs, 2, 2, 2)) == launches
 
 
-@pytest.mark.parametrize("name,count", [("f32", 262_147), ("f32", 771_011), ("f32", 771_012), ("f32", 794_376), ("f32", 794_377), ("f16", 794_377)])
-def test_reduce_of_32_buffers_through_either_window(orc, gen, name, count):
-    """The window of 6 loads in flight and, from 8 wavefronts per compute unit on, batches of 4; the accumulator on the lanes' lines and off them."""
+@pytest.mark.parametrize("name,count", [("f32", 262_147), ("f32", 524_281), ("f32", 524_293), ("f32", 794_377), ("f16", 794_377), ("f16", 1_048_561), ("f16", 1_048_585),
+                                        ("bf16", 400_003), ("bf16", 1_048_561), ("bf16", 1_048_585)])
+def test_reduce_of_32_buffers_on_both_sides_of_the_shallow_batches(orc, gen, name, count):
+    """The window of 6 loads in flight (bf16: two batches of 16) and, from 8 wavefronts per compute unit on, batches of 4; the accumulator on the lanes' lines and off them."""
     code = FORMATS[name][0]
     host, dev = rank_buffers(gen, name, 32, count + 8, [0])
     for offset, skew in ((0, 0), (5, 3)):
@@ -695,6 +696,7 @@ def test_reduce_in_one_even_workgroup_per_unit(orc, gen, name, p, per_unit, tens
 
 @pytest.mark.parametrize("r,count", [
     (3, 5), (3, 331_127), (3, 331_131), (3, 2_097_149), (3, 2_097_155), (5, 1_733_000), (5, 1_733_001), (6, 77_003), (6, 1_600_003), (6, 524_288), (7, 524_289), (12, 524_285), (7, 1_500_001), (7, 260_003), (7, 1_610_003), (8, 1_500_003),
+    (5, 262_147), (5, 300_003), (7, 393_216), (7, 393_221), (11, 393_216), (11, 393_221),
     (9, 1_048_579), (9, 140_003), (9, 419_431), (9, 5_242_883), (10, 262_147), (11, 300_003), (13, 349_531), (13, 3_744_923), (14, 280_003), (15, 4_191), (16, 246_727),
     (17, 1_783_003), (24, 700_001), (12, 510_103), (12, 510_104), (12, 1_416_993), (13, 40_001), (16, 420_003), (16, 1_515_002)])
 @pytest.mark.parametrize("skew", [0, 1])

@@ -29,6 +29,8 @@ def rules(tmp_path_factory):
     lib.rules_segments.restype = ctypes.c_longlong
     lib.rules_segments.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_size_t]
     lib.rules_in_step.argtypes = [ctypes.POINTER(ctypes.c_size_t), ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
+    lib.rules_reduce.restype = ctypes.c_longlong
+    lib.rules_reduce.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t]
     return lib
 
 
@@ -157,3 +159,15 @@ def test_buffers_in_step(rules):
         assert not answer(p, 16, per_unit=45) and not answer(p, 16, moved=2) and not answer(p, 16, moved=2**21)
         assert not any(answer(p, mib) for mib in (0, 4, 8, 14, 20, 24, 48, 64))
     assert not answer(31, 16) and not answer(16, 16)
+
+
+def test_partial_last_wavefronts_only_in_kernels_that_know_them(rules):
+    """Kernels that pass their stores through LDS: two-byte gradients, accumulator not left in the L2."""
+    seen = 0
+    for p in range(1, 129):
+        for nlanes in range(100, 512 * UNITS, 997):
+            for units in (UNITS, 104):
+                lanes = shape(rules.rules_reduce(p, 2, nlanes, 0, units))[0]
+                assert lanes % 8 == 0 and (lanes % 64 == 0 or rules.rules_partial_waves(p)), (p, nlanes, lanes)
+                seen += lanes % 64 != 0
+    assert seen > 1000
