@@ -64,6 +64,9 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // Calls that accumulate in a resident buffer still gain from it beyond the lines (p = 4..11, 16..24 MiB 1.03..1.07;
 // bf16, p = 4, 28 MiB 17.7 / 19.8 us); first micro-steps lose more (16 MiB 0.91..0.93).  With many gradients it would be gone before its turn (p = 16, 3 M, 12 MB 18.9 / 21.2, 19.9 / 20.2; 7.5 M, 30 MB 51.9 / 52.2,
 // 48.6 / 49.3; p = 32, 0.6 M, 2.5 MB 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
+// 16 to 31 buffers of f32 up to 4 MiB, since what passes the L2 is read in shallow batches; us, left there / past it, accumulating and first micro-step: p = 16 4.2 MiB 15.5 / 14.4, 14.8 /
+// 13.8, 6 MiB 20.6 / 19.9, 19.8 / 19.1, 7.9 MiB 25.0 / 24.1, 23.5 / 23.1; p = 24 4.2 MiB 21.6 / 19.4, 20.9 / 18.9, 7.9 MiB 35.7 / 33.6, 34.1 / 32.8; p = 31 6 MiB 34.6 / 33.4, 33.6 / 32.7.  (Below,
+// 3.2 MiB, 3 to 8 % too, but a resident accumulator is then lost.)
 inline int accum_policy(size_t count, int p, int elem_bytes)
 {
     constexpr size_t kSmall = 64u << 20;
