@@ -66,7 +66,7 @@ inline bool states_through(size_t traffic) { return traffic >= (300u << 20); }
 // 48.6 / 49.3; p = 32, 0.6 M, 2.5 MB 9.4 / 10.5, 10.0 / 9.9; of 32 and more buffers only the calls that are all latency).
 // 16 to 31 buffers of f32 up to 4 MiB, since what passes the L2 is read in shallow batches; us, left there / past it, accumulating and first micro-step: p = 16 4.2 MiB 15.5 / 14.4, 14.8 /
 // 13.8, 6 MiB 20.6 / 19.9, 19.8 / 19.1, 7.9 MiB 25.0 / 24.1, 23.5 / 23.1; p = 24 4.2 MiB 21.6 / 19.4, 20.9 / 18.9, 7.9 MiB 35.7 / 33.6, 34.1 / 32.8; p = 31 6 MiB 34.6 / 33.4, 33.6 / 32.7.  (Below,
-// 3.2 MiB, 3 to 8 % too, but a resident accumulator is then lost.)
+// 3.2 MiB, 3 to 8 % too with buffers in no cache; resident ones were not compared there.)
 inline int accum_policy(size_t count, int p, int elem_bytes)
 {
     constexpr size_t kSmall = 64u << 20;
