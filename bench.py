@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBPS = 8000.0   # MI355X HBM3E, published
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_per_launch.txt")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2205_00119_amd", "csrc", "kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2205_00119_amd", "csrc", name) for name in ("kernels.hip", "launch_rules.h")]
 
 
 def parse_args():
@@ -96,8 +96,12 @@ def stats(samples):
 
 
 def kernel_source_hash():
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    """Of the kernels and of the rules that choose between them."""
+    sha = hashlib.sha256()
+    for source in KERNEL_SOURCES:
+        with open(source, "rb") as f:
+            sha.update(f.read())
+    return sha.hexdigest()[:16]
 
 
 def traffic_from_profile(workload, view, variant):
@@ -114,8 +118,8 @@ def traffic_from_profile(workload, view, variant):
         f = line.split()
         if len(f) >= 5 and not line.startswith("#") and f[:3] == [workload, view, variant]:
             if f[3] == want:
-                return int(f[4]), f"profiles/{os.path.basename(TRAFFIC_FILE)} (kernels.hip sha256 {want})"
-            return None, f"stale: measured on kernels.hip sha256 {f[3]}, current {want}"
+                return int(f[4]), f"profiles/{os.path.basename(TRAFFIC_FILE)} (kernels.hip + launch_rules.h sha256 {want})"
+            return None, f"stale: measured on kernels.hip + launch_rules.h sha256 {f[3]}, current {want}"
     return None, None
 
 

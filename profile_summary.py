@@ -20,7 +20,7 @@ The summary holds the kernel trace statistics, the counters scaled by what they 
 copy of known size (the first reorder dispatch of the two counter runs), the algorithmic bytes of
 every kernel, and -- for the dominant kernel -- the HBM bytes per launch that bench.py reports as
 `roofline.traffic`.  That figure is also written to profiles/hbm_traffic_per_launch.txt next to
-the SHA-256 of the kernel source it was measured on; bench.py emits it only while that hash still
+the SHA-256 of the kernel source and launch rules it was measured on; bench.py emits it only while that hash still
 matches.  Nothing here runs on the GPU.
 """
 from __future__ import annotations
@@ -37,9 +37,17 @@ import sys
 ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2205_00119_amd", "csrc", "kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2205_00119_amd", "csrc", name) for name in ("kernels.hip", "launch_rules.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_per_launch.txt")
 KIB = 1024
+
+
+def kernel_source_hash() -> str:
+    sha = hashlib.sha256()
+    for source in KERNEL_SOURCES:
+        with open(source, "rb") as f:
+            sha.update(f.read())
+    return sha.hexdigest()[:16]
 
 
 def short_name(name: str) -> str:
@@ -112,12 +120,12 @@ def main():
     N = args.numel or cfg.N
     count = args.count or (cfg.N_pad if args.view == "group" else cfg.S)
     pb = 2
-    sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()[:16]
+    sha = kernel_source_hash()
     shown = "prof/" + os.path.basename(os.path.normpath(args.dir))
     out = [(f"\n---\n\n## {args.title}\n\n" if args.title else "") +
            f"# rocprofv3 summary: libmics kernels, workload {cfg.name} (p={cfg.p}, k={cfg.k}, r={cfg.r}, "
            f"s={cfg.s}), {args.view} view ({count} elements per reduce/average/Adam call), one MI355X\n",
-           f"Kernel source: `paper_2205_00119_amd/csrc/kernels.hip`, SHA-256 `{sha}`.\n",
+           f"Kernel source: `paper_2205_00119_amd/csrc/kernels.hip` and `launch_rules.h`, SHA-256 of both `{sha}`.\n",
            "Commands (from /tmp on the GPU machine, `R` = repository root; each in a run of its own), then "
            f"`python profile_summary.py --dir {shown} --config {args.config} --view {args.view} "
            f"--variant {args.variant} --bench-args \"{args.bench_args}\" --out {args.out}`:\n",
@@ -217,7 +225,7 @@ def main():
                 if not keep:
                     keep = ["# HBM bytes per launch of the dominant kernel (reduce-scatter-accumulate, averaged over a step's",
                             "# s launches) from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, written by profile_summary.py.",
-                            "# workload view variant sha256-16(kernels.hip) bytes fetch_factor write_factor summary"]
+                            "# workload view variant sha256-16(kernels.hip+launch_rules.h) bytes fetch_factor write_factor summary"]
                 keep.append(f"{cfg.name} {args.view} {args.variant} {sha} {per_launch:.0f} {ff:.4f} {fw:.4f} {args.out}")
                 open(TRAFFIC_FILE, "w").write("\n".join(keep) + "\n")
     open(args.out, "a" if args.append else "w").write("\n".join(out) + "\n")

@@ -27,3 +27,23 @@ def test_traffic_figure_is_only_reported_for_the_kernel_source_it_was_measured_o
     value, source = bench.traffic_from_profile("h8192", "group", "flat-bf16")              # other source hash
     assert value is None and source.startswith("stale")
     assert bench.traffic_from_profile("h4096", "rank", "flat-bf16") == (None, None)         # never measured
+
+
+def test_kernel_source_hash_covers_the_launch_rules(tmp_path, monkeypatch):
+    """Which kernel a call reaches, and so its traffic, is decided there."""
+    sys.path.insert(0, ROOT)
+    import bench
+    import profile_summary
+    sha = bench.kernel_source_hash()
+    assert profile_summary.kernel_source_hash() == sha
+    copies = []
+    for source in bench.KERNEL_SOURCES:
+        copies.append(tmp_path / os.path.basename(source))
+        with open(source, "rb") as f:
+            copies[-1].write_bytes(f.read())
+    assert {c.name for c in copies} == {"kernels.hip", "launch_rules.h"}
+    monkeypatch.setattr(bench, "KERNEL_SOURCES", [str(c) for c in copies])
+    assert bench.kernel_source_hash() == sha
+    with open(copies[-1], "a") as f:
+        f.write("\n")
+    assert bench.kernel_source_hash() != sha
