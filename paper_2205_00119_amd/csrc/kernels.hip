@@ -99,9 +99,9 @@ struct SmallTable {
 // kernel-argument segment, so that run-time indices stay scalar loads, of several pointers at once
 // where they are consecutive.  (Indexing the by-value parameter at run time makes one dependent
 // 8-byte load of every pointer, 64 of them 5 us; the averages' and updates' kernels for any number of copies still do, which
-// spaces their loads: in the middle of the range they are faster than unrolled ones, see unrolled_average.)  Its kernels have their table as the
-// first parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer repeat it
-// (pad_table).
+// spaces their loads: in the middle of the range they are faster than unrolled ones, see unrolled_average.)  Its kernels
+// have their table as the first parameter: offset 0 of the segment.  The entries of a PtrTable behind its last pointer
+// repeat it (pad_table).
 struct KernargTable {
     const void* const __attribute__((address_space(4)))* ptr;
 };
@@ -523,8 +523,9 @@ __global__ __launch_bounds__(kMaxBlock) void reorder_shift_kernel(
 // hold workgroup x: lane i takes entry i, the tensor's index is the number of entries at or below x.  Small calls
 // (ONE_ROUND, 64 entries) have every lane take entry i's record too, so that nothing waits for the index, and so do
 // the large reductions but those of up to 8 two-byte buffers, whose wavefronts move too little for 2 KiB of table (16
-// tensors, bf16, p = 4, 79 M elements: 194 us, without 190; p = 6, 335 MB 52.3, 50.7).  Looked up with scalar instructions, as the large gathers
-// do, in three dependent rounds, reductions take 1 to 4 % longer (p = 32, 16 tensors, 3.8 M elements 7 %).
+// tensors, bf16, p = 4, 79 M elements: 194 us, without 190; p = 6, 335 MB 52.3, 50.7).  Looked up with scalar instructions,
+// as the large gathers do, in three dependent rounds, reductions take 1 to 4 % longer (p = 32, 16 tensors, 3.8 M elements 7
+// %).
 template <typename Seg, int SEGS>
 struct TileTable {
     unsigned tile_begin[SEGS];                     // ascending; kNoTile behind the last
@@ -775,10 +776,12 @@ __device__ __forceinline__ void rsa_rest(float* s, const Tab& g, int q0, int n, 
 // what all wavefronts of a compute unit have in flight together, 8 x 2 to 4 KiB: deeper batches in fewer wavefronts end at the same rate,
 // but a wavefront then lives longer, and with it the end of the call, where units run dry.  The next pointers come while
 // these loads are out.  us, bf16, the best cap for each of 3 / 4 / 6 / 8 / 16 loads: p = 24 350 MB 53.3 / 52.7 / 53.3 / 54.0 / 55.6, 730 MB
-// 109.3 / 107.4 / 109.6 / 111.3 / 115.9; p = 32 159 MB 24.8 / 24.9 / 25.3 / 26.0 / 25.8; p = 64 301 MB 44.6 / 45.5 / 46.0 / 47.8 / 50.1; p = 128 482 MB
-// 73.1 / 71.1 / 76.3 / 76.9 / 80.2; f32, p = 24 325 MB 49.1 / 49.4 / 49.6 / 50.2 / 51.4, p = 64 430 MB 63.0 / 65.1 / 65.8 / 66.7 / 68.6.  A ring of 6 or 8
-// loads that moves on by two is 1 % slower.  The accumulator's loads go out with the last batch, of 4 to 7: where it took what 4 left over, one load was
-// alone in flight (speed of this against that, means of 40 to 70 calls: p = 17 1.014, 18 1.008, 21 1.011, 25 1.010; f32, 16 tensors, p = 17 318 MB 53.2 / 51.5, 1.1 GB 173.4 / 166.9).
+// 109.3 / 107.4 / 109.6 / 111.3 / 115.9; p = 32 159 MB 24.8 / 24.9 / 25.3 / 26.0 / 25.8; p = 64 301 MB 44.6 / 45.5 / 46.0 /
+// 47.8 / 50.1; p = 128 482 MB 73.1 / 71.1 / 76.3 / 76.9 / 80.2; f32, p = 24 325 MB 49.1 / 49.4 / 49.6 / 50.2 / 51.4, p = 64
+// 430 MB 63.0 / 65.1 / 65.8 / 66.7 / 68.6.  A ring of 6 or 8 loads that moves on by two is 1 % slower.  The accumulator's
+// loads go out with the last batch, of 4 to 7: where it took what 4 left over, one load was alone in flight (speed of this
+// against that, means of 40 to 70 calls: p = 17 1.014, 18 1.008, 21 1.011, 25 1.010; f32, 16 tensors, p = 17 318 MB 53.2 /
+// 51.5, 1.1 GB 173.4 / 166.9).
 constexpr int kShallow = 4;
 // The last kShallow to 2 kShallow - 1 of the n buffers from q0; the pointers of the first kShallow are there.
 template <int KIND, int N, typename Tab, typename Issue>
@@ -830,11 +833,12 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
         // A window of W loads that moves on by STEP buffers, held in this order.  Left to itself the compiler put as few as
         // one load in flight here and more than enough there, from one change of the source to the next: us, f16, 16
         // tensors, p = 16 900 MB 239 / so 139, 2 GB 524 / 324, p = 32 45 MB 20.5 / 10.6, 2 GB 752 / 313; f32, p = 32, 12 MB in two batches
-        // 3.95 / 3.69.  The bf16 kernels are better in the compiler's order (p = 32 300 MB 49.1, held 51).  (Of the calls past the L2, one tensor of 32 gets here below 8
-        // wavefronts per unit and segments of 32 below 12, of two-byte elements also from 40 on; long_call_in_step any.)
-        // The accumulator's loads go out behind the last gradients: in front, or behind the first window, they are one of the
-        // few in flight while nothing needs them (us, p = 32, 45 MB, in front / behind the first / behind the last: f32 9.0 / 9.2 /
-        // 8.6; f16 9.9 / 9.9 / 9.2).
+        // 3.95 / 3.69.  The bf16 kernels are better in the compiler's order (p = 32 300 MB 49.1, held 51).  (Of the calls
+        // past the L2, one tensor of 32 gets here below 8 wavefronts per unit and segments of 32 below 12, of two-byte
+        // elements also from 40 on; long_call_in_step any.)
+        // The accumulator's loads go out behind the last gradients: in front, or behind the first window, they are one of
+        // the few in flight while nothing needs them (us, p = 32, 45 MB, in front / behind the first / behind the last: f32
+        // 9.0 / 9.2 / 8.6; f16 9.9 / 9.9 / 9.2).
         constexpr int W = HOLD ? 16 : P == 16 ? 4 : 6, STEP = HOLD ? 4 : 2;
         static_assert((P - W) % STEP == 0, "");
         GradVec<KIND, VEC> v[W];
@@ -866,8 +870,9 @@ __device__ __forceinline__ void rsa_partial(float* s, const Tab& g, int p, size_
             // Up to 8 buffers: keep the compiler from trading the loads in flight for registers (left to
             // itself it ran f16, p = 8 one load at a time: 172 against 128 us at 33 M elements).  With 16
             // loads it keeps about 10 in flight by itself (f32: 4), and more cost occupancy (one tensor, p = 16, 7.5 M, which
-            // is read in shallow batches now: 52.4 against 50.7 us), except in the small calls that HOLD stands for, where latency counts (f32, p = 16,
-            // 42 k elements: 2.4 us, not held 4.0; p = 32, 59 k: 3.7, 5.4; bf16, p = 16, 75 k: 2.7, 3.1).
+            // is read in shallow batches now: 52.4 against 50.7 us), except in the small calls that HOLD stands for, where
+            // latency counts (f32, p = 16, 42 k elements: 2.4 us, not held 4.0; p = 32, 59 k: 3.7, 5.4; bf16, p = 16, 75 k:
+            // 2.7, 3.1).
             if constexpr (P <= 8 || HOLD) __builtin_amdgcn_sched_barrier(0);
             #pragma unroll
             for (int b = 0; b < BATCH; ++b) {
@@ -1136,8 +1141,8 @@ struct ReduceSeg {
 template <int SEGS> using ReduceTable = TileTable<ReduceSeg, SEGS>;
 
 // Whether a segment's ends get a workgroup of their own in front of the tiles, because a tile would wait for too many of its loads one
-// after another: 16 tensors, p = 96, 64 MB 18.5 / 15.9 us, f32 68 tensors 194 MB 45.2 / 40.9.  Not with up to 8 buffers, where the additional
-// branch costs more (p = 2, 75 MB 13.9 / 14.4; f32, p = 4, 75 MB 2.5 %), nor with 32 (28 MB 3 %).
+// after another: 16 tensors, p = 96, 64 MB 18.5 / 15.9 us, f32 68 tensors 194 MB 45.2 / 40.9.  Not with up to 8 buffers,
+// where the additional branch costs more (p = 2, 75 MB 13.9 / 14.4; f32, p = 4, 75 MB 2.5 %), nor with 32 (28 MB 3 %).
 template <int P, bool CACHED> constexpr bool kEdgeGroups = !CACHED && P == 0;
 template <int KIND, int VEC, int P, bool ACCUM, bool CACHED, bool SHALLOW, int SEGS, typename Tab>
 __global__ __launch_bounds__(VEC == 4 ? kMaxBlock : kNarrowBlock) void rsa_seg_kernel(
@@ -1479,8 +1484,8 @@ int dispatch_group(int p, F&& f)
     }
 }
 
-// Calls f(std::integral_constant<int, R>, table) for an average of r copies: R = r where there is an unrolled kernel, those of 3, 5, 6, 7 and 9 to 16
-// only if `all`, else R = 0 and the whole table.
+// Calls f(std::integral_constant<int, R>, table) for an average of r copies: R = r where there is an unrolled kernel, those
+// of 3, 5, 6, 7 and 9 to 16 only if `all`, else R = 0 and the whole table.
 template <typename F>
 int dispatch_copies(const PtrTable& t, int r, bool all, F&& f)
 {
@@ -1538,9 +1543,13 @@ namespace {
 //   6.9, 36 MB 8.9 / 8.2 (buffers in the L2: 10 MB 3.0 / 2.75); not aligned, whose wavefronts at the borders of chunks make a second
 //   round trip, never: 0.6 MB 2.35 / 2.05, 4 MB 3.75 / 3.3, 8 MB 4.3 / 4.0
 //   several tensors, all aligned: 16 of a layer, p = 4 33 MB 7.5 / 8.1, 40 MB 9.5 / 9.1, p = 128 33 MB 7.4 / 8.5, 40 MB 9.5 / 9.8
-//   not all aligned: 4 of them p = 4 23 MB 6.4 / 6.7, p = 16 22 MB 7.5 / 6.5, p = 64 19 MB 6.9 / 6.2; 16, 40, 60 and 93 of them p = 16 15 MB 5.5 / 6.1, 5.5 / 6.2, 5.7 / 6.0, 5.5 /
-//   6.2, 23 MB 7.5 / 7.3, 8.8 / 7.7, 8.4 / 7.3, 8.6 / 7.5; p = 32 19 MB 7.0 / 7.0, 7.3 / 7.6, 7.4 / 7.2, 7.9 / 7.7; p = 64 19 MB 7.2 / 7.4, 7.6 / 8.5, 7.9 / 8.1, 8.4 / 9.4, 27 MB 8.9 / 8.5,
-//   9.5 / 9.7, 10.9 / 9.5, 11.4 / 10.7; p = 128 27 MB 9.1 / 9.2, 9.9 / 12.0, 11.7 / 11.6, 12.3 / 13.6, 33 MB 13.1 / 10.3, 11.9 / 12.3, 12.2 / 12.5, 12.9 / 14.8
+//   not all aligned: 4 of them p = 4 23 MB 6.4 / 6.7, p = 16 22 MB 7.5 / 6.5, p = 64 19 MB 6.9 / 6.2; 16, 40, 60 and 93 of
+//   them p = 16 15 MB 5.5 / 6.1, 5.5 / 6.2, 5.7 / 6.0, 5.5 / 6.2, 23 MB 7.5 / 7.3, 8.8 / 7.7, 8.4 / 7.3, 8.6 / 7.5; p = 32
+//   19 MB 7.0 / 7.0, 7.3 / 7.6, 7.4 / 7.2, 7.9 / 7.7; p = 64 19 MB 7.2 / 7.4, 7.6 / 8.5, 7.9 / 8.1, 8.4 / 9.4, 27 MB 8.9 /
+//   8.5, 9.5 / 9.7, 10.9 / 9.5, 11.4 / 10.7; p = 128 27 MB 9.1 / 9.2, 9.9 / 12.0, 11.7 / 11.6, 12.3 / 13.6, 33 MB 13.1 /
+//   10.3, 11.9 / 12.3, 12.2 / 12.5, 12.9 / 14.8.  (Tensors of similar size would rather stay up to 24 MB, p = 16 40 tensors
+//   19 MB 6.9 / 7.5, 24 MB 7.9 / 8.2, p = 8 60 tensors 24 MB 7.6 / 8.1; lists that spread over three decades would rather
+//   go, 15 to 24 MB 15 % faster by chunks.)
 int flat_vectors(int n, size_t moved, int p, bool vec16)
 {
     const size_t mb = moved >> 20;
@@ -1660,24 +1669,26 @@ int lead_on_accumulator_lines(const float* acc, uintptr_t first, size_t elem_byt
 // over p = 1 .. 96, 12 MB .. 2.2 GB, the formats, positions and both kinds of micro-step; speed against the plain order on the
 // gradients' lines:
 //   - Gradients off their lines, each buffer at another position: in runs (bf16, p = 8 64 MB 1.06, 411 MB 1.15; p = 12..16 25..60 MB 1.07;
-//     p = 32 60..120 MB 1.09; p = 96 1.04; f32, p = 8 54 MB 1.23, 436 MB 1.09); below 12 MB the few instructions cost 1 to 2 %.  Not with few
-//     buffers, where the accumulator is most of the traffic: one (bf16, 24 MB .77; f32, 160 MB .81), two and three of f32 off 16
-//     bytes (p = 3 666 MB .88; on 16 bytes p = 2, 3 1.01 to 1.09).
+//     p = 32 60..120 MB 1.09; p = 96 1.04; f32, p = 8 54 MB 1.23, 436 MB 1.09); below 12 MB the few instructions cost 1 to
+//     2 %.  Not with few buffers, where the accumulator is most of the traffic: one (bf16, 24 MB .77; f32, 160 MB .81), two
+//     and three of f32 off 16 bytes (p = 3 666 MB .88; on 16 bytes p = 2, 3 1.01 to 1.09).
 //   - Gradients on lines, accumulator not: on the accumulator's lines and in runs, so that the gradients' shared lines are found in the
-//     L2 and no accumulator's line is written in parts (bf16, p = 5 321 MB 1.09, runs alone 1.04, 1.2 GB 1.07, .97; p = 8 416 MB 1.10, 1.04;
-//     p = 12..16 300..700 MB 1.06, 1.03, above 700 MB .97, 1.00; f32, p = 8 250 MB 1.03, .92, 1.8 GB .98, .94; p = 24 and more up to 5 % slower).  Not in
-//     runs this loses 1 to 10 %.  If the gradients are then off 16 bytes: p = 12 to 16 runs alone (bf16 120..700 MB 1.01 to 1.03, f32 p = 12 200..450
-//     MB 1.05 to 1.08, p = 16 1.04; above 700 MB 1.00, first micro-steps .96), fewer buffers neither (bf16, p = 8 120 MB and more .97 to 1.00).
-//   - Everything on lines, or many buffers: in runs in the middle of the range (bf16, p = 4 209 MB 1.06, p = 8 231 MB 1.05, p = 12..16 120..300
-//     MB 1.05, 300..700 MB 1.03, above .98; below 60 MB .99 to 1.00; f32, p = 8 124 MB 1.06, p = 12..16 60..120 MB .96, 120..300 MB 1.03, above 700 MB
-//     .97; first micro-steps 120..700 MB 1.01 to 1.03, above .95 to .96).
-//   - Segments, whose ends lie anywhere: in runs, up to 3 buffers below 60 MB only (bf16, p = 2 45 MB 1.07, 150 MB .97, 600 MB .94; f32, p = 3
-//     300..700 MB .84), from 32 on above 24 MB (f32, p = 32 14 MB .83), f32 below 1 GB (p = 16 2 GB .93), up to 8 buffers of f32 not from 300 to
-//     700 MB unless all can be on the accumulator's lines (p = 8 335 MB .93, 447 MB .88, 760 MB 1.09; if they can 335 MB 1.04).
-//     Accumulating, on the accumulator's lines where that can be (lines / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB
-//     1.02 / 1.00; f32, p = 8 120..300 MB 1.04 / .93), with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05,
-//     above 700 MB .98 / 1.03), with more never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (lines / so: p = 8 1.00 /
-//     1.03, p = 12..16 .99 / 1.01, p = 24 .97 / 1.00).
+//     L2 and no accumulator's line is written in parts (bf16, p = 5 321 MB 1.09, runs alone 1.04, 1.2 GB 1.07, .97; p = 8
+//     416 MB 1.10, 1.04; p = 12..16 300..700 MB 1.06, 1.03, above 700 MB .97, 1.00; f32, p = 8 250 MB 1.03, .92, 1.8 GB
+//     .98, .94; p = 24 and more up to 5 % slower).  Not in runs this loses 1 to 10 %.  If the gradients are then off 16
+//     bytes: p = 12 to 16 runs alone (bf16 120..700 MB 1.01 to 1.03, f32 p = 12 200..450 MB 1.05 to 1.08, p = 16 1.04;
+//     above 700 MB 1.00, first micro-steps .96), fewer buffers neither (bf16, p = 8 120 MB and more .97 to 1.00).
+//   - Everything on lines, or many buffers: in runs in the middle of the range (bf16, p = 4 209 MB 1.06, p = 8 231 MB 1.05,
+//     p = 12..16 120..300 MB 1.05, 300..700 MB 1.03, above .98; below 60 MB .99 to 1.00; f32, p = 8 124 MB 1.06, p = 12..16
+//     60..120 MB .96, 120..300 MB 1.03, above 700 MB .97; first micro-steps 120..700 MB 1.01 to 1.03, above .95 to .96).
+//   - Segments, whose ends lie anywhere: in runs, up to 3 buffers below 60 MB only (bf16, p = 2 45 MB 1.07, 150 MB .97, 600
+//     MB .94; f32, p = 3 300..700 MB .84), from 32 on above 24 MB (f32, p = 32 14 MB .83), f32 below 1 GB (p = 16 2 GB
+//     .93), up to 8 buffers of f32 not from 300 to 700 MB unless all can be on the accumulator's lines (p = 8 335 MB .93,
+//     447 MB .88, 760 MB 1.09; if they can 335 MB 1.04). Accumulating, on the accumulator's lines where that can be (lines
+//     / runs alone: bf16, p = 4 300..700 MB 1.06 / 1.01, p = 8 120..300 MB 1.02 / 1.00; f32, p = 8 120..300 MB 1.04 / .93),
+//     with 12 to 19 buffers from 60 to 700 MB (p = 16 25 MB 1.01 / 1.02, 400 MB 1.08 / 1.05, above 700 MB .98 / 1.03), with
+//     more never (p = 24 25..120 MB .99 / 1.01).  First micro-steps in runs alone (lines / so: p = 8 1.00 / 1.03, p =
+//     12..16 .99 / 1.01, p = 24 .97 / 1.00).
 struct ReduceOrder {
     bool in_runs, acc_lines;
 };
@@ -1714,10 +1725,11 @@ ReduceOrder reduce_order_segments(int p, int elem_bytes, size_t mb, bool accumul
 // and about half of that where the buffers sit at different positions inside their lines, which costs every dword
 // load (bf16, p = 24 12 MB 5.4 / 5.5, 23 MB 8.3 / 7.2; p = 48 21 MB 7.1 / 7.1, 35 MB 10.6 / 9.3; p = 64 31 MB 9.2 / 8.9;
 // p = 128 52 MB 14.5 / 15.2, 67 MB 18.4 / 17.7; f16, p = 128 59 MB 15.6 / 16.6).
-// Few segments change sooner, many as one tensor does (from 32 buffers on): speed against 128 bits a lane, 16 tensors of a layer / 60 of 1 k
-// elements and more: bf16, p = 20 10 MB 1.07 / 1.08, 18 MB .97 / .92, 23 MB .91 / .88; p = 32 10 MB 1.06 / 1.15, 18 MB .88 / 1.13; p = 40 23 MB
-// 1.02 / 1.09, 30 MB .72 / 1.13; p = 48 30 MB 1.18 / 1.22, 50 MB .94 / .95; p = 64 30 MB 1.09 / 1.34, 40 MB .86 / 1.22; p = 128 50 MB 1.01 / 1.34, 60 MB
-// .89 / 1.17; f32, p = 40 18 MB 1.13 / 1.20, 30 MB .92 / 1.00; p = 48 50 MB .87 / 1.04; p = 96 50 MB .96 / 1.19.  22 tensors go with the 60 (p = 32 20 MB 1.25).
+// Few segments change sooner, many as one tensor does (from 32 buffers on): speed against 128 bits a lane, 16 tensors of a
+// layer / 60 of 1 k elements and more: bf16, p = 20 10 MB 1.07 / 1.08, 18 MB .97 / .92, 23 MB .91 / .88; p = 32 10 MB 1.06
+// / 1.15, 18 MB .88 / 1.13; p = 40 23 MB 1.02 / 1.09, 30 MB .72 / 1.13; p = 48 30 MB 1.18 / 1.22, 50 MB .94 / .95; p = 64
+// 30 MB 1.09 / 1.34, 40 MB .86 / 1.22; p = 128 50 MB 1.01 / 1.34, 60 MB .89 / 1.17; f32, p = 40 18 MB 1.13 / 1.20, 30 MB
+// .92 / 1.00; p = 48 50 MB .87 / 1.04; p = 96 50 MB .96 / 1.19.  22 tensors go with the 60 (p = 32 20 MB 1.25).
 // segments: their number, 0 for one tensor.
 inline bool narrow_call(int p, size_t elem_bytes, size_t count, bool same_line, int segments)
 {
@@ -1776,7 +1788,8 @@ int rsa_launch_kind(float* acc, PtrTable g, int p, size_t count, bool accumulate
     const bool acc16 = ((uintptr_t)acc - 4 * (uintptr_t)lead) % 16 == 0;
     const int policy = accum_policy(count, p, GB), how = policy | (order.in_runs ? kInRuns : 0);
     const bool shallow = policy != kAccCached && shallow_call(p, nlanes, units) && !long_call_in_step(g, p, nlanes, units);
-    const Shape sh = shallow ? shallow_shape(p, nlanes, units) : reduce_shape(p, GradFormat<KIND>::kElemBytes, nlanes, line >= 16, acc16, accumulate, policy == kAccCached, units);
+    const Shape sh = shallow ? shallow_shape(p, nlanes, units)
+                             : reduce_shape(p, GB, nlanes, line >= 16, acc16, accumulate, policy == kAccCached, units);
     if (int e = grid_for(nlanes, sh.lanes, MICS_RSA_BPC, &blocks)) return e;
     return dispatch_bool(accumulate, [&](auto A) {
         if (policy == kAccCached)
@@ -1856,9 +1869,10 @@ int launch_adam(float* master, float* exp_avg, float* exp_avg_sq, uint16_t* para
 namespace {
 
 // A launch of SEGS tensors at most, none of them empty.
-// Full-size workgroups take tiles of 16 KiB, which small chunks do not fill: below 48 MB they are for calls whose chunks do (us, full-size / 128 lanes: 41 MB, 40
-// tensors, p = 128 (chunks of 4 KB) 22.9 / 13.6, p = 64 (8 KB) 15.9 / 11.7, p = 16 (32 KB) 11.3 / 10.5; 16 tensors, p = 32 (40 KB) 11.0 / 10.4; 93 tensors, p = 8 (27 KB) 10.6 / 10.7; 60
-// tensors, p = 4, 28 MB (58 KB) 7.7 / 7.9).
+// Full-size workgroups take tiles of 16 KiB, which small chunks do not fill: below 48 MB they are for calls whose chunks do
+// (us, full-size / 128 lanes: 41 MB, 40 tensors, p = 128 (chunks of 4 KB) 22.9 / 13.6, p = 64 (8 KB) 15.9 / 11.7, p = 16
+// (32 KB) 11.3 / 10.5; 16 tensors, p = 32 (40 KB) 11.0 / 10.4; 93 tensors, p = 8 (27 KB) 10.6 / 10.7; 60 tensors, p = 4, 28
+// MB (58 KB) 7.7 / 7.9).
 Shape reorder_tensors_shape(size_t moved, int n, int p)
 {
     const size_t chunk = moved / 2 / ((size_t)n * (size_t)p);
@@ -2059,7 +2073,8 @@ int reduce_coalesced_kind(float* acc, PtrTable g, const Segment* segs, int n, in
     const int policy = accum_policy(elements, p, (int)GB);
     const size_t nlanes = (elements + EPL - 1) / EPL;
     const bool shallow = policy != kAccCached && shallow_segments(p, (int)GB, nlanes, units) && !long_call_in_step(g, p, nlanes, units);
-    const Shape sh = shallow ? shallow_shape_segments(p, waves, full, half, n, units) : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
+    const Shape sh = shallow ? shallow_shape_segments(p, waves, full, half, n, units)
+                             : reduce_shape_segments(p, (int)GB, nlanes, n, line >= 16, acc16, accumulate, policy == kAccCached, units);
     return n <= 64 ? reduce_segments<KIND, 4, 64>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st)
                    : reduce_segments<KIND, 4, kMaxSegMany>(acc, g, base_lead, unit, segs, n, p, accumulate, sh, policy, order, shallow, st);
 }
