@@ -407,10 +407,15 @@ inline Shape reduce_shape_segments(int p, int elem_bytes, size_t nlanes, int n, 
 
 // Whether a reduction past the L2 reads its buffers in shallow batches (rsa_shallow): from 16 buffers on, if a compute unit gets wavefronts
 // enough, as it does wherever the accumulator of up to 31 does not stay in the L2.
-// us, batches of 16 / so, wavefronts per unit in front: p = 32 7 11.7 / 12.2, 8 13.1 / 12.9, f32 7 11.2 / 11.4, 9 13.1 /
-// 12.9; p = 48 5.2 13.2 / 13.3, 6.3 15.2 / 14.1; p = 64 5.2 16.5 / 16.3; p = 128 4.2 27.3 / 27.6, 5.2 29.5 / 29.4, 6.3 34.8
-// / 32.1.
-inline bool shallow_call(int p, size_t nlanes, size_t units) { return p >= 16 && (p < 32 || nlanes >= units * (p < 48 ? 512 : 352)); }
+// us, batches of 16 / so, wavefronts per unit in front: p = 32 7 11.7 / 12.2, f32 7 11.2 / 11.4, 9 13.1 / 12.9; p = 48 5.2
+// 13.2 / 13.3, 6.3 15.2 / 14.1; p = 64 5.2 16.5 / 16.3; p = 128 4.2 27.3 / 27.6, 5.2 29.5 / 29.4, 6.3 34.8 / 32.1.  At 8, one
+// full-size workgroup for every unit: p = 32 12.9 / 13.9, f32 12.1 / 13.0, p = 33 14.0 / 14.4, p = 40 15.8 / 15.2; 8 elements
+// more: p = 32 16.0 / 14.3.
+inline bool shallow_call(int p, size_t nlanes, size_t units)
+{
+    if (p < 32) return p >= 16;
+    return p < 40 ? nlanes > units * kMaxBlock : nlanes >= units * (p < 48 ? 512 : 352);
+}
 
 // Whether buffers lie 16 MiB (up to 63 of them also 32) from one to the next.  Four of them at a time meet in few memory
 // channels, which long calls feel: us, 58 wavefronts per unit, batches of 16 with 5 wavefronts / of 4, 16 MiB: p = 32 84.2

@@ -39,4 +39,5 @@ long long rules_reduce(int p, int elem_bytes, size_t nlanes, int cached, size_t 
     return code(reduce_shape(p, elem_bytes, nlanes, true, true, true, cached, units));
 }
 int rules_partial_waves(int p) { return partial_waves(unrolled_group(p), false); }
+int rules_shallow_call(int p, size_t nlanes, size_t units) { return shallow_call(p, nlanes, units); }
 }

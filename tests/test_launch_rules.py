@@ -31,6 +31,7 @@ def rules(tmp_path_factory):
     lib.rules_in_step.argtypes = [ctypes.POINTER(ctypes.c_size_t), ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     lib.rules_reduce.restype = ctypes.c_longlong
     lib.rules_reduce.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_size_t, ctypes.c_int, ctypes.c_size_t]
+    lib.rules_shallow_call.argtypes = [ctypes.c_int, ctypes.c_size_t, ctypes.c_size_t]
     return lib
 
 
@@ -171,3 +172,10 @@ def test_partial_last_wavefronts_only_in_kernels_that_know_them(rules):
                 assert lanes % 8 == 0 and (lanes % 64 == 0 or rules.rules_partial_waves(p)), (p, nlanes, lanes)
                 seen += lanes % 64 != 0
     assert seen > 1000
+
+
+def test_one_full_size_workgroup_for_every_unit_is_not_read_in_shallow_batches_by_32_buffers(rules):
+    """A power of two for counts that are: 64 MB messages over 32 ranks."""
+    one = 512 * UNITS
+    for p, at, above in ((15, 0, 0), (16, 1, 1), (31, 1, 1), (32, 0, 1), (39, 0, 1), (40, 1, 1), (64, 1, 1)):
+        assert bool(rules.rules_shallow_call(p, one, UNITS)) == bool(at) and bool(rules.rules_shallow_call(p, one + 1, UNITS)) == bool(above), p
